@@ -150,10 +150,10 @@ __host__ __device__ inline uint32_t pb_seg_len(uint32_t nfine, uint64_t pairs) {
 __host__ __device__ inline uint32_t pb_max_segs(uint32_t nfine, uint64_t pairs, uint32_t seg) {
     return nfine + (uint32_t)((pairs + seg - 1) / seg);
 }
-// hist[f] += pairs of pv[0, cnt) whose destination (pv[i] & vmask) lies in fine bin f
-// (hist zeroed by the caller).  A destination outside [0, nfine * PB_FINE) sets *err.
-hipError_t launch_pb_hist(const uint32_t* pv, uint32_t vmask, uint64_t cnt, uint32_t nfine, uint32_t* hist,
-                          uint32_t* err, hipStream_t st);
+// hist[f] += pairs of pv[0, cnt) whose destination (pv[i] & vmask) lies in fine bin f of
+// 2^fshift vertices (hist zeroed by the caller).  A destination outside the bins sets *err.
+hipError_t launch_pb_hist(const uint32_t* pv, uint32_t vmask, uint64_t cnt, uint32_t fshift, uint32_t nfine,
+                          uint32_t* hist, uint32_t* err, hipStream_t st);
 // From a piece's fine histogram: foff[0..nfine] = its exclusive prefix sum (bin starts in
 // the bucketed buffer), segs = the accumulation segments of `seg` pairs, two words each
 // (fine bin, segment index within the bin), *nsegs = their count (<= pb_max_segs).
@@ -161,8 +161,8 @@ hipError_t launch_pb_plan(const uint32_t* hist, uint32_t nfine, uint32_t seg, ui
                           uint32_t* nsegs, hipStream_t st);
 // A counting-sort pass with atomic cursors (the second, fine pass): pair i of
 // (in_v, in_c)[0, cnt) goes to the bin of key in_v[i] >> kshift, at the position its
-// cursor hands out.  Bins are fine bins (kshift = PB_FINE_SHIFT, stride 1) or coarse bins
-// (kshift = PB_FINE_SHIFT + 5, stride PB_FINE_PER_COARSE); bin k ends at
+// cursor hands out.  Bins are fine bins (kshift = the fine bins' shift, stride 1) or coarse
+// bins (kshift = the fine bins' shift + 5, stride PB_FINE_PER_COARSE); bin k ends at
 // foff[min((k + 1) * stride, nfine)], and a pair that would pass its bin's end is dropped
 // and sets *err (counts that do not match the pairs).
 hipError_t launch_pb_scatter(const uint32_t* in_v, const float* in_c, uint64_t cnt, uint32_t kshift, uint32_t stride,
@@ -171,7 +171,8 @@ hipError_t launch_pb_scatter(const uint32_t* in_v, const float* in_c, uint64_t c
 // Resident push of a piece with every vertex active: pc[t] = contrib of the source of the
 // piece's edge t, t in [0, cnt), for the resident list entries [ja, jb) whose work (edge)
 // ranges wpre[j] - wa tile [0, cnt).  tiles writes tj[k] = the entry holding slot
-// k * 4096, for the ceil(cnt / 4096) tiles (once per piece); expand uses it.
+// k * 4096, for the ceil(cnt / 4096) tiles (once per piece); expand uses it.  contrib = null:
+// pc[t] gets the source's id (its 32 bits) instead.
 hipError_t launch_pb_tiles(const uint64_t* wpre, uint32_t ja, uint32_t jb, uint64_t wa, uint64_t cnt, uint32_t* tj,
                            hipStream_t st);
 hipError_t launch_pb_expand(const uint32_t* list, const uint64_t* wpre, uint32_t jb, uint64_t wa, uint64_t cnt,
@@ -200,6 +201,28 @@ hipError_t launch_pb_scatter_a(const uint32_t* in_v, uint32_t vmask, const float
 hipError_t launch_pb_accum(const uint32_t* pv, const float* pc, const uint32_t* foff, const uint32_t* segs,
                            const uint32_t* nsegs, uint32_t max_segs, uint32_t seg, uint64_t n, float* acc,
                            uint32_t* err, hipStream_t st);
+
+// Gather plan of PageRank over a fully resident graph without a budget: the pairs of each
+// piece are sorted by destination bin of 2^shift vertices once, as (source id, place of the
+// destination in its bin's LDS sums), and kept; every iteration gathers the sources'
+// contributions and sums each bin in LDS.
+constexpr uint32_t PG_MIN_SHIFT = 6, PG_MAX_SHIFT = 14;
+// slot[i] = place of v[i] in its bin; a destination >= n sets *err.
+hipError_t launch_pg_pack(const uint32_t* v, uint64_t cnt, uint32_t shift, uint64_t n, uint16_t* slot, uint32_t* err,
+                          hipStream_t st);
+// acc[v] += the contributions of v's in-edges within the piece whose pairs start at e0 of src /
+// slot (16-byte aligned, padded to a multiple of eight pairs); foff, segs (nsegs of them, of
+// `seg` pairs) as launch_pb_plan made them for the piece.
+hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t e0, const uint32_t* foff,
+                            const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
+                            const float* contrib, float* acc, hipStream_t st);
+// contrib = x / D_o and acc = 0 (both n entries) before the first iteration.
+hipError_t launch_pg_start(uint64_t n, const uint64_t* off, const float* x, float* contrib, float* acc,
+                           hipStream_t st);
+// After an iteration's gathers, r = base (or restart * inv_n[v]) + damping * acc: the last
+// iteration writes x = r, the others contrib = r / D_o and acc = 0.
+hipError_t launch_pg_apply(uint64_t n, const uint64_t* off, float* x, float* contrib, float* acc, float base,
+                           float damping, const float* inv_n, float restart, bool last, hipStream_t st);
 
 hipError_t launch_init(const AlgoState& s, uint64_t n, uint32_t source, float pr_x0, float* pr_x, uint32_t* cur,
                        uint32_t nwords, hipStream_t st);

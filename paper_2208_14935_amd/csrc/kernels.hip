@@ -1430,7 +1430,7 @@ __device__ __forceinline__ uint32_t block_excl_sum(uint32_t x, uint32_t* s_w, ui
 }
 
 __global__ __launch_bounds__(PB_THREADS) void k_pb_hist(const uint32_t* __restrict__ pv, uint32_t vmask, uint64_t cnt,
-                                                        uint32_t nfine, uint32_t* __restrict__ hist,
+                                                        uint32_t fshift, uint32_t nfine, uint32_t* __restrict__ hist,
                                                         uint32_t* __restrict__ err) {
     __shared__ uint32_t s_h[PB_MAX_FINE];
     for (uint32_t f = threadIdx.x; f < nfine; f += PB_THREADS) s_h[f] = 0;
@@ -1438,7 +1438,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_pb_hist(const uint32_t* __restri
     bool bad = false;
     for (uint64_t i = blockIdx.x * (uint64_t)PB_THREADS + threadIdx.x; i < cnt;
          i += (uint64_t)gridDim.x * PB_THREADS) {
-        const uint32_t f = (pv[i] & vmask) >> PB_FINE_SHIFT;
+        const uint32_t f = (pv[i] & vmask) >> fshift;
         if (f < nfine)
             atomicAdd(&s_h[f], 1u);
         else
@@ -1659,6 +1659,8 @@ __global__ void k_pb_tiles(const uint64_t* __restrict__ wpre, uint32_t ja, uint3
     }
 }
 
+// IDS: the slot gets the source itself instead of its contribution.
+template <bool IDS>
 __global__ __launch_bounds__(256) void k_pb_expand(const uint32_t* __restrict__ list,
                                                    const uint64_t* __restrict__ wpre, uint32_t jb, uint64_t wa,
                                                    uint64_t cnt, const uint32_t* __restrict__ tj,
@@ -1681,7 +1683,8 @@ __global__ __launch_bounds__(256) void k_pb_expand(const uint32_t* __restrict__ 
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < nv; i += 256) {
             const uint32_t j = j0 + i;
-            s_val[i] = contrib[list[j]];
+            const uint32_t u = list[j];
+            s_val[i] = IDS ? __uint_as_float(u) : contrib[u];
             if (i) {
                 const uint64_t st = wpre[j] - wa;
                 if (st < t0 + tc) s_owner[st - t0] = (uint16_t)i;
@@ -1914,6 +1917,122 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
     } else {
         for (uint32_t q = threadIdx.x; q < lim4 * 4; q += PB_ACC_THREADS)
             if (s_a[q] != 0.0f) unsafeAtomicAdd(acc + base + q, s_a[q]);
+    }
+}
+
+// ------------------------------------------------- PageRank gather plan
+// The pairs of a piece, kept sorted by destination bin between iterations: the source id
+// and the 16-bit place of the destination in its bin's LDS sums.  An iteration then reads 6
+// bytes per edge and the source's contribution, instead of writing, sorting and reading
+// back (destination, contribution) pairs.
+
+// Place of a bin's k-th vertex in its LDS sums: the low 6 bits are XORed with a hash of the
+// rest (a bijection on each aligned run of 64), so that hub ids, which share many zero low
+// bits, spread over the banks.
+__device__ __forceinline__ uint32_t pg_place(uint32_t k) { return k ^ (((k >> 6) * 0x9E3779B1u) >> 26); }
+
+__global__ __launch_bounds__(256) void k_pg_pack(const uint32_t* __restrict__ v, uint64_t cnt, uint32_t shift,
+                                                 uint64_t n, uint16_t* __restrict__ slot,
+                                                 uint32_t* __restrict__ err) {
+    const uint32_t mask = (1u << shift) - 1;
+    bool bad = false;
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cnt; i += (uint64_t)gridDim.x * 256) {
+        const uint32_t d = v[i];
+        if (d >= n) bad = true;
+        slot[i] = (uint16_t)pg_place(d & mask);
+    }
+    if (bad) atomicOr(err, 1u);
+}
+
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// One workgroup per accumulation segment (as k_pb_accum): the segment's pairs are read eight
+// to a thread with 16-byte loads, each source's contribution is gathered and added into the
+// bin's sums in LDS, and the sums are added to acc (plain read-modify-write when the bin is
+// one segment, atomic adds of the non-zero sums when it spans several).  The pairs of the
+// piece start at e0 of src / slot, which are padded to a multiple of eight.
+// Bound by the lines that the gathers miss in the L2 (PMC on R-MAT 24, per launch of 67M
+// pairs: 1.2 GB fetched in 0.41 ms, 0.4 GB of it the 6-byte pairs).  A bin's pairs are in
+// source order, so concurrent workgroups share lines.  Measured there, 20 iterations: 0.16 T
+// edges/s, 32.7 ms against 135 ms for expanding, sorting and summing the pairs; bins of 2^14
+// / 2^13 / 2^12 / 2^11 / 2^10 sums 45.6 / 40.8 / 37.0 / 32.7 / 33.3 ms (smaller bins leave LDS
+// for more workgroups per CU); pieces of n / 2n / 4n / 8n / 16n pairs 51 / 37.9 / 32.7 / 33.6 /
+// 33.7 ms (each piece adds every vertex's sum once more).
+__global__ __launch_bounds__(512) void k_pg_gather(const uint32_t* __restrict__ src,
+                                                          const uint16_t* __restrict__ slot, uint64_t e0,
+                                                          const uint32_t* __restrict__ foff,
+                                                          const uint32_t* __restrict__ segs, uint32_t seg,
+                                                          uint32_t shift, uint64_t n,
+                                                          const float* __restrict__ contrib,
+                                                          float* __restrict__ acc) {
+    extern __shared__ float s_a[];
+    const uint32_t f = segs[2 * blockIdx.x], j = segs[2 * blockIdx.x + 1];
+    const uint32_t b0 = foff[f], b1 = foff[f + 1];
+    const bool multi = b1 - b0 > seg;
+    const uint64_t a0 = e0 + b0 + (uint64_t)j * seg, a1 = min(e0 + b1, a0 + seg);
+    const uint32_t fine = 1u << shift;
+    for (uint32_t k = threadIdx.x; k < fine; k += blockDim.x) s_a[k] = 0.0f;
+    __syncthreads();
+    const u32x4* src4 = (const u32x4*)src;
+    const u32x4* slot8 = (const u32x4*)slot;
+    for (uint64_t g = (a0 >> 3) + threadIdx.x; (g << 3) < a1; g += blockDim.x) {
+        const u32x4 p = __builtin_nontemporal_load(src4 + 2 * g), q = __builtin_nontemporal_load(src4 + 2 * g + 1);
+        const u32x4 z = __builtin_nontemporal_load(slot8 + g);
+        const uint32_t u[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+        const uint32_t zz[4] = {z.x, z.y, z.z, z.w};
+        const uint64_t i0 = g << 3;
+        float c[8];
+        if (i0 >= a0 && i0 + 8 <= a1) {
+#pragma unroll
+            for (int r = 0; r < 8; r++) c[r] = contrib[u[r]];
+#pragma unroll
+            for (int r = 0; r < 8; r++) atomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], c[r]);
+        } else {  // the segment's first or last group: its pairs only
+#pragma unroll
+            for (int r = 0; r < 8; r++)
+                if (i0 + r >= a0 && i0 + r < a1)
+                    atomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], contrib[u[r]]);
+        }
+    }
+    __syncthreads();
+    const uint64_t base = (uint64_t)f << shift;
+    const uint32_t lim = (uint32_t)min((uint64_t)fine, n - base);
+    if (!multi) {
+        for (uint32_t k = threadIdx.x; k < lim; k += blockDim.x) acc[base + k] += s_a[pg_place(k)];
+    } else {
+        for (uint32_t k = threadIdx.x; k < lim; k += blockDim.x) {
+            const float y = s_a[pg_place(k)];
+            if (y != 0.0f) unsafeAtomicAdd(acc + base + k, y);
+        }
+    }
+}
+
+// contrib = x / D_o, acc cleared: before the first iteration.
+__global__ void k_pg_start(uint64_t n, const uint64_t* __restrict__ off, const float* __restrict__ x,
+                           float* __restrict__ contrib, float* __restrict__ acc) {
+    for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t d = off[v + 1] - off[v];
+        contrib[v] = d ? x[v] / (float)d : 0.0f;
+        acc[v] = 0.0f;
+    }
+}
+
+// An iteration's ranks: x after the last one, else the next iteration's contributions
+// (with acc cleared for it), in one pass over the vertices.
+template <bool LAST>
+__global__ void k_pg_apply(uint64_t n, const uint64_t* __restrict__ off, float* __restrict__ x,
+                           float* __restrict__ contrib, float* __restrict__ acc, float base, float damping,
+                           const float* __restrict__ inv_n, float restart) {
+    for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x) {
+        const float r = (inv_n ? restart * inv_n[v] : base) + damping * acc[v];
+        if (LAST) {
+            x[v] = r;
+        } else {
+            const uint64_t d = off[v + 1] - off[v];
+            contrib[v] = d ? r / (float)d : 0.0f;
+            acc[v] = 0.0f;
+        }
     }
 }
 
@@ -2292,12 +2411,12 @@ hipError_t launch_pr_prepare(uint64_t n, const uint64_t* off, const float* x, fl
     return hipGetLastError();
 }
 
-hipError_t launch_pb_hist(const uint32_t* pv, uint32_t vmask, uint64_t cnt, uint32_t nfine, uint32_t* hist,
-                          uint32_t* err, hipStream_t st) {
+hipError_t launch_pb_hist(const uint32_t* pv, uint32_t vmask, uint64_t cnt, uint32_t fshift, uint32_t nfine,
+                          uint32_t* hist, uint32_t* err, hipStream_t st) {
     if (!cnt) return hipSuccess;
     if (nfine == 0 || nfine > PB_MAX_FINE) return hipErrorInvalidValue;
     const unsigned g = (unsigned)std::min<uint64_t>(256, (cnt + 4095) / 4096);
-    k_pb_hist<<<g, PB_THREADS, 0, st>>>(pv, vmask, cnt, nfine, hist, err);
+    k_pb_hist<<<g, PB_THREADS, 0, st>>>(pv, vmask, cnt, fshift, nfine, hist, err);
     return hipGetLastError();
 }
 
@@ -2312,9 +2431,7 @@ hipError_t launch_pb_scatter(const uint32_t* in_v, const float* in_c, uint64_t c
                              uint32_t nfine, const uint32_t* foff, uint32_t* cursor, uint32_t* out_v, float* out_c,
                              uint32_t* err, hipStream_t st) {
     if (!cnt) return hipSuccess;
-    if (nfine == 0 || nfine > PB_MAX_FINE || (stride != 1 && stride != PB_FINE_PER_COARSE) ||
-        (1u << kshift) != stride * PB_FINE)
-        return hipErrorInvalidValue;
+    if (nfine == 0 || nfine > PB_MAX_FINE || (stride != 1 && stride != PB_FINE_PER_COARSE)) return hipErrorInvalidValue;
     k_pb_scatter<<<grid_for(cnt, PB_TILE, 2048), PB_THREADS, 0, st>>>(in_v, in_c, cnt, kshift, stride, nfine, foff,
                                                                       cursor, out_v, out_c, err);
     return hipGetLastError();
@@ -2333,7 +2450,47 @@ hipError_t launch_pb_expand(const uint32_t* list, const uint64_t* wpre, uint32_t
                             const uint32_t* tj, const float* contrib, float* pc, hipStream_t st) {
     if (!cnt) return hipSuccess;
     const uint64_t ntiles = (cnt + PB_EXP_TILE - 1) / PB_EXP_TILE;
-    k_pb_expand<<<(unsigned)std::min<uint64_t>(ntiles, 4096), 256, 0, st>>>(list, wpre, jb, wa, cnt, tj, contrib, pc);
+    const unsigned g = (unsigned)std::min<uint64_t>(ntiles, 4096);
+    if (contrib)
+        k_pb_expand<false><<<g, 256, 0, st>>>(list, wpre, jb, wa, cnt, tj, contrib, pc);
+    else
+        k_pb_expand<true><<<g, 256, 0, st>>>(list, wpre, jb, wa, cnt, tj, nullptr, pc);
+    return hipGetLastError();
+}
+
+hipError_t launch_pg_pack(const uint32_t* v, uint64_t cnt, uint32_t shift, uint64_t n, uint16_t* slot, uint32_t* err,
+                          hipStream_t st) {
+    if (!cnt) return hipSuccess;
+    if (shift < PG_MIN_SHIFT || shift > PG_MAX_SHIFT) return hipErrorInvalidValue;
+    k_pg_pack<<<grid_for(cnt, 256, 8192), 256, 0, st>>>(v, cnt, shift, n, slot, err);
+    return hipGetLastError();
+}
+
+hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t e0, const uint32_t* foff,
+                            const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
+                            const float* contrib, float* acc, hipStream_t st) {
+    if (!nsegs) return hipSuccess;
+    // sums of 32 KB and more leave room for few workgroups per CU: larger ones
+    if (seg == 0 || shift < PG_MIN_SHIFT || shift > PG_MAX_SHIFT) return hipErrorInvalidValue;
+    k_pg_gather<<<nsegs, shift > 12 ? 512 : 256, sizeof(float) << shift, st>>>(src, slot, e0, foff, segs, seg, shift, n, contrib,
+                                                                   acc);
+    return hipGetLastError();
+}
+
+hipError_t launch_pg_start(uint64_t n, const uint64_t* off, const float* x, float* contrib, float* acc,
+                           hipStream_t st) {
+    if (!n) return hipSuccess;
+    k_pg_start<<<grid_for(n, 256, 8192), 256, 0, st>>>(n, off, x, contrib, acc);
+    return hipGetLastError();
+}
+
+hipError_t launch_pg_apply(uint64_t n, const uint64_t* off, float* x, float* contrib, float* acc, float base,
+                           float damping, const float* inv_n, float restart, bool last, hipStream_t st) {
+    if (!n) return hipSuccess;
+    if (last)
+        k_pg_apply<true><<<grid_for(n, 256, 8192), 256, 0, st>>>(n, off, x, contrib, acc, base, damping, inv_n, restart);
+    else
+        k_pg_apply<false><<<grid_for(n, 256, 8192), 256, 0, st>>>(n, off, x, contrib, acc, base, damping, inv_n, restart);
     return hipGetLastError();
 }
 
@@ -2349,7 +2506,7 @@ hipError_t launch_pb_plan_a(const uint32_t* pv, uint32_t vmask, uint64_t cnt, ui
                             uint32_t nfine, const uint32_t* foff, uint32_t* offA, uint32_t* err, hipStream_t st) {
     if (!cnt) return hipSuccess;
     const uint32_t nkeys = (nfine + stride - 1) / stride;
-    if (nfine == 0 || nfine > PB_MAX_FINE || nkeys > PB_LOCAL || (1u << kshift) != stride * PB_FINE)
+    if (nfine == 0 || nfine > PB_MAX_FINE || nkeys > PB_LOCAL || (stride != 1 && stride != PB_FINE_PER_COARSE))
         return hipErrorInvalidValue;
     uint32_t wg;
     uint64_t range;
@@ -2367,7 +2524,7 @@ hipError_t launch_pb_scatter_a(const uint32_t* in_v, uint32_t vmask, const float
                                hipStream_t st) {
     if (!cnt) return hipSuccess;
     const uint32_t nkeys = (nfine + stride - 1) / stride;
-    if (nfine == 0 || nfine > PB_MAX_FINE || nkeys > PB_LOCAL || (1u << kshift) != stride * PB_FINE)
+    if (nfine == 0 || nfine > PB_MAX_FINE || nkeys > PB_LOCAL || (stride != 1 && stride != PB_FINE_PER_COARSE))
         return hipErrorInvalidValue;
     uint32_t wg;
     uint64_t range;

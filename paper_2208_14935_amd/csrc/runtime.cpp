@@ -128,6 +128,15 @@ struct HostBuf {  // pinned host memory
     }
 };
 
+// A run of consecutive resident partitions whose edges fit one piece buffer (PageRank
+// with propagation blocking), with the part of the selection's resident list covering it.
+struct PbPiece {
+    uint64_t e0 = 0, cnt = 0;        // CSR edge range [e0, e0 + cnt): slot = edge - e0
+    uint32_t ja = 0, jb = 0;         // resident list range
+    uint64_t wa = 0, wb = 0;         // ... and its work range
+    uint64_t tj = 0;                 // first entry of its expand-tile table
+};
+
 constexpr uint32_t kMaxSlots = 16;
 constexpr int kClasses = 9;
 
@@ -248,6 +257,18 @@ struct hytm_graph {
     DevBuf<uint32_t> d_pb_v[3];
     DevBuf<float> d_pb_c[3];
     DevBuf<uint32_t> d_pb_hist, d_pb_foff, d_pb_segs, d_pb_nsegs, d_pb_offa, d_pb_fcur, d_pb_err, d_pb_tj;
+    // PageRank gather plan (graphs without a budget): every edge's (source, place) pair
+    // sorted by destination bin within each piece; made by the first run that uses it and
+    // kept while the graph stays without a budget (the edges never change)
+    struct {
+        bool ok = false;
+        uint64_t cap = 0;              // pairs per piece it was made for
+        uint32_t shift = 0, nfine = 0, seg = 0, max_segs = 0;
+        std::vector<PbPiece> pieces;
+        std::vector<uint32_t> nsegs;   // accumulation segments per piece
+        DevBuf<uint32_t> src, foff, segs;
+        DevBuf<uint16_t> slot;
+    } pg;
 
     // host mirrors of the per-iteration selection (views into h_sel, as the device arrays
     // d_hdr, d_wbase, d_lbase, d_mode are views into d_sel)
@@ -554,6 +575,12 @@ void ensure_streams(hytm_graph* g) {
     for (auto& e : g->ev_sel) HIP_CHECK(hipEventCreate(&e));
 }
 
+void pg_release(hytm_graph* g) {
+    g->pg.ok = false;
+    for (auto* b : {&g->pg.src, &g->pg.foff, &g->pg.segs}) b->release();
+    g->pg.slot.release();
+}
+
 void release_all(hytm_graph* g) {
     if (g->s_copy) (void)hipDeviceSynchronize();
     for (auto* b : {&g->d_val, &g->d_cur, &g->d_next, &g->d_visited, &g->d_list, &g->d_overflow, &g->d_nA, &g->d_nF,
@@ -595,6 +622,7 @@ void release_all(hytm_graph* g) {
     for (auto* b : {&g->d_pb_hist, &g->d_pb_foff, &g->d_pb_segs, &g->d_pb_nsegs, &g->d_pb_offa, &g->d_pb_fcur,
                     &g->d_pb_err, &g->d_pb_tj})
         b->release();
+    pg_release(g);
     for (uint32_t i = 0; i < kMaxSlots; i++) {
         g->d_slot_col[i].release();
         g->d_slot_w[i].release();
@@ -667,15 +695,6 @@ struct Totals {
     uint64_t av = 0, ae = 0, bf = 0, bc = 0, zcl = 0, d2h = 0, ftasks = 0, cchunks = 0;
 };
 
-// A run of consecutive resident partitions whose edges fit one piece buffer (PageRank
-// with propagation blocking), with the part of the selection's resident list covering it.
-struct PbPiece {
-    uint64_t e0 = 0, cnt = 0;        // CSR edge range [e0, e0 + cnt): slot = edge - e0
-    uint32_t ja = 0, jb = 0;         // resident list range
-    uint64_t wa = 0, wb = 0;         // ... and its work range
-    uint64_t tj = 0;                 // first entry of its expand-tile table
-};
-
 // One traversal: a single-source or whole-graph run, or one group of lanes (a batched
 // run or a lane group of the query server).  The per-graph scratch it steps through
 // (lists, selection, staging) is shared; the frontier and value state is its own.
@@ -703,6 +722,12 @@ struct RunCtx {
     } replay;
     uint32_t last_ftasks = 0;                  // streaming filter tasks of the last pass
     uint64_t last_fchunks = 0;
+    // PageRank over a gather plan (hytm_graph::pg): the selection, replayed every iteration
+    bool pg_on = false;
+    struct {
+        bool ok = false;
+        Header h{};
+    } pgr;
     // PageRank with propagation blocking: the first iteration's selection cut into pieces
     bool pb_on = false;
     struct {
@@ -955,7 +980,8 @@ void init_ctx(RunCtx& rc, hytm_graph* g, int algo, bool batched, const Plan& pl,
 // is pushed.  Transfer and activity counts are added to *rec; trace_t >= 0 records the
 // engine choice in the caller's mode trace.
 hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Header* hout, uint64_t* lanes,
-                        bool stop_if_empty, hytm_iter_stats* rec, int64_t trace_t, bool select_only = false) {
+                        bool stop_if_empty, hytm_iter_stats* rec, int64_t trace_t, bool select_only = false,
+                        bool lists = true) {
     hytm_graph* g = rc.g;
     KTimer& kt = g->timer;
     AlgoState& as = rc.as;
@@ -977,7 +1003,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
         return launch_scan(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_Rq.p, g->d_K.p, g->d_lbase.p,
                            g->d_wbase.p, g->d_hdr.p, g->d_wpre.p, g->d_scan.p, main);
     }));
-    HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
+    if (lists) HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
         return launch_build_lists(npart, g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p, g->d_wbase.p,
                                   g->d_list.p, g->d_wpre.p, main);
     }));
@@ -1157,14 +1183,10 @@ void record_iteration(RunCtx& rc, hytm_iter_stats& rec, uint32_t t, double t_it)
     }
 }
 
-// PageRank iterations after the first: the same pushes over the same lists and filter
-// tasks, ordered after the main stream's prepare by an event instead of a host round trip.
-hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t trace_t) {
-    hytm_graph* g = rc.g;
-    KTimer& kt = g->timer;
-    AlgoState& as = rc.as;
+// The counts and the trace row of an iteration that replays the selection `h`.
+void replay_record(const RunCtx& rc, const Header& h, hytm_iter_stats* rec, int64_t trace_t) {
+    const hytm_graph* g = rc.g;
     const uint32_t npart = g->npart;
-    const Header& h = rc.replay.h;
     uint32_t scheduled = 0;
     for (int s = 0; s < NSEG; s++) {
         rec->parts[s + 1] += h.seg_parts[s];
@@ -1176,6 +1198,16 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
     hytm_run_stats* stats = rc.stats;
     if (trace_t >= 0 && stats && stats->mode_trace && (uint64_t)(trace_t + 1) * npart <= stats->mode_trace_cap)
         memcpy(stats->mode_trace + (uint64_t)trace_t * npart, g->h_mode.p, npart);
+}
+
+// PageRank iterations after the first: the same pushes over the same lists and filter
+// tasks, ordered after the main stream's prepare by an event instead of a host round trip.
+hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t trace_t) {
+    hytm_graph* g = rc.g;
+    KTimer& kt = g->timer;
+    AlgoState& as = rc.as;
+    const Header& h = rc.replay.h;
+    replay_record(rc, h, rec, trace_t);
     HIP_CHECK(hipEventRecord(g->ev_go, main));
     if (h.seg_list_count[SEG_R])
         HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
@@ -1250,36 +1282,17 @@ uint64_t pb_capacity(const hytm_graph* g, uint64_t res_edges) {
     return std::max<uint64_t>(std::min<uint64_t>(std::max<uint64_t>(want, g->max_part_edges), res_edges), 1);
 }
 
-// Cut the resident partitions of the first iteration's selection into pieces, build the
-// streaming filter tasks of the streamed partitions, and put the buffers and bucket plans
-// in place.
-hytm_status pb_plan(RunCtx& rc, const Header& h, hipStream_t main) {
-    hytm_graph* g = rc.g;
-    auto& pb = rc.pb;
-    const uint32_t npart = g->npart;
+// Cut the resident partitions [0, nres) of the selection in the host mirrors into pieces:
+// runs of partitions with at most `cap` edges.  Returns the entries of their tile tables.
+uint64_t cut_pieces(const hytm_graph* g, uint32_t nres, uint64_t cap, const Header& h, std::vector<PbPiece>* out) {
     const uint8_t* md = g->h_mode.p;
-    const uint32_t nres = std::min(rc.plan.nres, npart);
-    pb.h = h;
-    pb.cap = pb_capacity(g, g->h_off[g->pv[nres]]);
-    pb.nfine = pb_fine_bins(g->n);
-    pb.seg = pb_seg_len(pb.nfine, pb.cap);
-    pb.max_segs = pb_max_segs(pb.nfine, pb.cap, pb.seg);
-    pb.keys_a = pb.nfine > PB_LOCAL_BINS ? pb_coarse_bins(pb.nfine) : pb.nfine;
-    pb.pieces.clear();
-    pb.ftasks = 0;
-    pb.fchunks = pb.fedges = 0;
-    for (uint32_t p = 0; p < npart; p++) {
-        if (md[p] == P_COMPACT) return fail(HYTM_E_STATE, "internal: compaction partition under PageRank blocking");
-        if ((p < nres) != (md[p] == P_RES) && g->pE[p] > 0)
-            return fail(HYTM_E_STATE, "internal: resident partitions are not the resident prefix");
-    }
-    // resident pieces: runs of partitions with at most cap edges
+    out->clear();
     uint64_t tj = 0;
     uint32_t pa = 0;
     while (pa < nres) {
         uint32_t pb_ = pa;
         uint64_t e = 0;
-        while (pb_ < nres && (pb_ == pa || e + g->pE[pb_] <= pb.cap)) e += g->pE[pb_++];
+        while (pb_ < nres && (pb_ == pa || e + g->pE[pb_] <= cap)) e += g->pE[pb_++];
         PbPiece pc;
         pc.e0 = g->h_off[g->pv[pa]];
         pc.cnt = g->h_off[g->pv[pb_]] - pc.e0;
@@ -1302,10 +1315,36 @@ hytm_status pb_plan(RunCtx& rc, const Header& h, hipStream_t main) {
             }
             pc.tj = tj;
             tj += pb_tiles(pc.cnt);
-            pb.pieces.push_back(pc);
+            out->push_back(pc);
         }
         pa = pb_;
     }
+    return tj;
+}
+
+// Cut the resident partitions of the first iteration's selection into pieces, build the
+// streaming filter tasks of the streamed partitions, and put the buffers and bucket plans
+// in place.
+hytm_status pb_plan(RunCtx& rc, const Header& h, hipStream_t main) {
+    hytm_graph* g = rc.g;
+    auto& pb = rc.pb;
+    const uint32_t npart = g->npart;
+    const uint8_t* md = g->h_mode.p;
+    const uint32_t nres = std::min(rc.plan.nres, npart);
+    pb.h = h;
+    pb.cap = pb_capacity(g, g->h_off[g->pv[nres]]);
+    pb.nfine = pb_fine_bins(g->n);
+    pb.seg = pb_seg_len(pb.nfine, pb.cap);
+    pb.max_segs = pb_max_segs(pb.nfine, pb.cap, pb.seg);
+    pb.keys_a = pb.nfine > PB_LOCAL_BINS ? pb_coarse_bins(pb.nfine) : pb.nfine;
+    pb.ftasks = 0;
+    pb.fchunks = pb.fedges = 0;
+    for (uint32_t p = 0; p < npart; p++) {
+        if (md[p] == P_COMPACT) return fail(HYTM_E_STATE, "internal: compaction partition under PageRank blocking");
+        if ((p < nres) != (md[p] == P_RES) && g->pE[p] > 0)
+            return fail(HYTM_E_STATE, "internal: resident partitions are not the resident prefix");
+    }
+    const uint64_t tj = cut_pieces(g, nres, pb.cap, h, &pb.pieces);
     // streamed filter partitions: tasks of <= k adjacent ones (Sec. 5.2), one launch per pass
     if (h.seg_list_count[SEG_F]) {
         g->h_tasks.ensure(npart);
@@ -1367,20 +1406,7 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
     KTimer& kt = g->timer;
     const auto& pb = rc.pb;
     const Header& h = pb.h;
-    const uint32_t npart = g->npart;
-    if (!first) {
-        uint32_t scheduled = 0;
-        for (int s = 0; s < NSEG; s++) {
-            rec->parts[s + 1] += h.seg_parts[s];
-            scheduled += h.seg_parts[s];
-        }
-        rec->parts[0] += npart - scheduled;
-        rec->active_vertices += h.total_active;
-        for (int s = 0; s < NSEG; s++) rec->active_edges += h.seg_edges[s];
-        hytm_run_stats* stats = rc.stats;
-        if (trace_t >= 0 && stats && stats->mode_trace && (uint64_t)(trace_t + 1) * npart <= stats->mode_trace_cap)
-            memcpy(stats->mode_trace + (uint64_t)trace_t * npart, g->h_mode.p, npart);
-    }
+    if (!first) replay_record(rc, h, rec, trace_t);
     HIP_CHECK(hipEventRecord(g->ev_go, main));
     for (hipStream_t s : {g->s_c, g->s_zc, g->s_fk, g->s_pb}) HIP_CHECK(hipStreamWaitEvent(s, g->ev_go, 0));
     AlgoState& as = rc.as;
@@ -1436,7 +1462,7 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
             hipError_t e;
             if (first) {
                 if ((e = launch_fill_u32(g->d_pb_hist.p, nfine, 0u, sp)) != hipSuccess) return e;
-                if ((e = launch_pb_hist(in_v, vmask, pc.cnt, nfine, g->d_pb_hist.p, err, sp)) != hipSuccess) return e;
+                if ((e = launch_pb_hist(in_v, vmask, pc.cnt, PB_FINE_SHIFT, nfine, g->d_pb_hist.p, err, sp)) != hipSuccess) return e;
                 if ((e = launch_pb_plan(g->d_pb_hist.p, nfine, pb.seg, foff, segs, nsegs, sp)) != hipSuccess) return e;
                 if ((e = launch_pb_plan_a(in_v, vmask, pc.cnt, shift_a, stride_a, nfine, foff, offa, err, sp)) !=
                     hipSuccess)
@@ -1464,6 +1490,153 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
     return HYTM_OK;
 }
 
+// --------------------------------------------------- PageRank gather plan
+// A graph without a budget keeps its edges on the device, and every PageRank iteration
+// moves the same (source, destination) pairs, so they are sorted by destination bin once
+// (6 bytes per edge beside the resident edges) and an iteration only gathers and sums.  The
+// pieces path above, which writes, sorts and reads back 28 bytes per edge in every
+// iteration, remains for budgeted graphs: there device memory per edge is what is short.
+bool pg_eligible(const RunCtx& rc) {
+    const hytm_graph* g = rc.g;
+    return pb_eligible(rc) && g->budget == UINT64_MAX;
+}
+
+// Vertices per destination bin, as a shift: 2^11 sums (8 KB of LDS) measured best, down to 512
+// bins on smaller graphs, so that a piece has workgroups for the 256 CUs, and more sums per
+// bin past 2^25 vertices, where the bins reach the sort's limit.
+uint32_t pg_shift(uint64_t n) {
+    uint32_t bits = 0;
+    while (bits < 32 && (n - 1) >> bits) bits++;
+    uint32_t sh = std::min(std::max(bits, PG_MIN_SHIFT + 9) - 9, 11u);
+    while ((n + (1ull << sh) - 1) >> sh > PB_MAX_FINE) sh++;  // n <= 2^28: at most PG_MAX_SHIFT
+    return sh;
+}
+
+// Pairs per piece: pr_block_pairs if given, else four per vertex (a piece costs a
+// read-modify-write of every vertex's sum) and at least 2^24 (a piece is a launch).
+uint64_t pg_capacity(const hytm_graph* g) {
+    if (g->params.pr_block_pairs) return pb_capacity(g, g->m);
+    const uint64_t want = std::max<uint64_t>(std::max<uint64_t>(4 * g->n, 1ull << 24), g->max_part_edges);
+    return std::max<uint64_t>(std::min<uint64_t>({want, g->m, (1ull << 31) - 1}), 1);
+}
+
+// Build the plan from the resident lists of the run's selection.  *made = false (and no
+// plan) when the device has no room for it.
+hytm_status pg_build(RunCtx& rc, const Header& h, hipStream_t main, bool* made) {
+    hytm_graph* g = rc.g;
+    KTimer& kt = g->timer;
+    auto& pg = g->pg;
+    *made = false;
+    pg_release(g);
+    struct Temps {
+        DevBuf<uint32_t> v, v2, hist, offa, fcur, tj, nsegs, err;
+        DevBuf<float> id, c;
+        ~Temps() {
+            for (auto* b : {&v, &v2, &hist, &offa, &fcur, &tj, &nsegs, &err}) b->release();
+            id.release();
+            c.release();
+        }
+    } t;
+    pg.cap = pg_capacity(g);
+    pg.shift = pg_shift(g->n);
+    pg.nfine = (uint32_t)((g->n + (1ull << pg.shift) - 1) >> pg.shift);
+    pg.seg = pb_seg_len(pg.nfine, pg.cap);
+    pg.max_segs = pb_max_segs(pg.nfine, pg.cap, pg.seg);
+    const uint64_t tj = cut_pieces(g, g->npart, pg.cap, h, &pg.pieces);
+    const uint32_t np = (uint32_t)pg.pieces.size();
+    const uint32_t nfine = pg.nfine;
+    const bool two = nfine > PB_LOCAL_BINS;
+    const uint32_t keys_a = two ? pb_coarse_bins(nfine) : nfine;
+    const uint32_t shift_a = two ? pg.shift + 5 : pg.shift, stride_a = two ? PB_FINE_PER_COARSE : 1;
+    const uint64_t pad = (g->m + 7) & ~uint64_t(7);
+    size_t room = 0, total = 0;
+    HIP_CHECK(hipMemGetInfo(&room, &total));
+    const uint64_t need = 6 * pad + 4 * pg.cap * (two ? 4 : 2) + 8ull * np * (nfine + 2 * pg.max_segs) +
+                          4 * (pb_max_offa(keys_a) + tj + 2ull * nfine) + (64ull << 20);
+    if (need > room) return HYTM_OK;
+    try {
+        pg.src.ensure(pad);
+        pg.slot.ensure(pad);
+        pg.foff.ensure((uint64_t)np * (nfine + 1));
+        pg.segs.ensure((uint64_t)np * 2 * pg.max_segs);
+        t.id.ensure(pg.cap);
+        t.v.ensure(pg.cap);
+        if (two) {
+            t.c.ensure(pg.cap);
+            t.v2.ensure(pg.cap);
+        }
+        t.hist.ensure(nfine);
+        t.offa.ensure(pb_max_offa(keys_a));
+        t.fcur.ensure(nfine);
+        t.tj.ensure(std::max<uint64_t>(tj, 1));
+        t.nsegs.ensure(std::max<uint32_t>(np, 1));
+        t.err.ensure(1);
+    } catch (const HipError& e) {
+        pg_release(g);
+        if (e.status != HYTM_E_NOMEM) throw;
+        return HYTM_OK;
+    }
+    HIP_CHECK(launch_fill_u32(t.err.p, 1, 0u, main));
+    const uint32_t vmask = g->pk.mask;
+    for (uint32_t pi = 0; pi < np; pi++) {
+        const PbPiece& pc = pg.pieces[pi];
+        const uint32_t* in_v = g->d_res_col.p + pc.e0;
+        uint32_t* foff = pg.foff.p + (uint64_t)pi * (nfine + 1);
+        uint32_t* tjp = t.tj.p + pc.tj;
+        float* src = (float*)(pg.src.p + pc.e0);
+        HIP_CHECK(kt.run(HYTM_K_OTHER, pc.cnt, main, [&]() -> hipError_t {
+            hipError_t e;
+            if ((e = launch_pb_tiles(g->d_wpre.p, pc.ja, pc.jb, pc.wa, pc.cnt, tjp, main)) != hipSuccess) return e;
+            if ((e = launch_pb_expand(g->d_list.p, g->d_wpre.p, pc.jb, pc.wa, pc.cnt, tjp, nullptr, t.id.p, main)) != hipSuccess)
+                return e;
+            if ((e = launch_fill_u32(t.hist.p, nfine, 0u, main)) != hipSuccess) return e;
+            if ((e = launch_pb_hist(in_v, vmask, pc.cnt, pg.shift, nfine, t.hist.p, t.err.p, main)) != hipSuccess) return e;
+            if ((e = launch_pb_plan(t.hist.p, nfine, pg.seg, foff, pg.segs.p + (uint64_t)pi * 2 * pg.max_segs,
+                                    t.nsegs.p + pi, main)) != hipSuccess)
+                return e;
+            if ((e = launch_pb_plan_a(in_v, vmask, pc.cnt, shift_a, stride_a, nfine, foff, t.offa.p, t.err.p, main)) !=
+                hipSuccess)
+                return e;
+            if ((e = launch_pb_scatter_a(in_v, vmask, t.id.p, pc.cnt, shift_a, stride_a, nfine, foff, t.offa.p, t.v.p,
+                                         two ? t.c.p : src, two ? t.fcur.p : nullptr, t.err.p, main)) != hipSuccess)
+                return e;
+            if (two && (e = launch_pb_scatter(t.v.p, t.c.p, pc.cnt, pg.shift, 1, nfine, foff, t.fcur.p, t.v2.p, src,
+                                              t.err.p, main)) != hipSuccess)
+                return e;
+            return launch_pg_pack(two ? t.v2.p : t.v.p, pc.cnt, pg.shift, g->n, pg.slot.p + pc.e0, t.err.p, main);
+        }));
+    }
+    // the plan is read only once its counts are known to match the pairs
+    uint32_t perr = 0;
+    pg.nsegs.resize(np);
+    HIP_CHECK(hipMemcpyAsync(pg.nsegs.data(), t.nsegs.p, np * sizeof(uint32_t), hipMemcpyDeviceToHost, main));
+    HIP_CHECK(hipMemcpyAsync(&perr, t.err.p, sizeof(perr), hipMemcpyDeviceToHost, main));
+    HIP_CHECK(hipStreamSynchronize(main));
+    if (perr) {
+        pg_release(g);
+        return fail(HYTM_E_DEVICE, "internal: PageRank pair buckets did not match the pushed pairs");
+    }
+    pg.ok = *made = true;
+    return HYTM_OK;
+}
+
+// One PageRank iteration over the gather plan.
+hytm_status pg_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t trace_t, bool first) {
+    hytm_graph* g = rc.g;
+    KTimer& kt = g->timer;
+    const auto& pg = g->pg;
+    if (!first) replay_record(rc, rc.pgr.h, rec, trace_t);
+    for (uint32_t pi = 0; pi < pg.pieces.size(); pi++) {
+        const PbPiece& pc = pg.pieces[pi];
+        HIP_CHECK(kt.run(HYTM_K_PR_BLOCK, pc.cnt, main, [&] {
+            return launch_pg_gather(pg.src.p, pg.slot.p, pc.e0, pg.foff.p + (uint64_t)pi * (pg.nfine + 1),
+                                    pg.segs.p + (uint64_t)pi * 2 * pg.max_segs, pg.nsegs[pi], pg.seg, pg.shift, g->n,
+                                    g->d_contrib.p, g->d_acc.p, main);
+        }));
+    }
+    return HYTM_OK;
+}
+
 // One iteration of a traversal.  *lanes_out: batched runs: the lanes with a non-empty
 // frontier at the start of the iteration.  *empty_out: BFS/SSSP/CC only: the frontier was
 // empty, nothing was pushed and the traversal is over.
@@ -1476,7 +1649,7 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
     const bool fixed_steps = rc.algo == HYTM_PAGERANK || rc.algo == HYTM_PPR;
     const double t_it = now_ms();
     const uint32_t copies = rc.pb_on ? as.acc_copies + 1 : as.acc_copies;  // + the blocking copy
-    if (rc.algo == HYTM_PAGERANK)
+    if (rc.algo == HYTM_PAGERANK && !rc.pg_on)
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
             return launch_pr_prepare(n, g->d_off.p, g->d_x.p, g->d_contrib.p, g->d_acc.p, copies, main);
         }));
@@ -1488,7 +1661,29 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
     *lanes_out = 0;
     *empty_out = false;
     hytm_status st;
-    if (rc.pb.ok) {
+    if (rc.pg_on && !rc.pgr.ok) {
+        // the selection gives the counts; its lists are only read while the plan is made
+        st = engine_pass(rc, rc.cur, main, &h, nullptr, false, &rec, t, true, !g->pg.ok);
+        if (st == HYTM_OK && !g->pg.ok) {
+            bool made = false;
+            st = pg_build(rc, h, main, &made);
+            if (st == HYTM_OK && !made) {  // no room for the plan: the pieces path from here on
+                rc.pg_on = false;
+                return step_once(rc, main, lanes_out, empty_out);
+            }
+        }
+        if (st == HYTM_OK) {
+            rc.pgr.ok = true;
+            rc.pgr.h = h;
+            HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
+                return launch_pg_start(n, g->d_off.p, g->d_x.p, g->d_contrib.p, g->d_acc.p, main);
+            }));
+            st = pg_pass(rc, main, &rec, t, true);
+        }
+    } else if (rc.pg_on) {
+        st = pg_pass(rc, main, &rec, t, false);
+        h = rc.pgr.h;
+    } else if (rc.pb.ok) {
         st = pb_pass(rc, main, &rec, t, false);
         h = rc.pb.h;
     } else if (rc.pb_on) {
@@ -1542,7 +1737,9 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
         const float d = (float)g->params.pr_damping;
         const float restart = (float)(1.0 - g->params.pr_damping);
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
-            return launch_pr_apply(n, g->d_x.p, g->d_acc.p, copies, base, d, as.inv_n, restart, main);
+            return rc.pg_on ? launch_pg_apply(n, g->d_off.p, g->d_x.p, g->d_contrib.p, g->d_acc.p, base, d, as.inv_n,
+                                              restart, t + 1 == g->params.pr_iterations, main)
+                            : launch_pr_apply(n, g->d_x.p, g->d_acc.p, copies, base, d, as.inv_n, restart, main);
         }));
     } else {
         if (rc.algo == HYTM_PPR) {
@@ -1717,6 +1914,8 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     HIP_CHECK(launch_fill_u32((uint32_t*)g->d_zcl.p, 2, 0u, main));
     init_ctx(rc, g, algo, batched, pl, stats);
     rc.pb_on = pb_eligible(rc);
+    rc.pg_on = pg_eligible(rc);
+    if (rc.pg_on && g->pg.ok && g->pg.cap != pg_capacity(g)) pg_release(g);  // other pieces were asked for
     rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on);
     rc.as.acc_copies = pr_acc_copies(rc.pb_on);
 
@@ -2486,7 +2685,13 @@ hytm_status hytm_set_device_budget(hytm_graph* g, uint64_t edge_bytes) {
     g_err.clear();
     if (!g) return fail(HYTM_E_INVAL, "graph is NULL");
     if (g->server) return fail(HYTM_E_STATE, "a query server is open on this graph");
-    if (edge_bytes != g->budget) g->res_valid = false;
+    if (edge_bytes != g->budget) {
+        g->res_valid = false;
+        if (edge_bytes != UINT64_MAX && g->pg.ok) {  // the gather plan is for graphs without a budget
+            (void)hipSetDevice(g->device);
+            pg_release(g);
+        }
+    }
     g->budget = edge_bytes;
     return HYTM_OK;
 }
