@@ -1325,33 +1325,27 @@ __global__ void k_reset_lanes(AlgoState s, uint64_t mask) {
     }
 }
 
-__global__ void k_ppr_prepare(AlgoState s, const uint64_t* __restrict__ off) {
-    for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < s.n; v += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t m = s.mcur[v];
+// x of each active (vertex, lane) scaled to x / D_o, one thread per value: a wave's accesses
+// are contiguous rows (a thread per vertex walking its row took 0.54 ms of 1M rows of 64).
+__global__ __launch_bounds__(256) void k_ppr_prepare(AlgoState s, const uint64_t* __restrict__ off) {
+    const uint64_t cells = s.n << s.lshift;
+    const uint32_t lmask = (1u << s.lshift) - 1;
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
+        const uint64_t v = i >> s.lshift;
+        if (!((s.mcur[v] >> ((uint32_t)i & lmask)) & 1)) continue;
         const uint64_t d = off[v + 1] - off[v];
-        if (!m || !d) continue;
-        float* row = s.lx + (v << s.lshift);
-        const float fd = (float)d;
-        while (m) {
-            const uint32_t l = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            row[l] = row[l] / fd;
-        }
+        if (d) s.lx[i] = s.lx[i] / (float)d;
     }
 }
 
-__global__ void k_ppr_apply(AlgoState s, float damping) {
-    for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < s.n; v += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t m = s.mcur[v] | s.mnext[v];
-        if (!m) continue;
-        float* x = s.lx + (v << s.lshift);
-        double* a = s.lacc + (v << s.lshift);
-        while (m) {
-            const uint32_t l = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            x[l] = (float)((double)damping * a[l]);
-            a[l] = 0.0;
-        }
+__global__ __launch_bounds__(256) void k_ppr_apply(AlgoState s, float damping) {
+    const uint64_t cells = s.n << s.lshift;
+    const uint32_t lmask = (1u << s.lshift) - 1;
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
+        const uint64_t v = i >> s.lshift;
+        if (!(((s.mcur[v] | s.mnext[v]) >> ((uint32_t)i & lmask)) & 1)) continue;
+        s.lx[i] = (float)((double)damping * s.lacc[i]);
+        s.lacc[i] = 0.0;
     }
 }
 
@@ -1920,6 +1914,276 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
     }
 }
 
+// ----------------------------------------------------------- in-edge lists
+// In-degrees, then their prefix sums (edges, and segments of IN_SEG edges per vertex), then
+// the sources placed by atomic cursors; a list's order is of no account.
+__global__ __launch_bounds__(256) void k_in_count(const uint32_t* __restrict__ col, uint32_t vmask, uint64_t m,
+                                                  uint64_t n, uint32_t* __restrict__ cnt) {
+    for (uint64_t e = blockIdx.x * 256ull + threadIdx.x; e < m; e += (uint64_t)gridDim.x * 256) {
+        const uint32_t v = col[e] & vmask;
+        if (v < n) atomicAdd(cnt + v, 1u);
+    }
+}
+
+constexpr uint32_t IN_TILE = 4096;  // vertices per workgroup of the prefix sums, 16 per thread
+
+__device__ __forceinline__ uint32_t in_segs(uint32_t c) { return (c + IN_SEG - 1) / IN_SEG; }
+
+// tot[2 k], tot[2 k + 1] = edges and segments of tile k.
+__global__ __launch_bounds__(256) void k_in_tot(const uint32_t* __restrict__ cnt, uint64_t n,
+                                                uint64_t* __restrict__ tot) {
+    __shared__ uint64_t s_t[4][2];
+    uint64_t a = 0, b = 0;
+    for (uint32_t q = threadIdx.x; q < IN_TILE; q += 256) {
+        const uint64_t v = (uint64_t)blockIdx.x * IN_TILE + q;
+        const uint32_t c = v < n ? cnt[v] : 0u;
+        a += c;
+        b += in_segs(c);
+    }
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if ((threadIdx.x & 63) == 0) {
+        s_t[threadIdx.x >> 6][0] = a;
+        s_t[threadIdx.x >> 6][1] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        tot[2 * (uint64_t)blockIdx.x + threadIdx.x] =
+            s_t[0][threadIdx.x] + s_t[1][threadIdx.x] + s_t[2][threadIdx.x] + s_t[3][threadIdx.x];
+}
+
+// One wave: the tiles' totals become their bases; toff[n] and soff[n] the grand totals.
+__global__ __launch_bounds__(64) void k_in_base(uint64_t tiles, uint64_t* __restrict__ tot, uint64_t n,
+                                                uint64_t* __restrict__ toff, uint32_t* __restrict__ soff) {
+    uint64_t ra = 0, rb = 0;
+    for (uint64_t k0 = 0; k0 < tiles; k0 += 64) {
+        const uint64_t k = k0 + threadIdx.x;
+        uint64_t ta, tb;
+        const uint64_t a = wave_exclusive_sum(k < tiles ? tot[2 * k] : 0, &ta);
+        const uint64_t b = wave_exclusive_sum(k < tiles ? tot[2 * k + 1] : 0, &tb);
+        if (k < tiles) {
+            tot[2 * k] = ra + a;
+            tot[2 * k + 1] = rb + b;
+        }
+        ra += ta;
+        rb += tb;
+    }
+    if (threadIdx.x == 0) {
+        toff[n] = ra;
+        soff[n] = (uint32_t)rb;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_in_write(uint32_t* __restrict__ cnt, uint64_t n,
+                                                  const uint64_t* __restrict__ tot, uint64_t* __restrict__ toff,
+                                                  uint32_t* __restrict__ soff, uint32_t* __restrict__ seg_v) {
+    constexpr uint32_t PER = IN_TILE / 256;
+    __shared__ uint64_t s_t[4][2];
+    const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const uint64_t v0 = (uint64_t)blockIdx.x * IN_TILE + threadIdx.x * PER;
+    uint32_t c[PER];
+    uint64_t a = 0, b = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+        c[q] = v0 + q < n ? cnt[v0 + q] : 0u;
+        a += c[q];
+        b += in_segs(c[q]);
+    }
+    uint64_t ta, tb;
+    uint64_t ea = wave_exclusive_sum(a, &ta), eb = wave_exclusive_sum(b, &tb);
+    if (lane == 0) {
+        s_t[wid][0] = ta;
+        s_t[wid][1] = tb;
+    }
+    __syncthreads();
+    ea += tot[2 * (uint64_t)blockIdx.x];
+    eb += tot[2 * (uint64_t)blockIdx.x + 1];
+    for (uint32_t w = 0; w < wid; w++) {
+        ea += s_t[w][0];
+        eb += s_t[w][1];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+        const uint64_t v = v0 + q;
+        if (v >= n) break;
+        toff[v] = ea;
+        soff[v] = (uint32_t)eb;
+        const uint32_t sg = in_segs(c[q]);
+        for (uint32_t k = 0; k < sg; k++) seg_v[eb + k] = (uint32_t)v;
+        ea += c[q];
+        eb += sg;
+        cnt[v] = 0;  // the scatter's cursors
+    }
+}
+
+// Largest u in [lo, hi) with off[u] <= e (off[lo] <= e): the source of edge e.
+__device__ __forceinline__ uint64_t source_of(const uint64_t* __restrict__ off, uint64_t lo, uint64_t hi, uint64_t e) {
+    while (hi - lo > 1) {
+        const uint64_t mid = lo + (hi - lo) / 2;
+        if (off[mid] <= e)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// A wave takes 64 consecutive edges: it finds the sources of the first and the last, and each
+// lane its own between them.
+__global__ __launch_bounds__(256) void k_in_scatter(const uint64_t* __restrict__ off, const uint32_t* __restrict__ col,
+                                                    uint32_t vmask, uint64_t m, uint64_t n,
+                                                    const uint64_t* __restrict__ toff, uint32_t* __restrict__ cur,
+                                                    uint32_t* __restrict__ tsrc, uint32_t* __restrict__ tdst) {
+    for (uint64_t e0 = (blockIdx.x * 256ull + threadIdx.x) & ~63ull; e0 < m; e0 += (uint64_t)gridDim.x * 256) {
+        const uint64_t e = e0 + (threadIdx.x & 63);
+        const uint64_t u0 = source_of(off, 0, n, e0);
+        const uint64_t u1 = source_of(off, u0, n, min(e0 + 63, m - 1));
+        if (e >= m) continue;
+        const uint64_t u = source_of(off, u0, u1 + 1, e);
+        const uint32_t v = col[e] & vmask;
+        if (v < n) {
+            const uint64_t at = toff[v] + atomicAdd(cur + v, 1u);
+            tsrc[at] = (uint32_t)u;
+            tdst[at] = v;
+        }
+    }
+}
+
+// Personalized PageRank over in-edges.  Two forms by the width of a value row, S = 2^LSH:
+//
+// Rows of 16 lanes and more (k_ppr_pull_runs): S threads take a run of IN_RUN consecutive
+// in-edges, S of them at a time: each thread loads one edge's source, destination and lane
+// mask, then all of them add the sources' share rows, one lane per thread, IN_UNROLL rows in
+// flight, and hand the sums over whenever the destination changes.  A destination inside the
+// run is written with plain stores (its sums are zero before); the run's first and last one
+// may continue in the neighbouring runs and are added atomically.
+//
+// Narrower rows (k_ppr_pull_segs): 16 threads take a segment of one vertex's in-list, 16 / S
+// of its edges at once.
+//
+// Bound by the gathered rows; before, a wave per vertex waited through six dependent loads for
+// the few edges of an average in-list.  Measured per dense step on R-MAT 20 with 64 lanes
+// (16M edges, 256-byte rows): see kPullShare.
+constexpr int IN_UNROLL = 8;
+constexpr uint32_t IN_RUN = 128;
+
+// The sums of a destination handed over by one run of S threads (lane ln of the row each).
+template <int LSH>
+__device__ __forceinline__ void ppr_hand_over(const AlgoState& s, uint32_t v, uint32_t ln, double acc, uint64_t m,
+                                              bool shared) {
+    if (!m) return;
+    double* av = s.lacc + ((uint64_t)v << LSH);
+    if (shared) {
+        if ((m >> ln) & 1) unsafeAtomicAdd(av + ln, acc);
+        if (ln == 0) atomicOr((unsigned long long*)(s.mnext + v), (unsigned long long)m);
+    } else {
+        av[ln] = acc;
+        if (ln == 0) s.mnext[v] = m;
+    }
+    if (ln == 0) {
+        const uint32_t bit = 1u << (v & 31);
+        if (!(s.next[v >> 5] & bit)) atomicOr(s.next + (v >> 5), bit);
+    }
+}
+
+template <int LSH>
+__global__ __launch_bounds__(256) void k_ppr_pull_runs(AlgoState s, const uint32_t* __restrict__ tsrc,
+                                                       const uint32_t* __restrict__ tdst, uint64_t m) {
+    constexpr uint32_t S = 1u << LSH;
+    const uint32_t lane = threadIdx.x & 63, ln = lane & (S - 1), g0 = lane & ~(S - 1);
+    const uint64_t groups = (uint64_t)gridDim.x * (256u >> LSH);
+    const uint64_t runs = (m + IN_RUN - 1) / IN_RUN;
+    const uint64_t first = (blockIdx.x * 256ull + threadIdx.x) >> LSH;
+    // whole waves stay together: a group past the last run goes through the loop with no edges
+    for (uint64_t w0 = first - (lane >> LSH); w0 < runs; w0 += groups) {
+        const uint64_t run = w0 + (lane >> LSH);
+        const uint64_t b = min(run * IN_RUN, m), e = min(b + IN_RUN, m);
+        uint32_t cur = UNREACHED;
+        bool head = b > 0 && b < e && tdst[b - 1] == tdst[b];  // the first destination began earlier
+        double acc = 0.0;
+        uint64_t got = 0;
+        for (uint32_t k = 0; k < IN_RUN; k += S) {
+            const uint64_t i = b + k + ln;
+            const bool in = i < e;
+            const uint32_t u = in ? tsrc[i] : 0u, d = in ? tdst[i] : UNREACHED;
+            const uint64_t mu = in ? s.mcur[u] : 0ull;
+            for (uint32_t t = 0; t < S; t += IN_UNROLL) {
+                float x[IN_UNROLL];
+                uint32_t dd[IN_UNROLL];
+                uint64_t mm[IN_UNROLL];
+#pragma unroll
+                for (int r = 0; r < IN_UNROLL; r++) {
+                    uint32_t uu;
+                    if constexpr (LSH == 6) {
+                        uu = __builtin_amdgcn_readlane(u, t + r);
+                        dd[r] = __builtin_amdgcn_readlane(d, t + r);
+                        mm[r] = (uint32_t)__builtin_amdgcn_readlane((uint32_t)mu, t + r) |
+                                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mu >> 32), t + r) << 32;
+                    } else {
+                        uu = __shfl(u, g0 + t + r, 64);
+                        dd[r] = __shfl(d, g0 + t + r, 64);
+                        mm[r] = __shfl((uint32_t)mu, g0 + t + r, 64);
+                    }
+                    x[r] = mm[r] ? s.lx[((uint64_t)uu << LSH) + ln] : 0.0f;
+                }
+#pragma unroll
+                for (int r = 0; r < IN_UNROLL; r++) {
+                    if (dd[r] != cur) {
+                        if (cur != UNREACHED) ppr_hand_over<LSH>(s, cur, ln, acc, got, head);
+                        if (cur != UNREACHED) head = false;
+                        cur = dd[r];
+                        acc = 0.0;
+                        got = 0;
+                    }
+                    acc += (double)x[r];
+                    got |= mm[r];
+                }
+            }
+        }
+        // the last destination: past a short run's end it has been handed over already
+        if (cur != UNREACHED) ppr_hand_over<LSH>(s, cur, ln, acc, got, head || (e < m && tdst[e] == cur));
+    }
+}
+
+template <int LSH>
+__global__ __launch_bounds__(256) void k_ppr_pull_segs(AlgoState s, const uint64_t* __restrict__ toff,
+                                                       const uint32_t* __restrict__ soff,
+                                                       const uint32_t* __restrict__ seg_v,
+                                                       const uint32_t* __restrict__ tsrc, uint32_t nseg) {
+    constexpr uint32_t S = 1u << LSH, W = 16, E = W / S;
+    const uint32_t sl = threadIdx.x & (W - 1), grp = sl >> LSH, ln = sl & (S - 1);
+    const uint32_t groups = gridDim.x * (256 / W);
+    for (uint32_t sg = (blockIdx.x * 256 + threadIdx.x) / W; sg < nseg; sg += groups) {  // uniform over 16 threads
+        const uint32_t v = seg_v[sg];
+        const uint32_t s0 = soff[v];
+        const bool multi = soff[v + 1] - s0 > 1;
+        const uint64_t b = toff[v] + (uint64_t)(sg - s0) * IN_SEG;
+        const uint64_t e = min(b + IN_SEG, toff[v + 1]);
+        double acc = 0.0;
+        uint32_t m = 0;  // S <= 8 lanes
+        for (uint64_t i = b; i < e; i += W) {
+            const bool in = i + sl < e;
+            const uint32_t u = in ? tsrc[i + sl] : 0u;
+            const uint32_t mu = in ? (uint32_t)s.mcur[u] : 0u;
+            m |= mu;
+            float x[S];
+#pragma unroll
+            for (uint32_t t = 0; t < S; t++) {
+                const uint32_t q = t * E + grp;
+                const uint32_t uu = __shfl(u, q, W), mm = __shfl(mu, q, W);
+                x[t] = mm ? s.lx[((uint64_t)uu << LSH) + ln] : 0.0f;
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < S; t++) acc += (double)x[t];
+        }
+#pragma unroll
+        for (uint32_t d = W / 2; d >= 1; d >>= 1) m |= __shfl_xor(m, d, W);
+#pragma unroll
+        for (uint32_t d = S; d < W; d <<= 1) acc += __shfl_xor(acc, (int)d, W);
+        if (grp == 0) ppr_hand_over<LSH>(s, v, ln, acc, m, multi);
+    }
+}
+
 // ------------------------------------------------- PageRank gather plan
 // The pairs of a piece, kept sorted by destination bin between iterations: the source id
 // and the 16-bit place of the destination in its bin's LDS sums.  An iteration then reads 6
@@ -2267,13 +2531,45 @@ hipError_t launch_reset_lanes(const AlgoState& s, uint64_t mask, hipStream_t st)
 
 hipError_t launch_ppr_prepare(const AlgoState& s, const uint64_t* off, hipStream_t st) {
     if (!s.n) return hipSuccess;
-    k_ppr_prepare<<<grid_for(s.n, 256, 8192), 256, 0, st>>>(s, off);
+    k_ppr_prepare<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, off);
     return hipGetLastError();
 }
 
 hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st) {
     if (!s.n) return hipSuccess;
-    k_ppr_apply<<<grid_for(s.n, 256, 8192), 256, 0, st>>>(s, damping);
+    k_ppr_apply<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, damping);
+    return hipGetLastError();
+}
+
+hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t n,
+                           uint32_t* cnt, uint64_t* tot, uint64_t* toff, uint32_t* soff, uint32_t* seg_v,
+                           uint32_t* tsrc, uint32_t* tdst, hipStream_t st) {
+    if (!n || !m) return hipErrorInvalidValue;
+    const uint64_t tiles = in_tiles(n);
+    hipError_t e = launch_fill_u32(cnt, n, 0u, st);
+    if (e != hipSuccess) return e;
+    k_in_count<<<grid_for(m, 256, 16384), 256, 0, st>>>(col, vmask, m, n, cnt);
+    k_in_tot<<<(unsigned)tiles, 256, 0, st>>>(cnt, n, tot);
+    k_in_base<<<1, 64, 0, st>>>(tiles, tot, n, toff, soff);
+    k_in_write<<<(unsigned)tiles, 256, 0, st>>>(cnt, n, tot, toff, soff, seg_v);
+    k_in_scatter<<<grid_for(m, 256, 16384), 256, 0, st>>>(off, col, vmask, m, n, toff, cnt, tsrc, tdst);
+    return hipGetLastError();
+}
+
+hipError_t launch_ppr_pull(const AlgoState& s, const uint64_t* toff, const uint32_t* soff, const uint32_t* seg_v,
+                           const uint32_t* tsrc, const uint32_t* tdst, uint64_t m, uint32_t nseg, hipStream_t st) {
+    if (!nseg) return hipSuccess;
+    const unsigned gs = grid_for(nseg, 16, GRID_CAP), gr = grid_for((m + IN_RUN - 1) / IN_RUN, 256u >> s.lshift, GRID_CAP);
+    switch (s.lshift) {
+    case 0: k_ppr_pull_segs<0><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
+    case 1: k_ppr_pull_segs<1><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
+    case 2: k_ppr_pull_segs<2><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
+    case 3: k_ppr_pull_segs<3><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
+    case 4: k_ppr_pull_runs<4><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
+    case 5: k_ppr_pull_runs<5><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
+    case 6: k_ppr_pull_runs<6><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

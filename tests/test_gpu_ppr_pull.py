@@ -1,0 +1,66 @@
+"""GPU: personalized PageRank steps over the in-edge lists (dense steps of graphs without a
+budget) against the FP64 oracle: row widths from 1 to 64 lanes, edge counts around a run's 128
+edges and a segment's 256, and in-lists spanning many runs and segments."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+import paper_2208_14935_amd as hy
+
+pytestmark = pytest.mark.gpu
+
+
+def star(n, m):
+    spokes = np.arange(1, m + 1, dtype=np.uint32)
+    hub = np.zeros(m, dtype=np.uint32)
+    return gen.from_pairs(n, np.concatenate([spokes, hub]), np.concatenate([hub, spokes]))
+
+
+def ring(n):
+    """n vertices of one in- and one out-edge, and an isolated one."""
+    v = np.arange(n, dtype=np.uint32)
+    return gen.from_pairs(n + 1, v, (v + 1) % n)
+
+
+GRAPHS = {
+    "2 edges": lambda: ring(2),
+    "127 edges": lambda: ring(127),
+    "128 edges": lambda: ring(128),
+    "129 edges": lambda: ring(129),
+    "star": lambda: star(3000, 2500),
+    "er": lambda: gen.er(1001, 9000, seed=5),
+    "rmat": lambda: gen.rmat(11, 16, seed=11),
+}
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 3, 8, 9, 17, 33, 64])
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_pulled_steps_match_oracle(name, lanes):
+    off, col = GRAPHS[name]()
+    rng = np.random.default_rng(lanes)
+    srcs = rng.choice(np.nonzero(np.diff(off.astype(np.int64)))[0], lanes).astype(np.uint32)
+    srcs[-1] = srcs[0]  # a repeated source
+    with hy.Graph(off, col) as g:
+        got, iters, _ = g.run_batch("ppr", srcs)
+        again, _, _ = g.run_batch("ppr", srcs)
+    assert (iters == 10).all()
+    for l, s in enumerate(srcs):
+        want = oracle.ppr(off, col, int(s), 0.85, 10)
+        for x in (got[l], again[l]):
+            # per step one FP32 rounding of the share and one of the value, sums in FP64: ten
+            # steps keep every value within 20 * 2^-24 = 1.2e-6 of itself
+            assert np.all(np.abs(x - want) <= 1.3e-6 * want + 1e-30)
+
+
+def test_in_lists_are_given_up_for_a_budget():
+    off, col = gen.rmat(12, 16, seed=12)
+    with hy.Graph(off, col) as g:
+        g.set_params(partition_edges=2048, compact_chunk_edges=4096)
+        want = oracle.ppr(off, col, 7, 0.85, 10)
+        for budget in (False, True, False):
+            if budget:
+                g.set_resident_fraction("ppr", 0.4)
+            else:
+                g.set_budget(None)
+            assert np.abs(g.run("ppr", 7).values - want).max() <= 1e-6
