@@ -60,7 +60,7 @@ struct SelParams {
     uint32_t zc_tie;      // 1: a Tiz = Tef tie selects zero-copy instead of filter
 };
 
-// Written by the scan kernel, copied to the host every iteration.
+// Written by the scan, into pinned host memory or copied there, every iteration.
 struct Header {
     uint32_t seg_parts[NSEG];
     uint32_t seg_list_start[NSEG];
@@ -68,9 +68,11 @@ struct Header {
     uint64_t seg_work_start[NSEG];
     uint64_t seg_work_total[NSEG];
     uint64_t seg_edges[NSEG];
-    uint64_t seg_cost_lines[NSEG];
     uint64_t total_active;   // list entries (active vertices with out-edges)
     uint64_t frontier;       // all active vertices, including those without out-edges
+    uint64_t lanes;          // batched runs: the lanes active at some vertex
+    uint64_t overflow;       // the SSSP overflow words when the selection ran
+    uint64_t seq;            // number of the selection, stored after everything else (launch_scan_one)
 };
 
 // Edge word layout.  shift < 32: neighbour and weight share one word, neighbour in the low
@@ -227,16 +229,35 @@ hipError_t launch_pg_apply(uint64_t n, const uint64_t* off, float* x, float* con
 hipError_t launch_init(const AlgoState& s, uint64_t n, uint32_t source, float pr_x0, float* pr_x, uint32_t* cur,
                        uint32_t nwords, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStream_t st);
+// p[0, np) and q[0, nq) in one launch.
+hipError_t launch_fill2_u32(uint32_t* p, uint64_t np, uint32_t* q, uint64_t nq, uint32_t value, hipStream_t st);
 
-hipError_t launch_stats_select(uint32_t npart, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
-                               const SelParams& sp, uint8_t* mode, uint32_t* nA, uint32_t* nF, uint64_t* Ea,
-                               uint64_t* Rq, uint64_t* K, hipStream_t st);
+// Partitions cut into units of at most 64 aligned windows of 64 vertices, in order: unit u
+// covers partition part[u]'s windows q[u] .. q[u] + 63; partition i's units are first[i] ..
+// first[i + 1).  multi: the partitions of several units; rec: one record per unit (those of
+// the other partitions are not used).
+struct UnitRec {
+    uint32_t c, f;       // list entries, active vertices
+    uint64_t ea, kl;     // their edges, kernel lines
+    uint64_t rq;         // request lines (both arrays)
+    uint64_t first, last, first_w, last_w;  // (line + 1) of the first and last line, 0 = none
+};
+struct Units {
+    uint32_t count, multis;
+    const uint32_t *part, *q, *first, *multi;
+    UnitRec* rec;
+};
+constexpr uint32_t UNIT_WINDOWS = 64;
+// Statistics and engine of every partition.  clear (or null): nwords words to zero; mcur and
+// lanes (or null): *lanes |= the lane masks of the active vertices.
+hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
+                               const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
+                               unsigned long long* lanes, const SelParams& sp, uint8_t* mode, uint32_t* nA,
+                               uint32_t* nF, uint64_t* Ea, uint64_t* K, hipStream_t st);
 
 // Batched runs: initialise lane masks, lane values and the union frontier.
 hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_t* cur_union, uint32_t nwords,
                              hipStream_t st);
-// OR of the lane masks of all vertices into *lanes (one uint64, zeroed by the caller).
-hipError_t launch_lane_union(const uint64_t* mask, uint64_t n, unsigned long long* lanes, hipStream_t st);
 // Rows k = 0.. of out (n values each) <- the lanes of `set` in increasing lane order,
 // from n rows of 2^lshift 32-bit values; with sub_base, a value other than UNREACHED has
 // the lane's base subtracted (BFS levels of lanes that joined late).  order (or null):
@@ -298,12 +319,32 @@ constexpr int SCAN_THREADS = 512;
 constexpr int SCAN_PER = 8;                                        // partitions per thread
 constexpr uint32_t SCAN_TILE = (uint32_t)SCAN_THREADS * SCAN_PER;  // partitions per workgroup
 inline uint32_t scan_tiles(uint32_t npart) { return (npart + SCAN_TILE - 1) / SCAN_TILE; }
-inline uint64_t scan_scratch_words(uint32_t npart) { return (uint64_t)std::max(scan_tiles(npart), 1u) * (7 * NSEG + 1); }
+inline uint64_t scan_scratch_words(uint32_t npart) { return (uint64_t)std::max(scan_tiles(npart), 1u) * (6 * NSEG + 1); }
+// Header words besides the scan's (each may be null): *lanes is reported and cleared,
+// overflow's two words are reported.
+struct ScanExtra {
+    uint64_t* lanes;
+    const uint32_t* overflow;
+};
 hipError_t launch_scan(uint32_t npart, const uint8_t* mode, const uint32_t* nA, const uint32_t* nF,
-                       const uint64_t* Ea, const uint64_t* Rq, const uint64_t* K, uint32_t* lbase, uint64_t* wbase,
-                       Header* hdr, uint64_t* wpre, uint64_t* scratch, hipStream_t st);
+                       const uint64_t* Ea, const uint64_t* K, uint32_t* lbase, uint64_t* wbase, Header* hdr,
+                       uint64_t* wpre, uint64_t* scratch, const ScanExtra& x, hipStream_t st);
+// The same in one launch for up to SCAN_ONE_MAX partitions, with the header written to pinned
+// host memory (device addresses), beside it, unless null, the host's copies of lbase, wbase
+// and mode, and after them seq into hdr->seq.
+constexpr uint32_t SCAN_ONE_MAX = 16384;
+struct ScanHost {
+    Header* hdr;
+    uint64_t* wbase;
+    uint32_t* lbase;
+    uint8_t* mode;
+    uint64_t seq;
+};
+hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* nA, const uint32_t* nF,
+                           const uint64_t* Ea, const uint64_t* K, uint32_t* lbase, uint64_t* wbase, uint64_t* wpre,
+                           const ScanExtra& x, const ScanHost& host, hipStream_t st);
 
-hipError_t launch_build_lists(uint32_t npart, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
+hipError_t launch_build_lists(const Units& un, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
                               const uint8_t* mode, const uint32_t* lbase, const uint64_t* wbase, uint32_t* list,
                               uint64_t* wpre, hipStream_t st);
 

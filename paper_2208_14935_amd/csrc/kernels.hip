@@ -1,14 +1,15 @@
 // Device side of the hybrid-transfer traversal, written for gfx950 (wave64).
 //
 // Per iteration (Sec. 4 overview, Algorithm 1):
-//   k_stats_select  one wave per partition: active vertices, active edges and request
-//                   lines from the frontier bitmap, then the engine choice of Sec. 5.1
-//                   (Eq. 1-3, alpha/beta rule) in exact integer arithmetic;
+//   k_unit_stats    one wave per run of at most 4,096 vertices of a partition: active vertices,
+//                   active edges and request lines from the frontier bitmap, then (in
+//                   k_part_combine for partitions of several runs) the engine choice of
+//                   Sec. 5.1 (Eq. 1-3, alpha/beta rule) in exact integer arithmetic;
 //   k_scan_*        per-engine prefix sums over partitions (tile totals, tile bases,
 //                   offsets), which place every partition's active vertices in one list
 //                   ordered by engine segment and partition ("pre-combine" of Vc and Vz,
 //                   Algorithm 1);
-//   k_build_lists   one wave per scheduled partition: ordered compaction of its active
+//   k_build_lists   one wave per run of a scheduled partition: ordered compaction of its active
 //                   vertices into the list plus the work prefix (edges, or 128-byte
 //                   lines for zero-copy) used for load balancing;
 //   k_push_edges    edge-balanced push over a list slice reading device memory
@@ -96,12 +97,18 @@ __device__ __forceinline__ uint8_t select_engine(uint64_t E, uint64_t nA, uint64
 }
 
 // ------------------------------------------------------------------- stats
-// One wave per partition (four partitions per workgroup, no workgroup barriers).  The
-// partition's vertices are taken in rounds of 64 aligned windows of 64 vertices: lane l loads
-// the active bits of window l, a wave scan counts them, and then the round's active vertices
-// are dealt out in order, one per lane, in batches of 64 (SEL_B batches with their offset
-// loads in flight together).  Lanes are busy whatever the density, and where the frontier
-// is dense consecutive lanes hold consecutive vertices, so the offset loads coalesce.
+// One wave per unit (four units per workgroup, no workgroup barriers): a unit is a run of at
+// most 64 aligned windows of 64 vertices of one partition, so a partition of many vertices
+// (they are cut by edges: R-MAT's low-degree tail puts up to 0.5M vertices into one) is
+// walked by many waves.  Lane l loads the active bits of window l, a wave scan counts them,
+// and then the unit's active vertices are dealt out in order, one per lane, in batches of 64
+// (SEL_B batches with their offset loads in flight together).  Lanes are busy whatever the
+// density, and where the frontier is dense consecutive lanes hold consecutive vertices, so
+// the offset loads coalesce.  A partition of one unit is finished here; the units of a larger
+// one leave records that k_part_combine joins.
+// Bound by the offset gathers of scattered frontiers, by latency on small ones.  One wave per
+// partition took, all vertices active, 1.68 + 1.49 ms (statistics + lists) on R-MAT 24 and
+// 0.73 + 0.62 ms on symmetrized R-MAT 21.
 constexpr int SEL_B = 4;
 
 // Active bits of window q (vertices 64 q .. 64 q + 63) restricted to [vb, ve).
@@ -162,9 +169,12 @@ __device__ __forceinline__ uint32_t round_vertex(uint32_t k, uint32_t incl, uint
 // lines per list and distinct (Eq. 3), kernel lines; with a byte weight array its request
 // lines are counted apart (a list of D edges spans D bytes there).  carry / carry_w: (line + 1)
 // of the latest list's last line in each array, 0 = none.
+// lm: the lanes active at the vertices seen (batched runs).
 struct SelAcc {
     uint64_t c = 0, ea = 0, rq = 0, kl = 0, rqd = 0, carry = 0;
     uint64_t rqw = 0, rqdw = 0, carry_w = 0;
+    uint64_t first = 0, first_w = 0;  // (line + 1) of the unit's first list's first line
+    uint64_t lm = 0;
 };
 
 // The lines of a list [s, e) in an array whose lines hold 2^sh entries: (first + 1, last + 1).
@@ -179,7 +189,7 @@ __device__ __forceinline__ void list_lines(uint64_t s, uint64_t e, uint32_t sh, 
 template <int G>
 __device__ __forceinline__ void stats_batches(uint32_t b0, uint32_t T, uint32_t incl, uint32_t cnt, uint64_t wbits,
                                               uint32_t q0, const uint64_t* __restrict__ off, const SelParams& sp,
-                                              SelAcc& a) {
+                                              const uint64_t* __restrict__ mcur, bool lines, SelAcc& a) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t sh = sp.cost_shift, shw = sp.cost_shift + 2;  // byte weights: 4x the entries per line
     const bool bytew = sp.wbytes == 1;
@@ -190,6 +200,7 @@ __device__ __forceinline__ void stats_batches(uint32_t b0, uint32_t T, uint32_t 
         const uint32_t v = round_vertex(k < T ? k : T - 1, incl, cnt, wbits, q0);
         s[g] = off[v];
         e[g] = off[v + 1];
+        if (mcur) a.lm |= mcur[v];
     }
 #pragma unroll
     for (int g = 0; g < G; g++) {
@@ -199,6 +210,9 @@ __device__ __forceinline__ void stats_batches(uint32_t b0, uint32_t T, uint32_t 
         if (has) {
             a.c += 1;
             a.ea += e[g] - s[g];
+        }
+        if (!lines) continue;  // uniform: a resident partition, or one whose engine is forced
+        if (has) {
             a.rq += lines_of(s[g], e[g], sh);
             a.kl += lines_of(s[g], e[g], ZC_LINE_SHIFT);
             list_lines(s[g], e[g], sh, fl, ll);
@@ -211,6 +225,14 @@ __device__ __forceinline__ void stats_batches(uint32_t b0, uint32_t T, uint32_t 
         uint64_t tot;
         const uint64_t ex = wave_exclusive_max(ll, &tot);
         const uint64_t prev = a.carry > ex ? a.carry : ex;
+        if (!a.first) {  // uniform: the first list of the unit holds its smallest line
+            const uint64_t A = __ballot(has);
+            if (A) {
+                const int l0 = (int)__ffsll((unsigned long long)A) - 1;
+                a.first = __shfl(fl, l0, 64);
+                a.first_w = __shfl(flw, l0, 64);
+            }
+        }
         if (has) a.rqd += ll - fl + 1 - (prev == fl ? 1 : 0);
         a.carry = a.carry > tot ? a.carry : tot;
         if (bytew) {  // uniform
@@ -222,60 +244,146 @@ __device__ __forceinline__ void stats_batches(uint32_t b0, uint32_t T, uint32_t 
     }
 }
 
-__global__ __launch_bounds__(256) void k_stats_select(uint32_t npart, const uint32_t* __restrict__ pv,
-                                                      const uint64_t* __restrict__ off,
-                                                      const uint32_t* __restrict__ cur, SelParams sp,
-                                                      uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
-                                                      uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
-                                                      uint64_t* __restrict__ Rq, uint64_t* __restrict__ K) {
+// Engine of a partition from its statistics.
+__device__ __forceinline__ uint8_t engine_of(uint32_t i, uint64_t E, uint64_t c, uint64_t ea, uint64_t rq,
+                                             const SelParams& sp) {
+    if (ea == 0) return P_NONE;
+    if (i < sp.nres) return P_RES;
+    if (sp.force) return (uint8_t)sp.force;
+    return select_engine(E, c, ea, rq, sp);
+}
+
+// clear (or null): a bitmap of nwords words zeroed along the way (the frontier after next).
+// mcur, lanes (or null): *lanes |= the lane masks of the active vertices.
+__global__ __launch_bounds__(256) void k_unit_stats(Units un, const uint32_t* __restrict__ pv,
+                                                    const uint64_t* __restrict__ off,
+                                                    const uint32_t* __restrict__ cur, uint32_t* __restrict__ clear,
+                                                    uint32_t nwords, const uint64_t* __restrict__ mcur,
+                                                    unsigned long long* __restrict__ lanes, SelParams sp,
+                                                    uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
+                                                    uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
+                                                    uint64_t* __restrict__ K) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
-    for (uint32_t i = blockIdx.x * wpb + (threadIdx.x >> 6); i < npart; i += waves) {
+    for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
+        const uint32_t i = un.part[u], q0 = un.q[u];
         const uint32_t vb = pv[i], ve = pv[i + 1];
-        const uint32_t qb = vb >> 6, qe = (ve + 63) >> 6;
+        const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+        const bool one = un.first[i + 1] - un.first[i] == 1;
+        // request lines matter where the cost model decides, kernel lines to zero-copy
+        const bool lines = i >= sp.nres && (!sp.force || sp.force == P_ZC);
         SelAcc a;
+        const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
+        if (clear && q0 + lane < qe) {  // windows shared by two partitions are zeroed by both
+            const uint32_t w = 2 * (q0 + lane);
+            clear[w] = 0;
+            if (w + 1 < nwords) clear[w + 1] = 0;
+        }
         uint64_t f = 0;
-        for (uint32_t q0 = qb; q0 < qe; q0 += 64) {  // uniform across the wave
-            const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
-            if (!__ballot(wbits != 0)) continue;
+        if (__ballot(wbits != 0)) {
             const uint32_t cnt = __popcll(wbits);
             const uint32_t incl = wave_inclusive_sum_u32(cnt);
             const uint32_t T = __shfl(incl, 63, 64);
-            f += cnt;
-            // a round of at most 64 active vertices takes one batch, larger ones SEL_B at a time
+            f = T;
+            // at most 64 active vertices take one batch, more SEL_B at a time
             if (T <= 64)
-                stats_batches<1>(0, T, incl, cnt, wbits, q0, off, sp, a);
+                stats_batches<1>(0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
             else
                 for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
-                    stats_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, sp, a);
+                    stats_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
+            a.c = wave_sum(a.c);
+            a.ea = wave_sum(a.ea);
+            if (lines) {
+                // request lines: the neighbour array, and the weight array beside it (Eq. 3)
+                a.rq = wave_sum(sp.rq_distinct ? a.rqd : a.rq);
+                if (sp.wbytes == 1)
+                    a.rq += wave_sum(sp.rq_distinct ? a.rqdw : a.rqw);
+                else if (sp.wbytes)
+                    a.rq *= 2;  // 4-byte weights: the neighbour array's lines again
+                a.kl = wave_sum(a.kl);
+            }
+            if (mcur) {
+#pragma unroll
+                for (int d = 32; d >= 1; d >>= 1) a.lm |= __shfl_xor(a.lm, d, 64);
+                if (lane == 0 && (a.lm & ~(uint64_t)*lanes)) atomicOr(lanes, (unsigned long long)a.lm);
+            }
         }
-        const uint64_t c = wave_sum(a.c);
-        f = wave_sum(f);
-        const uint64_t ea = wave_sum(a.ea);
-        // request lines: the neighbour array, and the weight array beside it (Eq. 3)
-        uint64_t rq = wave_sum(sp.rq_distinct ? a.rqd : a.rq);
-        if (sp.wbytes == 1)
-            rq += wave_sum(sp.rq_distinct ? a.rqdw : a.rqw);
-        else if (sp.wbytes)
-            rq *= 2;  // 4-byte weights: the neighbour array's lines again
-        const uint64_t kl = wave_sum(a.kl);
-        if (lane == 0) {
-            uint8_t p;
-            if (ea == 0)
-                p = P_NONE;
-            else if (i < sp.nres)
-                p = P_RES;
-            else if (sp.force)
-                p = (uint8_t)sp.force;
-            else
-                p = select_engine(off[ve] - off[vb], c, ea, rq, sp);
-            mode[i] = p;
-            nA[i] = (uint32_t)c;
+        if (lane != 0) continue;
+        if (one) {
+            mode[i] = engine_of(i, off[ve] - off[vb], a.c, a.ea, a.rq, sp);
+            nA[i] = (uint32_t)a.c;
             nF[i] = (uint32_t)f;
-            Ea[i] = ea;
-            Rq[i] = rq;
-            K[i] = kl;
+            Ea[i] = a.ea;
+            K[i] = a.kl;
+        } else {
+            UnitRec r;
+            r.c = (uint32_t)a.c;
+            r.f = (uint32_t)f;
+            r.ea = a.ea;
+            r.kl = a.kl;
+            r.rq = a.rq;
+            r.first = a.first;
+            r.last = a.carry;
+            r.first_w = a.first_w;
+            r.last_w = a.carry_w;
+            un.rec[u] = r;
         }
+    }
+}
+
+// Partitions of several units, one wave each: the units' records joined (a line that one
+// unit's last list ends and the next one's first list starts in counts once where distinct
+// lines are counted), the engine chosen, and every record turned into the list entries, edges
+// and lines of the partition's earlier units, where the unit's part of the lists starts.
+__global__ __launch_bounds__(256) void k_part_combine(Units un, const uint32_t* __restrict__ pv,
+                                                      const uint64_t* __restrict__ off, SelParams sp,
+                                                      uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
+                                                      uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
+                                                      uint64_t* __restrict__ K) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= un.multis) return;  // the same for the whole wave
+    const uint32_t i = un.multi[k];
+    const uint32_t u0 = un.first[i], u1 = un.first[i + 1];
+    uint64_t c = 0, f = 0, ea = 0, kl = 0, rq = 0, dup = 0, last = 0, last_w = 0;
+    const uint64_t twice = sp.wbytes == 4 ? 2 : 1;
+    for (uint32_t b = u0; b < u1; b += 64) {
+        const bool in = b + lane < u1;
+        UnitRec r{};
+        if (in) r = un.rec[b + lane];
+        uint64_t tc, te, tk, tot, totw;
+        const uint64_t xc = wave_exclusive_sum(r.c, &tc);
+        const uint64_t xe = wave_exclusive_sum(r.ea, &te);
+        const uint64_t xk = wave_exclusive_sum(r.kl, &tk);
+        f += wave_sum(r.f);
+        rq += wave_sum(r.rq);
+        // the last line of the latest earlier list (lines never decrease along the units)
+        uint64_t pl = wave_exclusive_max(r.last, &tot), plw = wave_exclusive_max(r.last_w, &totw);
+        if (last > pl) pl = last;
+        if (last_w > plw) plw = last_w;
+        uint64_t d = r.first && pl == r.first ? twice : 0;
+        if (r.first_w && plw == r.first_w) d += 1;
+        dup += wave_sum(d);
+        if (in) {
+            UnitRec o = r;
+            o.c = (uint32_t)(c + xc);
+            o.ea = ea + xe;
+            o.kl = kl + xk;
+            un.rec[b + lane] = o;
+        }
+        c += tc;
+        ea += te;
+        kl += tk;
+        last = last > tot ? last : tot;
+        last_w = last_w > totw ? last_w : totw;
+    }
+    if (lane == 0) {
+        if (sp.rq_distinct) rq -= dup;
+        mode[i] = engine_of(i, off[pv[i + 1]] - off[pv[i]], c, ea, rq, sp);
+        nA[i] = (uint32_t)c;
+        nF[i] = (uint32_t)f;
+        Ea[i] = ea;
+        K[i] = kl;
     }
 }
 
@@ -298,12 +406,13 @@ __global__ void k_select_only(uint64_t npart, const uint64_t* __restrict__ E, co
 }
 
 // -------------------------------------------------------------------- scan
-// The engine segments' list and work offsets and the selection header, in three launches:
-// per tile of SCAN_TILE partitions the totals of every value (one workgroup per tile), then
-// the segment starts and each tile's bases from the tile totals (one small workgroup), then
-// per tile the offsets of each partition (one workgroup per tile).  Every thread takes a
-// contiguous run of SCAN_PER partitions, so a workgroup needs one barrier per pass.
-constexpr int SCAN_NV = 5 * NSEG + 1;  // cnt[4], work[4], parts[4], edges[4], lines[4], frontier
+// The engine segments' list and work offsets and the selection header.  Up to SCAN_ONE_MAX
+// partitions one workgroup does it (k_scan_one below); past that, three launches: per tile of
+// SCAN_TILE partitions the totals of every value (one workgroup per tile), then the segment
+// starts and each tile's bases from the tile totals (one small workgroup), then per tile the
+// offsets of each partition (one workgroup per tile).  Every thread takes a contiguous run of
+// partitions, so a workgroup needs one barrier per pass.
+constexpr int SCAN_NV = 4 * NSEG + 1;  // cnt[4], work[4], parts[4], edges[4], frontier
 constexpr int SCAN_NB = 2 * NSEG;      // scanned per segment: list entries, work items
 constexpr int SCAN_NW = SCAN_THREADS / 64;
 
@@ -311,7 +420,7 @@ constexpr int SCAN_NW = SCAN_THREADS / 64;
 template <int NV>
 __device__ __forceinline__ void scan_run_sums(uint32_t i0, uint32_t i1, const uint8_t* __restrict__ mode,
                                               const uint32_t* __restrict__ nA, const uint32_t* __restrict__ nF,
-                                              const uint64_t* __restrict__ Ea, const uint64_t* __restrict__ Rq,
+                                              const uint64_t* __restrict__ Ea,
                                               const uint64_t* __restrict__ K, uint64_t (&val)[NV]) {
 #pragma unroll
     for (int k = 0; k < NV; k++) val[k] = 0;
@@ -328,7 +437,6 @@ __device__ __forceinline__ void scan_run_sums(uint32_t i0, uint32_t i1, const ui
             if (NV == SCAN_NV) {
                 val[2 * NSEG + sg] += 1;
                 val[3 * NSEG + sg] += ea;
-                val[4 * NSEG + sg] += Rq[i];
             }
         }
     }
@@ -336,13 +444,13 @@ __device__ __forceinline__ void scan_run_sums(uint32_t i0, uint32_t i1, const ui
 
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_tot(uint32_t npart, const uint8_t* __restrict__ mode,
                                                    const uint32_t* __restrict__ nA, const uint32_t* __restrict__ nF,
-                                                   const uint64_t* __restrict__ Ea, const uint64_t* __restrict__ Rq,
-                                                   const uint64_t* __restrict__ K, uint64_t* __restrict__ tile_tot) {
+                                                   const uint64_t* __restrict__ Ea, const uint64_t* __restrict__ K,
+                                                   uint64_t* __restrict__ tile_tot) {
     __shared__ uint64_t s_tot[SCAN_NW][SCAN_NV];
     const uint32_t i0 = min(blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_PER, npart), i1 = min(i0 + SCAN_PER, npart);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     uint64_t val[SCAN_NV];
-    scan_run_sums<SCAN_NV>(i0, i1, mode, nA, nF, Ea, Rq, K, val);
+    scan_run_sums<SCAN_NV>(i0, i1, mode, nA, nF, Ea, K, val);
 #pragma unroll
     for (int k = 0; k < SCAN_NV; k++) {
         const uint64_t v = wave_sum(val[k]);
@@ -356,12 +464,161 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_tot(uint32_t npart, const
     }
 }
 
+// The header's words besides the scan's: the lanes met (their word is cleared for the next
+// selection) and the overflow lanes.
+__device__ __forceinline__ void scan_extra(Header* hdr, const ScanExtra& x) {
+    hdr->lanes = x.lanes ? *x.lanes : 0;
+    if (x.lanes) *x.lanes = 0;
+    hdr->overflow = x.overflow ? x.overflow[0] | ((uint64_t)x.overflow[1] << 32) : 0;
+}
+
+// One workgroup for up to 1024 * PER partitions, each thread a run of PER held in registers;
+// segments without partitions (three of four when everything is resident) are skipped.  The
+// header goes straight to pinned host memory, and after it (and the partitions' bases and
+// modes, where the host asks for them) its number, which the host polls: no copy and no
+// synchronisation between the selection and the pushes, and the list kernel overlaps the
+// host's launches.  Bound by latency.  Measured per selection on R-MAT 22 (2,036 partitions):
+// the three launches took 25 us of kernels, this one 8 us.
+template <int PER>
+__global__ __launch_bounds__(1024) void k_scan_one(uint32_t npart, const uint8_t* __restrict__ mode,
+                                                   const uint32_t* __restrict__ nA, const uint32_t* __restrict__ nF,
+                                                   const uint64_t* __restrict__ Ea, const uint64_t* __restrict__ K,
+                                                   uint32_t* __restrict__ lbase, uint64_t* __restrict__ wbase,
+                                                   uint64_t* __restrict__ wpre, ScanExtra x, ScanHost host) {
+    constexpr int NW = 16;
+    // per segment and wave: list entries, work, partitions, edges; then the waves' bases
+    __shared__ uint64_t s_t[NSEG][4][NW];
+    __shared__ uint64_t s_f[NW];
+    __shared__ uint64_t s_tot[NSEG][4];
+    __shared__ uint32_t s_present;
+    const uint32_t t = threadIdx.x, lane = t & 63, wid = t >> 6, i0 = t * PER;
+    uint32_t m[PER], na[PER];
+    uint64_t ea[PER], wk[PER], f = 0;
+    uint32_t has = 0;
+#pragma unroll
+    for (int r = 0; r < PER; r++) {
+        const uint32_t i = i0 + r;
+        const bool in = i < npart;
+        m[r] = in ? mode[i] : (uint32_t)P_NONE;
+        na[r] = in ? nA[i] : 0u;
+        ea[r] = in ? Ea[i] : 0ull;
+        wk[r] = in ? K[i] : 0ull;
+        f += in ? nF[i] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < PER; r++) {
+        has |= 1u << m[r];
+        if (m[r] != P_ZC) wk[r] = ea[r];
+    }
+    if (t == 0) s_present = 0;
+    for (uint32_t q = t; q < NSEG * 4 * NW; q += 1024) (&s_t[0][0][0])[q] = 0;
+    f = wave_sum(f);
+    if (lane == 0) s_f[wid] = f;
+    __syncthreads();
+    uint32_t wave_has = 0;
+#pragma unroll
+    for (int sg = 0; sg < NSEG; sg++)
+        if (__ballot((has >> (sg + 1)) & 1)) wave_has |= 1u << sg;
+    if (lane == 0 && wave_has) atomicOr(&s_present, wave_has);
+    uint64_t xc[NSEG], xw[NSEG];
+#pragma unroll
+    for (int sg = 0; sg < NSEG; sg++) {
+        xc[sg] = xw[sg] = 0;
+        if (!((wave_has >> sg) & 1)) continue;  // uniform across the wave
+        uint64_t c = 0, w = 0, e = 0;
+        uint32_t p = 0;
+#pragma unroll
+        for (int r = 0; r < PER; r++)
+            if (m[r] == (uint32_t)sg + 1) {
+                c += na[r];
+                w += wk[r];
+                e += ea[r];
+                p += 1;
+            }
+        uint64_t tc, tw;
+        xc[sg] = wave_exclusive_sum(c, &tc);
+        xw[sg] = wave_exclusive_sum(w, &tw);
+        const uint64_t tp = wave_sum(p), te = sg == SEG_Z ? wave_sum(e) : tw;
+        if (lane == 0) {
+            s_t[sg][0][wid] = tc;
+            s_t[sg][1][wid] = tw;
+            s_t[sg][2][wid] = tp;
+            s_t[sg][3][wid] = te;
+        }
+    }
+    __syncthreads();
+    if (t < NSEG * 4) {
+        const int sg = t >> 2, k = t & 3;
+        uint64_t run = 0;
+        for (int w = 0; w < NW; w++) {
+            const uint64_t y = s_t[sg][k][w];
+            s_t[sg][k][w] = run;
+            run += y;
+        }
+        s_tot[sg][k] = run;
+    }
+    __syncthreads();
+    uint64_t la = 0, wa = 0, bc[NSEG], bw[NSEG];
+#pragma unroll
+    for (int sg = 0; sg < NSEG; sg++) {
+        bc[sg] = la + s_t[sg][0][wid] + xc[sg];
+        bw[sg] = wa + s_t[sg][1][wid] + xw[sg];
+        la += s_tot[sg][0];
+        wa += s_tot[sg][1];
+    }
+#pragma unroll
+    for (int r = 0; r < PER; r++) {
+        const uint32_t i = i0 + r;
+        if (i >= npart) break;
+        uint32_t lb = 0xFFFFFFFFu;
+        uint64_t wb = ~0ull;
+#pragma unroll
+        for (int sg = 0; sg < NSEG; sg++)
+            if (m[r] == (uint32_t)sg + 1) {
+                lb = (uint32_t)bc[sg];
+                wb = bw[sg];
+                bc[sg] += na[r];
+                bw[sg] += wk[r];
+            }
+        lbase[i] = lb;
+        wbase[i] = wb;
+        if (host.mode) {
+            host.lbase[i] = lb;
+            host.wbase[i] = wb;
+            host.mode[i] = (uint8_t)m[r];
+        }
+    }
+    if (t == 0) {
+        Header* hdr = host.hdr;
+        uint64_t l = 0, w = 0, fr = 0;
+#pragma unroll
+        for (int sg = 0; sg < NSEG; sg++) {
+            hdr->seg_parts[sg] = (uint32_t)s_tot[sg][2];
+            hdr->seg_list_start[sg] = (uint32_t)l;
+            hdr->seg_list_count[sg] = (uint32_t)s_tot[sg][0];
+            hdr->seg_work_start[sg] = w;
+            hdr->seg_work_total[sg] = s_tot[sg][1];
+            hdr->seg_edges[sg] = s_tot[sg][3];
+            l += s_tot[sg][0];
+            w += s_tot[sg][1];
+        }
+        for (int q = 0; q < NW; q++) fr += s_f[q];
+        hdr->total_active = l;
+        hdr->frontier = fr;
+        scan_extra(hdr, x);
+        wpre[l] = w;
+    }
+    __threadfence_system();
+    __syncthreads();
+    if (t == 0) __hip_atomic_store(&host.hdr->seq, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // One workgroup of 64 threads: grand totals, segment starts (segments lie one after another:
 // RESIDENT, FILTER, ZEROCOPY, COMPACT), each tile's bases, the header, and the work prefix's
 // closing entry.
 __global__ __launch_bounds__(64) void k_scan_base(uint32_t ntiles, const uint64_t* __restrict__ tile_tot,
                                                   uint64_t* __restrict__ tile_base, Header* __restrict__ hdr,
-                                                  uint64_t* __restrict__ wpre) {
+                                                  uint64_t* __restrict__ wpre, ScanExtra x) {
     __shared__ uint64_t s_g[SCAN_NV];
     const uint32_t k = threadIdx.x;
     if (k < SCAN_NV) {
@@ -389,12 +646,12 @@ __global__ __launch_bounds__(64) void k_scan_base(uint32_t ntiles, const uint64_
             hdr->seg_work_start[sg] = wa;
             hdr->seg_work_total[sg] = s_g[NSEG + sg];
             hdr->seg_edges[sg] = s_g[3 * NSEG + sg];
-            hdr->seg_cost_lines[sg] = s_g[4 * NSEG + sg];
             la += s_g[sg];
             wa += s_g[NSEG + sg];
         }
         hdr->total_active = la;
         hdr->frontier = s_g[SCAN_NV - 1];
+        scan_extra(hdr, x);
         wpre[la] = wa;
     }
 }
@@ -408,7 +665,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_write(uint32_t npart, con
     const uint32_t i0 = min(blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_PER, npart), i1 = min(i0 + SCAN_PER, npart);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     uint64_t val[SCAN_NB];
-    scan_run_sums<SCAN_NB>(i0, i1, mode, nA, nullptr, Ea, nullptr, K, val);
+    scan_run_sums<SCAN_NB>(i0, i1, mode, nA, nullptr, Ea, K, val);
     uint64_t ex[SCAN_NB];
 #pragma unroll
     for (int k = 0; k < SCAN_NB; k++) {
@@ -447,8 +704,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_write(uint32_t npart, con
 }
 
 // ------------------------------------------------------------------ lists
-// One wave per scheduled partition, dealing out each round's active vertices as in
-// k_stats_select; a batch's entries are written in lane order, so the stores coalesce.
+// One wave per unit of the scheduled partitions, dealing out its active vertices as in
+// k_unit_stats; a batch's entries are written in lane order, so the stores coalesce.
 // Batches [b0, b0 + 64 G) of a round's active vertices, loaded as in stats_batches; the
 // entries of vertices with edges go to list[pos...) in lane order with their work prefix.
 template <int G>
@@ -485,7 +742,7 @@ __device__ __forceinline__ void list_batches(uint32_t b0, uint32_t T, uint32_t i
     }
 }
 
-__global__ __launch_bounds__(256) void k_build_lists(uint32_t npart, const uint32_t* __restrict__ pv,
+__global__ __launch_bounds__(256) void k_build_lists(Units un, const uint32_t* __restrict__ pv,
                                                      const uint64_t* __restrict__ off,
                                                      const uint32_t* __restrict__ cur,
                                                      const uint8_t* __restrict__ mode,
@@ -494,25 +751,28 @@ __global__ __launch_bounds__(256) void k_build_lists(uint32_t npart, const uint3
                                                      uint32_t* __restrict__ list, uint64_t* __restrict__ wpre) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
-    for (uint32_t i = blockIdx.x * wpb + (threadIdx.x >> 6); i < npart; i += waves) {
+    for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
+        const uint32_t i = un.part[u], q0 = un.q[u];
         const uint8_t m = mode[i];
         if (m == P_NONE) continue;
         const bool by_lines = m == P_ZC;
         const uint32_t vb = pv[i], ve = pv[i + 1];
-        const uint32_t qb = vb >> 6, qe = (ve + 63) >> 6;
+        const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+        const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
+        if (!__ballot(wbits != 0)) continue;
         uint64_t pos = lbase[i], wp = wbase[i];
-        for (uint32_t q0 = qb; q0 < qe; q0 += 64) {  // uniform across the wave
-            const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
-            if (!__ballot(wbits != 0)) continue;
-            const uint32_t cnt = __popcll(wbits);
-            const uint32_t incl = wave_inclusive_sum_u32(cnt);
-            const uint32_t T = __shfl(incl, 63, 64);
-            if (T <= 64)
-                list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
-            else
-                for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
-                    list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
+        if (un.first[i + 1] - un.first[i] > 1) {  // after the partition's earlier units
+            pos += un.rec[u].c;
+            wp += by_lines ? un.rec[u].kl : un.rec[u].ea;
         }
+        const uint32_t cnt = __popcll(wbits);
+        const uint32_t incl = wave_inclusive_sum_u32(cnt);
+        const uint32_t T = __shfl(incl, 63, 64);
+        if (T <= 64)
+            list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
+        else
+            for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
+                list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
     }
 }
 
@@ -1064,16 +1324,6 @@ __global__ void k_init_lanes(AlgoState s, LaneSources src, uint32_t* __restrict_
     if (blockIdx.x == 0 && threadIdx.x == 0 && s.overflow) s.overflow[0] = s.overflow[1] = 0;
 }
 
-__global__ __launch_bounds__(256) void k_lane_union(const uint64_t* __restrict__ mask, uint64_t n,
-                                                    unsigned long long* __restrict__ lanes) {
-    uint64_t m = 0;
-    for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x)
-        m |= mask[v];
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) m |= __shfl_xor(m, d, 64);
-    if ((threadIdx.x & 63) == 0 && m) atomicOr(lanes, (unsigned long long)m);
-}
-
 // Lane extraction through LDS: a workgroup loads the rows of EX_V vertices with
 // coalesced reads (row pitch padded by one word against bank conflicts), then writes
 // each requested lane as a contiguous run of EX_V values.
@@ -1362,6 +1612,16 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint64_t count, uint32_t va
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < count;
          i += (uint64_t)gridDim.x * blockDim.x)
         p[i] = value;
+}
+
+__global__ __launch_bounds__(256) void k_fill2_u32(uint32_t* __restrict__ p, uint64_t np, uint32_t* __restrict__ q,
+                                                   uint64_t nq, uint32_t value) {
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < np + nq; i += (uint64_t)gridDim.x * 256) {
+        if (i < np)
+            p[i] = value;
+        else
+            q[i - np] = value;
+    }
 }
 
 __global__ void k_pr_prepare(uint64_t n, const uint64_t* __restrict__ off, const float* __restrict__ x,
@@ -2436,11 +2696,6 @@ hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_
     return hipGetLastError();
 }
 
-hipError_t launch_lane_union(const uint64_t* mask, uint64_t n, unsigned long long* lanes, hipStream_t st) {
-    k_lane_union<<<grid_for(n, 256, 2048), 256, 0, st>>>(mask, n, lanes);
-    return hipGetLastError();
-}
-
 hipError_t launch_extract_lanes(const uint32_t* vals, uint64_t n, uint32_t lshift, const LaneSet& set, bool sub_base,
                                 const uint32_t* order, uint32_t* out, hipStream_t st) {
     const uint32_t nsel = (uint32_t)__builtin_popcountll(set.mask);
@@ -2585,33 +2840,54 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_stats_select(uint32_t npart, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
-                               const SelParams& sp, uint8_t* mode, uint32_t* nA, uint32_t* nF, uint64_t* Ea,
-                               uint64_t* Rq, uint64_t* K, hipStream_t st) {
+hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
+                               const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
+                               unsigned long long* lanes, const SelParams& sp, uint8_t* mode, uint32_t* nA,
+                               uint32_t* nF, uint64_t* Ea, uint64_t* K, hipStream_t st) {
     if (!npart) return hipSuccess;
-    k_stats_select<<<grid_for(npart, 4, GRID_CAP), 256, 0, st>>>(npart, pv, off, cur, sp, mode, nA, nF, Ea,
-                                                                         Rq, K);
+    k_unit_stats<<<grid_for(un.count, 4, GRID_CAP), 256, 0, st>>>(un, pv, off, cur, clear, nwords, mcur, lanes, sp,
+                                                                  mode, nA, nF, Ea, K);
+    if (un.multis)
+        k_part_combine<<<(un.multis + 3) / 4, 256, 0, st>>>(un, pv, off, sp, mode, nA, nF, Ea, K);
     return hipGetLastError();
 }
 
 hipError_t launch_scan(uint32_t npart, const uint8_t* mode, const uint32_t* nA, const uint32_t* nF,
-                       const uint64_t* Ea, const uint64_t* Rq, const uint64_t* K, uint32_t* lbase, uint64_t* wbase,
-                       Header* hdr, uint64_t* wpre, uint64_t* scratch, hipStream_t st) {
+                       const uint64_t* Ea, const uint64_t* K, uint32_t* lbase, uint64_t* wbase, Header* hdr,
+                       uint64_t* wpre, uint64_t* scratch, const ScanExtra& x, hipStream_t st) {
     const uint32_t ntiles = scan_tiles(npart);
     uint64_t* tile_tot = scratch;
     uint64_t* tile_base = scratch + (uint64_t)ntiles * SCAN_NV;
-    if (ntiles) k_scan_tot<<<ntiles, SCAN_THREADS, 0, st>>>(npart, mode, nA, nF, Ea, Rq, K, tile_tot);
-    k_scan_base<<<1, 64, 0, st>>>(ntiles, tile_tot, tile_base, hdr, wpre);
+    if (ntiles) k_scan_tot<<<ntiles, SCAN_THREADS, 0, st>>>(npart, mode, nA, nF, Ea, K, tile_tot);
+    k_scan_base<<<1, 64, 0, st>>>(ntiles, tile_tot, tile_base, hdr, wpre, x);
     if (ntiles) k_scan_write<<<ntiles, SCAN_THREADS, 0, st>>>(npart, mode, nA, Ea, K, tile_base, lbase, wbase);
     return hipGetLastError();
 }
 
-hipError_t launch_build_lists(uint32_t npart, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
+hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* nA, const uint32_t* nF,
+                           const uint64_t* Ea, const uint64_t* K, uint32_t* lbase, uint64_t* wbase, uint64_t* wpre,
+                           const ScanExtra& x, const ScanHost& host, hipStream_t st) {
+    if (npart > SCAN_ONE_MAX) return hipErrorInvalidValue;
+    if (npart <= 1024)
+        k_scan_one<1><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
+    else if (npart <= 4096)
+        k_scan_one<4><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
+    else
+        k_scan_one<16><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_build_lists(const Units& un, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
                               const uint8_t* mode, const uint32_t* lbase, const uint64_t* wbase, uint32_t* list,
                               uint64_t* wpre, hipStream_t st) {
-    if (!npart) return hipSuccess;
-    k_build_lists<<<grid_for(npart, 4, GRID_CAP), 256, 0, st>>>(npart, pv, off, cur, mode, lbase, wbase,
-                                                                        list, wpre);
+    if (!un.count) return hipSuccess;
+    k_build_lists<<<grid_for(un.count, 4, GRID_CAP), 256, 0, st>>>(un, pv, off, cur, mode, lbase, wbase, list, wpre);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill2_u32(uint32_t* p, uint64_t np, uint32_t* q, uint64_t nq, uint32_t value, hipStream_t st) {
+    if (!(np + nq)) return hipSuccess;
+    k_fill2_u32<<<grid_for(np + nq, 1024, 8192), 256, 0, st>>>(p, np, q, nq, value);
     return hipGetLastError();
 }
 

@@ -32,6 +32,7 @@
 #include <string>
 #include <thread>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "hytm.h"
@@ -220,11 +221,19 @@ struct hytm_graph {
     uint64_t max_part_edges = 0;
     DevBuf<uint32_t> d_pv;
     DevBuf<uint64_t> d_off;
+    // units of the partitions (see Units): part, q, first and multi behind one another
+    DevBuf<uint32_t> d_units;
+    DevBuf<UnitRec> d_unit_rec;
+    uint32_t nunits = 0, nmulti = 0;
+    Units units() const {
+        const uint32_t* p = d_units.p;
+        return Units{nunits, nmulti, p, p + nunits, p + 2 * (size_t)nunits, p + 2 * (size_t)nunits + npart + 1, d_unit_rec.p};
+    }
 
     // per-vertex / per-partition device state
-    DevBuf<uint32_t> d_val, d_cur, d_next, d_visited, d_list, d_overflow;
+    DevBuf<uint32_t> d_val, d_cur, d_next, d_spare, d_visited, d_list, d_overflow;
     DevBuf<float> d_x, d_contrib, d_acc;
-    DevBuf<uint64_t> d_wpre, d_Ea, d_Rq, d_K, d_wbase;
+    DevBuf<uint64_t> d_wpre, d_Ea, d_K, d_wbase;
     DevBuf<uint32_t> d_nA, d_nF, d_lbase;
     DevBuf<uint8_t> d_mode;
     DevBuf<Header> d_hdr;
@@ -250,7 +259,6 @@ struct hytm_graph {
     HostBuf<double> h_psum;
     DevBuf<uint8_t> d_sched;      // ... partitions scheduled this iteration
     HostBuf<uint8_t> h_sched;
-    HostBuf<uint64_t> h_lanes;
     // PageRank propagation blocking: contribution buffers [0], [1] of alternate pieces
     // (destination words [0], [1] only for the second sort pass, which writes them), [2] =
     // the first sort pass's target; bucket plans per piece
@@ -285,6 +293,8 @@ struct hytm_graph {
     DevBuf<uint8_t> d_sel;
     HostBuf<uint8_t> h_sel;
     uint32_t sel_npart = UINT32_MAX;  // partitions the views were laid out for
+    uint8_t* h_sel_dev = nullptr;     // device address of h_sel
+    uint64_t sel_seq = 0;             // number of the last selection that reported into h_sel
     HostBuf<Header> h_hdr;
     HostBuf<uint8_t> h_mode;
     HostBuf<uint32_t> h_lbase;
@@ -311,7 +321,7 @@ struct hytm_graph {
     hipStream_t s_main = nullptr, s_copy = nullptr, s_fk = nullptr, s_zc = nullptr, s_c = nullptr, s_pb = nullptr;
     hipEvent_t ev_copied[kMaxSlots] = {}, ev_free[kMaxSlots] = {};
     hipEvent_t ev_pbpush = nullptr, ev_pbfree[2] = {};
-    hipEvent_t ev_cdone[2] = {}, ev_join[4] = {}, ev_start = nullptr, ev_clist = nullptr, ev_go = nullptr;
+    hipEvent_t ev_cdone[2] = {}, ev_join[4] = {}, ev_clist = nullptr, ev_go = nullptr;
     hipEvent_t ev_sel[2] = {};    // timing events around each pass's selection (statistics to D2H)
 
     Pool* pool = nullptr;
@@ -390,6 +400,24 @@ void partition_graph(hytm_graph* g) {
     g->d_pv.ensure(g->pv.size());
     HIP_CHECK(hipMemcpy(g->d_pv.p, g->pv.data(), g->pv.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     g->res_valid = false;
+    std::vector<uint32_t> part, q, first, multi;
+    for (uint32_t p = 0; p < g->npart; p++) {
+        first.push_back((uint32_t)part.size());
+        const uint32_t qe = (uint32_t)(((uint64_t)g->pv[p + 1] + 63) >> 6);
+        for (uint32_t w = g->pv[p] >> 6; w < qe; w += UNIT_WINDOWS) {
+            part.push_back(p);
+            q.push_back(w);
+        }
+        if (part.size() - first[p] > 1) multi.push_back(p);
+    }
+    first.push_back((uint32_t)part.size());
+    g->nunits = (uint32_t)part.size();
+    g->nmulti = (uint32_t)multi.size();
+    std::vector<uint32_t> all;
+    for (const auto* v : {&part, &q, &first, &multi}) all.insert(all.end(), v->begin(), v->end());
+    g->d_units.ensure(all.size());
+    HIP_CHECK(hipMemcpy(g->d_units.p, all.data(), all.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    g->d_unit_rec.ensure(g->nunits);
 }
 
 // Edge arrays an algorithm reads per edge: SSSP reads neighbours and weights, unless the
@@ -587,7 +615,6 @@ void ensure_streams(hytm_graph* g) {
     }
     for (auto& e : g->ev_cdone) HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     for (auto& e : g->ev_join) HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    HIP_CHECK(hipEventCreateWithFlags(&g->ev_start, hipEventDisableTiming));
     HIP_CHECK(hipEventCreateWithFlags(&g->ev_clist, hipEventDisableTiming));
     HIP_CHECK(hipEventCreateWithFlags(&g->ev_go, hipEventDisableTiming));
     for (auto& e : g->ev_sel) HIP_CHECK(hipEventCreate(&e));
@@ -607,11 +634,13 @@ void in_release(hytm_graph* g) {
 
 void release_all(hytm_graph* g) {
     if (g->s_copy) (void)hipDeviceSynchronize();
-    for (auto* b : {&g->d_val, &g->d_cur, &g->d_next, &g->d_visited, &g->d_list, &g->d_overflow, &g->d_nA, &g->d_nF,
+    g->d_units.release();
+    g->d_unit_rec.release();
+    for (auto* b : {&g->d_val, &g->d_cur, &g->d_next, &g->d_spare, &g->d_visited, &g->d_list, &g->d_overflow, &g->d_nA, &g->d_nF,
                     &g->d_lbase, &g->d_pv, &g->d_res_col, &g->d_res_w, &g->d_res})
         b->release();
     for (auto* b : {&g->d_x, &g->d_contrib, &g->d_acc}) b->release();
-    for (auto* b : {&g->d_wpre, &g->d_Ea, &g->d_Rq, &g->d_K, &g->d_wbase, &g->d_off, &g->d_sel_in}) b->release();
+    for (auto* b : {&g->d_wpre, &g->d_Ea, &g->d_K, &g->d_wbase, &g->d_off, &g->d_sel_in}) b->release();
     g->d_mode.release();
     g->d_sel_out.release();
     g->d_tasks.release();
@@ -637,7 +666,6 @@ void release_all(hytm_graph* g) {
     g->d_order.release();
     g->d_minold.release();
     g->d_inv_n.release();
-    g->h_lanes.release();
     g->d_hdr.release();
     for (int i = 0; i < 3; i++) {
         g->d_pb_v[i].release();
@@ -683,7 +711,6 @@ void release_all(hytm_graph* g) {
         if (e) (void)hipEventDestroy(e);
     for (auto e : g->ev_join)
         if (e) (void)hipEventDestroy(e);
-    if (g->ev_start) (void)hipEventDestroy(g->ev_start);
     if (g->ev_clist) (void)hipEventDestroy(g->ev_clist);
     if (g->ev_go) (void)hipEventDestroy(g->ev_go);
     for (auto e : g->ev_sel)
@@ -734,6 +761,8 @@ struct RunCtx {
     hytm_run_stats* stats = nullptr;
     uint32_t nwords = 0;
     uint32_t *cur = nullptr, *nxt = nullptr;   // frontier bitmaps (union over lanes)
+    uint32_t* spare = nullptr;                 // single-source runs: the bitmap after nxt, cleared by the selection
+    uint64_t overflow = 0;                     // the SSSP overflow words as of the last selection
     uint64_t *mcur = nullptr, *mnxt = nullptr; // lane masks
     LaneSet ppr{};                             // PPR lanes stepping, restarted at their sources
     bool reprocess = false;                    // second pass over loaded partitions (Sec. 6.1)
@@ -859,13 +888,11 @@ hytm_status prepare_graph(hytm_graph* g, uint32_t plan_arrays, hipStream_t main,
     g->d_overflow.ensure(2);
     g->d_zcl.ensure(1);
     g->d_lanes.ensure(1);
-    g->h_lanes.ensure(1);
 
     g->d_nA.ensure(npart);
     g->d_nF.ensure(npart);
 
     g->d_Ea.ensure(npart);
-    g->d_Rq.ensure(npart);
     g->d_K.ensure(npart);
     // the selection that crosses to the host every iteration -- header, list and work bases,
     // engine codes -- is one block on each side, moved by one copy
@@ -874,12 +901,15 @@ hytm_status prepare_graph(hytm_graph* g, uint32_t plan_arrays, hipStream_t main,
     if (g->sel_npart != npart || g->d_sel.n < sel_bytes || g->h_sel.n < sel_bytes) {
         g->d_sel.ensure(sel_bytes);
         g->h_sel.ensure(sel_bytes);
+        HIP_CHECK(hipHostGetDevicePointer((void**)&g->h_sel_dev, g->h_sel.p, 0));
         const SelLayout L = sel_layout(npart);
         g->d_hdr.view(g->d_sel.p, 1);
         g->d_wbase.view(g->d_sel.p + L.wbase, npart);
         g->d_lbase.view(g->d_sel.p + L.lbase, npart);
         g->d_mode.view(g->d_sel.p + L.mode, npart);
         g->h_hdr.view(g->h_sel.p, 1);
+        g->h_hdr.p->seq = 0;
+        g->sel_seq = 0;
         g->h_wbase.view(g->h_sel.p + L.wbase, npart);
         g->h_lbase.view(g->h_sel.p + L.lbase, npart);
         g->h_mode.view(g->h_sel.p + L.mode, npart);
@@ -1001,6 +1031,26 @@ void init_ctx(RunCtx& rc, hytm_graph* g, int algo, bool batched, const Plan& pl,
     rc.as.acc_copies = pr_acc_copies(false);  // a run decides once it knows whether it blocks
 }
 
+// Where the zero-copy pushes count the distinct lines they read (a statistic), or null.
+unsigned long long* zcl_of(const RunCtx& rc) { return rc.stats ? (unsigned long long*)rc.g->d_zcl.p : nullptr; }
+
+// Wait until selection `seq` has reported into the host's header: a poll for the short
+// selections of small frontiers (a wake-up from a stream wait costs ~10 us, a tenth of such an
+// iteration), then a stream wait.
+void wait_selection(hytm_graph* g, uint64_t seq, hipStream_t main) {
+    const uint64_t* at = &g->h_hdr.p->seq;
+    const double t0 = now_ms();
+    do {
+        for (int k = 0; k < 64; k++)
+            if (__atomic_load_n(at, __ATOMIC_ACQUIRE) == seq) return;
+    } while (now_ms() - t0 < 0.2);
+    HIP_CHECK(hipStreamSynchronize(main));
+    if (__atomic_load_n(at, __ATOMIC_ACQUIRE) != seq) {
+        fail(HYTM_E_DEVICE, "internal: the selection did not report");
+        throw HipError{HYTM_E_DEVICE};
+    }
+}
+
 // The in-edge lists of a graph without a budget, made on first use (the edges never
 // change).  False when the device has no room for them.
 bool in_ready(RunCtx& rc, hipStream_t main) {
@@ -1058,46 +1108,65 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     hytm_graph* g = rc.g;
     KTimer& kt = g->timer;
     AlgoState& as = rc.as;
-    const uint64_t n = g->n;
     const uint32_t npart = g->npart;
     const Plan& pl = rc.plan;
     const bool fstream = g->params.filter_engine == HYTM_FILTER_STREAM;
     const uint64_t d1b = edge_bytes(g, rc.arrays);
-    // 1. statistics, engine selection, active lists (Algorithm 1, GPU part); timed on the
-    // device from the statistics kernel to the end of the D2H copy, so the time the stream
-    // spends finishing the previous iteration's pushes is not counted
-    HIP_CHECK(hipEventRecord(g->ev_sel[0], main));
+    // 1. statistics, engine selection, active lists (Algorithm 1, GPU part), and the selection
+    // back to the host (Algorithm 1: copy Vc, p and A to host)
+    hytm_run_stats* stats = rc.stats;
+    const bool traced = trace_t >= 0 && stats && stats->mode_trace && (uint64_t)(trace_t + 1) * npart <= stats->mode_trace_cap;
+    const bool one = npart <= SCAN_ONE_MAX;
+    // the partitions' engines and bases are read here only where transfers are planned from them
+    const bool parts_to_host = g->budget != UINT64_MAX || select_only || traced;
+    if (stats) HIP_CHECK(hipEventRecord(g->ev_sel[0], main));
     HIP_CHECK(kt.run(HYTM_K_STATS, npart, main, [&] {
-        return launch_stats_select(npart, g->d_pv.p, g->d_off.p, cur, rc.sp, g->d_mode.p, g->d_nA.p, g->d_nF.p,
-                                   g->d_Ea.p, g->d_Rq.p, g->d_K.p, main);
+        return launch_stats_select(npart, g->units(), g->d_pv.p, g->d_off.p, cur, rc.spare, rc.nwords,
+                                   lanes ? rc.mcur : nullptr, (unsigned long long*)g->d_lanes.p, rc.sp, g->d_mode.p,
+                                   g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, main);
     }));
-    g->d_scan.ensure(scan_scratch_words(npart));
+    const ScanExtra extra{lanes ? g->d_lanes.p : nullptr, g->d_overflow.p};
+    const uint64_t seq = ++g->sel_seq;
     HIP_CHECK(kt.run(HYTM_K_SCAN, npart, main, [&] {
-        return launch_scan(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_Rq.p, g->d_K.p, g->d_lbase.p,
-                           g->d_wbase.p, g->d_hdr.p, g->d_wpre.p, g->d_scan.p, main);
+        if (!one) {
+            g->d_scan.ensure(scan_scratch_words(npart));
+            return launch_scan(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, g->d_lbase.p,
+                               g->d_wbase.p, g->d_hdr.p, g->d_wpre.p, g->d_scan.p, extra, main);
+        }
+        const SelLayout L = sel_layout(npart);
+        ScanHost host{(Header*)g->h_sel_dev, nullptr, nullptr, nullptr, seq};
+        if (parts_to_host) {
+            host.wbase = (uint64_t*)(g->h_sel_dev + L.wbase);
+            host.lbase = (uint32_t*)(g->h_sel_dev + L.lbase);
+            host.mode = g->h_sel_dev + L.mode;
+        }
+        return launch_scan_one(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, g->d_lbase.p,
+                               g->d_wbase.p, g->d_wpre.p, extra, host, main);
     }));
+    if (!one)
+        HIP_CHECK(hipMemcpyAsync(g->h_sel.p, g->d_sel.p, sel_block_bytes(npart), hipMemcpyDeviceToHost, main));
     if (lists) HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
-        return launch_build_lists(npart, g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p, g->d_wbase.p,
+        return launch_build_lists(g->units(), g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p, g->d_wbase.p,
                                   g->d_list.p, g->d_wpre.p, main);
     }));
-    // 2. selection back to the host (Algorithm 1: copy Vc, p and A to host)
-    HIP_CHECK(hipMemcpyAsync(g->h_sel.p, g->d_sel.p, sel_block_bytes(npart), hipMemcpyDeviceToHost, main));
-    if (lanes) {
-        // which lanes have a non-empty frontier this iteration
-        HIP_CHECK(launch_fill_u32((uint32_t*)g->d_lanes.p, 2, 0u, main));
-        HIP_CHECK(launch_lane_union(rc.mcur, n, (unsigned long long*)g->d_lanes.p, main));
-        HIP_CHECK(hipMemcpyAsync(g->h_lanes.p, g->d_lanes.p, sizeof(uint64_t), hipMemcpyDeviceToHost, main));
-    }
-    HIP_CHECK(hipEventRecord(g->ev_sel[1], main));
-    HIP_CHECK(hipStreamSynchronize(main));
+    if (stats) HIP_CHECK(hipEventRecord(g->ev_sel[1], main));
+    if (one)
+        wait_selection(g, seq, main);
+    else
+        HIP_CHECK(hipStreamSynchronize(main));
     Totals& tt = rc.tot;
-    tt.d2h += sizeof(Header) + npart * (1 + 4 + 8);
+    tt.d2h += sizeof(Header) + (parts_to_host || !one ? (uint64_t)npart * (1 + 4 + 8) : 0);
     const Header h = *g->h_hdr.p;
     *hout = h;
-    float sel_ms = 0.f;
-    HIP_CHECK(hipEventElapsedTime(&sel_ms, g->ev_sel[0], g->ev_sel[1]));
-    tt.select_ms += sel_ms;
-    if (lanes) *lanes = *g->h_lanes.p;
+    rc.overflow = h.overflow;
+    if (stats) {
+        // on the device, from the statistics kernel to the end of the lists
+        float sel_ms = 0.f;
+        HIP_CHECK(hipEventSynchronize(g->ev_sel[1]));
+        HIP_CHECK(hipEventElapsedTime(&sel_ms, g->ev_sel[0], g->ev_sel[1]));
+        tt.select_ms += sel_ms;
+    }
+    if (lanes) *lanes = h.lanes;
     if (stop_if_empty && h.frontier == 0) return HYTM_OK;
 
     // bookkeeping of the pass
@@ -1109,10 +1178,17 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     rec->parts[0] += npart - scheduled;
     rec->active_vertices += h.total_active;
     for (int s = 0; s < NSEG; s++) rec->active_edges += h.seg_edges[s];
-    hytm_run_stats* stats = rc.stats;
-    if (trace_t >= 0 && stats && stats->mode_trace && (uint64_t)(trace_t + 1) * npart <= stats->mode_trace_cap)
-        memcpy(stats->mode_trace + (uint64_t)trace_t * npart, g->h_mode.p, npart);
+    if (traced) memcpy(stats->mode_trace + (uint64_t)trace_t * npart, g->h_mode.p, npart);
     if (select_only) return HYTM_OK;
+
+    // the other engines' streams start after the lists
+    const bool use_z = h.seg_list_count[SEG_Z], use_c = h.seg_list_count[SEG_C], use_f = h.seg_list_count[SEG_F];
+    if (use_z || use_c || use_f) {
+        HIP_CHECK(hipEventRecord(g->ev_go, main));
+        if (use_z) HIP_CHECK(hipStreamWaitEvent(g->s_zc, g->ev_go, 0));
+        if (use_c) HIP_CHECK(hipStreamWaitEvent(g->s_c, g->ev_go, 0));
+        if (use_f) HIP_CHECK(hipStreamWaitEvent(g->s_fk, g->ev_go, 0));
+    }
 
     // resident partitions: no transfer
     if (rc.pull && h.seg_work_total[SEG_R] >= g->m / kPullShare && in_ready(rc, main))
@@ -1133,7 +1209,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
             return launch_push_lines(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
-                                     g->d_w_map, (unsigned long long*)g->d_zcl.p, g->s_zc);
+                                     g->d_w_map, zcl_of(rc), g->s_zc);
         }));
         rec->zc_lines += h.seg_work_total[SEG_Z];
     }
@@ -1236,10 +1312,12 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     tt.d2h += c_d2h;
     tt.cchunks += c_chunks;
     // 3. join every engine into the main stream
-    HIP_CHECK(hipEventRecord(g->ev_join[0], g->s_fk));
-    HIP_CHECK(hipEventRecord(g->ev_join[1], g->s_zc));
-    HIP_CHECK(hipEventRecord(g->ev_join[2], g->s_c));
-    for (int q = 0; q < 3; q++) HIP_CHECK(hipStreamWaitEvent(main, g->ev_join[q], 0));
+    const std::pair<bool, hipStream_t> used[3] = {{use_f, g->s_fk}, {use_z, g->s_zc}, {use_c, g->s_c}};
+    for (int q = 0; q < 3; q++) {
+        if (!used[q].first) continue;
+        HIP_CHECK(hipEventRecord(g->ev_join[q], used[q].second));
+        HIP_CHECK(hipStreamWaitEvent(main, g->ev_join[q], 0));
+    }
     return HYTM_OK;
 }
 
@@ -1300,7 +1378,7 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
             return launch_push_lines(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
-                                     g->d_w_map, (unsigned long long*)g->d_zcl.p, g->s_zc);
+                                     g->d_w_map, zcl_of(rc), g->s_zc);
         }));
         rec->zc_lines += h.seg_work_total[SEG_Z];
     }
@@ -1497,7 +1575,7 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
             return launch_push_lines(al, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
-                                     g->d_w_map, (unsigned long long*)g->d_zcl.p, g->s_zc);
+                                     g->d_w_map, zcl_of(rc), g->s_zc);
         }));
         rec->zc_lines += h.seg_work_total[SEG_Z];
     }
@@ -1826,16 +1904,24 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
             HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] { return launch_ppr_apply(as, d, main); }));
             HIP_CHECK(kt.run(HYTM_K_OTHER, 1, main, [&] { return launch_ppr_restart(as, rc.ppr, restart, main); }));
         }
-        std::swap(rc.cur, rc.nxt);
+        if (rc.spare) {  // cleared by this iteration's selection
+            uint32_t* done = rc.cur;
+            rc.cur = rc.nxt;
+            rc.nxt = rc.spare;
+            rc.spare = done;
+        } else {
+            std::swap(rc.cur, rc.nxt);
+        }
         as.next = rc.nxt;
-        HIP_CHECK(kt.run(HYTM_K_OTHER, rc.nwords, main, [&] { return launch_fill_u32(rc.nxt, rc.nwords, 0u, main); }));
         if (rc.batched) {
             std::swap(rc.mcur, rc.mnxt);
             as.mcur = rc.mcur;
             as.mnext = rc.mnxt;
-            HIP_CHECK(kt.run(HYTM_K_OTHER, n, main,
-                             [&] { return launch_fill_u32((uint32_t*)rc.mnxt, 2 * n, 0u, main); }));
         }
+        if (!rc.spare)
+            HIP_CHECK(kt.run(HYTM_K_OTHER, rc.nwords, main, [&] {
+                return launch_fill2_u32(rc.nxt, rc.nwords, (uint32_t*)rc.mnxt, rc.batched ? 2 * n : 0, 0u, main);
+            }));
     }
     record_iteration(rc, rec, t, t_it);
     rc.t++;
@@ -1988,8 +2074,8 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     Plan pl;
     hytm_status ps = prepare_graph(g, arrays, main, &pl, &rc.tot);
     if (ps != HYTM_OK) return ps;
-    HIP_CHECK(hipEventRecord(g->ev_start, main));
-    HIP_CHECK(launch_fill_u32((uint32_t*)g->d_zcl.p, 2, 0u, main));
+    if (stats) HIP_CHECK(launch_fill_u32((uint32_t*)g->d_zcl.p, 2, 0u, main));
+    if (batched) HIP_CHECK(launch_fill_u32((uint32_t*)g->d_lanes.p, 2, 0u, main));
     init_ctx(rc, g, algo, batched, pl, stats);
     rc.pb_on = pb_eligible(rc);
     rc.pg_on = pg_eligible(rc);
@@ -2057,6 +2143,10 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     }
     rc.cur = g->d_cur.p;
     rc.nxt = g->d_next.p;
+    if (!batched && !pr_like) {
+        g->d_spare.ensure(nwords);
+        rc.spare = g->d_spare.p;
+    }
     if (batched) {
         rc.mcur = g->d_mcur.p;
         rc.mnxt = g->d_mnext.p;
@@ -2105,16 +2195,15 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
         if (empty) break;
         for (uint32_t l = 0; l < lanes; l++) lane_iters[l] += (uint32_t)((active >> l) & 1);
     }
-    HIP_CHECK(hipStreamSynchronize(main));
     if (rc.pb.ok) {
+        HIP_CHECK(hipStreamSynchronize(main));
         uint32_t perr = 0;
         HIP_CHECK(hipMemcpy(&perr, g->d_pb_err.p, sizeof(perr), hipMemcpyDeviceToHost));
         if (perr) return fail(HYTM_E_DEVICE, "internal: PageRank pair buckets did not match the pushed pairs");
     }
     if (algo == HYTM_SSSP) {
-        uint32_t of[2] = {0, 0};
-        HIP_CHECK(hipMemcpy(of, g->d_overflow.p, sizeof(of), hipMemcpyDeviceToHost));
-        const uint64_t flagged = batched ? ((uint64_t)of[0] | ((uint64_t)of[1] << 32)) & rc.ppr.mask : (of[0] ? 1ull : 0ull);
+        // the last selection, which found the frontier empty, ran after every push
+        const uint64_t flagged = batched ? rc.overflow & rc.ppr.mask : ((uint32_t)rc.overflow ? 1ull : 0ull);
         if (sssp_overflow_lanes(g, batched ? g->d_lval.p : g->d_val.p, batched ? lsh : 0, flagged, main))
             return fail(HYTM_E_RANGE, "an SSSP distance reaches 2^32-1 and does not fit in uint32");
     }
@@ -2488,6 +2577,7 @@ hytm_status server_setup(hytm_server* s) {
         HIP_CHECK(launch_reset_lanes(as, gr.all(), main));
     }
     HIP_CHECK(launch_fill_u32(g->d_overflow.p, 2, 0u, main));
+    HIP_CHECK(launch_fill_u32((uint32_t*)g->d_lanes.p, 2, 0u, main));
     g->d_xout.ensure(n * EXTRACT_LANES);
     HIP_CHECK(hipStreamSynchronize(main));
     return HYTM_OK;
