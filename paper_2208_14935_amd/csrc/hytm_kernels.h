@@ -346,21 +346,29 @@ hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* 
 
 hipError_t launch_build_lists(const Units& un, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
                               const uint8_t* mode, const uint32_t* lbase, const uint64_t* wbase, uint32_t* list,
-                              uint64_t* wpre, hipStream_t st);
+                              uint64_t* wpre, uint32_t* tile_e, uint32_t* tile_l, hipStream_t st);
+// The lists come with tile tables: tile[t] = the list entry holding work item t << shift, in
+// tile_e for entries whose work is edges and in tile_l for zero-copy's, whose work is lines.
+constexpr uint32_t EDGE_TILE_SHIFT = 10, LINE_TILE_SHIFT = 6;
+// Entries of the two tables for any selection of a graph: all work items are below m + n +
+// the lines, of which every list has at most its edges / 32 + 2.
+inline uint64_t tile_entries(uint64_t n, uint64_t m, uint32_t shift) { return ((m + m / 32 + 2 * n) >> shift) + 2; }
 
 // Push over edge items [item_lo, item_hi) of list entries [ja, jb).  Edge e of vertex
 // list[j] is read at col[off[v] - shift + (item - wpre[j])]; with compacted = true it
-// is read at col[item - shift] (the compaction buffer starts at item `shift`).
-hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, uint32_t ja,
+// is read at col[item - shift] (the compaction buffer starts at item `shift`).  Unless
+// compacted, item_lo = wpre[ja] and tile = the edge tile table.
+hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, uint64_t shift, bool compacted,
                              hipStream_t st);
 
-// Push over 128-byte line items [item_lo, item_hi) of list entries [ja, jb), reading
+// Push over 128-byte line items [item_lo, item_hi) of list entries [ja, jb) (item_lo =
+// wpre[ja]; tile = the line tile table), reading
 // the mapped host arrays col / w at absolute edge indices.  distinct (or null) gains the
 // number of different lines read: an item that is its vertex's first line and the
 // previous list entry's last line counts once.
-hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, uint32_t ja,
+hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, unsigned long long* distinct, hipStream_t st);
 

@@ -711,8 +711,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_write(uint32_t npart, con
 template <int G>
 __device__ __forceinline__ void list_batches(uint32_t b0, uint32_t T, uint32_t incl, uint32_t cnt, uint64_t wbits,
                                              uint32_t q0, const uint64_t* __restrict__ off, bool by_lines,
-                                             uint32_t* __restrict__ list, uint64_t* __restrict__ wpre, uint64_t& pos,
-                                             uint64_t& wp) {
+                                             uint32_t* __restrict__ list, uint64_t* __restrict__ wpre,
+                                             uint32_t* __restrict__ tile, uint64_t& pos, uint64_t& wp) {
     const uint32_t lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
     uint64_t s[G], e[G];
@@ -735,7 +735,12 @@ __device__ __forceinline__ void list_batches(uint32_t b0, uint32_t T, uint32_t i
         if (has) {
             const uint64_t at = pos + __popcll(A & below);
             list[at] = vv[g];
-            wpre[at] = wp + ew;
+            const uint64_t w0 = wp + ew;
+            wpre[at] = w0;
+            // the tiles whose first item is this entry's
+            const uint32_t sh = by_lines ? LINE_TILE_SHIFT : EDGE_TILE_SHIFT;
+            const uint64_t t1 = (w0 + wk - 1) >> sh;
+            for (uint64_t t = (w0 + (1u << sh) - 1) >> sh; t <= t1; t++) tile[t] = (uint32_t)at;
         }
         pos += __popcll(A);
         wp += tw;
@@ -748,7 +753,8 @@ __global__ __launch_bounds__(256) void k_build_lists(Units un, const uint32_t* _
                                                      const uint8_t* __restrict__ mode,
                                                      const uint32_t* __restrict__ lbase,
                                                      const uint64_t* __restrict__ wbase,
-                                                     uint32_t* __restrict__ list, uint64_t* __restrict__ wpre) {
+                                                     uint32_t* __restrict__ list, uint64_t* __restrict__ wpre,
+                                                     uint32_t* __restrict__ tile_e, uint32_t* __restrict__ tile_l) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
     for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
@@ -769,39 +775,51 @@ __global__ __launch_bounds__(256) void k_build_lists(Units un, const uint32_t* _
         const uint32_t incl = wave_inclusive_sum_u32(cnt);
         const uint32_t T = __shfl(incl, 63, 64);
         if (T <= 64)
-            list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
+            list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, by_lines ? tile_l : tile_e, pos, wp);
         else
             for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
-                list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, pos, wp);
+                list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, by_lines ? tile_l : tile_e, pos, wp);
     }
 }
 
 // --------------------------------------------------------------- operators
 // src(u): the value u pushes (read when the workgroup stages its vertices; it may
 // already reflect updates made earlier in the same iteration, which only helps the
-// monotone operators).  push(value, v, w): relax edge (u, v) with weight w.
+// monotone operators).  Relaxing edge (u, v) with weight w is split into steps that a thread
+// takes for several edges side by side (push_batch), so that each step's accesses are in
+// flight together: probe(v) reads the target's state, want(value, p, w) decides from it
+// whether the edge may improve it, update(...) makes the atomic update and returns the old
+// state, and mark(...) records an improvement.  Probes are ordinary loads that may return a
+// value of earlier in the kernel: states only move one way, so an old one lets at most an
+// unneeded update through, and the update's own result decides.
+// mark_next sets v's bit in a bitmap unless it is seen there already.
+__device__ __forceinline__ void mark_next(uint32_t* map, uint32_t v) {
+    const uint32_t bit = 1u << (v & 31);
+    if (!(map[v >> 5] & bit)) atomicOr(map + (v >> 5), bit);
+}
+
 struct OpBfs {
-    static constexpr bool wave = false;
+    static constexpr bool steps = true;
     static constexpr bool weighted = false;
     uint32_t* visited;
     uint32_t* next;
     uint32_t* lvl;
     uint32_t level_next;
     __device__ __forceinline__ uint32_t src(uint32_t) const { return 0; }
-    __device__ __forceinline__ void push(uint32_t, uint32_t v, uint32_t) const {
-        const uint32_t bit = 1u << (v & 31);
-        uint32_t* wp = visited + (v >> 5);
-        if (__builtin_nontemporal_load(wp) & bit) return;
-        const uint32_t old = atomicOr(wp, bit);
-        if (!(old & bit)) {  // exactly one thread discovers v
-            lvl[v] = level_next;
-            atomicOr(next + (v >> 5), bit);
-        }
+    __device__ __forceinline__ uint32_t probe(uint32_t v) const { return visited[v >> 5]; }
+    __device__ __forceinline__ bool want(uint32_t, uint32_t v, uint32_t, uint32_t p) const { return !((p >> (v & 31)) & 1); }
+    __device__ __forceinline__ uint32_t update(uint32_t, uint32_t v, uint32_t) const {
+        return atomicOr(visited + (v >> 5), 1u << (v & 31));
+    }
+    __device__ __forceinline__ void mark(uint32_t, uint32_t v, uint32_t, uint32_t old) const {
+        if ((old >> (v & 31)) & 1) return;  // exactly one thread discovers v
+        lvl[v] = level_next;
+        atomicOr(next + (v >> 5), 1u << (v & 31));
     }
 };
 
 struct OpSssp {
-    static constexpr bool wave = false;
+    static constexpr bool steps = true;
     static constexpr bool weighted = true;
     uint32_t* dist;
     uint32_t* next;
@@ -809,45 +827,51 @@ struct OpSssp {
     uint32_t* far;   // improved vertices at or above `bound` wait here (bound 0xFFFFFFFF: never)
     uint32_t bound;
     __device__ __forceinline__ uint32_t src(uint32_t u) const { return dist[u]; }
-    __device__ __forceinline__ void push(uint32_t du, uint32_t v, uint32_t w) const {
+    __device__ __forceinline__ uint32_t probe(uint32_t v) const { return dist[v]; }
+    __device__ __forceinline__ bool want(uint32_t du, uint32_t, uint32_t w, uint32_t p) const {
         const uint64_t nd = (uint64_t)du + w;
         if (nd >= UNREACHED) {
             *overflow = 1u;
-            return;
+            return false;
         }
-        if ((uint32_t)nd < dist[v]) {
-            const uint32_t old = atomicMin(dist + v, (uint32_t)nd);
-            if ((uint32_t)nd < old) atomicOr(((uint32_t)nd < bound ? next : far) + (v >> 5), 1u << (v & 31));
-        }
+        return (uint32_t)nd < p;
+    }
+    __device__ __forceinline__ uint32_t update(uint32_t du, uint32_t v, uint32_t w) const {
+        return atomicMin(dist + v, du + w);
+    }
+    __device__ __forceinline__ void mark(uint32_t du, uint32_t v, uint32_t w, uint32_t old) const {
+        const uint32_t nd = du + w;
+        if (nd < old) mark_next(nd < bound ? next : far, v);
     }
 };
 
 struct OpBfsRelax {
-    static constexpr bool wave = false;
+    static constexpr bool steps = true;
     static constexpr bool weighted = false;
     uint32_t* lvl;
     uint32_t* next;
     __device__ __forceinline__ uint32_t src(uint32_t u) const { return lvl[u]; }
-    __device__ __forceinline__ void push(uint32_t lu, uint32_t v, uint32_t) const {
-        const uint32_t nl = lu + 1;
-        if (nl < lvl[v]) {
-            const uint32_t old = atomicMin(lvl + v, nl);
-            if (nl < old) atomicOr(next + (v >> 5), 1u << (v & 31));
-        }
+    __device__ __forceinline__ uint32_t probe(uint32_t v) const { return lvl[v]; }
+    __device__ __forceinline__ bool want(uint32_t lu, uint32_t, uint32_t, uint32_t p) const { return lu + 1 < p; }
+    __device__ __forceinline__ uint32_t update(uint32_t lu, uint32_t v, uint32_t) const {
+        return atomicMin(lvl + v, lu + 1);
+    }
+    __device__ __forceinline__ void mark(uint32_t lu, uint32_t v, uint32_t, uint32_t old) const {
+        if (lu + 1 < old) mark_next(next, v);
     }
 };
 
 struct OpCc {
-    static constexpr bool wave = false;
+    static constexpr bool steps = true;
     static constexpr bool weighted = false;
     uint32_t* lab;
     uint32_t* next;
     __device__ __forceinline__ uint32_t src(uint32_t u) const { return lab[u]; }
-    __device__ __forceinline__ void push(uint32_t lu, uint32_t v, uint32_t) const {
-        if (lu < lab[v]) {
-            const uint32_t old = atomicMin(lab + v, lu);
-            if (lu < old) atomicOr(next + (v >> 5), 1u << (v & 31));
-        }
+    __device__ __forceinline__ uint32_t probe(uint32_t v) const { return lab[v]; }
+    __device__ __forceinline__ bool want(uint32_t lu, uint32_t, uint32_t, uint32_t p) const { return lu < p; }
+    __device__ __forceinline__ uint32_t update(uint32_t lu, uint32_t v, uint32_t) const { return atomicMin(lab + v, lu); }
+    __device__ __forceinline__ void mark(uint32_t lu, uint32_t v, uint32_t, uint32_t old) const {
+        if (lu < old) mark_next(next, v);
     }
 };
 
@@ -862,7 +886,7 @@ __device__ __forceinline__ uint32_t acc_copy(uint32_t cmask) {
 }
 
 struct OpPr {
-    static constexpr bool wave = false;
+    static constexpr bool wave = false, steps = false;
     static constexpr bool weighted = false;
     float* acc;
     uint64_t stride;  // floats per accumulator copy
@@ -877,7 +901,7 @@ struct OpPr {
 // Batched BFS: lanes of u's mask that have not reached v yet reach it now (one 64-bit
 // atomicOr decides, per lane, which edge discovers v first).  The staged value is u.
 struct OpMBfs {
-    static constexpr bool wave = false;
+    static constexpr bool wave = false, steps = false;
     static constexpr bool weighted = false;
     const uint64_t* mcur;
     uint64_t* mnext;
@@ -905,7 +929,7 @@ struct OpMBfs {
 
 // Batched SSSP: every lane active at u relaxes (u, v) in its own distance row.
 struct OpMSssp {
-    static constexpr bool wave = true;
+    static constexpr bool wave = true, steps = false;
     static constexpr bool weighted = true;
     const uint64_t* mcur;
     uint64_t* mnext;
@@ -986,7 +1010,7 @@ struct OpMSssp {
 // sum of up to ~10^5 shares per step, which FP32 adds in atomic order would carry ~1e-4
 // relative error; in FP64 only the FP32 rounding of x and of the shares remains).
 struct OpMPpr {
-    static constexpr bool wave = true;
+    static constexpr bool wave = true, steps = false;
     static constexpr bool weighted = false;
     const uint64_t* mcur;
     uint64_t* mnext;
@@ -1042,14 +1066,36 @@ struct OpMPpr {
     }
 };
 
-// push(val, v, w) where ok holds, called by every thread of the wave together: operators
-// with a wave form (Op::wave) share the work across the wave.
-template <class Op>
-__device__ __forceinline__ void push_if(const Op& op, bool ok, uint32_t val, uint32_t v, uint32_t w) {
-    if constexpr (Op::wave)
-        op.push_wave(ok, val, v, w);
-    else if (ok)
-        op.push(val, v, w);
+// Relax N edges per thread where ok holds, called by every thread of the wave together:
+// operators in steps take each step for all N, those with a wave form (Op::wave) share an
+// edge's work across the wave.
+// On R-MAT 22 BFS's widest iteration (49M edges) one edge after another, with probes past the
+// caches, took 1.45 ms.
+template <int N, class Op>
+__device__ __forceinline__ void push_batch(const Op& op, const bool (&ok)[N], const uint32_t (&val)[N],
+                                           const uint32_t (&v)[N], const uint32_t (&w)[N]) {
+    if constexpr (Op::steps) {
+        uint32_t p[N];
+        bool go[N];
+#pragma unroll
+        for (int r = 0; r < N; r++) p[r] = op.probe(ok[r] ? v[r] : 0u);
+#pragma unroll
+        for (int r = 0; r < N; r++) go[r] = ok[r] && op.want(val[r], v[r], w[r], p[r]);
+#pragma unroll
+        for (int r = 0; r < N; r++)
+            if (go[r]) p[r] = op.update(val[r], v[r], w[r]);
+#pragma unroll
+        for (int r = 0; r < N; r++)
+            if (go[r]) op.mark(val[r], v[r], w[r], p[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < N; r++) {
+            if constexpr (Op::wave)
+                op.push_wave(ok[r], val[r], v[r], w[r]);
+            else if (ok[r])
+                op.push(val[r], v[r], w[r]);
+        }
+    }
 }
 
 // Largest j in [lo, hi) with pred(j) true, for a predicate that is true on a prefix of
@@ -1120,29 +1166,44 @@ __device__ __forceinline__ uint32_t load_w(const uint32_t* __restrict__ w, uint6
 }
 
 constexpr int EDGE_THREADS = 256;
-constexpr int EDGE_IPB = 1024;  // edge items per workgroup pass
+constexpr int EDGE_IPB = 1 << EDGE_TILE_SHIFT;  // edge items per workgroup pass
+constexpr int EDGE_PER = EDGE_IPB / EDGE_THREADS;
 
+// A pass covers the items of one tile (EDGE_IPB items, aligned) that lie in [item_lo,
+// item_hi).  The list entries it meets come from the tile table that k_build_lists wrote
+// (tile[t] = the entry holding item t * EDGE_IPB), so a pass waits for one load instead of two
+// searches of the list; a compaction chunk, which may start inside an entry, searches.
 template <class Op, bool COMPACTED>
 __global__ __launch_bounds__(EDGE_THREADS) void k_push_edges(const uint32_t* __restrict__ list,
-                                                             const uint64_t* __restrict__ wpre, uint32_t ja,
+                                                             const uint64_t* __restrict__ wpre,
+                                                             const uint32_t* __restrict__ tile, uint32_t ja,
                                                              uint32_t jb, uint64_t item_lo, uint64_t item_hi,
                                                              const uint64_t* __restrict__ off,
                                                              const uint32_t* __restrict__ col,
                                                              const uint32_t* __restrict__ w, uint64_t shift,
                                                              Op op, Pack pk) {
-    __shared__ uint64_t s_pre[EDGE_IPB];
-    __shared__ uint64_t s_st[EDGE_IPB];
+    __shared__ uint64_t s_at[EDGE_IPB];     // staged vertex: edge index of item x is s_at + x
     __shared__ uint32_t s_val[EDGE_IPB];
     __shared__ uint16_t s_owner[EDGE_IPB];  // item -> staged vertex
     __shared__ uint32_t s_tmp, s_wave[EDGE_THREADS / 64];
-    for (uint64_t blk = blockIdx.x;; blk += gridDim.x) {
-        const uint64_t i0 = item_lo + blk * EDGE_IPB;
+    for (uint64_t t = (item_lo >> EDGE_TILE_SHIFT) + blockIdx.x;; t += gridDim.x) {
+        const uint64_t i0 = max(t << EDGE_TILE_SHIFT, item_lo);
         if (i0 >= item_hi) break;
-        const uint64_t i1 = min(i0 + (uint64_t)EDGE_IPB, item_hi);
+        const uint64_t i1 = min((t + 1) << EDGE_TILE_SHIFT, item_hi);
         // list entries whose items meet [i0, i1): every one has at least one item there,
         // so there are at most EDGE_IPB of them
-        const uint32_t j0 = block_search_last(ja, jb, [&](uint32_t j) { return wpre[j] <= i0; }, &s_tmp);
-        const uint32_t j1 = block_search_last(j0, jb, [&](uint32_t j) { return wpre[j] < i1; }, &s_tmp);
+        uint32_t j0, j1;
+        if constexpr (COMPACTED) {
+            j0 = block_search_last(ja, jb, [&](uint32_t j) { return wpre[j] <= i0; }, &s_tmp);
+            j1 = block_search_last(j0, jb, [&](uint32_t j) { return wpre[j] < i1; }, &s_tmp);
+        } else {
+            j0 = i0 == item_lo ? ja : tile[t];
+            j1 = jb - 1;
+            if (i1 < item_hi) {
+                j1 = tile[t + 1];
+                if (wpre[j1] == i1) j1--;
+            }
+        }
         const uint32_t nv = j1 - j0 + 1;
         const uint32_t cnt = (uint32_t)(i1 - i0);
         for (uint32_t q = threadIdx.x; q < cnt; q += EDGE_THREADS) s_owner[q] = 0;
@@ -1150,26 +1211,33 @@ __global__ __launch_bounds__(EDGE_THREADS) void k_push_edges(const uint32_t* __r
         for (uint32_t k = threadIdx.x; k < nv; k += EDGE_THREADS) {
             const uint32_t v = list[j0 + k];
             const uint64_t pre = wpre[j0 + k];
-            s_pre[k] = pre;
-            s_st[k] = (COMPACTED ? pre : off[v]) - shift;
+            s_at[k] = (COMPACTED ? 0 : off[v] - pre) - shift;
             s_val[k] = op.src(v);
             if (k) s_owner[pre - i0] = (uint16_t)k;  // first item of every later vertex
         }
         __syncthreads();
-        block_prefix_max_u16(s_owner, cnt, s_wave);
-        for (uint32_t q0 = 0; q0 < cnt; q0 += EDGE_THREADS) {  // whole waves stay together
-            const uint32_t q = q0 + threadIdx.x;
-            const bool ok = q < cnt;
-            uint32_t val = 0, v = 0, wt = 0;
-            if (ok) {
+        block_prefix_max_u16<EDGE_PER>(s_owner, cnt, s_wave);
+        uint32_t val[EDGE_PER], v[EDGE_PER], wt[EDGE_PER];
+        bool ok[EDGE_PER];
+#pragma unroll
+        for (int r = 0; r < EDGE_PER; r++) {
+            const uint32_t q = r * EDGE_THREADS + threadIdx.x;
+            ok[r] = q < cnt;
+            val[r] = v[r] = wt[r] = 0;
+            if (ok[r]) {
                 const uint32_t k = s_owner[q];
-                const uint64_t e = s_st[k] + (i0 + q - s_pre[k]);
-                v = col[e];
-                if (Op::weighted && pk.shift == 32) wt = load_w(w, e, pk);
-                val = s_val[k];
+                const uint64_t e = s_at[k] + (i0 + q);
+                v[r] = col[e];
+                if (Op::weighted && pk.shift == 32) wt[r] = load_w(w, e, pk);
+                val[r] = s_val[k];
             }
-            push_if(op, ok, val, pk_v(v, pk), Op::weighted ? pk_w(v, wt, pk) : 0u);
         }
+#pragma unroll
+        for (int r = 0; r < EDGE_PER; r++) {
+            if (Op::weighted) wt[r] = pk_w(v[r], wt[r], pk);
+            v[r] = pk_v(v[r], pk);
+        }
+        push_batch<EDGE_PER>(op, ok, val, v, wt);
         __syncthreads();
     }
 }
@@ -1179,10 +1247,12 @@ constexpr int LINE_THREADS = 256;
 constexpr int LINE_HALVES = LINE_THREADS / 32;  // half waves per workgroup
 constexpr int LINE_UNROLL = 8;                  // lines per half wave per pass
 constexpr int LINE_IPB = LINE_HALVES * LINE_UNROLL;
+static_assert(LINE_IPB == 1 << LINE_TILE_SHIFT, "the tile table's lines per pass");
 
 template <class Op>
 __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __restrict__ list,
-                                                             const uint64_t* __restrict__ wpre, uint32_t ja,
+                                                             const uint64_t* __restrict__ wpre,
+                                                             const uint32_t* __restrict__ tile, uint32_t ja,
                                                              uint32_t jb, uint64_t item_lo, uint64_t item_hi,
                                                              const uint64_t* __restrict__ off,
                                                              const uint32_t* __restrict__ col,
@@ -1192,17 +1262,21 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __r
     __shared__ uint64_t s_s[LINE_IPB];
     __shared__ uint64_t s_e[LINE_IPB];
     __shared__ uint32_t s_val[LINE_IPB];
-    __shared__ uint32_t s_tmp;
     __shared__ uint64_t s_prev_end;  // end offset of the list entry before the staged ones
     __shared__ uint32_t s_cnt;
     uint32_t my_lines = 0;  // distinct lines of the items this half wave loaded
     const uint32_t half = threadIdx.x >> 5, lane = threadIdx.x & 31;
-    for (uint64_t blk = blockIdx.x;; blk += gridDim.x) {
-        const uint64_t i0 = item_lo + blk * LINE_IPB;
+    for (uint64_t t = (item_lo >> LINE_TILE_SHIFT) + blockIdx.x;; t += gridDim.x) {
+        const uint64_t i0 = max(t << LINE_TILE_SHIFT, item_lo);
         if (i0 >= item_hi) break;
-        const uint64_t i1 = min(i0 + (uint64_t)LINE_IPB, item_hi);
-        const uint32_t j0 = block_search_last(ja, jb, [&](uint32_t j) { return wpre[j] <= i0; }, &s_tmp);
-        const uint32_t j1 = block_search_last(j0, jb, [&](uint32_t j) { return wpre[j] < i1; }, &s_tmp);
+        const uint64_t i1 = min((t + 1) << LINE_TILE_SHIFT, item_hi);
+        // the entries met, from the tile table as in k_push_edges
+        const uint32_t j0 = i0 == item_lo ? ja : tile[t];
+        uint32_t j1 = jb - 1;
+        if (i1 < item_hi) {
+            j1 = tile[t + 1];
+            if (wpre[j1] == i1) j1--;
+        }
         const uint32_t nv = j1 - j0 + 1;
         for (uint32_t k = threadIdx.x; k < nv; k += LINE_THREADS) {
             const uint32_t v = list[j0 + k];
@@ -1250,8 +1324,12 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __r
             }
         }
 #pragma unroll
-        for (int r = 0; r < LINE_UNROLL; r++)
-            push_if(op, ok[r], s_val[kk[r]], pk_v(cv[r], pk), Op::weighted ? pk_w(cv[r], wv[r], pk) : 0u);
+        for (int r = 0; r < LINE_UNROLL; r++) {
+            kk[r] = s_val[kk[r]];
+            if (Op::weighted) wv[r] = pk_w(cv[r], wv[r], pk);
+            cv[r] = pk_v(cv[r], pk);
+        }
+        push_batch<LINE_UNROLL>(op, ok, kk, cv, wv);
         __syncthreads();
     }
     if (distinct) {
@@ -2626,19 +2704,23 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_fstream(const FTask* __re
             }
             __syncthreads();
             block_prefix_max_u16<8>(s_owner, cnt, s_wave);
+            bool ok[UNROLL];
+            uint32_t val[UNROLL];
 #pragma unroll
             for (int r = 0; r < UNROLL; r++) {
                 const uint64_t e = ((line0 + half + (uint64_t)LINE_HALVES * r) << ZC_LINE_SHIFT) + lane;
-                bool ok = false;
-                uint32_t val = 0;
+                ok[r] = false;
+                val[r] = 0;
                 if (e >= ce0 && e < ce1) {
                     const uint32_t q = (uint32_t)(e - ce0);
                     const uint32_t k = s_owner[q];
-                    ok = q >= s_s[k] && q < s_e[k];
-                    val = s_val[k];
+                    ok[r] = q >= s_s[k] && q < s_e[k];
+                    val[r] = s_val[k];
                 }
-                push_if(op, ok, val, pk_v(cv[r], pk), Op::weighted ? pk_w(cv[r], wv[r], pk) : 0u);
+                if (Op::weighted) wv[r] = pk_w(cv[r], wv[r], pk);
+                cv[r] = pk_v(cv[r], pk);
             }
+            push_batch<UNROLL>(op, ok, val, cv, wv);
         }
         __syncthreads();
     }
@@ -2879,9 +2961,10 @@ hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* 
 
 hipError_t launch_build_lists(const Units& un, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
                               const uint8_t* mode, const uint32_t* lbase, const uint64_t* wbase, uint32_t* list,
-                              uint64_t* wpre, hipStream_t st) {
+                              uint64_t* wpre, uint32_t* tile_e, uint32_t* tile_l, hipStream_t st) {
     if (!un.count) return hipSuccess;
-    k_build_lists<<<grid_for(un.count, 4, GRID_CAP), 256, 0, st>>>(un, pv, off, cur, mode, lbase, wbase, list, wpre);
+    k_build_lists<<<grid_for(un.count, 4, GRID_CAP), 256, 0, st>>>(un, pv, off, cur, mode, lbase, wbase, list, wpre,
+                                                                   tile_e, tile_l);
     return hipGetLastError();
 }
 
@@ -2892,85 +2975,85 @@ hipError_t launch_fill2_u32(uint32_t* p, uint64_t np, uint32_t* q, uint64_t nq, 
 }
 
 template <class Op>
-static hipError_t push_edges_op(const Op& op, const uint32_t* list, const uint64_t* wpre, uint32_t ja, uint32_t jb,
+static hipError_t push_edges_op(const Op& op, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja, uint32_t jb,
                                 uint64_t lo, uint64_t hi, const uint64_t* off, const uint32_t* col,
                                 const uint32_t* w, uint64_t shift, bool compacted, const Pack& pk, hipStream_t st) {
-    const unsigned g = grid_for(hi - lo, EDGE_IPB, GRID_CAP);
+    const unsigned g = grid_for(((hi - 1) >> EDGE_TILE_SHIFT) - (lo >> EDGE_TILE_SHIFT) + 1, 1, GRID_CAP);
     if (compacted)
-        k_push_edges<Op, true><<<g, EDGE_THREADS, 0, st>>>(list, wpre, ja, jb, lo, hi, off, col, w, shift, op, pk);
+        k_push_edges<Op, true><<<g, EDGE_THREADS, 0, st>>>(list, wpre, tile, ja, jb, lo, hi, off, col, w, shift, op, pk);
     else
-        k_push_edges<Op, false><<<g, EDGE_THREADS, 0, st>>>(list, wpre, ja, jb, lo, hi, off, col, w, shift, op, pk);
+        k_push_edges<Op, false><<<g, EDGE_THREADS, 0, st>>>(list, wpre, tile, ja, jb, lo, hi, off, col, w, shift, op, pk);
     return hipGetLastError();
 }
 
-hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, uint32_t ja,
+hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, uint64_t shift, bool compacted,
                              hipStream_t st) {
     if (item_hi <= item_lo || jb <= ja) return hipSuccess;
     switch (s.algo) {
     case ALGO_BFS:
-        return push_edges_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, ja, jb, item_lo, item_hi,
+        return push_edges_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
                              off, col, w, shift, compacted, s.pk, st);
     case ALGO_SSSP:
-        return push_edges_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, ja, jb, item_lo, item_hi, off, col, w,
+        return push_edges_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w,
                              shift, compacted, s.pk, st);
     case ALGO_CC:
-        return push_edges_op(OpCc{s.val, s.next}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, shift,
+        return push_edges_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
     case ALGO_BFS_RELAX:
-        return push_edges_op(OpBfsRelax{s.val, s.next}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, shift,
+        return push_edges_op(OpBfsRelax{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
     case ALGO_MBFS:
-        return push_edges_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, ja, jb,
+        return push_edges_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, tile, ja, jb,
                              item_lo, item_hi, off, col, w, shift, compacted, s.pk, st);
     case ALGO_MSSSP:
-        return push_edges_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, ja, jb, item_lo,
+        return push_edges_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, shift, compacted, s.pk, st);
     case ALGO_MPPR:
-        return push_edges_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, ja, jb, item_lo,
+        return push_edges_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, shift, compacted, s.pk, st);
     default:
-        return push_edges_op(OpPr{s.acc, acc_slots(s.n), s.contrib, s.acc_copies - 1}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, shift,
+        return push_edges_op(OpPr{s.acc, acc_slots(s.n), s.contrib, s.acc_copies - 1}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
     }
 }
 
 template <class Op>
-static hipError_t push_lines_op(const Op& op, const uint32_t* list, const uint64_t* wpre, uint32_t ja, uint32_t jb,
+static hipError_t push_lines_op(const Op& op, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja, uint32_t jb,
                                 uint64_t lo, uint64_t hi, const uint64_t* off, const uint32_t* col,
                                 const uint32_t* w, unsigned long long* distinct, const Pack& pk, hipStream_t st,
                                 unsigned cap = GRID_CAP) {
-    const unsigned g = grid_for(hi - lo, LINE_IPB, cap ? cap : GRID_CAP);
-    k_push_lines<Op><<<g, LINE_THREADS, 0, st>>>(list, wpre, ja, jb, lo, hi, off, col, w, op, distinct, pk);
+    const unsigned g = grid_for(((hi - 1) >> LINE_TILE_SHIFT) - (lo >> LINE_TILE_SHIFT) + 1, 1, cap ? cap : GRID_CAP);
+    k_push_lines<Op><<<g, LINE_THREADS, 0, st>>>(list, wpre, tile, ja, jb, lo, hi, off, col, w, op, distinct, pk);
     return hipGetLastError();
 }
 
-hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, uint32_t ja,
+hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, unsigned long long* distinct, hipStream_t st) {
     if (item_hi <= item_lo || jb <= ja) return hipSuccess;
     switch (s.algo) {
     case ALGO_BFS:
-        return push_lines_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, ja, jb, item_lo, item_hi,
+        return push_lines_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
                              off, col, w, distinct, s.pk, st);
     case ALGO_SSSP:
-        return push_lines_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
+        return push_lines_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_CC:
-        return push_lines_op(OpCc{s.val, s.next}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
+        return push_lines_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_BFS_RELAX:
-        return push_lines_op(OpBfsRelax{s.val, s.next}, list, wpre, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
+        return push_lines_op(OpBfsRelax{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_MBFS:
-        return push_lines_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, ja, jb,
+        return push_lines_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, tile, ja, jb,
                              item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_MSSSP:
-        return push_lines_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, ja, jb, item_lo,
+        return push_lines_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_MPPR:
-        return push_lines_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, ja, jb, item_lo,
+        return push_lines_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, distinct, s.pk, st);
     default:
-        return push_lines_op(OpPr{s.acc, acc_slots(s.n), s.contrib, s.acc_copies - 1}, list, wpre, ja, jb, item_lo, item_hi, off, col, w,
+        return push_lines_op(OpPr{s.acc, acc_slots(s.n), s.contrib, s.acc_copies - 1}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w,
                              distinct, s.pk, st, s.link_grid);
     }
 }

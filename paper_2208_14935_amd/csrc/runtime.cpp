@@ -248,6 +248,7 @@ struct hytm_graph {
     DevBuf<double> d_lacc;        // ... and accumulator rows (FP64)
     DevBuf<uint32_t> d_xout;      // lanes extracted for the copy back
     DevBuf<uint32_t> d_cur2;      // frontier of the reprocessing pass
+    DevBuf<uint32_t> d_tile_e, d_tile_l;  // list entries at the work tiles' starts
     DevBuf<uint64_t> d_scan;      // selection scan: per-tile totals and bases
     DevBuf<uint32_t> d_far;       // SSSP with sssp_delta: improved vertices waiting for a higher bound
     DevBuf<uint32_t> d_farmin;    // smallest waiting distance
@@ -653,6 +654,8 @@ void release_all(hytm_graph* g) {
     g->d_cur2.release();
     g->d_far.release();
     g->d_scan.release();
+    g->d_tile_e.release();
+    g->d_tile_l.release();
     g->d_farmin.release();
     g->h_farmin.release();
     g->d_zcl.release();
@@ -856,7 +859,7 @@ void run_compaction(RunCtx* rc, uint32_t cs, uint32_t cc, uint64_t w0, uint64_t 
                 HIP_CHECK(hipMemcpyAsync(g->d_cbuf_w[b].p, g->h_cbuf_w[b].p, (x1 - x0) * g->pk.wbytes,
                                          hipMemcpyHostToDevice, g->s_c));
             HIP_CHECK(g->timer.run(HYTM_K_PUSH_C, x1 - x0, g->s_c, [&] {
-                return launch_push_edges(rc->as, g->d_list.p, g->d_wpre.p, cs, cs + cc, x0, x1, g->d_off.p,
+                return launch_push_edges(rc->as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, cs, cs + cc, x0, x1, g->d_off.p,
                                          g->d_cbuf_col[b].p, g->d_cbuf_w[b].p, x0, true, g->s_c);
             }));
             HIP_CHECK(hipEventRecord(g->ev_cdone[b], g->s_c));
@@ -885,6 +888,8 @@ hytm_status prepare_graph(hytm_graph* g, uint32_t plan_arrays, hipStream_t main,
     const uint32_t npart = g->npart;
     g->d_list.ensure(n);
     g->d_wpre.ensure(n + 1);
+    g->d_tile_e.ensure(tile_entries(n, g->m, EDGE_TILE_SHIFT));
+    g->d_tile_l.ensure(tile_entries(n, g->m, LINE_TILE_SHIFT));
     g->d_overflow.ensure(2);
     g->d_zcl.ensure(1);
     g->d_lanes.ensure(1);
@@ -1147,7 +1152,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
         HIP_CHECK(hipMemcpyAsync(g->h_sel.p, g->d_sel.p, sel_block_bytes(npart), hipMemcpyDeviceToHost, main));
     if (lists) HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
         return launch_build_lists(g->units(), g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p, g->d_wbase.p,
-                                  g->d_list.p, g->d_wpre.p, main);
+                                  g->d_list.p, g->d_wpre.p, g->d_tile_e.p, g->d_tile_l.p, main);
     }));
     if (stats) HIP_CHECK(hipEventRecord(g->ev_sel[1], main));
     if (one)
@@ -1198,7 +1203,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
         }));
     else if (h.seg_list_count[SEG_R])
         HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_R],
+            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
                                      h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
                                      h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
                                      g->d_res_w.p, 0, false, main);
@@ -1206,7 +1211,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     // zero-copy: one kernel over all zero-copy vertices (Vz)
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
-            return launch_push_lines(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
+            return launch_push_lines(as, g->d_list.p, g->d_wpre.p, g->d_tile_l.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
                                      g->d_w_map, zcl_of(rc), g->s_zc);
@@ -1278,7 +1283,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
                 HIP_CHECK(hipEventRecord(g->ev_copied[s], g->s_copy));
                 HIP_CHECK(hipStreamWaitEvent(g->s_fk, g->ev_copied[s], 0));
                 HIP_CHECK(kt.run(HYTM_K_PUSH_F, wb - wa, g->s_fk, [&] {
-                    return launch_push_edges(as, g->d_list.p, g->d_wpre.p, ja, jb, wa, wb, g->d_off.p,
+                    return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, ja, jb, wa, wb, g->d_off.p,
                                              g->d_slot_col[s].p, g->d_slot_w[s].p, ebeg, false, g->s_fk);
                 }));
                 HIP_CHECK(hipEventRecord(g->ev_free[s], g->s_fk));
@@ -1367,7 +1372,7 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
     HIP_CHECK(hipEventRecord(g->ev_go, main));
     if (h.seg_list_count[SEG_R])
         HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_R],
+            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
                                      h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
                                      h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
                                      g->d_res_w.p, 0, false, main);
@@ -1375,7 +1380,7 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(hipStreamWaitEvent(g->s_zc, g->ev_go, 0));
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
-            return launch_push_lines(as, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
+            return launch_push_lines(as, g->d_list.p, g->d_wpre.p, g->d_tile_l.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
                                      g->d_w_map, zcl_of(rc), g->s_zc);
@@ -1572,7 +1577,7 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
     al.link_grid = kPbLinkGrid;
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
-            return launch_push_lines(al, g->d_list.p, g->d_wpre.p, h.seg_list_start[SEG_Z],
+            return launch_push_lines(al, g->d_list.p, g->d_wpre.p, g->d_tile_l.p, h.seg_list_start[SEG_Z],
                                      h.seg_list_start[SEG_Z] + h.seg_list_count[SEG_Z], h.seg_work_start[SEG_Z],
                                      h.seg_work_start[SEG_Z] + h.seg_work_total[SEG_Z], g->d_off.p, g->d_col_map,
                                      g->d_w_map, zcl_of(rc), g->s_zc);
