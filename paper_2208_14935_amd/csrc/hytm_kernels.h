@@ -295,6 +295,10 @@ hipError_t launch_reset_lanes(const AlgoState& s, uint64_t mask, hipStream_t st)
 // adds 1 - damping at each lane's source and marks it active for the next step.
 hipError_t launch_ppr_prepare(const AlgoState& s, const uint64_t* off, hipStream_t st);
 hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st);
+// apply, the values of restart and the next step's prepare in one pass (restart 0 then only
+// marks the sources).
+hipError_t launch_ppr_apply_next(const AlgoState& s, const uint64_t* off, const LaneSet& set, float damping,
+                                 float restart, hipStream_t st);
 hipError_t launch_ppr_restart(const AlgoState& s, const LaneSet& set, float restart, hipStream_t st);
 // In-edge lists of the n vertices of a CSR held on the device (m > 0 edges, destinations
 // col[e] & vmask): tsrc[toff[v] .. toff[v + 1]) = the sources of v's in-edges, tdst their

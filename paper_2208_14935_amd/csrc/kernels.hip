@@ -483,62 +483,55 @@ template <int PER>
 __global__ __launch_bounds__(1024) void k_scan_one(uint32_t npart, const uint8_t* __restrict__ mode,
                                                    const uint32_t* __restrict__ nA, const uint32_t* __restrict__ nF,
                                                    const uint64_t* __restrict__ Ea, const uint64_t* __restrict__ K,
-                                                   uint32_t* __restrict__ lbase, uint64_t* __restrict__ wbase,
+                                                   uint32_t* lbase, uint64_t* wbase,
                                                    uint64_t* __restrict__ wpre, ScanExtra x, ScanHost host) {
     constexpr int NW = 16;
     // per segment and wave: list entries, work, partitions, edges; then the waves' bases
     __shared__ uint64_t s_t[NSEG][4][NW];
     __shared__ uint64_t s_f[NW];
     __shared__ uint64_t s_tot[NSEG][4];
-    __shared__ uint32_t s_present;
     const uint32_t t = threadIdx.x, lane = t & 63, wid = t >> 6, i0 = t * PER;
-    uint32_t m[PER], na[PER];
-    uint64_t ea[PER], wk[PER], f = 0;
+    uint32_t na[PER];
+    uint8_t m[PER];
+    uint64_t wk[PER], ze = 0, f = 0;  // ze: edges of the zero-copy partitions, whose work is lines
     uint32_t has = 0;
 #pragma unroll
     for (int r = 0; r < PER; r++) {
         const uint32_t i = i0 + r;
         const bool in = i < npart;
-        m[r] = in ? mode[i] : (uint32_t)P_NONE;
+        m[r] = in ? mode[i] : (uint8_t)P_NONE;
         na[r] = in ? nA[i] : 0u;
-        ea[r] = in ? Ea[i] : 0ull;
-        wk[r] = in ? K[i] : 0ull;
+        wk[r] = in ? Ea[i] : 0ull;
+        const uint64_t k = in ? K[i] : 0ull;
         f += in ? nF[i] : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < PER; r++) {
         has |= 1u << m[r];
-        if (m[r] != P_ZC) wk[r] = ea[r];
+        if (m[r] == P_ZC) {
+            ze += wk[r];
+            wk[r] = k;
+        }
     }
-    if (t == 0) s_present = 0;
     for (uint32_t q = t; q < NSEG * 4 * NW; q += 1024) (&s_t[0][0][0])[q] = 0;
     f = wave_sum(f);
     if (lane == 0) s_f[wid] = f;
     __syncthreads();
-    uint32_t wave_has = 0;
-#pragma unroll
-    for (int sg = 0; sg < NSEG; sg++)
-        if (__ballot((has >> (sg + 1)) & 1)) wave_has |= 1u << sg;
-    if (lane == 0 && wave_has) atomicOr(&s_present, wave_has);
     uint64_t xc[NSEG], xw[NSEG];
 #pragma unroll
     for (int sg = 0; sg < NSEG; sg++) {
         xc[sg] = xw[sg] = 0;
-        if (!((wave_has >> sg) & 1)) continue;  // uniform across the wave
-        uint64_t c = 0, w = 0, e = 0;
+        if (!__ballot((has >> (sg + 1)) & 1)) continue;  // uniform across the wave
+        uint64_t c = 0, w = 0;
         uint32_t p = 0;
 #pragma unroll
         for (int r = 0; r < PER; r++)
-            if (m[r] == (uint32_t)sg + 1) {
+            if (m[r] == sg + 1) {
                 c += na[r];
                 w += wk[r];
-                e += ea[r];
                 p += 1;
             }
         uint64_t tc, tw;
         xc[sg] = wave_exclusive_sum(c, &tc);
         xw[sg] = wave_exclusive_sum(w, &tw);
-        const uint64_t tp = wave_sum(p), te = sg == SEG_Z ? wave_sum(e) : tw;
+        const uint64_t tp = wave_sum(p), te = sg == SEG_Z ? wave_sum(ze) : tw;
         if (lane == 0) {
             s_t[sg][0][wid] = tc;
             s_t[sg][1][wid] = tw;
@@ -574,7 +567,7 @@ __global__ __launch_bounds__(1024) void k_scan_one(uint32_t npart, const uint8_t
         uint64_t wb = ~0ull;
 #pragma unroll
         for (int sg = 0; sg < NSEG; sg++)
-            if (m[r] == (uint32_t)sg + 1) {
+            if (m[r] == sg + 1) {
                 lb = (uint32_t)bc[sg];
                 wb = bw[sg];
                 bc[sg] += na[r];
@@ -582,11 +575,6 @@ __global__ __launch_bounds__(1024) void k_scan_one(uint32_t npart, const uint8_t
             }
         lbase[i] = lb;
         wbase[i] = wb;
-        if (host.mode) {
-            host.lbase[i] = lb;
-            host.wbase[i] = wb;
-            host.mode[i] = (uint8_t)m[r];
-        }
     }
     if (t == 0) {
         Header* hdr = host.hdr;
@@ -607,6 +595,15 @@ __global__ __launch_bounds__(1024) void k_scan_one(uint32_t npart, const uint8_t
         hdr->frontier = fr;
         scan_extra(hdr, x);
         wpre[l] = w;
+    }
+    if (host.mode) {
+        // across the link in whole lines: a thread's own run of entries took a transaction each
+        __syncthreads();
+        for (uint32_t i = t; i < npart; i += 1024) {
+            host.wbase[i] = wbase[i];
+            host.lbase[i] = lbase[i];
+            host.mode[i] = mode[i];
+        }
     }
     __threadfence_system();
     __syncthreads();
@@ -918,7 +915,7 @@ struct OpMBfs {
         uint64_t gained = want & ~old;
         if (!gained) return;
         atomicOr((unsigned long long*)(mnext + v), (unsigned long long)gained);
-        atomicOr(next + (v >> 5), 1u << (v & 31));
+        mark_next(next, v);
         uint32_t* row = lvl + ((uint64_t)v << lshift);
         while (gained) {
             row[__ffsll((unsigned long long)gained) - 1] = level_next;
@@ -957,20 +954,26 @@ struct OpMSssp {
         }
         if (gained) {
             atomicOr((unsigned long long*)(mnext + v), (unsigned long long)gained);
-            atomicOr(next + (v >> 5), 1u << (v & 31));
+            mark_next(next, v);
         }
     }
     // Wave form (see OpMPpr::push_wave): each pass gives 64 >> lshift of the wave's edges one
     // thread per lane, so an edge's relaxations are one atomicMin instruction over its
     // contiguous distance row; the lanes that improved are collected by ballot and one
-    // thread per edge marks them.  It pays when the rows are dense (a batch started
-    // together); when the wave's edges carry fewer than a quarter row of active lanes on
-    // average (queries at different stages) each thread relaxes its own edge's lanes.
-    // Called by every thread of the wave.
+    // thread per edge marks them.  The wave's edges are first moved to its front, and WU of
+    // them per thread go through each step together, so that their rows are in flight at once
+    // (one at a time, 262K vertices with 37 lanes: 0.93 ms of the widest iteration's 4M edges).
+    // It pays when the rows are dense (a batch started together); when the wave's edges
+    // carry fewer than a quarter row of active lanes on average (queries at different stages)
+    // each thread relaxes its own edge's lanes.  Called by every thread of the wave.
+    static constexpr int WU = 4;
     __device__ __forceinline__ void push_wave(bool ok, uint32_t u, uint32_t v, uint32_t w) const {
-        const uint64_t active = wave_sum(ok ? (uint64_t)__popcll(mcur[u]) : 0ull);
-        const uint64_t edges = (uint64_t)__popcll(__ballot(ok));
-        if (lshift < 3 || active * 4 < (edges << lshift)) {
+        uint32_t active = ok ? (uint32_t)__popcll(mcur[u]) : 0u;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) active += __shfl_xor(active, d, 64);
+        const uint64_t act = __ballot(ok);
+        const uint32_t cnt = __popcll(act);
+        if (lshift < 3 || active * 4 < (cnt << lshift)) {
             if (ok) push(u, v, w);
             return;
         }
@@ -978,29 +981,41 @@ struct OpMSssp {
         const uint32_t slot = me >> lshift, ln = me & ((1u << lshift) - 1);
         const uint32_t per = 64u >> lshift;
         const uint64_t rowmask = lshift >= 6 ? ~0ull : ((1ull << (1u << lshift)) - 1);
-        uint64_t act = __ballot(ok);
-        while (act) {
-            uint64_t a = act;
-            for (uint32_t k = 0; k < slot; k++) a &= a - 1;
-            const int from = a ? (int)__ffsll((unsigned long long)a) - 1 : 0;
-            const uint32_t uu = __shfl(u, from, 64), vv = __shfl(v, from, 64), ww = __shfl(w, from, 64);
-            bool gained = false;
-            if (a && ((mcur[uu] >> ln) & 1)) {
-                const uint64_t nd = (uint64_t)dist[((uint64_t)uu << lshift) + ln] + ww;
-                uint32_t* dv = dist + ((uint64_t)vv << lshift) + ln;
-                if (nd >= UNREACHED) {
+        const uint64_t below = (1ull << me) - 1ull;
+        const int to = (int)((ok ? __popcll(act & below) : cnt + __popcll(~act & below)) << 2);
+        const int uc = __builtin_amdgcn_ds_permute(to, (int)u), vc = __builtin_amdgcn_ds_permute(to, (int)v);
+        const int wc = __builtin_amdgcn_ds_permute(to, (int)w);
+        for (uint32_t j = 0; j < cnt; j += WU * per) {
+            uint32_t vv[WU], nd[WU], dv[WU];
+            bool go[WU];
+#pragma unroll
+            for (int r = 0; r < WU; r++) {
+                const uint32_t q = j + r * per + slot;
+                const int from = (int)(q & 63);
+                const uint32_t uu = (uint32_t)__shfl(uc, from, 64), ww = (uint32_t)__shfl(wc, from, 64);
+                vv[r] = (uint32_t)__shfl(vc, from, 64);
+                go[r] = q < cnt && ((mcur[uu] >> ln) & 1);
+                const uint64_t x = go[r] ? (uint64_t)dist[((uint64_t)uu << lshift) + ln] + ww : 0ull;
+                dv[r] = go[r] ? dist[((uint64_t)vv[r] << lshift) + ln] : 0u;
+                if (x >= UNREACHED) {
                     atomicOr(overflow + (ln >> 5), 1u << (ln & 31));
-                } else if ((uint32_t)nd < *dv) {
-                    const uint32_t old = atomicMin(dv, (uint32_t)nd);
-                    gained = (uint32_t)nd < old;
+                    go[r] = false;
+                }
+                nd[r] = (uint32_t)x;
+            }
+#pragma unroll
+            for (int r = 0; r < WU; r++) {
+                go[r] = go[r] && nd[r] < dv[r];
+                if (go[r]) dv[r] = atomicMin(dist + ((uint64_t)vv[r] << lshift) + ln, nd[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < WU; r++) {
+                const uint64_t g = (__ballot(go[r] && nd[r] < dv[r]) >> (slot << lshift)) & rowmask;
+                if (ln == 0 && g) {
+                    atomicOr((unsigned long long*)(mnext + vv[r]), (unsigned long long)g);
+                    mark_next(next, vv[r]);
                 }
             }
-            const uint64_t g = (__ballot(gained) >> (slot << lshift)) & rowmask;
-            if (a && ln == 0 && g) {
-                atomicOr((unsigned long long*)(mnext + vv), (unsigned long long)g);
-                atomicOr(next + (vv >> 5), 1u << (vv & 31));
-            }
-            for (uint32_t k = 0; k < per && act; k++) act &= act - 1;
         }
     }
 };
@@ -1677,11 +1692,34 @@ __global__ __launch_bounds__(256) void k_ppr_apply(AlgoState s, float damping) {
     }
 }
 
+// k_ppr_apply and the next step's k_ppr_prepare in one pass, for lanes that all step on: the
+// values after the restart of each lane's source, scaled by 1 / D_o where there are out-edges.
+__global__ __launch_bounds__(256) void k_ppr_apply_next(AlgoState s, const uint64_t* __restrict__ off, LaneSet set,
+                                                        float damping, float restart) {
+    __shared__ uint32_t s_src[MAX_LANES];
+    if (threadIdx.x < MAX_LANES) s_src[threadIdx.x] = (set.mask >> threadIdx.x) & 1 ? set.src[threadIdx.x] : UNREACHED;
+    __syncthreads();
+    const uint64_t cells = s.n << s.lshift;
+    const uint32_t lmask = (1u << s.lshift) - 1;
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
+        const uint64_t v = i >> s.lshift;
+        const uint32_t l = (uint32_t)i & lmask;
+        const bool source = s_src[l] == v;
+        const bool got = ((s.mcur[v] | s.mnext[v]) >> l) & 1;
+        if (!got && !source) continue;
+        float x = got ? (float)((double)damping * s.lacc[i]) : s.lx[i];
+        if (source) x += restart;
+        const uint64_t d = off[v + 1] - off[v];
+        s.lx[i] = d ? x / (float)d : x;
+        if (got) s.lacc[i] = 0.0;
+    }
+}
+
 __global__ void k_ppr_restart(AlgoState s, LaneSet set, float restart) {
     const uint32_t l = threadIdx.x;
     if (l >= MAX_LANES || !((set.mask >> l) & 1)) return;
     const uint32_t v = set.src[l];
-    s.lx[((uint64_t)v << s.lshift) + l] += restart;
+    if (restart != 0.0f) s.lx[((uint64_t)v << s.lshift) + l] += restart;
     atomicOr((unsigned long long*)(s.mnext + v), 1ull << l);
     atomicOr(s.next + (v >> 5), 1u << (v & 31));
 }
@@ -2445,6 +2483,7 @@ __global__ __launch_bounds__(256) void k_ppr_pull_runs(AlgoState s, const uint32
             const bool in = i < e;
             const uint32_t u = in ? tsrc[i] : 0u, d = in ? tdst[i] : UNREACHED;
             const uint64_t mu = in ? s.mcur[u] : 0ull;
+#pragma unroll 1
             for (uint32_t t = 0; t < S; t += IN_UNROLL) {
                 float x[IN_UNROLL];
                 uint32_t dd[IN_UNROLL];
@@ -2872,6 +2911,13 @@ hipError_t launch_ppr_prepare(const AlgoState& s, const uint64_t* off, hipStream
     return hipGetLastError();
 }
 
+hipError_t launch_ppr_apply_next(const AlgoState& s, const uint64_t* off, const LaneSet& set, float damping,
+                                 float restart, hipStream_t st) {
+    if (!s.n) return hipSuccess;
+    k_ppr_apply_next<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, off, set, damping, restart);
+    return hipGetLastError();
+}
+
 hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st) {
     if (!s.n) return hipSuccess;
     k_ppr_apply<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, damping);
@@ -2954,6 +3000,8 @@ hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* 
         k_scan_one<1><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
     else if (npart <= 4096)
         k_scan_one<4><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
+    else if (npart <= 8192)
+        k_scan_one<8><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
     else
         k_scan_one<16><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
     return hipGetLastError();

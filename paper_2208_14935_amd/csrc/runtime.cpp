@@ -768,6 +768,8 @@ struct RunCtx {
     uint64_t overflow = 0;                     // the SSSP overflow words as of the last selection
     uint64_t *mcur = nullptr, *mnxt = nullptr; // lane masks
     LaneSet ppr{};                             // PPR lanes stepping, restarted at their sources
+    uint32_t ppr_together = 0;                 // steps that all of them take (0: a server's lanes)
+    bool ppr_scaled = false;                   // their values are scaled for the coming push
     bool reprocess = false;                    // second pass over loaded partitions (Sec. 6.1)
     // PageRank's frontier is every vertex in every iteration, so the first iteration's
     // selection, lists and filter tasks hold for all of them: later iterations replay them
@@ -1195,19 +1197,9 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
         if (use_f) HIP_CHECK(hipStreamWaitEvent(g->s_fk, g->ev_go, 0));
     }
 
-    // resident partitions: no transfer
-    if (rc.pull && h.seg_work_total[SEG_R] >= g->m / kPullShare && in_ready(rc, main))
-        HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-            return launch_ppr_pull(as, g->in.toff.p, g->in.soff.p, g->in.seg_v.p, g->in.tsrc.p, g->in.tdst.p,
-                                   g->in.m, g->in.nseg, main);
-        }));
-    else if (h.seg_list_count[SEG_R])
-        HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
-                                     h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
-                                     h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
-                                     g->d_res_w.p, 0, false, main);
-        }));
+    // The engines that use the host link are launched first: it bounds a pass that uses it,
+    // and a resident push that has filled the GPU delays even the copy of the filter tasks
+    // (80 us on R-MAT 20 with 64 lanes), while it finds its CUs beside them.
     // zero-copy: one kernel over all zero-copy vertices (Vz)
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
@@ -1303,6 +1295,19 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
             }
             rec->filter_tasks += gidx;
         }
+        // resident partitions: no transfer
+        if (rc.pull && h.seg_work_total[SEG_R] >= g->m / kPullShare && in_ready(rc, main))
+            HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
+                return launch_ppr_pull(as, g->in.toff.p, g->in.soff.p, g->in.seg_v.p, g->in.tsrc.p, g->in.tdst.p,
+                                       g->in.m, g->in.nseg, main);
+            }));
+        else if (h.seg_list_count[SEG_R])
+            HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
+                return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
+                                         h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
+                                         h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
+                                         g->d_res_w.p, 0, false, main);
+            }));
     } catch (const HipError& e) {
         fst = e.status;
     }
@@ -1814,7 +1819,7 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
             return launch_pr_prepare(n, g->d_off.p, g->d_x.p, g->d_contrib.p, g->d_acc.p, copies, main);
         }));
-    if (rc.algo == HYTM_PPR)
+    if (rc.algo == HYTM_PPR && !rc.ppr_scaled)
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] { return launch_ppr_prepare(as, g->d_off.p, main); }));
     as.level_next = t + 1;
     hytm_iter_stats rec{};
@@ -1906,8 +1911,16 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
         if (rc.algo == HYTM_PPR) {
             const float d = (float)g->params.pr_damping;
             const float restart = (float)(1.0 - g->params.pr_damping);
-            HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] { return launch_ppr_apply(as, d, main); }));
-            HIP_CHECK(kt.run(HYTM_K_OTHER, 1, main, [&] { return launch_ppr_restart(as, rc.ppr, restart, main); }));
+            // lanes that run their steps together (not a server's, which retire one by one) are
+            // left scaled for the next step
+            rc.ppr_scaled = t + 1 < rc.ppr_together;
+            HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
+                return rc.ppr_scaled ? launch_ppr_apply_next(as, g->d_off.p, rc.ppr, d, restart, main)
+                                     : launch_ppr_apply(as, d, main);
+            }));
+            HIP_CHECK(kt.run(HYTM_K_OTHER, 1, main, [&] {
+                return launch_ppr_restart(as, rc.ppr, rc.ppr_scaled ? 0.f : restart, main);
+            }));
         }
         if (rc.spare) {  // cleared by this iteration's selection
             uint32_t* done = rc.cur;
@@ -1991,30 +2004,42 @@ uint32_t lane_shift(uint32_t lanes) {
 }
 
 // Copy the lanes of `set` (values of n vertices each, in rows of 2^lshift) into
-// consecutive n-value rows of the host buffer `out`, EXTRACT_LANES lanes per device pass.
+// consecutive n-value rows of the host buffer `out`: the device rows' two halves of
+// EXTRACT_LANES / 2 lanes alternate, one being copied while the other is extracted.
 constexpr uint32_t EXTRACT_LANES = 8;
 void copy_lanes_out(hytm_graph* g, const uint32_t* vals, uint32_t lshift, const LaneSet& set, bool sub_base,
                     void* const* outs, hipStream_t main) {
     const uint64_t n = g->n;
     g->d_xout.ensure(n * EXTRACT_LANES);
+    constexpr uint32_t HALF = EXTRACT_LANES / 2;
     uint64_t rest = set.mask;
     uint32_t k = 0;
-    while (rest) {
+    for (uint32_t pass = 0; rest; pass++) {
+        const uint32_t b = pass & 1;
         LaneSet part = set;
         part.mask = 0;
-        for (uint32_t c = 0; c < EXTRACT_LANES && rest; c++) {
+        for (uint32_t c = 0; c < HALF && rest; c++) {
             part.mask |= rest & (~rest + 1);
             rest &= rest - 1;
         }
-        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, g->hub_sorted() ? g->d_order.p : nullptr,
-                                       g->d_xout.p, main));
+        uint32_t* rows = g->d_xout.p + b * HALF * n;
+        if (pass >= 2) HIP_CHECK(hipStreamWaitEvent(main, g->ev_free[b], 0));  // copied out
+        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, g->hub_sorted() ? g->d_order.p : nullptr, rows,
+                                       main));
+        HIP_CHECK(hipEventRecord(g->ev_copied[b], main));
+        HIP_CHECK(hipStreamWaitEvent(g->s_copy, g->ev_copied[b], 0));
         const uint32_t cnt = (uint32_t)__builtin_popcountll(part.mask);
-        for (uint32_t c = 0; c < cnt; c++)
-            HIP_CHECK(hipMemcpyAsync(outs[k + c], g->d_xout.p + (uint64_t)c * n, n * 4, hipMemcpyDeviceToHost, main));
-        // the staging rows are reused by the next pass
-        HIP_CHECK(hipStreamSynchronize(main));
+        // rows that lie behind one another in the caller's memory go in one copy: copies of a
+        // few MB stand 11 us apart, an eighth of their time
+        for (uint32_t c = 0, c1; c < cnt; c = c1) {
+            for (c1 = c + 1; c1 < cnt && (char*)outs[k + c1] == (char*)outs[k + c] + (uint64_t)(c1 - c) * n * 4;) c1++;
+            HIP_CHECK(hipMemcpyAsync(outs[k + c], rows + (uint64_t)c * n, (uint64_t)(c1 - c) * n * 4,
+                                     hipMemcpyDeviceToHost, g->s_copy));
+        }
+        HIP_CHECK(hipEventRecord(g->ev_free[b], g->s_copy));
         k += cnt;
     }
+    HIP_CHECK(hipStreamSynchronize(g->s_copy));
 }
 
 // One run.  lanes == 0: single source `sources[0]` (BFS/SSSP) or none (CC/PR), values_out
@@ -2167,6 +2192,7 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
         for (uint32_t l = 0; l < lanes; l++) ls.src[l] = g->inner(sources[l]);
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] { return launch_init_lanes(as, ls, rc.cur, nwords, main); }));
         rc.ppr.mask = lanes == 64 ? ~0ull : (1ull << lanes) - 1;
+        rc.ppr_together = algo == HYTM_PPR ? g->params.ppr_iterations : 0;
         for (uint32_t l = 0; l < lanes; l++) rc.ppr.src[l] = ls.src[l];
     } else if (algo == HYTM_PAGERANK_DELTA) {
         // x = 0, every vertex holds delta = (1 - d) / n (n of its own graph), nothing pushed yet
