@@ -300,23 +300,26 @@ hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st);
 hipError_t launch_ppr_apply_next(const AlgoState& s, const uint64_t* off, const LaneSet& set, float damping,
                                  float restart, hipStream_t st);
 hipError_t launch_ppr_restart(const AlgoState& s, const LaneSet& set, float restart, hipStream_t st);
-// In-edge lists of the n vertices of a CSR held on the device (m > 0 edges, destinations
-// col[e] & vmask): tsrc[toff[v] .. toff[v + 1]) = the sources of v's in-edges, tdst their
-// destinations (v; a destination >= n is left out, toff[n] counts the others).  Vertex v's
-// list is cut into segments of IN_SEG edges, numbers soff[v] .. soff[v + 1); seg_v[s] = the
-// vertex of segment s (at most in_max_segs of them).  cnt (n words) and tot (2 in_tiles(n))
-// are scratch.
+// In-edge lists of the n vertices of a CSR held on the device (m > 0 edges): tsrc[toff[v] ..
+// toff[v + 1]) = the sources of v's in-edges, tdst their destinations (v; a destination >= n
+// is left out, toff[n] counts the others), tw their weights (or null).  Vertex v's list is cut
+// into segments of IN_SEG edges, numbers soff[v] .. soff[v + 1); seg_v[s] = the vertex of
+// segment s (at most in_max_segs of them).  cnt (n words) and tot (2 in_tiles(n)) are scratch.
 constexpr uint32_t IN_SEG = 256;
 inline uint64_t in_tiles(uint64_t n) { return (n + 4095) / 4096; }
 inline uint64_t in_max_segs(uint64_t n, uint64_t m) { return std::min(m, n + m / IN_SEG); }
-hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t n,
-                           uint32_t* cnt, uint64_t* tot, uint64_t* toff, uint32_t* soff, uint32_t* seg_v,
-                           uint32_t* tsrc, uint32_t* tdst, hipStream_t st);
-// The push of a PPR step (OpMPpr over all active vertices), done from the receiving side:
-// every vertex's in-edge segments sum the shares of their active sources, mark the lanes
-// that received one in mnext and the vertex in next.
-hipError_t launch_ppr_pull(const AlgoState& s, const uint64_t* toff, const uint32_t* soff, const uint32_t* seg_v,
-                           const uint32_t* tsrc, const uint32_t* tdst, uint64_t m, uint32_t nseg, hipStream_t st);
+hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, const uint32_t* w, const Pack& pk, uint64_t m,
+                           uint64_t n, uint32_t* cnt, uint64_t* tot, uint64_t* toff, uint32_t* soff, uint32_t* seg_v,
+                           uint32_t* tsrc, uint32_t* tdst, uint32_t* tw, hipStream_t st);
+struct InLists {
+    uint64_t m;     // edges listed
+    uint32_t nseg;  // segments
+    const uint64_t* toff;
+    const uint32_t *soff, *seg_v, *tsrc, *tdst, *tw;
+};
+// The push of a batched PPR step, or of a batched SSSP step of rows of at least 16 lanes (all
+// active vertices), done from the receiving side.
+hipError_t launch_pull(const AlgoState& s, const InLists& in, hipStream_t st);
 
 // Scan of the selection: scratch holds scan_scratch_words(npart) uint64 (tile totals and bases).
 constexpr int SCAN_THREADS = 512;

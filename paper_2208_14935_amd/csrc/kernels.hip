@@ -2407,157 +2407,221 @@ __device__ __forceinline__ uint64_t source_of(const uint64_t* __restrict__ off, 
 // A wave takes 64 consecutive edges: it finds the sources of the first and the last, and each
 // lane its own between them.
 __global__ __launch_bounds__(256) void k_in_scatter(const uint64_t* __restrict__ off, const uint32_t* __restrict__ col,
-                                                    uint32_t vmask, uint64_t m, uint64_t n,
+                                                    const uint32_t* __restrict__ w, Pack pk, uint64_t m, uint64_t n,
                                                     const uint64_t* __restrict__ toff, uint32_t* __restrict__ cur,
-                                                    uint32_t* __restrict__ tsrc, uint32_t* __restrict__ tdst) {
+                                                    uint32_t* __restrict__ tsrc, uint32_t* __restrict__ tdst,
+                                                    uint32_t* __restrict__ tw) {
     for (uint64_t e0 = (blockIdx.x * 256ull + threadIdx.x) & ~63ull; e0 < m; e0 += (uint64_t)gridDim.x * 256) {
         const uint64_t e = e0 + (threadIdx.x & 63);
         const uint64_t u0 = source_of(off, 0, n, e0);
         const uint64_t u1 = source_of(off, u0, n, min(e0 + 63, m - 1));
         if (e >= m) continue;
         const uint64_t u = source_of(off, u0, u1 + 1, e);
-        const uint32_t v = col[e] & vmask;
+        const uint32_t c = col[e], v = pk_v(c, pk);
         if (v < n) {
             const uint64_t at = toff[v] + atomicAdd(cur + v, 1u);
             tsrc[at] = (uint32_t)u;
             tdst[at] = v;
+            if (tw) tw[at] = pk_w(c, pk.shift == 32 ? load_w(w, e, pk) : 0u, pk);
         }
     }
 }
 
-// Personalized PageRank over in-edges.  Two forms by the width of a value row, S = 2^LSH:
+// Lane rows over in-edges: a step of personalized PageRank (the active sources' shares summed)
+// or of batched SSSP (the least distance over the active sources).  Two forms by the width
+// of a row, S = 2^LSH:
 //
-// Rows of 16 lanes and more (k_ppr_pull_runs): S threads take a run of IN_RUN consecutive
+// Rows of 16 lanes and more (k_pull_runs): S threads take a run of IN_RUN consecutive
 // in-edges, S of them at a time: each thread loads one edge's source, destination and lane
-// mask, then all of them add the sources' share rows, one lane per thread, IN_UNROLL rows in
-// flight, and hand the sums over whenever the destination changes.  A destination inside the
-// run is written with plain stores (its sums are zero before); the run's first and last one
-// may continue in the neighbouring runs and are added atomically.
+// mask, then all of them take the sources' rows, one lane per thread, IN_UNROLL rows in
+// flight, and hand the result over whenever the destination changes.  A destination inside
+// the run is written with plain stores (no other run holds its edges); the run's first and
+// last one may continue in the neighbouring runs and are updated atomically.
 //
-// Narrower rows (k_ppr_pull_segs): 16 threads take a segment of one vertex's in-list, 16 / S
-// of its edges at once.
+// Narrower rows (k_pull_segs): 16 threads take a segment of one vertex's in-list, 16 / S of
+// its edges at once.
 //
-// Bound by the gathered rows; before, a wave per vertex waited through six dependent loads for
-// the few edges of an average in-list.  Measured per dense step on R-MAT 20 with 64 lanes
-// (16M edges, 256-byte rows): see kPullShare.
+// Bound by the gathered rows (a wave per vertex waited through six dependent loads for the
+// few edges of an average in-list).  Measured on R-MAT 20 with 64 PPR lanes: 16M rows of 256
+// bytes in 1.6 ms, 2.6 TB/s; the push's FP64 atomic adds took 10 ms.
 constexpr int IN_UNROLL = 8;
 constexpr uint32_t IN_RUN = 128;
 
-// The sums of a destination handed over by one run of S threads (lane ln of the row each).
-template <int LSH>
-__device__ __forceinline__ void ppr_hand_over(const AlgoState& s, uint32_t v, uint32_t ln, double acc, uint64_t m,
-                                              bool shared) {
-    if (!m) return;
-    double* av = s.lacc + ((uint64_t)v << LSH);
-    if (shared) {
-        if ((m >> ln) & 1) unsafeAtomicAdd(av + ln, acc);
-        if (ln == 0) atomicOr((unsigned long long*)(s.mnext + v), (unsigned long long)m);
-    } else {
-        av[ln] = acc;
-        if (ln == 0) s.mnext[v] = m;
+// What a destination gathers: PPR sums in FP64 and the lanes that received a share, SSSP the
+// least candidate distance.
+struct PullPpr {
+    typedef double Acc;
+    static constexpr bool weighted = false, narrow = true;  // narrow: rows of 1..8 lanes too
+    static __device__ __forceinline__ Acc none() { return 0.0; }
+    static __device__ __forceinline__ Acc join(Acc a, Acc b) { return a + b; }
+    // value of lane ln of source u's row, for an edge of weight w whose source has the lanes mu active
+    template <int LSH>
+    static __device__ __forceinline__ float take(const AlgoState& s, uint32_t u, uint64_t mu, uint32_t ln) {
+        return mu ? s.lx[((uint64_t)u << LSH) + ln] : 0.0f;
     }
-    if (ln == 0) {
-        const uint32_t bit = 1u << (v & 31);
-        if (!(s.next[v >> 5] & bit)) atomicOr(s.next + (v >> 5), bit);
+    static __device__ __forceinline__ Acc value(const AlgoState&, float x, uint32_t, uint64_t, uint32_t) { return x; }
+    // the result of destination v, handed over by the S threads of its row
+    template <int LSH>
+    static __device__ __forceinline__ void hand_over(const AlgoState& s, uint32_t v, uint32_t ln, Acc acc, uint64_t m,
+                                                     bool shared) {
+        if (!m) return;
+        double* av = s.lacc + ((uint64_t)v << LSH);
+        if (shared) {
+            if ((m >> ln) & 1) unsafeAtomicAdd(av + ln, acc);
+            if (ln == 0) atomicOr((unsigned long long*)(s.mnext + v), (unsigned long long)m);
+        } else {
+            av[ln] = acc;  // the sums are zero before
+            if (ln == 0) s.mnext[v] = m;
+        }
+        if (ln == 0) mark_next(s.next, v);
     }
-}
+};
 
-template <int LSH>
-__global__ __launch_bounds__(256) void k_ppr_pull_runs(AlgoState s, const uint32_t* __restrict__ tsrc,
-                                                       const uint32_t* __restrict__ tdst, uint64_t m) {
+struct PullSssp {
+    typedef uint32_t Acc;
+    static constexpr bool weighted = true, narrow = false;
+    static __device__ __forceinline__ Acc none() { return UNREACHED; }
+    static __device__ __forceinline__ Acc join(Acc a, Acc b) { return a < b ? a : b; }
+    template <int LSH>
+    static __device__ __forceinline__ uint32_t take(const AlgoState& s, uint32_t u, uint64_t mu, uint32_t ln) {
+        return (mu >> ln) & 1 ? s.lval[((uint64_t)u << LSH) + ln] : 0u;
+    }
+    static __device__ __forceinline__ Acc value(const AlgoState& s, uint32_t x, uint32_t w, uint64_t mu, uint32_t ln) {
+        if (!((mu >> ln) & 1)) return UNREACHED;
+        const uint64_t nd = (uint64_t)x + w;
+        if (nd >= UNREACHED) {
+            atomicOr(s.overflow + (ln >> 5), 1u << (ln & 31));
+            return UNREACHED;
+        }
+        return (uint32_t)nd;
+    }
+    template <int LSH>
+    static __device__ __forceinline__ void hand_over(const AlgoState& s, uint32_t v, uint32_t ln, Acc acc, uint64_t m,
+                                                     bool shared) {
+        if (!m) return;
+        uint32_t* dv = s.lval + ((uint64_t)v << LSH) + ln;
+        bool better = acc < *dv;
+        if (better) {
+            if (shared)
+                better = acc < atomicMin(dv, acc);
+            else
+                *dv = acc;
+        }
+        const uint64_t rowmask = LSH >= 6 ? ~0ull : ((1ull << (1u << LSH)) - 1);
+        const uint64_t g = (__ballot(better) >> (__lane_id() & ~((1u << LSH) - 1))) & rowmask;
+        if (ln == 0 && g) {
+            if (shared)
+                atomicOr((unsigned long long*)(s.mnext + v), (unsigned long long)g);
+            else
+                s.mnext[v] = g;
+            mark_next(s.next, v);
+        }
+    }
+};
+
+template <int LSH, class P>
+__global__ __launch_bounds__(256) void k_pull_runs(AlgoState s, InLists in) {
     constexpr uint32_t S = 1u << LSH;
     const uint32_t lane = threadIdx.x & 63, ln = lane & (S - 1), g0 = lane & ~(S - 1);
     const uint64_t groups = (uint64_t)gridDim.x * (256u >> LSH);
-    const uint64_t runs = (m + IN_RUN - 1) / IN_RUN;
+    const uint64_t runs = (in.m + IN_RUN - 1) / IN_RUN;
     const uint64_t first = (blockIdx.x * 256ull + threadIdx.x) >> LSH;
     // whole waves stay together: a group past the last run goes through the loop with no edges
     for (uint64_t w0 = first - (lane >> LSH); w0 < runs; w0 += groups) {
         const uint64_t run = w0 + (lane >> LSH);
-        const uint64_t b = min(run * IN_RUN, m), e = min(b + IN_RUN, m);
+        const uint64_t b = min(run * IN_RUN, in.m), e = min(b + IN_RUN, in.m);
         uint32_t cur = UNREACHED;
-        bool head = b > 0 && b < e && tdst[b - 1] == tdst[b];  // the first destination began earlier
-        double acc = 0.0;
+        bool head = b > 0 && b < e && in.tdst[b - 1] == in.tdst[b];  // the first destination began earlier
+        typename P::Acc acc = P::none();
         uint64_t got = 0;
         for (uint32_t k = 0; k < IN_RUN; k += S) {
             const uint64_t i = b + k + ln;
-            const bool in = i < e;
-            const uint32_t u = in ? tsrc[i] : 0u, d = in ? tdst[i] : UNREACHED;
-            const uint64_t mu = in ? s.mcur[u] : 0ull;
+            const bool ok = i < e;
+            const uint32_t u = ok ? in.tsrc[i] : 0u, d = ok ? in.tdst[i] : UNREACHED;
+            const uint32_t w = P::weighted && ok ? in.tw[i] : 0u;
+            const uint64_t mu = ok ? s.mcur[u] : 0ull;
 #pragma unroll 1
             for (uint32_t t = 0; t < S; t += IN_UNROLL) {
-                float x[IN_UNROLL];
-                uint32_t dd[IN_UNROLL];
+                decltype(P::template take<LSH>(s, 0u, 0ull, 0u)) x[IN_UNROLL];
+                uint32_t dd[IN_UNROLL], ww[IN_UNROLL];
                 uint64_t mm[IN_UNROLL];
 #pragma unroll
                 for (int r = 0; r < IN_UNROLL; r++) {
                     uint32_t uu;
+                    ww[r] = 0;
                     if constexpr (LSH == 6) {
                         uu = __builtin_amdgcn_readlane(u, t + r);
                         dd[r] = __builtin_amdgcn_readlane(d, t + r);
+                        if (P::weighted) ww[r] = __builtin_amdgcn_readlane(w, t + r);
                         mm[r] = (uint32_t)__builtin_amdgcn_readlane((uint32_t)mu, t + r) |
                                 (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mu >> 32), t + r) << 32;
                     } else {
                         uu = __shfl(u, g0 + t + r, 64);
                         dd[r] = __shfl(d, g0 + t + r, 64);
+                        if (P::weighted) ww[r] = __shfl(w, g0 + t + r, 64);
                         mm[r] = __shfl((uint32_t)mu, g0 + t + r, 64);
                     }
-                    x[r] = mm[r] ? s.lx[((uint64_t)uu << LSH) + ln] : 0.0f;
+                    x[r] = P::template take<LSH>(s, uu, mm[r], ln);
                 }
 #pragma unroll
                 for (int r = 0; r < IN_UNROLL; r++) {
                     if (dd[r] != cur) {
-                        if (cur != UNREACHED) ppr_hand_over<LSH>(s, cur, ln, acc, got, head);
-                        if (cur != UNREACHED) head = false;
+                        if (cur != UNREACHED) {
+                            P::template hand_over<LSH>(s, cur, ln, acc, got, head);
+                            head = false;
+                        }
                         cur = dd[r];
-                        acc = 0.0;
+                        acc = P::none();
                         got = 0;
                     }
-                    acc += (double)x[r];
+                    acc = P::join(acc, P::value(s, x[r], ww[r], mm[r], ln));
                     got |= mm[r];
                 }
             }
         }
         // the last destination: past a short run's end it has been handed over already
-        if (cur != UNREACHED) ppr_hand_over<LSH>(s, cur, ln, acc, got, head || (e < m && tdst[e] == cur));
+        if (cur != UNREACHED)
+            P::template hand_over<LSH>(s, cur, ln, acc, got, head || (e < in.m && in.tdst[e] == cur));
     }
 }
 
-template <int LSH>
-__global__ __launch_bounds__(256) void k_ppr_pull_segs(AlgoState s, const uint64_t* __restrict__ toff,
-                                                       const uint32_t* __restrict__ soff,
-                                                       const uint32_t* __restrict__ seg_v,
-                                                       const uint32_t* __restrict__ tsrc, uint32_t nseg) {
+template <int LSH, class P>
+__global__ __launch_bounds__(256) void k_pull_segs(AlgoState s, InLists in) {
     constexpr uint32_t S = 1u << LSH, W = 16, E = W / S;
     const uint32_t sl = threadIdx.x & (W - 1), grp = sl >> LSH, ln = sl & (S - 1);
     const uint32_t groups = gridDim.x * (256 / W);
-    for (uint32_t sg = (blockIdx.x * 256 + threadIdx.x) / W; sg < nseg; sg += groups) {  // uniform over 16 threads
-        const uint32_t v = seg_v[sg];
-        const uint32_t s0 = soff[v];
-        const bool multi = soff[v + 1] - s0 > 1;
-        const uint64_t b = toff[v] + (uint64_t)(sg - s0) * IN_SEG;
-        const uint64_t e = min(b + IN_SEG, toff[v + 1]);
-        double acc = 0.0;
+    for (uint32_t sg = (blockIdx.x * 256 + threadIdx.x) / W; sg < in.nseg; sg += groups) {  // uniform over 16 threads
+        const uint32_t v = in.seg_v[sg];
+        const uint32_t s0 = in.soff[v];
+        const bool multi = in.soff[v + 1] - s0 > 1;
+        const uint64_t b = in.toff[v] + (uint64_t)(sg - s0) * IN_SEG;
+        const uint64_t e = min(b + IN_SEG, in.toff[v + 1]);
+        typename P::Acc acc = P::none();
         uint32_t m = 0;  // S <= 8 lanes
         for (uint64_t i = b; i < e; i += W) {
-            const bool in = i + sl < e;
-            const uint32_t u = in ? tsrc[i + sl] : 0u;
-            const uint32_t mu = in ? (uint32_t)s.mcur[u] : 0u;
+            const bool ok = i + sl < e;
+            const uint32_t u = ok ? in.tsrc[i + sl] : 0u;
+            const uint32_t w = P::weighted && ok ? in.tw[i + sl] : 0u;
+            const uint32_t mu = ok ? (uint32_t)s.mcur[u] : 0u;
             m |= mu;
-            float x[S];
+            decltype(P::template take<LSH>(s, 0u, 0ull, 0u)) x[S];
+            uint32_t mm[S], ww[S];
 #pragma unroll
             for (uint32_t t = 0; t < S; t++) {
                 const uint32_t q = t * E + grp;
-                const uint32_t uu = __shfl(u, q, W), mm = __shfl(mu, q, W);
-                x[t] = mm ? s.lx[((uint64_t)uu << LSH) + ln] : 0.0f;
+                const uint32_t uu = __shfl(u, q, W);
+                mm[t] = __shfl(mu, q, W);
+                ww[t] = P::weighted ? __shfl(w, q, W) : 0u;
+                x[t] = P::template take<LSH>(s, uu, mm[t], ln);
             }
 #pragma unroll
-            for (uint32_t t = 0; t < S; t++) acc += (double)x[t];
+            for (uint32_t t = 0; t < S; t++) acc = P::join(acc, P::value(s, x[t], ww[t], mm[t], ln));
         }
 #pragma unroll
         for (uint32_t d = W / 2; d >= 1; d >>= 1) m |= __shfl_xor(m, d, W);
 #pragma unroll
-        for (uint32_t d = S; d < W; d <<= 1) acc += __shfl_xor(acc, (int)d, W);
-        if (grp == 0) ppr_hand_over<LSH>(s, v, ln, acc, m, multi);
+        for (uint32_t d = S; d < W; d <<= 1) acc = P::join(acc, __shfl_xor(acc, (int)d, W));
+        if (grp == 0) P::template hand_over<LSH>(s, v, ln, acc, m, multi);
     }
 }
 
@@ -2924,36 +2988,46 @@ hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t n,
-                           uint32_t* cnt, uint64_t* tot, uint64_t* toff, uint32_t* soff, uint32_t* seg_v,
-                           uint32_t* tsrc, uint32_t* tdst, hipStream_t st) {
+hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, const uint32_t* w, const Pack& pk, uint64_t m,
+                           uint64_t n, uint32_t* cnt, uint64_t* tot, uint64_t* toff, uint32_t* soff, uint32_t* seg_v,
+                           uint32_t* tsrc, uint32_t* tdst, uint32_t* tw, hipStream_t st) {
     if (!n || !m) return hipErrorInvalidValue;
     const uint64_t tiles = in_tiles(n);
     hipError_t e = launch_fill_u32(cnt, n, 0u, st);
     if (e != hipSuccess) return e;
-    k_in_count<<<grid_for(m, 256, 16384), 256, 0, st>>>(col, vmask, m, n, cnt);
+    k_in_count<<<grid_for(m, 256, 16384), 256, 0, st>>>(col, pk.mask, m, n, cnt);
     k_in_tot<<<(unsigned)tiles, 256, 0, st>>>(cnt, n, tot);
     k_in_base<<<1, 64, 0, st>>>(tiles, tot, n, toff, soff);
     k_in_write<<<(unsigned)tiles, 256, 0, st>>>(cnt, n, tot, toff, soff, seg_v);
-    k_in_scatter<<<grid_for(m, 256, 16384), 256, 0, st>>>(off, col, vmask, m, n, toff, cnt, tsrc, tdst);
+    k_in_scatter<<<grid_for(m, 256, 16384), 256, 0, st>>>(off, col, w, pk, m, n, toff, cnt, tsrc, tdst, tw);
     return hipGetLastError();
 }
 
-hipError_t launch_ppr_pull(const AlgoState& s, const uint64_t* toff, const uint32_t* soff, const uint32_t* seg_v,
-                           const uint32_t* tsrc, const uint32_t* tdst, uint64_t m, uint32_t nseg, hipStream_t st) {
-    if (!nseg) return hipSuccess;
-    const unsigned gs = grid_for(nseg, 16, GRID_CAP), gr = grid_for((m + IN_RUN - 1) / IN_RUN, 256u >> s.lshift, GRID_CAP);
+template <class P>
+static hipError_t pull_op(const AlgoState& s, const InLists& in, hipStream_t st) {
+    if (!in.nseg) return hipSuccess;
+    const unsigned gs = grid_for(in.nseg, 16, GRID_CAP);
+    const unsigned gr = grid_for((in.m + IN_RUN - 1) / IN_RUN, 256u >> s.lshift, GRID_CAP);
+    if constexpr (P::narrow) {
+        if (s.lshift == 0) k_pull_segs<0, P><<<gs, 256, 0, st>>>(s, in);
+        if (s.lshift == 1) k_pull_segs<1, P><<<gs, 256, 0, st>>>(s, in);
+        if (s.lshift == 2) k_pull_segs<2, P><<<gs, 256, 0, st>>>(s, in);
+        if (s.lshift == 3) k_pull_segs<3, P><<<gs, 256, 0, st>>>(s, in);
+        if (s.lshift < 4) return hipGetLastError();
+    }
     switch (s.lshift) {
-    case 0: k_ppr_pull_segs<0><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
-    case 1: k_ppr_pull_segs<1><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
-    case 2: k_ppr_pull_segs<2><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
-    case 3: k_ppr_pull_segs<3><<<gs, 256, 0, st>>>(s, toff, soff, seg_v, tsrc, nseg); break;
-    case 4: k_ppr_pull_runs<4><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
-    case 5: k_ppr_pull_runs<5><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
-    case 6: k_ppr_pull_runs<6><<<gr, 256, 0, st>>>(s, tsrc, tdst, m); break;
+    case 4: k_pull_runs<4, P><<<gr, 256, 0, st>>>(s, in); break;
+    case 5: k_pull_runs<5, P><<<gr, 256, 0, st>>>(s, in); break;
+    case 6: k_pull_runs<6, P><<<gr, 256, 0, st>>>(s, in); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_pull(const AlgoState& s, const InLists& in, hipStream_t st) {
+    if (s.algo == ALGO_MPPR) return pull_op<PullPpr>(s, in, st);
+    if (s.algo == ALGO_MSSSP && in.tw) return pull_op<PullSssp>(s, in, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_ppr_restart(const AlgoState& s, const LaneSet& set, float restart, hipStream_t st) {

@@ -279,14 +279,15 @@ struct hytm_graph {
         DevBuf<uint16_t> slot;
     } pg;
 
-    // In-edge lists (graphs without a budget): made by the first batched PPR step that
-    // pulls, kept while the graph stays without a budget
+    // In-edge lists (graphs without a budget): made by the first batched PPR or SSSP step that
+    // pulls (with the weights once SSSP asks), kept while the graph stays without a budget
     struct {
         bool ok = false;
         uint32_t nseg = 0;
         DevBuf<uint64_t> toff;
         uint64_t m = 0;
-        DevBuf<uint32_t> soff, seg_v, tsrc, tdst;
+        DevBuf<uint32_t> soff, seg_v, tsrc, tdst, tw;
+        InLists lists() const { return InLists{m, nseg, toff.p, soff.p, seg_v.p, tsrc.p, tdst.p, tw.p}; }
     } in;
 
     // host mirrors of the per-iteration selection (views into h_sel, as the device arrays
@@ -489,13 +490,19 @@ struct Plan {
     bool allow_filter = false, allow_compact = false;
 };
 
-// A PPR step of a graph without a budget goes over the in-edge lists (launch_ppr_pull) when its
-// active vertices hold at least 1/kPullShare of the edges: the push's FP64 atomic adds run at
-// 13-16 G/s, the pull reads every in-edge's row whatever the frontier.  Measured on R-MAT 20
-// (16M edges), ten steps, eight of them dense: 64 lanes 78.4 ms pushed, 13.4 ms with the rule
-// (14.1 ms always pulled); 5 lanes 16.4 -> 4.0 ms (4.3); one lane 16.3 -> 2.7 ms (3.0); uniform
-// random graph of 8M edges, 20 lanes 8.9 -> 5.3 ms (5.6).
-constexpr uint64_t kPullShare = 8;
+// A batched PPR or SSSP step of a graph without a budget goes over the in-edge lists
+// (launch_pull) when its active vertices hold at least 1/kPullPpr (1/kPullSssp) of the edges.
+// PPR: the push's FP64 atomic adds run at 13-16 G/s, the pull reads every in-edge's row whatever
+// the frontier.  Measured on R-MAT 20 (16M edges), ten steps, eight of them dense: 64 lanes 78.4 ms
+// pushed, 13.4 ms with the rule (14.1 ms always pulled); 5 lanes 16.4 -> 4.0 ms (4.3); one lane
+// 16.3 -> 2.7 ms (3.0); uniform random graph of 8M edges, 20 lanes 8.9 -> 5.3 ms (5.6).
+// SSSP reads the same rows either way and saves the atomic minima of the widest steps; whole runs
+// on 262K vertices of 4M edges: 37 lanes 5.00 ms pushed, 3.99 / 4.11 / 4.46 ms pulled from 1/2, 1/8
+// and 1/128; 64 lanes 6.39 -> 5.30 / 5.41 / 5.65; 20 lanes 3.12 -> 2.74 / 2.88 / 3.24.  In rows of
+// fewer than 2^kPullSsspShift lanes it does not pay: 4 lanes of 1M vertices 2.40 -> 2.35 / 2.60, one lane
+// 1.14 -> 1.31 / 1.44.
+constexpr uint64_t kPullPpr = 8, kPullSssp = 3;
+constexpr uint32_t kPullSsspShift = 4;
 
 // Edge-budget bytes the engines' buffers take: filter = `streams` staging slots, each
 // holding the largest combined task; compaction = two chunk buffers.
@@ -630,7 +637,7 @@ void pg_release(hytm_graph* g) {
 void in_release(hytm_graph* g) {
     g->in.ok = false;
     g->in.toff.release();
-    for (auto* b : {&g->in.soff, &g->in.seg_v, &g->in.tsrc, &g->in.tdst}) b->release();
+    for (auto* b : {&g->in.soff, &g->in.seg_v, &g->in.tsrc, &g->in.tdst, &g->in.tw}) b->release();
 }
 
 void release_all(hytm_graph* g) {
@@ -781,7 +788,7 @@ struct RunCtx {
     } replay;
     uint32_t last_ftasks = 0;                  // streaming filter tasks of the last pass
     uint64_t last_fchunks = 0;
-    bool pull = false;                         // PPR: dense steps may go over the in-edge lists
+    bool pull = false;                         // batched PPR / SSSP: dense steps may go over the in-edge lists
     // PageRank over a gather plan (hytm_graph::pg): the selection, replayed every iteration
     bool pg_on = false;
     struct {
@@ -1029,7 +1036,8 @@ void init_ctx(RunCtx& rc, hytm_graph* g, int algo, bool batched, const Plan& pl,
     rc.sp.allow_filter = pl.allow_filter || g->budget == UINT64_MAX;
     rc.sp.allow_compact = pl.allow_compact || g->budget == UINT64_MAX;
     rc.nwords = (uint32_t)((g->n + 31) / 32);
-    rc.pull = algo == HYTM_PPR && g->budget == UINT64_MAX && g->m > 0 && in_max_segs(g->n, g->m) < UINT32_MAX;
+    rc.pull = (algo == HYTM_PPR || (algo == HYTM_SSSP && batched)) && g->budget == UINT64_MAX && g->m > 0 &&
+              in_max_segs(g->n, g->m) < UINT32_MAX;
     rc.as.n = g->n;
     rc.as.overflow = g->d_overflow.p;
     rc.as.pk = g->pk;
@@ -1063,7 +1071,9 @@ void wait_selection(hytm_graph* g, uint64_t seq, hipStream_t main) {
 bool in_ready(RunCtx& rc, hipStream_t main) {
     hytm_graph* g = rc.g;
     auto& in = g->in;
-    if (in.ok) return true;
+    const bool weights = rc.algo == HYTM_SSSP;
+    if (in.ok && (!weights || in.tw.p)) return true;
+    in_release(g);
     const uint64_t n = g->n, m = g->m, segs = in_max_segs(n, m);
     DevBuf<uint32_t> cnt;
     DevBuf<uint64_t> tot;
@@ -1074,7 +1084,7 @@ bool in_ready(RunCtx& rc, hipStream_t main) {
     try {
         size_t room = 0, total = 0;
         HIP_CHECK(hipMemGetInfo(&room, &total));
-        if (8 * m + 16 * n + 4 * segs + 16 * in_tiles(n) + (64ull << 20) > room) {
+        if ((weights ? 12 : 8) * m + 16 * n + 4 * segs + 16 * in_tiles(n) + (64ull << 20) > room) {
             rc.pull = false;
             return false;
         }
@@ -1083,11 +1093,12 @@ bool in_ready(RunCtx& rc, hipStream_t main) {
         in.seg_v.ensure(segs);
         in.tsrc.ensure(m);
         in.tdst.ensure(m);
+        if (weights) in.tw.ensure(m);
         cnt.ensure(n);
         tot.ensure(2 * in_tiles(n));
         HIP_CHECK(g->timer.run(HYTM_K_OTHER, m, main, [&] {
-            return launch_in_lists(g->d_off.p, g->d_res_col.p, g->pk.mask, m, n, cnt.p, tot.p, in.toff.p, in.soff.p,
-                                   in.seg_v.p, in.tsrc.p, in.tdst.p, main);
+            return launch_in_lists(g->d_off.p, g->d_res_col.p, g->d_res_w.p, g->pk, m, n, cnt.p, tot.p, in.toff.p,
+                                   in.soff.p, in.seg_v.p, in.tsrc.p, in.tdst.p, in.tw.p, main);
         }));
         HIP_CHECK(hipMemcpyAsync(&in.m, in.toff.p + n, sizeof(uint64_t), hipMemcpyDeviceToHost, main));
         HIP_CHECK(hipMemcpyAsync(&in.nseg, in.soff.p + n, sizeof(uint32_t), hipMemcpyDeviceToHost, main));
@@ -1296,10 +1307,11 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
             rec->filter_tasks += gidx;
         }
         // resident partitions: no transfer
-        if (rc.pull && h.seg_work_total[SEG_R] >= g->m / kPullShare && in_ready(rc, main))
+        const bool wide = rc.algo == HYTM_PPR ? h.seg_work_total[SEG_R] >= g->m / kPullPpr
+                                              : as.lshift >= kPullSsspShift && h.seg_work_total[SEG_R] >= g->m / kPullSssp;
+        if (rc.pull && wide && in_ready(rc, main))
             HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-                return launch_ppr_pull(as, g->in.toff.p, g->in.soff.p, g->in.seg_v.p, g->in.tsrc.p, g->in.tdst.p,
-                                       g->in.m, g->in.nseg, main);
+                return launch_pull(as, g->in.lists(), main);
             }));
         else if (h.seg_list_count[SEG_R])
             HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {

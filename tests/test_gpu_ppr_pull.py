@@ -1,5 +1,5 @@
-"""GPU: personalized PageRank steps over the in-edge lists (dense steps of graphs without a
-budget) against the FP64 oracle: row widths from 1 to 64 lanes, edge counts around a run's 128
+"""GPU: personalized PageRank and batched SSSP steps over the in-edge lists (dense steps of
+graphs without a budget) against the oracle (PPR in FP64, distances exact): row widths from 1 to 64 lanes, edge counts around a run's 128
 edges and a segment's 256, and in-lists spanning many runs and segments."""
 import numpy as np
 import pytest
@@ -64,3 +64,37 @@ def test_in_lists_are_given_up_for_a_budget():
             else:
                 g.set_budget(None)
             assert np.abs(g.run("ppr", 7).values - want).max() <= 1e-6
+
+
+@pytest.mark.parametrize("lanes", [8, 9, 17, 64])
+@pytest.mark.parametrize("weights", ["packed", "bytes", "words"])
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_pulled_sssp_matches_oracle(name, weights, lanes):
+    off, col = GRAPHS[name]()
+    w = gen.weights(off, col, 77)
+    rng = np.random.default_rng(lanes)
+    srcs = rng.choice(np.nonzero(np.diff(off.astype(np.int64)))[0], lanes).astype(np.uint32)
+    with hy.Graph(off, col, weights=w, pack=weights == "packed", narrow=weights != "words") as g:
+        g.run_batch("ppr", srcs)  # lists without weights come first
+        got, _, _ = g.run_batch("sssp", srcs)
+        again, _, _ = g.run_batch("sssp", srcs)
+    for s in set(srcs.tolist()):
+        want = oracle.sssp(off, col, w, s)
+        for l in np.nonzero(srcs == s)[0]:
+            assert np.array_equal(got[l], want) and np.array_equal(again[l], want)
+
+
+def test_pulled_sssp_reports_overflow():
+    """One lane's distances pass 2^32 - 1 over a dense step, the others' do not exist."""
+    n = 40
+    v = np.arange(n - 1, dtype=np.uint32)
+    off, col = gen.from_pairs(n, v, v + 1)
+    w = np.full(len(col), 0x20000000, dtype=np.uint32)
+    srcs = np.arange(20, 40, dtype=np.uint32)
+    with hy.Graph(off, col, weights=w) as g:
+        with pytest.raises(hy.HytmError) as ei:
+            g.run_batch("sssp", srcs)
+        assert ei.value.status == hy.E_RANGE
+        got, _, _ = g.run_batch("sssp", srcs[13:].repeat(3))  # at most six edges from the end
+        for l, s in enumerate(srcs[13:].repeat(3)):
+            assert np.array_equal(got[l], oracle.sssp(off, col, w, int(s)))
