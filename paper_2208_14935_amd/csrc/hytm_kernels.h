@@ -351,6 +351,18 @@ hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* 
                            const uint64_t* Ea, const uint64_t* K, uint32_t* lbase, uint64_t* wbase, uint64_t* wpre,
                            const ScanExtra& x, const ScanHost& host, hipStream_t st);
 
+// Statistics, scan and lists of a graph of at most SMALL_UNITS units in one launch (mode is
+// written, the other per-partition arrays are not).  One unit per wave of the workgroup:
+// measured per selection and push of a 64-vertex path 22.2 us with four launches, 18.7 us with
+// one; BFS of 1,024 vertices 203 -> 178 us, 8,192 267 -> 238 us, 64K 315 us either way; with four
+// units per wave a dense 128K-vertex BFS took 506 us instead of 355 us.
+constexpr uint32_t SMALL_UNITS = 16;
+hipError_t launch_select_small(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
+                               const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
+                               const SelParams& sp, uint8_t* mode, uint32_t* list, uint64_t* wpre, uint32_t* tile_e,
+                               uint32_t* tile_l, bool lists, const ScanExtra& x, const ScanHost& host,
+                               hipStream_t st);
+
 hipError_t launch_build_lists(const Units& un, const uint32_t* pv, const uint64_t* off, const uint32_t* cur,
                               const uint8_t* mode, const uint32_t* lbase, const uint64_t* wbase, uint32_t* list,
                               uint64_t* wpre, uint32_t* tile_e, uint32_t* tile_l, hipStream_t st);

@@ -253,8 +253,62 @@ __device__ __forceinline__ uint8_t engine_of(uint32_t i, uint64_t E, uint64_t c,
     return select_engine(E, c, ea, rq, sp);
 }
 
-// clear (or null): a bitmap of nwords words zeroed along the way (the frontier after next).
-// mcur, lanes (or null): *lanes |= the lane masks of the active vertices.
+// The record of unit u, taken by a whole wave (the same in every lane).  clear (or null): a
+// bitmap of nwords words zeroed along the way (the frontier after next).  mcur (or null): *lm
+// gains the lane masks of the active vertices.
+__device__ __forceinline__ UnitRec unit_record(const Units& un, uint32_t u, const uint32_t* __restrict__ pv,
+                                               const uint64_t* __restrict__ off, const uint32_t* __restrict__ cur,
+                                               uint32_t* __restrict__ clear, uint32_t nwords,
+                                               const uint64_t* __restrict__ mcur, const SelParams& sp, uint64_t* lm) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t i = un.part[u], q0 = un.q[u];
+    const uint32_t vb = pv[i], ve = pv[i + 1];
+    const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+    // request lines matter where the cost model decides, kernel lines to zero-copy
+    const bool lines = i >= sp.nres && (!sp.force || sp.force == P_ZC);
+    SelAcc a;
+    const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
+    if (clear && q0 + lane < qe) {  // windows shared by two partitions are zeroed by both
+        const uint32_t w = 2 * (q0 + lane);
+        clear[w] = 0;
+        if (w + 1 < nwords) clear[w + 1] = 0;
+    }
+    UnitRec r{};
+    if (!__ballot(wbits != 0)) return r;
+    const uint32_t cnt = __popcll(wbits);
+    const uint32_t incl = wave_inclusive_sum_u32(cnt);
+    const uint32_t T = __shfl(incl, 63, 64);
+    r.f = T;
+    // at most 64 active vertices take one batch, more SEL_B at a time
+    if (T <= 64)
+        stats_batches<1>(0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
+    else
+        for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
+            stats_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
+    r.c = (uint32_t)wave_sum(a.c);
+    r.ea = wave_sum(a.ea);
+    if (lines) {
+        // request lines: the neighbour array, and the weight array beside it (Eq. 3)
+        r.rq = wave_sum(sp.rq_distinct ? a.rqd : a.rq);
+        if (sp.wbytes == 1)
+            r.rq += wave_sum(sp.rq_distinct ? a.rqdw : a.rqw);
+        else if (sp.wbytes)
+            r.rq *= 2;  // 4-byte weights: the neighbour array's lines again
+        r.kl = wave_sum(a.kl);
+        r.first = a.first;
+        r.last = a.carry;
+        r.first_w = a.first_w;
+        r.last_w = a.carry_w;
+    }
+    if (mcur) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) a.lm |= __shfl_xor(a.lm, d, 64);
+        *lm |= a.lm;
+    }
+    return r;
+}
+
+// lanes: *lanes |= the lane masks of the active vertices (with mcur).
 __global__ __launch_bounds__(256) void k_unit_stats(Units un, const uint32_t* __restrict__ pv,
                                                     const uint64_t* __restrict__ off,
                                                     const uint32_t* __restrict__ cur, uint32_t* __restrict__ clear,
@@ -266,91 +320,35 @@ __global__ __launch_bounds__(256) void k_unit_stats(Units un, const uint32_t* __
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
     for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
-        const uint32_t i = un.part[u], q0 = un.q[u];
-        const uint32_t vb = pv[i], ve = pv[i + 1];
-        const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
-        const bool one = un.first[i + 1] - un.first[i] == 1;
-        // request lines matter where the cost model decides, kernel lines to zero-copy
-        const bool lines = i >= sp.nres && (!sp.force || sp.force == P_ZC);
-        SelAcc a;
-        const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
-        if (clear && q0 + lane < qe) {  // windows shared by two partitions are zeroed by both
-            const uint32_t w = 2 * (q0 + lane);
-            clear[w] = 0;
-            if (w + 1 < nwords) clear[w + 1] = 0;
-        }
-        uint64_t f = 0;
-        if (__ballot(wbits != 0)) {
-            const uint32_t cnt = __popcll(wbits);
-            const uint32_t incl = wave_inclusive_sum_u32(cnt);
-            const uint32_t T = __shfl(incl, 63, 64);
-            f = T;
-            // at most 64 active vertices take one batch, more SEL_B at a time
-            if (T <= 64)
-                stats_batches<1>(0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
-            else
-                for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
-                    stats_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, sp, mcur, lines, a);
-            a.c = wave_sum(a.c);
-            a.ea = wave_sum(a.ea);
-            if (lines) {
-                // request lines: the neighbour array, and the weight array beside it (Eq. 3)
-                a.rq = wave_sum(sp.rq_distinct ? a.rqd : a.rq);
-                if (sp.wbytes == 1)
-                    a.rq += wave_sum(sp.rq_distinct ? a.rqdw : a.rqw);
-                else if (sp.wbytes)
-                    a.rq *= 2;  // 4-byte weights: the neighbour array's lines again
-                a.kl = wave_sum(a.kl);
-            }
-            if (mcur) {
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) a.lm |= __shfl_xor(a.lm, d, 64);
-                if (lane == 0 && (a.lm & ~(uint64_t)*lanes)) atomicOr(lanes, (unsigned long long)a.lm);
-            }
-        }
+        uint64_t lm = 0;
+        const UnitRec r = unit_record(un, u, pv, off, cur, clear, nwords, mcur, sp, &lm);
         if (lane != 0) continue;
-        if (one) {
-            mode[i] = engine_of(i, off[ve] - off[vb], a.c, a.ea, a.rq, sp);
-            nA[i] = (uint32_t)a.c;
-            nF[i] = (uint32_t)f;
-            Ea[i] = a.ea;
-            K[i] = a.kl;
+        if (lm && (lm & ~(uint64_t)*lanes)) atomicOr(lanes, (unsigned long long)lm);
+        const uint32_t i = un.part[u];
+        if (un.first[i + 1] - un.first[i] == 1) {
+            mode[i] = engine_of(i, off[pv[i + 1]] - off[pv[i]], r.c, r.ea, r.rq, sp);
+            nA[i] = r.c;
+            nF[i] = r.f;
+            Ea[i] = r.ea;
+            K[i] = r.kl;
         } else {
-            UnitRec r;
-            r.c = (uint32_t)a.c;
-            r.f = (uint32_t)f;
-            r.ea = a.ea;
-            r.kl = a.kl;
-            r.rq = a.rq;
-            r.first = a.first;
-            r.last = a.carry;
-            r.first_w = a.first_w;
-            r.last_w = a.carry_w;
             un.rec[u] = r;
         }
     }
 }
 
-// Partitions of several units, one wave each: the units' records joined (a line that one
-// unit's last list ends and the next one's first list starts in counts once where distinct
-// lines are counted), the engine chosen, and every record turned into the list entries, edges
-// and lines of the partition's earlier units, where the unit's part of the lists starts.
-__global__ __launch_bounds__(256) void k_part_combine(Units un, const uint32_t* __restrict__ pv,
-                                                      const uint64_t* __restrict__ off, SelParams sp,
-                                                      uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
-                                                      uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
-                                                      uint64_t* __restrict__ K) {
+// The records rec[u0, u1) of a partition's units joined by a wave (a line that one unit's last
+// list ends and the next one's first list starts in counts once where distinct lines are
+// counted); every record becomes the list entries, edges and lines of the partition's
+// earlier units, where the unit's part of the lists starts.
+__device__ __forceinline__ UnitRec join_units(UnitRec* rec, uint32_t u0, uint32_t u1, const SelParams& sp) {
     const uint32_t lane = threadIdx.x & 63;
-    const uint32_t k = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (k >= un.multis) return;  // the same for the whole wave
-    const uint32_t i = un.multi[k];
-    const uint32_t u0 = un.first[i], u1 = un.first[i + 1];
     uint64_t c = 0, f = 0, ea = 0, kl = 0, rq = 0, dup = 0, last = 0, last_w = 0;
     const uint64_t twice = sp.wbytes == 4 ? 2 : 1;
     for (uint32_t b = u0; b < u1; b += 64) {
         const bool in = b + lane < u1;
         UnitRec r{};
-        if (in) r = un.rec[b + lane];
+        if (in) r = rec[b + lane];
         uint64_t tc, te, tk, tot, totw;
         const uint64_t xc = wave_exclusive_sum(r.c, &tc);
         const uint64_t xe = wave_exclusive_sum(r.ea, &te);
@@ -369,7 +367,7 @@ __global__ __launch_bounds__(256) void k_part_combine(Units un, const uint32_t* 
             o.c = (uint32_t)(c + xc);
             o.ea = ea + xe;
             o.kl = kl + xk;
-            un.rec[b + lane] = o;
+            rec[b + lane] = o;
         }
         c += tc;
         ea += te;
@@ -377,13 +375,31 @@ __global__ __launch_bounds__(256) void k_part_combine(Units un, const uint32_t* 
         last = last > tot ? last : tot;
         last_w = last_w > totw ? last_w : totw;
     }
-    if (lane == 0) {
-        if (sp.rq_distinct) rq -= dup;
-        mode[i] = engine_of(i, off[pv[i + 1]] - off[pv[i]], c, ea, rq, sp);
-        nA[i] = (uint32_t)c;
-        nF[i] = (uint32_t)f;
-        Ea[i] = ea;
-        K[i] = kl;
+    UnitRec r{};
+    r.c = (uint32_t)c;
+    r.f = (uint32_t)f;
+    r.ea = ea;
+    r.kl = kl;
+    r.rq = sp.rq_distinct ? rq - dup : rq;
+    return r;
+}
+
+// Partitions of several units, one wave each: their records joined and the engine chosen.
+__global__ __launch_bounds__(256) void k_part_combine(Units un, const uint32_t* __restrict__ pv,
+                                                      const uint64_t* __restrict__ off, SelParams sp,
+                                                      uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
+                                                      uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
+                                                      uint64_t* __restrict__ K) {
+    const uint32_t k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= un.multis) return;  // the same for the whole wave
+    const uint32_t i = un.multi[k];
+    const UnitRec r = join_units(un.rec, un.first[i], un.first[i + 1], sp);
+    if ((threadIdx.x & 63) == 0) {
+        mode[i] = engine_of(i, off[pv[i + 1]] - off[pv[i]], r.c, r.ea, r.rq, sp);
+        nA[i] = r.c;
+        nF[i] = r.f;
+        Ea[i] = r.ea;
+        K[i] = r.kl;
     }
 }
 
@@ -744,6 +760,31 @@ __device__ __forceinline__ void list_batches(uint32_t b0, uint32_t T, uint32_t i
     }
 }
 
+// The list entries of unit u (of a partition with engine m), from list position pos and work
+// position wp on.
+__device__ __forceinline__ void unit_list(const Units& un, uint32_t u, uint32_t m, uint64_t pos, uint64_t wp,
+                                          const uint32_t* __restrict__ pv, const uint64_t* __restrict__ off,
+                                          const uint32_t* __restrict__ cur, uint32_t* __restrict__ list,
+                                          uint64_t* __restrict__ wpre, uint32_t* __restrict__ tile_e,
+                                          uint32_t* __restrict__ tile_l) {
+    const uint32_t lane = threadIdx.x & 63;
+    const bool by_lines = m == P_ZC;
+    const uint32_t i = un.part[u], q0 = un.q[u];
+    const uint32_t vb = pv[i], ve = pv[i + 1];
+    const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+    const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
+    if (!__ballot(wbits != 0)) return;
+    const uint32_t cnt = __popcll(wbits);
+    const uint32_t incl = wave_inclusive_sum_u32(cnt);
+    const uint32_t T = __shfl(incl, 63, 64);
+    uint32_t* tile = by_lines ? tile_l : tile_e;
+    if (T <= 64)
+        list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, tile, pos, wp);
+    else
+        for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
+            list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, tile, pos, wp);
+}
+
 __global__ __launch_bounds__(256) void k_build_lists(Units un, const uint32_t* __restrict__ pv,
                                                      const uint64_t* __restrict__ off,
                                                      const uint32_t* __restrict__ cur,
@@ -752,30 +793,120 @@ __global__ __launch_bounds__(256) void k_build_lists(Units un, const uint32_t* _
                                                      const uint64_t* __restrict__ wbase,
                                                      uint32_t* __restrict__ list, uint64_t* __restrict__ wpre,
                                                      uint32_t* __restrict__ tile_e, uint32_t* __restrict__ tile_l) {
-    const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
     for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
-        const uint32_t i = un.part[u], q0 = un.q[u];
+        const uint32_t i = un.part[u];
         const uint8_t m = mode[i];
-        if (m == P_NONE) continue;
-        const bool by_lines = m == P_ZC;
-        const uint32_t vb = pv[i], ve = pv[i + 1];
-        const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
-        const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
-        if (!__ballot(wbits != 0)) continue;
+        if (m == P_NONE) continue;  // uniform across the wave
         uint64_t pos = lbase[i], wp = wbase[i];
         if (un.first[i + 1] - un.first[i] > 1) {  // after the partition's earlier units
             pos += un.rec[u].c;
-            wp += by_lines ? un.rec[u].kl : un.rec[u].ea;
+            wp += m == P_ZC ? un.rec[u].kl : un.rec[u].ea;
         }
-        const uint32_t cnt = __popcll(wbits);
-        const uint32_t incl = wave_inclusive_sum_u32(cnt);
-        const uint32_t T = __shfl(incl, 63, 64);
-        if (T <= 64)
-            list_batches<1>(0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, by_lines ? tile_l : tile_e, pos, wp);
-        else
-            for (uint32_t b0 = 0; b0 < T; b0 += 64 * SEL_B)
-                list_batches<SEL_B>(b0, T, incl, cnt, wbits, q0, off, by_lines, list, wpre, by_lines ? tile_l : tile_e, pos, wp);
+        unit_list(un, u, m, pos, wp, pv, off, cur, list, wpre, tile_e, tile_l);
+    }
+}
+
+// The whole selection of a small graph (at most SMALL_UNITS units) in one workgroup: the units'
+// records (in LDS), their partitions joined and their engines chosen, the segments laid out
+// by one wave with the header reported to the host, and the lists written while the host
+// reads it.  Four launches, whose gaps are as long as their work on such a graph, become one.
+__global__ __launch_bounds__(1024) void k_select_small(uint32_t npart, Units un, const uint32_t* __restrict__ pv,
+                                                       const uint64_t* __restrict__ off,
+                                                       const uint32_t* __restrict__ cur,
+                                                       uint32_t* __restrict__ clear, uint32_t nwords,
+                                                       const uint64_t* __restrict__ mcur, SelParams sp,
+                                                       uint8_t* __restrict__ mode, uint32_t* __restrict__ list,
+                                                       uint64_t* __restrict__ wpre, uint32_t* __restrict__ tile_e,
+                                                       uint32_t* __restrict__ tile_l, bool lists, ScanExtra x,
+                                                       ScanHost host) {
+    __shared__ UnitRec s_rec[SMALL_UNITS];  // per unit
+    __shared__ UnitRec s_part[SMALL_UNITS];  // per partition: joined
+    __shared__ uint32_t s_mode[SMALL_UNITS], s_lb[SMALL_UNITS];
+    __shared__ uint64_t s_wb[SMALL_UNITS];
+    __shared__ unsigned long long s_lanes;
+    const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (threadIdx.x == 0) s_lanes = 0;
+    __syncthreads();
+    for (uint32_t u = wid; u < un.count; u += 16) {
+        uint64_t lm = 0;
+        const UnitRec r = unit_record(un, u, pv, off, cur, clear, nwords, mcur, sp, &lm);
+        if (lane == 0) {
+            s_rec[u] = r;
+            if (lm) atomicOr(&s_lanes, (unsigned long long)lm);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = wid; i < npart; i += 16) {
+        const UnitRec r = join_units(s_rec, un.first[i], un.first[i + 1], sp);
+        if (lane == 0) {
+            s_part[i] = r;
+            s_mode[i] = engine_of(i, off[pv[i + 1]] - off[pv[i]], r.c, r.ea, r.rq, sp);
+        }
+    }
+    __syncthreads();
+    if (wid == 0) {  // npart <= un.count: lane i holds partition i
+        const bool in = lane < npart;
+        UnitRec r{};
+        if (in) r = s_part[lane];
+        const uint32_t m = in ? s_mode[lane] : (uint32_t)P_NONE;
+        const uint64_t wk = m == P_ZC ? r.kl : r.ea;
+        Header* hdr = host.hdr;
+        uint64_t l = 0, w = 0;
+        uint32_t lb = 0xFFFFFFFFu;
+        uint64_t wb = ~0ull;
+        for (int sg = 0; sg < NSEG; sg++) {
+            const bool mine = m == (uint32_t)sg + 1;
+            const uint64_t who = __ballot(mine);
+            uint64_t tc = 0, tw = 0, te = 0;
+            if (who) {  // uniform
+                const uint64_t xc = wave_exclusive_sum(mine ? r.c : 0u, &tc);
+                const uint64_t xw = wave_exclusive_sum(mine ? wk : 0ull, &tw);
+                te = sg == SEG_Z ? wave_sum(mine ? r.ea : 0ull) : tw;
+                if (mine) {
+                    lb = (uint32_t)(l + xc);
+                    wb = w + xw;
+                }
+            }
+            if (lane == 0) {
+                hdr->seg_parts[sg] = (uint32_t)__popcll(who);
+                hdr->seg_list_start[sg] = (uint32_t)l;
+                hdr->seg_list_count[sg] = (uint32_t)tc;
+                hdr->seg_work_start[sg] = w;
+                hdr->seg_work_total[sg] = tw;
+                hdr->seg_edges[sg] = te;
+            }
+            l += tc;
+            w += tw;
+        }
+        const uint64_t fr = wave_sum(r.f);
+        if (in) {
+            s_lb[lane] = lb;
+            s_wb[lane] = wb;
+            mode[lane] = (uint8_t)m;
+            if (host.mode) {
+                host.lbase[lane] = lb;
+                host.wbase[lane] = wb;
+                host.mode[lane] = (uint8_t)m;
+            }
+        }
+        if (lane == 0) {
+            hdr->total_active = l;
+            hdr->frontier = fr;
+            scan_extra(hdr, x);
+            hdr->lanes = s_lanes;
+            wpre[l] = w;
+        }
+        __threadfence_system();
+        if (lane == 0) __hip_atomic_store(&hdr->seq, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (!lists) return;
+    __syncthreads();
+    for (uint32_t u = wid; u < un.count; u += 16) {
+        const uint32_t i = un.part[u], m = s_mode[i];
+        if (m == P_NONE) continue;  // uniform across the wave
+        unit_list(un, u, m, s_lb[i] + (uint64_t)s_rec[u].c, s_wb[i] + (m == P_ZC ? s_rec[u].kl : s_rec[u].ea), pv, off,
+                  cur, list, wpre, tile_e, tile_l);
     }
 }
 
@@ -3078,6 +3209,18 @@ hipError_t launch_scan_one(uint32_t npart, const uint8_t* mode, const uint32_t* 
         k_scan_one<8><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
     else
         k_scan_one<16><<<1, 1024, 0, st>>>(npart, mode, nA, nF, Ea, K, lbase, wbase, wpre, x, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_select_small(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
+                               const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
+                               const SelParams& sp, uint8_t* mode, uint32_t* list, uint64_t* wpre, uint32_t* tile_e,
+                               uint32_t* tile_l, bool lists, const ScanExtra& x, const ScanHost& host,
+                               hipStream_t st) {
+    static_assert(SMALL_UNITS <= 64, "one wave lays the partitions out");
+    if (!npart || un.count > SMALL_UNITS) return hipErrorInvalidValue;
+    k_select_small<<<1, 1024, 0, st>>>(npart, un, pv, off, cur, clear, nwords, mcur, sp, mode, list, wpre, tile_e,
+                                       tile_l, lists, x, host);
     return hipGetLastError();
 }
 

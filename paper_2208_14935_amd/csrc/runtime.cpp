@@ -1138,35 +1138,44 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     // the partitions' engines and bases are read here only where transfers are planned from them
     const bool parts_to_host = g->budget != UINT64_MAX || select_only || traced;
     if (stats) HIP_CHECK(hipEventRecord(g->ev_sel[0], main));
-    HIP_CHECK(kt.run(HYTM_K_STATS, npart, main, [&] {
-        return launch_stats_select(npart, g->units(), g->d_pv.p, g->d_off.p, cur, rc.spare, rc.nwords,
-                                   lanes ? rc.mcur : nullptr, (unsigned long long*)g->d_lanes.p, rc.sp, g->d_mode.p,
-                                   g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, main);
-    }));
+    const uint64_t* mcur = lanes ? rc.mcur : nullptr;
     const ScanExtra extra{lanes ? g->d_lanes.p : nullptr, g->d_overflow.p};
     const uint64_t seq = ++g->sel_seq;
-    HIP_CHECK(kt.run(HYTM_K_SCAN, npart, main, [&] {
-        if (!one) {
+    const SelLayout L = sel_layout(npart);
+    ScanHost host{(Header*)g->h_sel_dev, nullptr, nullptr, nullptr, seq};
+    if (parts_to_host) {
+        host.wbase = (uint64_t*)(g->h_sel_dev + L.wbase);
+        host.lbase = (uint32_t*)(g->h_sel_dev + L.lbase);
+        host.mode = g->h_sel_dev + L.mode;
+    }
+    if (g->nunits <= SMALL_UNITS) {
+        HIP_CHECK(kt.run(HYTM_K_STATS, npart, main, [&] {
+            return launch_select_small(npart, g->units(), g->d_pv.p, g->d_off.p, cur, rc.spare, rc.nwords, mcur, rc.sp,
+                                       g->d_mode.p, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, g->d_tile_l.p, lists,
+                                       extra, host, main);
+        }));
+    } else {
+        HIP_CHECK(kt.run(HYTM_K_STATS, npart, main, [&] {
+            return launch_stats_select(npart, g->units(), g->d_pv.p, g->d_off.p, cur, rc.spare, rc.nwords, mcur,
+                                       (unsigned long long*)g->d_lanes.p, rc.sp, g->d_mode.p, g->d_nA.p, g->d_nF.p,
+                                       g->d_Ea.p, g->d_K.p, main);
+        }));
+        HIP_CHECK(kt.run(HYTM_K_SCAN, npart, main, [&] {
+            if (one)
+                return launch_scan_one(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, g->d_lbase.p,
+                                       g->d_wbase.p, g->d_wpre.p, extra, host, main);
             g->d_scan.ensure(scan_scratch_words(npart));
             return launch_scan(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, g->d_lbase.p,
                                g->d_wbase.p, g->d_hdr.p, g->d_wpre.p, g->d_scan.p, extra, main);
-        }
-        const SelLayout L = sel_layout(npart);
-        ScanHost host{(Header*)g->h_sel_dev, nullptr, nullptr, nullptr, seq};
-        if (parts_to_host) {
-            host.wbase = (uint64_t*)(g->h_sel_dev + L.wbase);
-            host.lbase = (uint32_t*)(g->h_sel_dev + L.lbase);
-            host.mode = g->h_sel_dev + L.mode;
-        }
-        return launch_scan_one(npart, g->d_mode.p, g->d_nA.p, g->d_nF.p, g->d_Ea.p, g->d_K.p, g->d_lbase.p,
-                               g->d_wbase.p, g->d_wpre.p, extra, host, main);
-    }));
-    if (!one)
-        HIP_CHECK(hipMemcpyAsync(g->h_sel.p, g->d_sel.p, sel_block_bytes(npart), hipMemcpyDeviceToHost, main));
-    if (lists) HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
-        return launch_build_lists(g->units(), g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p, g->d_wbase.p,
-                                  g->d_list.p, g->d_wpre.p, g->d_tile_e.p, g->d_tile_l.p, main);
-    }));
+        }));
+        if (!one)
+            HIP_CHECK(hipMemcpyAsync(g->h_sel.p, g->d_sel.p, sel_block_bytes(npart), hipMemcpyDeviceToHost, main));
+        if (lists)
+            HIP_CHECK(kt.run(HYTM_K_LISTS, npart, main, [&] {
+                return launch_build_lists(g->units(), g->d_pv.p, g->d_off.p, cur, g->d_mode.p, g->d_lbase.p,
+                                          g->d_wbase.p, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, g->d_tile_l.p, main);
+            }));
+    }
     if (stats) HIP_CHECK(hipEventRecord(g->ev_sel[1], main));
     if (one)
         wait_selection(g, seq, main);

@@ -1,6 +1,7 @@
 """GPU: the selection kernels at their edges, against the oracle's engine choice: partitions of
 many vertices (several 4,096-vertex units, more than the 64 that one pass of the combining
-wave takes) and partition counts around the one-workgroup scan's 1,024, 4,096 and 16,384."""
+wave takes) and partition counts around the one-workgroup scan's 1,024, 4,096 and 16,384; and the one-launch selection
+of graphs of at most 16 units."""
 import numpy as np
 import pytest
 
@@ -79,3 +80,21 @@ def test_sssp_byte_weights_over_many_units():
             nA, Ea, Rq = oracle.partition_stats(bounds, off, act[t], arrays=2, weight_bytes=1, distinct=distinct)
             want = oracle.select(E, nA, Ea, Rq, nres=res.stats["nres"], params=oracle.CostParams(d1=5))
             np.testing.assert_array_equal(res.mode_trace[t], want, err_msg=f"iteration {t}")
+
+
+@pytest.mark.parametrize("n", [65, 4096, 4097, 61440, 65536, 65537])
+@pytest.mark.parametrize("pe", [1000, 1 << 20])
+def test_small_graphs_around_the_one_launch_selection(n, pe):
+    """Up to 16 units (of one partition, or of several) in one launch, 17 in four."""
+    off, col = gen.er(n, 6 * n if n < 10_000 else n // 20, seed=n)
+    source = int(np.nonzero(np.diff(off.astype(np.int64)))[0][0])
+    for distinct in (False, True):
+        bfs_trace(off, col, source, pe, distinct, 0.4)
+    w = gen.weights(off, col, 5)
+    srcs = np.nonzero(np.diff(off.astype(np.int64)))[0][:40].astype(np.uint32)
+    with hy.Graph(off, col, weights=w) as g:
+        assert np.array_equal(g.run("sssp", source).values, oracle.sssp(off, col, w, source))
+        got, its, _ = g.run_batch("bfs", srcs)
+        for l, s in enumerate(srcs):
+            want, it = oracle.bfs(off, col, int(s))
+            assert np.array_equal(got[l], want) and its[l] == it
