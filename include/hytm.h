@@ -367,7 +367,9 @@ hytm_status hytm_partition_bounds(const hytm_graph *g, uint64_t *bounds, uint64_
    Sec. 5.1 (PageRank: pr_iterations synchronous steps, Sec. 7.1).
    source     : start vertex for BFS/SSSP (ignored by CC and PageRank); E_RANGE if >= n.
    values_out : host buffer of n 4-byte values (see hytm_algo).
-   iterations_out : number of non-empty frontiers processed (NULL ok).
+   iterations_out : number of non-empty frontiers processed (NULL ok).  CC on a graph without
+                a budget joins the edges' ends in a forest instead of sending labels along
+                them and counts as one.
    stats      : NULL or a hytm_run_stats to fill.
    hip_stream : hipStream_t to order the run after (NULL = the null stream); the call
                 returns only once values_out is written.

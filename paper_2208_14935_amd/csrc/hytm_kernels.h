@@ -23,7 +23,8 @@ constexpr int SEG_R = 0, SEG_F = 1, SEG_Z = 2, SEG_C = 3;
 // the asynchronous reprocessing that first-visit marking would get wrong.
 enum Algo : int {
     ALGO_BFS = 0, ALGO_SSSP = 1, ALGO_CC = 2, ALGO_PR = 3, ALGO_MBFS = 4, ALGO_MSSSP = 5, ALGO_MPPR = 6,
-    ALGO_BFS_RELAX = 7
+    ALGO_BFS_RELAX = 7,
+    ALGO_CC_LINK = 8  // edges of a resident graph join their ends' trees (launch_push_edges only)
 };
 constexpr uint32_t MAX_LANES = 64;
 
@@ -271,6 +272,16 @@ hipError_t launch_gather_u32(const uint32_t* src, const uint32_t* rank, uint64_t
 // original -> new ids; minold: n words of scratch.
 hipError_t launch_cc_relabel(const uint32_t* lab, const uint32_t* order, const uint32_t* rank, uint64_t n,
                              uint32_t* minold, uint32_t* dst, hipStream_t st);
+// Components of a resident symmetric graph over a parent forest par (at first every vertex its
+// own parent; parents are smaller ids, so a component's root is its smallest id): link joins
+// every vertex with its r-th neighbour, compress moves every vertex below its root, and rest
+// marks the vertices with more than `done` edges outside the largest tree of a sample
+// (*giant: one word of scratch): by symmetry the edges that leave that tree are theirs too.
+hipError_t launch_cc_link(uint64_t n, const uint64_t* off, const uint32_t* col, uint32_t vmask, uint32_t r, uint32_t* par,
+                          hipStream_t st);
+hipError_t launch_cc_compress(uint64_t n, uint32_t* par, hipStream_t st);
+hipError_t launch_cc_rest(uint64_t n, const uint64_t* off, uint32_t done, const uint32_t* par, uint32_t* giant,
+                          uint32_t* rest, uint32_t nwords, hipStream_t st);
 // SSSP's far set: *out = min(*out, smallest distance of a far vertex) (the caller sets *out
 // to 0xFFFFFFFF first); then the far vertices with distance below `bound` move into `cur`.
 hipError_t launch_far_min(const uint32_t* far, const uint32_t* dist, uint32_t nwords, uint32_t* out, hipStream_t st);

@@ -1003,6 +1003,37 @@ struct OpCc {
     }
 };
 
+// Join the trees of u and v in a parent forest whose parents are smaller ids: the larger of the
+// two walked-to ids climbs to its parent, or, a root, is hooked below the smaller one.  Every
+// step lowers the larger id (a failed hook returns the parent someone else set), so it ends
+// whatever the loads return; a root stays the smallest id of its tree.
+__device__ __forceinline__ void link_trees(uint32_t* par, uint32_t u, uint32_t v) {
+    uint32_t a = __hip_atomic_load(par + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t b = __hip_atomic_load(par + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (a != b) {
+        if (a < b) {
+            const uint32_t t = a;
+            a = b;
+            b = t;
+        }
+        uint32_t p = __hip_atomic_load(par + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (p == a) {
+            p = atomicCAS(par + a, a, b);
+            if (p == a) return;
+        }
+        a = p;
+    }
+}
+
+// Components over a parent forest: every edge joins its ends' trees.
+struct OpLink {
+    static constexpr bool wave = false, steps = false;
+    static constexpr bool weighted = false;
+    uint32_t* par;
+    __device__ __forceinline__ uint32_t src(uint32_t u) const { return u; }
+    __device__ __forceinline__ void push(uint32_t u, uint32_t v, uint32_t) const { link_trees(par, u, v); }
+};
+
 // Accumulator copy of the XCD (accelerator complex die) the wave runs on, masked to the
 // copies in use.  Any value in [0, copies) would be correct -- the adds are device-scope
 // atomics and the copies are summed afterwards -- the die id just keeps each copy's lines in
@@ -1688,6 +1719,73 @@ __global__ void k_cc_canon(const uint32_t* __restrict__ lab, const uint32_t* __r
                            const uint32_t* __restrict__ rank, uint64_t n, uint32_t* __restrict__ dst) {
     for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x)
         dst[v] = minold[lab[rank[v]]];
+}
+
+// ----------------------------------------- components of a resident graph
+// The r-th edge of every vertex joined (par = a parent forest, at first every vertex its own).
+__global__ __launch_bounds__(256) void k_cc_link(uint64_t n, const uint64_t* __restrict__ off,
+                                                 const uint32_t* __restrict__ col, uint32_t vmask, uint32_t r,
+                                                 uint32_t* par) {
+    for (uint64_t v = blockIdx.x * 256ull + threadIdx.x; v < n; v += (uint64_t)gridDim.x * 256) {
+        const uint64_t e = off[v] + r;
+        if (e < off[v + 1]) link_trees(par, (uint32_t)v, col[e] & vmask);
+    }
+}
+
+// Every vertex moved below its root.  Only roots' entries stay as they are, so a value read
+// before or after another vertex's move is an ancestor either way.
+__global__ __launch_bounds__(256) void k_cc_compress(uint64_t n, uint32_t* par) {
+    for (uint64_t v = blockIdx.x * 256ull + threadIdx.x; v < n; v += (uint64_t)gridDim.x * 256) {
+        const uint32_t p = par[v];
+        uint32_t r = p;
+        for (uint32_t q = par[r]; q != r; q = par[r]) r = q;
+        if (r != p) par[v] = r;
+    }
+}
+
+// The most frequent root among 4,096 sampled vertices (one workgroup; counted in an LDS table
+// where colliding roots share a counter of whoever came first, so the answer may be off, which
+// costs time only).
+__global__ __launch_bounds__(1024) void k_cc_giant(uint64_t n, const uint32_t* __restrict__ par,
+                                                   uint32_t* __restrict__ giant) {
+    constexpr uint32_t T = 2048;
+    __shared__ uint32_t s_key[T], s_cnt[T];
+    __shared__ unsigned long long s_best;
+    for (uint32_t q = threadIdx.x; q < T; q += 1024) {
+        s_key[q] = UNREACHED;
+        s_cnt[q] = 0;
+    }
+    if (threadIdx.x == 0) s_best = 0;
+    __syncthreads();
+    for (uint32_t k = 0; k < 4; k++) {
+        const uint64_t i = k * 1024 + threadIdx.x;
+        const uint32_t l = par[(i * 0x9E3779B97F4A7C15ull >> 11) % n];
+        const uint32_t slot = (l * 0x9E3779B1u) >> 21;
+        const uint32_t was = atomicCAS(&s_key[slot], UNREACHED, l);
+        if (was == UNREACHED || was == l) atomicAdd(&s_cnt[slot], 1u);
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < T; q += 1024)
+        if (s_cnt[q]) atomicMax(&s_best, (unsigned long long)s_cnt[q] << 32 | s_key[q]);
+    __syncthreads();
+    if (threadIdx.x == 0) *giant = (uint32_t)s_best;
+}
+
+// rest = the vertices outside the giant's tree with more than `done` edges (one wave per two
+// words of the bitmap).
+__global__ __launch_bounds__(256) void k_cc_rest(uint64_t n, const uint64_t* __restrict__ off, uint32_t done,
+                                                 const uint32_t* __restrict__ par,
+                                                 const uint32_t* __restrict__ giant, uint32_t* __restrict__ rest,
+                                                 uint32_t nwords) {
+    const uint32_t g = *giant;
+    for (uint64_t v = blockIdx.x * 256ull + threadIdx.x; (v & ~63ull) < n; v += (uint64_t)gridDim.x * 256) {
+        const uint64_t b = __ballot(v < n && par[v] != g && off[v + 1] - off[v] > done);
+        const uint32_t w = (uint32_t)(v >> 6) * 2;
+        if ((v & 63) == 0) {
+            rest[w] = (uint32_t)b;
+            if (w + 1 < nwords) rest[w + 1] = (uint32_t)(b >> 32);
+        }
+    }
 }
 
 // Smallest distance among the far vertices: one word of the far bitmap per thread, a wave
@@ -3068,6 +3166,27 @@ hipError_t launch_cc_relabel(const uint32_t* lab, const uint32_t* order, const u
     return hipGetLastError();
 }
 
+hipError_t launch_cc_link(uint64_t n, const uint64_t* off, const uint32_t* col, uint32_t vmask, uint32_t r, uint32_t* par,
+                          hipStream_t st) {
+    if (!n) return hipSuccess;
+    k_cc_link<<<grid_for(n, 256, 16384), 256, 0, st>>>(n, off, col, vmask, r, par);
+    return hipGetLastError();
+}
+
+hipError_t launch_cc_compress(uint64_t n, uint32_t* par, hipStream_t st) {
+    if (!n) return hipSuccess;
+    k_cc_compress<<<grid_for(n, 256, 16384), 256, 0, st>>>(n, par);
+    return hipGetLastError();
+}
+
+hipError_t launch_cc_rest(uint64_t n, const uint64_t* off, uint32_t done, const uint32_t* par, uint32_t* giant,
+                          uint32_t* rest, uint32_t nwords, hipStream_t st) {
+    if (!n) return hipSuccess;
+    k_cc_giant<<<1, 1024, 0, st>>>(n, par, giant);
+    k_cc_rest<<<grid_for(n, 256, 16384), 256, 0, st>>>(n, off, done, par, giant, rest, nwords);
+    return hipGetLastError();
+}
+
 hipError_t launch_far_min(const uint32_t* far, const uint32_t* dist, uint32_t nwords, uint32_t* out, hipStream_t st) {
     if (!nwords) return hipSuccess;
     k_far_min<<<grid_for(nwords, 256, 8192), 256, 0, st>>>(far, dist, nwords, out);
@@ -3266,6 +3385,9 @@ hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uin
     case ALGO_CC:
         return push_edges_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
+    case ALGO_CC_LINK:
+        return push_edges_op(OpLink{s.val}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift, compacted,
+                             s.pk, st);
     case ALGO_BFS_RELAX:
         return push_edges_op(OpBfsRelax{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
