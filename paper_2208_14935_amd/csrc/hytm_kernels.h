@@ -115,13 +115,14 @@ struct AlgoState {
 
 // PageRank spreads its atomic adds over up to one accumulator copy per XCD (the die id,
 // masked to the copies in use), plus one copy after them for the sums of propagation
-// blocking; the apply step sums them.  Copies relieve contention on hub slots, which only
-// adds at HBM speed create: a run with blocking (whose atomic adds come from the host link)
-// uses one, other runs four.  Measured on MI355X: R-MAT 28 at 8 GB with blocking, 20 steps:
-// 3.72 s with one copy, 3.77-3.79 s with eight; R-MAT 24 at 25% without blocking: 410 ms with
-// one, 311 ms with two, four or eight.
+// blocking; the apply step sums them.  Copies relieve contention on hub slots: eight while
+// they fit the 256 MB Infinity Cache, four on larger graphs, where clearing and summing eight
+// costs as much as they save, and one beside the sorting passes of the pieces.  Measured on
+// MI355X, 20 iterations: R-MAT 22 at 25 / 50% resident beside the compact plan 78 / 68 ms with
+// eight, 83 / 78 with four, 89 / 85 with one; 300K vertices 15.8, 17.9, 21.8 ms; R-MAT 24 at 25%
+// 298, 295, 326 ms; R-MAT 28 at 8 GB with pieces 3.72 s with one, 3.77-3.79 s with eight.
 constexpr uint32_t ACC_COPIES = 8;
-inline uint32_t pr_acc_copies(bool blocked) { return blocked ? 1u : 4u; }
+inline uint32_t pr_acc_copies(bool pieces, uint64_t n) { return pieces ? 1u : n <= (1ull << 23) ? 8u : 4u; }
 
 // Propagation blocking of PageRank's adds over resident edges.  Random float atomics run
 // at a fixed rate (about 20 G/s on MI355X whatever the footprint): above what the host
@@ -217,6 +218,21 @@ hipError_t launch_pg_pack(const uint32_t* v, uint64_t cnt, uint32_t shift, uint6
 // slot (16-byte aligned, padded to a multiple of eight pairs); foff, segs (nsegs of them, of
 // `seg` pairs) as launch_pb_plan made them for the piece.
 hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t e0, const uint32_t* foff,
+                            const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
+                            const float* contrib, float* acc, hipStream_t st);
+// The same for the resident edges [0, m) of a budgeted graph (sources below nv), in one word per
+// pair: sorted by bin and within it by block of 2^16 sources (blocks = ceil(nv / 2^16)).  build:
+// start (nfine * blocks + 1 entries), foff, segs, nsegs (as launch_pb_plan's) and pairs (padded to
+// a multiple of eight, 16-byte aligned) are kept; cnt (nfine * blocks), tot (2 in_tiles(nfine *
+// blocks)) and hist (nfine) are scratch; a destination >= n sets *err.  gather: the sums are
+// added into acc in acc_slot order.
+constexpr size_t RG_MAX_LDS = 60 << 10;
+constexpr uint32_t RG_MAX_FINE = 8192;  // bins that the sort counts in LDS
+hipError_t launch_rg_build(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t nv, uint64_t n,
+                           uint32_t shift, uint32_t nfine, uint32_t blocks, uint32_t seg, uint32_t* cnt, uint64_t* tot,
+                           uint32_t* hist, uint64_t* start, uint32_t* foff, uint32_t* segs, uint32_t* nsegs,
+                           uint32_t* pairs, uint32_t* err, hipStream_t st);
+hipError_t launch_rg_gather(const uint32_t* pairs, const uint64_t* start, uint32_t blocks, const uint32_t* foff,
                             const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
                             const float* contrib, float* acc, hipStream_t st);
 // contrib = x / D_o and acc = 0 (both n entries) before the first iteration.

@@ -2575,7 +2575,7 @@ __global__ __launch_bounds__(64) void k_in_base(uint64_t tiles, uint64_t* __rest
     }
     if (threadIdx.x == 0) {
         toff[n] = ra;
-        soff[n] = (uint32_t)rb;
+        if (soff) soff[n] = (uint32_t)rb;
     }
 }
 
@@ -2612,11 +2612,13 @@ __global__ __launch_bounds__(256) void k_in_write(uint32_t* __restrict__ cnt, ui
         const uint64_t v = v0 + q;
         if (v >= n) break;
         toff[v] = ea;
-        soff[v] = (uint32_t)eb;
-        const uint32_t sg = in_segs(c[q]);
-        for (uint32_t k = 0; k < sg; k++) seg_v[eb + k] = (uint32_t)v;
+        if (soff) {  // else only the edges are wanted
+            soff[v] = (uint32_t)eb;
+            const uint32_t sg = in_segs(c[q]);
+            for (uint32_t k = 0; k < sg; k++) seg_v[eb + k] = (uint32_t)v;
+            eb += sg;
+        }
         ea += c[q];
-        eb += sg;
         cnt[v] = 0;  // the scatter's cursors
     }
 }
@@ -2939,6 +2941,135 @@ __global__ __launch_bounds__(512) void k_pg_gather(const uint32_t* __restrict__ 
             const float y = s_a[pg_place(k)];
             if (y != 0.0f) unsafeAtomicAdd(acc + base + k, y);
         }
+    }
+}
+
+// The compact plan of a budgeted graph's resident edges: a pair is one word, the low 16 bits of
+// the source under the destination's place in its bin, and pairs are sorted by bin and within
+// it by block of 2^16 sources; start[f * blocks + p] = the first pair of bin f from block p.
+// A workgroup takes chunks of RG_CHUNK consecutive edges and of each its source blocks one by
+// one: the bins' pairs are counted in LDS and added to cnt, one atomic per bin (an atomic per
+// pair took 25 ms of 16M pairs on R-MAT 22, whose hub bin takes one pair in twenty); SCATTER
+// takes the places so reserved and deals them out in LDS.
+constexpr uint32_t RG_CHUNK = 1u << 15;
+template <bool SCATTER>
+__global__ __launch_bounds__(512) void k_rg_sort(const uint64_t* __restrict__ off, const uint32_t* __restrict__ col,
+                                                 uint32_t vmask, uint64_t m, uint64_t nv, uint64_t n, uint32_t shift,
+                                                 uint32_t nfine, uint32_t blocks, const uint64_t* __restrict__ start,
+                                                 uint32_t* __restrict__ cnt, uint32_t* __restrict__ pairs,
+                                                 uint32_t* __restrict__ err) {
+    extern __shared__ uint32_t s_h[];
+    __shared__ uint64_t s_u[2];
+    const uint32_t mask = (1u << shift) - 1, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    bool bad = false;
+    for (uint64_t e0 = (uint64_t)blockIdx.x * RG_CHUNK; e0 < m; e0 += (uint64_t)gridDim.x * RG_CHUNK) {
+        const uint64_t e1 = min(e0 + RG_CHUNK, m);
+        if (threadIdx.x < 2) s_u[threadIdx.x] = source_of(off, 0, nv, threadIdx.x ? e1 - 1 : e0);
+        __syncthreads();
+        const uint64_t ua = s_u[0], ub = s_u[1];
+        for (uint64_t p = ua >> 16; p <= ub >> 16; p++) {  // uniform across the workgroup
+            const uint64_t ea = max(e0, off[min(p << 16, nv)]), eb = min(e1, off[min((p + 1) << 16, nv)]);
+            if (ea >= eb) continue;
+            for (uint32_t f = threadIdx.x; f < nfine; f += 512) s_h[f] = 0;
+            __syncthreads();
+            for (uint64_t e = ea + threadIdx.x; e < eb; e += 512) {
+                const uint32_t v = col[e] & vmask;
+                if (v < n)
+                    atomicAdd(&s_h[v >> shift], 1u);
+                else
+                    bad = true;
+            }
+            __syncthreads();
+            for (uint32_t f = threadIdx.x; f < nfine; f += 512) {
+                if (!s_h[f]) continue;
+                const uint64_t key = (uint64_t)f * blocks + p;
+                const uint32_t base = atomicAdd(cnt + key, s_h[f]);
+                if (SCATTER) s_h[f] = (uint32_t)start[key] + base;
+            }
+            __syncthreads();
+            if (SCATTER) {
+                const uint64_t ul = max(ua, p << 16), uh = min(ub, (p << 16) | 0xFFFF);
+                for (uint64_t w0 = ea + wid * 64; w0 < eb; w0 += 512) {  // uniform across the wave
+                    const uint64_t e = w0 + lane;
+                    const uint64_t u0 = source_of(off, ul, uh + 1, w0);
+                    const uint64_t u1 = source_of(off, u0, uh + 1, min(w0 + 63, eb - 1));
+                    if (e >= eb) continue;
+                    const uint64_t u = source_of(off, u0, u1 + 1, e);
+                    const uint32_t v = col[e] & vmask;
+                    if (v < n)
+                        pairs[atomicAdd(&s_h[v >> shift], 1u)] = (uint32_t)(u & 0xFFFFu) | pg_place(v & mask) << 16;
+                }
+                __syncthreads();
+            }
+        }
+        __syncthreads();  // s_u is written again
+    }
+    if (bad) atomicOr(err, 1u);
+}
+
+__global__ void k_rg_hist(const uint64_t* __restrict__ start, uint32_t nfine, uint32_t blocks,
+                          uint32_t* __restrict__ hist) {
+    const uint32_t f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f < nfine) hist[f] = (uint32_t)(start[(uint64_t)(f + 1) * blocks] - start[(uint64_t)f * blocks]);
+}
+
+// As k_pg_gather over the compact plan: eight pairs to a thread, whose source block is found
+// among the bin's block starts (in LDS) for the first pair and followed from there.  The sums go
+// to the accumulator copy of the blocked adds (acc_slot order) beside the streamed atomic adds.
+__global__ __launch_bounds__(256) void k_rg_gather(const uint32_t* __restrict__ pairs,
+                                                   const uint64_t* __restrict__ start, uint32_t blocks,
+                                                   const uint32_t* __restrict__ foff,
+                                                   const uint32_t* __restrict__ segs, uint32_t seg, uint32_t shift,
+                                                   uint64_t n, const float* __restrict__ contrib,
+                                                   float* __restrict__ acc) {
+    extern __shared__ float s_a[];
+    const uint32_t fine = 1u << shift;
+    uint32_t* s_b = (uint32_t*)(s_a + fine);  // blocks + 1 starts
+    const uint32_t f = segs[2 * blockIdx.x], j = segs[2 * blockIdx.x + 1];
+    const uint32_t b0 = foff[f], b1 = foff[f + 1];
+    const bool multi = b1 - b0 > seg;
+    const uint64_t a0 = b0 + (uint64_t)j * seg, a1 = min((uint64_t)b1, a0 + seg);
+    for (uint32_t k = threadIdx.x; k < fine; k += 256) s_a[k] = 0.0f;
+    for (uint32_t k = threadIdx.x; k <= blocks; k += 256) s_b[k] = (uint32_t)start[(uint64_t)f * blocks + k];
+    __syncthreads();
+    const u32x4* p4 = (const u32x4*)pairs;
+    for (uint64_t g = (a0 >> 3) + threadIdx.x; (g << 3) < a1; g += 256) {
+        const u32x4 x = __builtin_nontemporal_load(p4 + 2 * g), y = __builtin_nontemporal_load(p4 + 2 * g + 1);
+        const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        const uint64_t i0 = g << 3, ia = max(i0, a0);
+        uint32_t lo = 0, hi = blocks;  // s_b[lo] <= ia < s_b[hi]
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (s_b[mid] <= ia)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        float c[8];
+#pragma unroll
+        for (int r = 0; r < 8; r++) {
+            const uint64_t i = i0 + r;
+            if (i >= a0 && i < a1) {
+                while (i >= s_b[lo + 1]) lo++;  // i < a1 <= s_b[blocks]
+                c[r] = contrib[(lo << 16) + (w[r] & 0xFFFFu)];
+            } else {
+                c[r] = 0.0f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 8; r++)
+            if (i0 + r >= a0 && i0 + r < a1) atomicAdd(&s_a[w[r] >> 16], c[r]);
+    }
+    __syncthreads();
+    const uint64_t base = (uint64_t)f << shift;
+    const uint32_t lim = (uint32_t)min((uint64_t)fine, n - base);
+    for (uint32_t k = threadIdx.x; k < lim; k += 256) {
+        const float y = s_a[pg_place(k)];
+        float* at = acc + acc_slot((uint32_t)(base + k));
+        if (!multi)
+            *at += y;
+        else if (y != 0.0f)
+            unsafeAtomicAdd(at, y);
     }
 }
 
@@ -3516,6 +3647,36 @@ hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t 
     if (seg == 0 || shift < PG_MIN_SHIFT || shift > PG_MAX_SHIFT) return hipErrorInvalidValue;
     k_pg_gather<<<nsegs, shift > 12 ? 512 : 256, sizeof(float) << shift, st>>>(src, slot, e0, foff, segs, seg, shift, n, contrib,
                                                                    acc);
+    return hipGetLastError();
+}
+
+hipError_t launch_rg_build(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t nv, uint64_t n,
+                           uint32_t shift, uint32_t nfine, uint32_t blocks, uint32_t seg, uint32_t* cnt, uint64_t* tot,
+                           uint32_t* hist, uint64_t* start, uint32_t* foff, uint32_t* segs, uint32_t* nsegs,
+                           uint32_t* pairs, uint32_t* err, hipStream_t st) {
+    if (!m || !nv || !blocks || m > UINT32_MAX || shift < PG_MIN_SHIFT || shift > PG_MAX_SHIFT) return hipErrorInvalidValue;
+    const uint64_t keys = (uint64_t)nfine * blocks, tiles = in_tiles(keys);
+    hipError_t e = launch_fill_u32(cnt, keys, 0u, st);
+    if (e != hipSuccess) return e;
+    const unsigned g = grid_for(m, RG_CHUNK, 8192);
+    const size_t lds = (size_t)nfine * 4;
+    if (nfine > RG_MAX_FINE) return hipErrorInvalidValue;
+    k_rg_sort<false><<<g, 512, lds, st>>>(off, col, vmask, m, nv, n, shift, nfine, blocks, nullptr, cnt, nullptr, err);
+    k_in_tot<<<(unsigned)tiles, 256, 0, st>>>(cnt, keys, tot);
+    k_in_base<<<1, 64, 0, st>>>(tiles, tot, keys, start, nullptr);
+    k_in_write<<<(unsigned)tiles, 256, 0, st>>>(cnt, keys, tot, start, nullptr, nullptr);
+    k_rg_sort<true><<<g, 512, lds, st>>>(off, col, vmask, m, nv, n, shift, nfine, blocks, start, cnt, pairs, err);
+    k_rg_hist<<<(nfine + 255) / 256, 256, 0, st>>>(start, nfine, blocks, hist);
+    return launch_pb_plan(hist, nfine, seg, foff, segs, nsegs, st);
+}
+
+hipError_t launch_rg_gather(const uint32_t* pairs, const uint64_t* start, uint32_t blocks, const uint32_t* foff,
+                            const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
+                            const float* contrib, float* acc, hipStream_t st) {
+    if (!nsegs) return hipSuccess;
+    const size_t lds = (sizeof(float) << shift) + 4 * ((size_t)blocks + 1);
+    if (seg == 0 || shift < PG_MIN_SHIFT || lds > RG_MAX_LDS) return hipErrorInvalidValue;
+    k_rg_gather<<<nsegs, 256, lds, st>>>(pairs, start, blocks, foff, segs, seg, shift, n, contrib, acc);
     return hipGetLastError();
 }
 

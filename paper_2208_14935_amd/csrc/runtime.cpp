@@ -279,6 +279,15 @@ struct hytm_graph {
         DevBuf<uint16_t> slot;
     } pg;
 
+    // Compact PageRank plan of the resident edges of a budgeted graph, kept until the budget
+    // or the resident edges change
+    struct {
+        bool ok = false;
+        uint64_t edges = 0;            // resident edges it covers
+        uint32_t shift = 0, nfine = 0, blocks = 0, seg = 0, nsegs = 0;
+        DevBuf<uint64_t> start;
+        DevBuf<uint32_t> pairs, foff, segs;
+    } rg;
     // In-edge lists (graphs without a budget): made by the first batched PPR or SSSP step that
     // pulls (with the weights once SSSP asks), kept while the graph stays without a budget
     struct {
@@ -640,6 +649,12 @@ void in_release(hytm_graph* g) {
     for (auto* b : {&g->in.soff, &g->in.seg_v, &g->in.tsrc, &g->in.tdst, &g->in.tw}) b->release();
 }
 
+void rg_release(hytm_graph* g) {
+    g->rg.ok = false;
+    g->rg.start.release();
+    for (auto* b : {&g->rg.pairs, &g->rg.foff, &g->rg.segs}) b->release();
+}
+
 void release_all(hytm_graph* g) {
     if (g->s_copy) (void)hipDeviceSynchronize();
     g->d_units.release();
@@ -686,6 +701,7 @@ void release_all(hytm_graph* g) {
         b->release();
     pg_release(g);
     in_release(g);
+    rg_release(g);
     for (uint32_t i = 0; i < kMaxSlots; i++) {
         g->d_slot_col[i].release();
         g->d_slot_w[i].release();
@@ -789,6 +805,10 @@ struct RunCtx {
     uint32_t last_ftasks = 0;                  // streaming filter tasks of the last pass
     uint64_t last_fchunks = 0;
     bool pull = false;                         // batched PPR / SSSP: dense steps may go over the in-edge lists
+    uint32_t rg_parts = 0;                     // PageRank: partitions whose edges go through the compact plan
+    uint32_t rg_ja = 0;                        // ... and where the other resident ones start in the lists
+    uint64_t rg_wa = 0;
+    bool rg_block = false;                     // ... where the pieces of pr_blocking would have
     // PageRank over a gather plan (hytm_graph::pg): the selection, replayed every iteration
     bool pg_on = false;
     struct {
@@ -1016,7 +1036,8 @@ hytm_status prepare_graph(hytm_graph* g, uint32_t plan_arrays, hipStream_t main,
 // located, each line read once) moves them faster than zero-copy's per-list passes (R-MAT 28
 // at 8 GB: 3.82 s against 4.21 s); without blocking PageRank's pushes fill the GPU and zero-copy
 // is the faster (R-MAT 24 at 25%: 313 against 340 ms).  Ties to filter are as fast or faster
-// for BFS, SSSP and CC on both graphs.
+// for BFS, SSSP and CC on both graphs, and for PageRank beside the compact plan (R-MAT 22 at 25%:
+// 82.9 against 84.6 ms, R-MAT 24 295 against 303 ms).  pb_on: the resident adds are blocked either way.
 uint32_t resolve_tie(const hytm_graph* g, int algo, bool pb_on) {
     const uint32_t t = g->params.zc_tie;
     if (t != 2) return t;
@@ -1043,7 +1064,7 @@ void init_ctx(RunCtx& rc, hytm_graph* g, int algo, bool batched, const Plan& pl,
     rc.as.pk = g->pk;
     rc.as.far = nullptr;
     rc.as.bound = 0xFFFFFFFFu;  // no far set unless a single-source SSSP run asks for one
-    rc.as.acc_copies = pr_acc_copies(false);  // a run decides once it knows whether it blocks
+    rc.as.acc_copies = 4;  // a PageRank run decides once it knows whether it blocks
 }
 
 // Where the zero-copy pushes count the distinct lines they read (a statistic), or null.
@@ -1113,6 +1134,143 @@ bool in_ready(RunCtx& rc, hipStream_t main) {
     drop();
     in.ok = true;
     return true;
+}
+
+// Vertices per destination bin, as a shift: 2^11 sums (8 KB of LDS) measured best, down to 512
+// bins on smaller graphs, so that a piece has workgroups for the 256 CUs, and more sums per
+// bin past 2^25 vertices, where the bins reach the sort's limit.
+uint32_t pg_shift(uint64_t n) {
+    uint32_t bits = 0;
+    while (bits < 32 && (n - 1) >> bits) bits++;
+    uint32_t sh = std::min(std::max(bits, PG_MIN_SHIFT + 9) - 9, 11u);
+    while ((n + (1ull << sh) - 1) >> sh > PB_MAX_FINE) sh++;  // n <= 2^28: at most PG_MAX_SHIFT
+    return sh;
+}
+
+// Bytes of the compact plan over `edges` resident edges of vertices below nv.
+uint64_t rg_bytes(const hytm_graph* g, uint64_t edges, uint64_t nv, uint32_t* shift, uint32_t* nfine, uint32_t* blocks,
+                  uint32_t* seg) {
+    *shift = pg_shift(g->n);
+    while (*nfine = (uint32_t)((g->n + (1ull << *shift) - 1) >> *shift), *nfine > RG_MAX_FINE) ++*shift;
+    *blocks = (uint32_t)((nv + 0xFFFF) >> 16);
+    *seg = pb_seg_len(*nfine, edges);
+    return 4 * (edges + 8) + 8 * ((uint64_t)*nfine * *blocks + 1) + 4 * (*nfine + 1) +
+           8ull * pb_max_segs(*nfine, edges, *seg);
+}
+
+// The compact plan.  A budgeted graph's resident edges compete with the streamed ones for the
+// atomic units (12-18 G adds/s, below what the link and the resident cache feed together), and
+// the sorting passes of the pieces compete for CUs; the plan takes the resident adds into LDS at
+// 4 bytes of pairs per edge.  20 iterations, atomic or pieces (automatic) -> plan: R-MAT 22 at
+// 25 / 35 / 50% resident 98 / 93 / 87 -> 78 / 71 / 68 ms, R-MAT 24 at 25 / 50% 338 / 302 -> 295 / 256,
+// uniform 3M vertices 64 / 52 -> 57 / 47 ms.
+// PageRank's resident edges of a budgeted graph go through the compact plan as far as it fits
+// the device memory that pr_blocking may take outside the budget (16 bytes per vertex, at
+// least 16 MiB): the longest prefix of the resident partitions whose plan does, the others are
+// pushed with atomic adds.  Returns that many partitions, 0 = no plan.  Automatic blocking
+// only: pr_blocking = 2 asks for the pieces.
+uint32_t rg_partitions(const RunCtx& rc) {
+    const hytm_graph* g = rc.g;
+    if (rc.algo != HYTM_PAGERANK || rc.batched || g->budget == UINT64_MAX || g->params.pr_blocking != 1 ||
+        g->params.mode == HYTM_MODE_COMPACT || g->params.filter_engine != HYTM_FILTER_STREAM ||
+        pb_fine_bins(g->n) > PB_MAX_FINE)
+        return 0;
+    auto fits = [&](uint32_t p) {
+        const uint64_t edges = g->h_off[g->pv[p]];
+        uint32_t shift, nfine, blocks, seg;
+        return edges < UINT32_MAX && g->n <= (1ull << 26) &&  // bins of at most 2^13 sums
+               rg_bytes(g, edges, g->pv[p], &shift, &nfine, &blocks, &seg) <= 16 * std::max<uint64_t>(g->n, 1ull << 20) &&
+               (sizeof(float) << shift) + 4 * (blocks + 1ull) <= RG_MAX_LDS;
+    };
+    uint32_t lo = 0, hi = std::min(rc.plan.nres, g->npart) + 1;  // fits(lo), not fits(hi)
+    while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (fits(mid))
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return g->h_off[g->pv[lo]] ? lo : 0;
+}
+
+// The compact plan of the run's resident edges, made on first use.
+void rg_build(RunCtx& rc, hipStream_t main) {
+    hytm_graph* g = rc.g;
+    auto& rg = g->rg;
+    const uint64_t nv = g->pv[rc.rg_parts], edges = g->h_off[nv];
+    if (rg.ok && rg.edges == edges) return;
+    rg_release(g);
+    rg_bytes(g, edges, nv, &rg.shift, &rg.nfine, &rg.blocks, &rg.seg);
+    const uint64_t keys = (uint64_t)rg.nfine * rg.blocks;
+    struct Temps {
+        DevBuf<uint32_t> cnt, hist, nsegs, err;
+        DevBuf<uint64_t> tot;
+        ~Temps() {
+            for (auto* b : {&cnt, &hist, &nsegs, &err}) b->release();
+            tot.release();
+        }
+    } t;
+    rg.start.ensure(keys + 1);
+    rg.pairs.ensure((edges + 7) & ~uint64_t(7));
+    rg.foff.ensure(rg.nfine + 1);
+    rg.segs.ensure(2ull * pb_max_segs(rg.nfine, edges, rg.seg));
+    t.cnt.ensure(keys);
+    t.hist.ensure(rg.nfine);
+    t.nsegs.ensure(1);
+    t.err.ensure(1);
+    t.tot.ensure(2 * in_tiles(keys));
+    HIP_CHECK(launch_fill_u32(t.err.p, 1, 0u, main));
+    HIP_CHECK(g->timer.run(HYTM_K_OTHER, edges, main, [&] {
+        return launch_rg_build(g->d_off.p, g->d_res_col.p, g->pk.mask, edges, nv, g->n, rg.shift, rg.nfine, rg.blocks,
+                               rg.seg, t.cnt.p, t.tot.p, t.hist.p, rg.start.p, rg.foff.p, rg.segs.p, t.nsegs.p,
+                               rg.pairs.p, t.err.p, main);
+    }));
+    uint32_t out[2] = {0, 0};
+    HIP_CHECK(hipMemcpyAsync(&out[0], t.nsegs.p, sizeof(uint32_t), hipMemcpyDeviceToHost, main));
+    HIP_CHECK(hipMemcpyAsync(&out[1], t.err.p, sizeof(uint32_t), hipMemcpyDeviceToHost, main));
+    HIP_CHECK(hipStreamSynchronize(main));
+    if (out[1]) {
+        rg_release(g);
+        fail(HYTM_E_DEVICE, "internal: PageRank pairs point outside the graph");
+        throw HipError{HYTM_E_DEVICE};
+    }
+    rg.nsegs = out[0];
+    rg.edges = edges;
+    rg.ok = true;
+}
+
+// The push over the resident segment of a selection.
+void push_resident(RunCtx& rc, const Header& h, hipStream_t main) {
+    hytm_graph* g = rc.g;
+    KTimer& kt = g->timer;
+    const AlgoState& as = rc.as;
+    const uint64_t work = h.seg_work_total[SEG_R];
+    if (!h.seg_list_count[SEG_R]) return;
+    const uint32_t jb = h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R];
+    uint32_t ja = h.seg_list_start[SEG_R];
+    uint64_t wa = h.seg_work_start[SEG_R];
+    const uint64_t wb = wa + work;
+    if (rc.rg_parts) {
+        const auto& rg = g->rg;
+        float* acc = as.acc + (uint64_t)as.acc_copies * acc_slots(g->n);  // the blocked adds' copy
+        HIP_CHECK(kt.run(rc.rg_block ? HYTM_K_PR_BLOCK : HYTM_K_PUSH_RES, rg.edges, main, [&] {
+            return launch_rg_gather(rg.pairs.p, rg.start.p, rg.blocks, rg.foff.p, rg.segs.p, rg.nsegs, rg.seg, rg.shift,
+                                    g->n, as.contrib, acc, main);
+        }));
+        ja = rc.rg_ja;
+        wa = rc.rg_wa;
+        if (ja == jb) return;
+    }
+    const bool wide = rc.algo == HYTM_PPR ? work >= g->m / kPullPpr
+                                          : as.lshift >= kPullSsspShift && work >= g->m / kPullSssp;
+    if (rc.pull && wide && in_ready(rc, main)) {
+        HIP_CHECK(kt.run(HYTM_K_PUSH_RES, work, main, [&] { return launch_pull(as, g->in.lists(), main); }));
+        return;
+    }
+    HIP_CHECK(kt.run(HYTM_K_PUSH_RES, wb - wa, main, [&] {
+        return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, ja, jb, wa, wb, g->d_off.p,
+                                 g->d_res_col.p, g->d_res_w.p, 0, false, main);
+    }));
 }
 
 // One engine pass over the frontier `cur` (Algorithm 1 plus the engines of Sec. 6.2),
@@ -1206,6 +1364,12 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
     rec->active_vertices += h.total_active;
     for (int s = 0; s < NSEG; s++) rec->active_edges += h.seg_edges[s];
     if (traced) memcpy(stats->mode_trace + (uint64_t)trace_t * npart, g->h_mode.p, npart);
+    if (rc.rg_parts) {  // the resident partitions past the compact plan's, in the lists just made
+        uint32_t p = rc.rg_parts;
+        while (p < npart && g->h_mode.p[p] != P_RES) p++;
+        rc.rg_ja = p < npart ? g->h_lbase.p[p] : h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R];
+        rc.rg_wa = p < npart ? g->h_wbase.p[p] : h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R];
+    }
     if (select_only) return HYTM_OK;
 
     // the other engines' streams start after the lists
@@ -1315,20 +1479,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
             }
             rec->filter_tasks += gidx;
         }
-        // resident partitions: no transfer
-        const bool wide = rc.algo == HYTM_PPR ? h.seg_work_total[SEG_R] >= g->m / kPullPpr
-                                              : as.lshift >= kPullSsspShift && h.seg_work_total[SEG_R] >= g->m / kPullSssp;
-        if (rc.pull && wide && in_ready(rc, main))
-            HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-                return launch_pull(as, g->in.lists(), main);
-            }));
-        else if (h.seg_list_count[SEG_R])
-            HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-                return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
-                                         h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
-                                         h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
-                                         g->d_res_w.p, 0, false, main);
-            }));
+        push_resident(rc, h, main);  // no transfer
     } catch (const HipError& e) {
         fst = e.status;
     }
@@ -1396,13 +1547,6 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
     const Header& h = rc.replay.h;
     replay_record(rc, h, rec, trace_t);
     HIP_CHECK(hipEventRecord(g->ev_go, main));
-    if (h.seg_list_count[SEG_R])
-        HIP_CHECK(kt.run(HYTM_K_PUSH_RES, h.seg_work_total[SEG_R], main, [&] {
-            return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, h.seg_list_start[SEG_R],
-                                     h.seg_list_start[SEG_R] + h.seg_list_count[SEG_R], h.seg_work_start[SEG_R],
-                                     h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R], g->d_off.p, g->d_res_col.p,
-                                     g->d_res_w.p, 0, false, main);
-        }));
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(hipStreamWaitEvent(g->s_zc, g->ev_go, 0));
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
@@ -1422,6 +1566,7 @@ hytm_status replay_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int6
         rec->filter_tasks += rc.replay.ftasks;
         rec->bytes_filter += rc.replay.fbytes;
     }
+    push_resident(rc, h, main);
     HIP_CHECK(hipEventRecord(g->ev_join[0], g->s_fk));
     HIP_CHECK(hipEventRecord(g->ev_join[1], g->s_zc));
     for (int q = 0; q < 2; q++) HIP_CHECK(hipStreamWaitEvent(main, g->ev_join[q], 0));
@@ -1688,17 +1833,6 @@ bool pg_eligible(const RunCtx& rc) {
     return pb_eligible(rc) && g->budget == UINT64_MAX;
 }
 
-// Vertices per destination bin, as a shift: 2^11 sums (8 KB of LDS) measured best, down to 512
-// bins on smaller graphs, so that a piece has workgroups for the 256 CUs, and more sums per
-// bin past 2^25 vertices, where the bins reach the sort's limit.
-uint32_t pg_shift(uint64_t n) {
-    uint32_t bits = 0;
-    while (bits < 32 && (n - 1) >> bits) bits++;
-    uint32_t sh = std::min(std::max(bits, PG_MIN_SHIFT + 9) - 9, 11u);
-    while ((n + (1ull << sh) - 1) >> sh > PB_MAX_FINE) sh++;  // n <= 2^28: at most PG_MAX_SHIFT
-    return sh;
-}
-
 // Pairs per piece: pr_block_pairs if given, else four per vertex (a piece costs a
 // read-modify-write of every vertex's sum) and at least 2^24 (a piece is a launch).
 uint64_t pg_capacity(const hytm_graph* g) {
@@ -1835,7 +1969,7 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
     const uint32_t t = rc.t;
     const bool fixed_steps = rc.algo == HYTM_PAGERANK || rc.algo == HYTM_PPR;
     const double t_it = now_ms();
-    const uint32_t copies = rc.pb_on ? as.acc_copies + 1 : as.acc_copies;  // + the blocking copy
+    const uint32_t copies = rc.pb_on || rc.rg_parts ? as.acc_copies + 1 : as.acc_copies;  // + the blocking copy
     if (rc.algo == HYTM_PAGERANK && !rc.pg_on)
         HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] {
             return launch_pr_prepare(n, g->d_off.p, g->d_x.p, g->d_contrib.p, g->d_acc.p, copies, main);
@@ -2173,8 +2307,24 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     rc.pb_on = pb_eligible(rc);
     rc.pg_on = pg_eligible(rc);
     if (rc.pg_on && g->pg.ok && g->pg.cap != pg_capacity(g)) pg_release(g);  // other pieces were asked for
-    rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on);
-    rc.as.acc_copies = pr_acc_copies(rc.pb_on);
+    if ((rc.rg_parts = rg_partitions(rc))) {
+        rc.rg_block = rc.pb_on;
+        rc.pb_on = false;
+    }
+    rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on || rc.rg_parts);
+    if (algo == HYTM_PAGERANK) rc.as.acc_copies = pr_acc_copies(rc.pb_on, g->n);
+    if (rc.rg_parts) {
+        try {
+            rg_build(rc, main);
+        } catch (const HipError& e) {
+            if (e.status != HYTM_E_NOMEM) throw;
+            rg_release(g);  // no room for it: as without
+            rc.rg_parts = 0;
+            rc.pb_on = rc.rg_block;
+            rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on);
+            rc.as.acc_copies = pr_acc_copies(rc.pb_on, g->n);
+        }
+    }
 
     const uint64_t n = g->n;
     const uint32_t nwords = rc.nwords;
@@ -2958,6 +3108,10 @@ hytm_status hytm_set_device_budget(hytm_graph* g, uint64_t edge_bytes) {
             (void)hipSetDevice(g->device);
             pg_release(g);
             in_release(g);
+        }
+        if (g->rg.ok) {
+            (void)hipSetDevice(g->device);
+            rg_release(g);
         }
     }
     g->budget = edge_bytes;

@@ -101,3 +101,53 @@ def test_plan_on_a_union_of_graphs(hub_sort):
     for i, (o, c) in enumerate(graphs):
         want = oracle.pagerank(o, c, 0.85, 20)
         assert np.abs(got[int(bounds[i]):int(bounds[i + 1])] - want).max() <= 1e-6
+
+
+@pytest.mark.parametrize("mode", ["hybrid", "filter", "zerocopy"])
+@pytest.mark.parametrize("resident", [0.05, 0.3, 0.7])
+@pytest.mark.parametrize("name", ["4095", "2^15 + 1", "rmat 16", "2^20 + 3", "2^21 + 1"])
+def test_compact_plan_matches_oracle(name, resident, mode):
+    """Budgeted graphs: the resident edges in one-word pairs, sources in blocks of 2^16."""
+    off, col = GRAPHS[name]()
+    want = oracle.pagerank(off, col, 0.85, 20)
+    with hy.Graph(off, col) as g:
+        g.set_params(partition_edges=512, mode=mode, compact_chunk_edges=1 << 14)
+        g.set_resident_fraction("pagerank", resident)
+        first = g.run("pagerank", stats=True)
+        check(first, want)
+        check(g.run("pagerank"), want)
+        assert 0 < first.stats["nres"] < first.stats["npart"]
+        g.set_params(pr_blocking=0)
+        off_run = g.run("pagerank", stats=True)
+        check(off_run, want)
+        # the same partitions are read over the link: only the resident adds changed
+        assert first.stats["active_edges"] == off_run.stats["active_edges"]
+        assert first.stats["nres"] == off_run.stats["nres"]
+
+
+def test_compact_plan_ends_inside_the_resident_prefix():
+    """More resident edges than 16 MiB hold pairs for (2^20 vertices, 6.3M resident edges): the
+    partitions past the plan's are added atomically."""
+    rng = np.random.default_rng(2)
+    n = 1 << 20
+    off, col = gen.from_pairs(n, rng.integers(0, n // 8, 9 << 20).astype(np.uint32),
+                              rng.integers(0, n, 9 << 20).astype(np.uint32))
+    want = oracle.pagerank(off, col, 0.85, 20)
+    with hy.Graph(off, col) as g:
+        g.set_resident_fraction("pagerank", 0.7)
+        res = g.run("pagerank", stats=True, time_kernels=True)
+        check(res, want)
+        check(g.run("pagerank"), want)
+        g.set_resident_fraction("pagerank", 0.2)  # another plan
+        check(g.run("pagerank"), want)
+    assert res.stats["kernel_launches"][hy.KERNEL_CLASSES.index("push_resident")] >= 20  # the rest of them
+    assert res.stats["kernel_launches"][hy.KERNEL_CLASSES.index("pr_blocking")] == 20
+
+
+def test_compact_plan_of_wide_bins():
+    """17M vertices: 2^12 vertices per bin keep the bins within the sort's LDS."""
+    off, col = gen.er(17_000_000, 34_000_000, seed=9)
+    want = oracle.pagerank(off, col, 0.85, 20)
+    with hy.Graph(off, col) as g:
+        g.set_resident_fraction("pagerank", 0.4)
+        check(g.run("pagerank"), want)
