@@ -137,7 +137,7 @@ inline uint32_t pr_acc_copies(bool pieces, uint64_t n) { return pieces ? 1u : n 
 // read-modify-writes.  Bucket sizes of a piece are the same in every PageRank iteration
 // (every vertex is active), so they are counted once.
 constexpr uint32_t PB_FINE_SHIFT = 14;
-constexpr uint32_t PB_FINE = 1u << PB_FINE_SHIFT;   // accumulator slots per fine bin (64 KB of LDS)
+constexpr uint32_t PB_FINE = 1u << PB_FINE_SHIFT;   // accumulator slots per fine bin (128 KB of LDS)
 constexpr uint32_t PB_MAX_FINE = 16384;             // fine bins (LDS histogram): n <= 2^28
 constexpr uint32_t PB_FINE_PER_COARSE = 32;
 // Fine bins of n vertices; the accumulation segment length for pieces of `pairs` (twice a
@@ -226,7 +226,7 @@ hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t 
 // a multiple of eight, 16-byte aligned) are kept; cnt (nfine * blocks), tot (2 in_tiles(nfine *
 // blocks)) and hist (nfine) are scratch; a destination >= n sets *err.  gather: the sums are
 // added into acc in acc_slot order.
-constexpr size_t RG_MAX_LDS = 60 << 10;
+constexpr size_t RG_MAX_LDS = 80 << 10;
 constexpr uint32_t RG_MAX_FINE = 8192;  // bins that the sort counts in LDS
 hipError_t launch_rg_build(const uint64_t* off, const uint32_t* col, uint32_t vmask, uint64_t m, uint64_t nv, uint64_t n,
                            uint32_t shift, uint32_t nfine, uint32_t blocks, uint32_t seg, uint32_t* cnt, uint64_t* tot,

@@ -2446,7 +2446,7 @@ __global__ __launch_bounds__(PB_THREADS) void k_pb_scatter_a(const uint32_t* __r
     if (bad) atomicOr(err, 1u);
 }
 
-constexpr int PB_ACC_THREADS = 512;
+constexpr int PB_ACC_THREADS = 1024;
 constexpr uint32_t PB_ACC_BATCH = 8;  // pairs per thread with loads in flight together
 
 __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __restrict__ pv,
@@ -2457,8 +2457,7 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
                                                              uint64_t n, float* __restrict__ acc,
                                                              uint32_t* __restrict__ err) {
     constexpr uint32_t Q4 = PB_FINE / 4 / PB_ACC_THREADS;  // float4 slots per thread
-    __shared__ float4 s_a4[PB_FINE / 4];
-    float* s_a = (float*)s_a4;
+    extern __shared__ double s_a[];  // PB_FINE sums (FP64 adds: see k_pg_gather)
     const uint32_t s = blockIdx.x;
     if (s >= *nsegs) return;  // the same for every thread of the workgroup
     const uint32_t f = segs[2 * s], j = segs[2 * s + 1];
@@ -2467,7 +2466,7 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
     const uint32_t end = min(b1, start + seg);
     const bool multi = b1 - b0 > seg;
 #pragma unroll
-    for (uint32_t q = 0; q < Q4; q++) s_a4[q * PB_ACC_THREADS + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (uint32_t q = 0; q < 4 * Q4; q++) s_a[q * PB_ACC_THREADS + threadIdx.x] = 0.0;
     __syncthreads();
     bool bad = false;
     for (uint32_t i0 = start; i0 < end; i0 += PB_ACC_BATCH * PB_ACC_THREADS) {
@@ -2483,7 +2482,7 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
         for (uint32_t r = 0; r < PB_ACC_BATCH; r++) {
             if (i0 + r * PB_ACC_THREADS + threadIdx.x >= end) continue;
             if ((v[r] >> PB_FINE_SHIFT) == f && v[r] < n)
-                atomicAdd(&s_a[acc_slot(v[r]) & (PB_FINE - 1)], c[r]);
+                unsafeAtomicAdd(&s_a[acc_slot(v[r]) & (PB_FINE - 1)], (double)c[r]);
             else
                 bad = true;
         }
@@ -2505,17 +2504,16 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
         for (uint32_t q = 0; q < Q4; q++) {
             const uint32_t k = q * PB_ACC_THREADS + threadIdx.x;
             if (k < lim4) {
-                const float4 y = s_a4[k];
-                x[q].x += y.x;
-                x[q].y += y.y;
-                x[q].z += y.z;
-                x[q].w += y.w;
+                x[q].x += (float)s_a[4 * k];
+                x[q].y += (float)s_a[4 * k + 1];
+                x[q].z += (float)s_a[4 * k + 2];
+                x[q].w += (float)s_a[4 * k + 3];
                 a4[k] = x[q];
             }
         }
     } else {
         for (uint32_t q = threadIdx.x; q < lim4 * 4; q += PB_ACC_THREADS)
-            if (s_a[q] != 0.0f) unsafeAtomicAdd(acc + base + q, s_a[q]);
+            if (s_a[q] != 0.0) unsafeAtomicAdd(acc + base + q, (float)s_a[q]);
     }
 }
 
@@ -2888,13 +2886,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // bin's sums in LDS, and the sums are added to acc (plain read-modify-write when the bin is
 // one segment, atomic adds of the non-zero sums when it spans several).  The pairs of the
 // piece start at e0 of src / slot, which are padded to a multiple of eight.
-// Bound by the lines that the gathers miss in the L2 (PMC on R-MAT 24, per launch of 67M
-// pairs: 1.2 GB fetched in 0.41 ms, 0.4 GB of it the 6-byte pairs).  A bin's pairs are in
-// source order, so concurrent workgroups share lines.  Measured there, 20 iterations: 0.16 T
-// edges/s, 32.7 ms against 135 ms for expanding, sorting and summing the pairs; bins of 2^14
-// / 2^13 / 2^12 / 2^11 / 2^10 sums 45.6 / 40.8 / 37.0 / 32.7 / 33.3 ms (smaller bins leave LDS
-// for more workgroups per CU); pieces of n / 2n / 4n / 8n / 16n pairs 51 / 37.9 / 32.7 / 33.6 /
-// 33.7 ms (each piece adds every vertex's sum once more).
+// The sums are FP64: an LDS add of 64 lanes takes 193 cycles of a CU in FP32 whatever the
+// places (3 per lane), 20 in FP64 at random places, 9 in order.
+// Measured on R-MAT 24 (263M pairs, 20 iterations), against 135 ms for expanding, sorting and
+// summing the pairs: FP32 sums 32.6 ms (32.2 without the gathers, 21.8 without the adds), FP64
+// 22.1, with the next pairs loaded ahead 20.6 ms, 0.26 T edges/s.  Bound by the gathers then
+// (contributions without the gaps of vertices that have no out-edges fetch fewer lines and take
+// as long).  Bins of 2^11 / 2^12 / 2^13 / 2^14 sums 22.0 / 21.6 / 20.6 / 21.8 ms; pieces of 3n /
+// 4n pairs 21.4 / 20.6 ms, of 8n at 2^12 24.7 against 22.9 ms (each piece adds every vertex's
+// sum once more, larger ones spread their sources over more of the L2).
 __global__ __launch_bounds__(512) void k_pg_gather(const uint32_t* __restrict__ src,
                                                           const uint16_t* __restrict__ slot, uint64_t e0,
                                                           const uint32_t* __restrict__ foff,
@@ -2902,43 +2902,59 @@ __global__ __launch_bounds__(512) void k_pg_gather(const uint32_t* __restrict__ 
                                                           uint32_t shift, uint64_t n,
                                                           const float* __restrict__ contrib,
                                                           float* __restrict__ acc) {
-    extern __shared__ float s_a[];
+    extern __shared__ double s_a[];
     const uint32_t f = segs[2 * blockIdx.x], j = segs[2 * blockIdx.x + 1];
     const uint32_t b0 = foff[f], b1 = foff[f + 1];
     const bool multi = b1 - b0 > seg;
     const uint64_t a0 = e0 + b0 + (uint64_t)j * seg, a1 = min(e0 + b1, a0 + seg);
     const uint32_t fine = 1u << shift;
-    for (uint32_t k = threadIdx.x; k < fine; k += blockDim.x) s_a[k] = 0.0f;
+    for (uint32_t k = threadIdx.x; k < fine; k += blockDim.x) s_a[k] = 0.0;
     __syncthreads();
     const u32x4* src4 = (const u32x4*)src;
     const u32x4* slot8 = (const u32x4*)slot;
-    for (uint64_t g = (a0 >> 3) + threadIdx.x; (g << 3) < a1; g += blockDim.x) {
-        const u32x4 p = __builtin_nontemporal_load(src4 + 2 * g), q = __builtin_nontemporal_load(src4 + 2 * g + 1);
-        const u32x4 z = __builtin_nontemporal_load(slot8 + g);
+    // the next group's pairs are on their way while the present one's contributions are gathered
+    uint64_t g = (a0 >> 3) + threadIdx.x;
+    u32x4 p{}, q{}, z{};
+    if ((g << 3) < a1) {
+        p = __builtin_nontemporal_load(src4 + 2 * g);
+        q = __builtin_nontemporal_load(src4 + 2 * g + 1);
+        z = __builtin_nontemporal_load(slot8 + g);
+    }
+    while ((g << 3) < a1) {
         const uint32_t u[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
         const uint32_t zz[4] = {z.x, z.y, z.z, z.w};
         const uint64_t i0 = g << 3;
+        const bool whole = i0 >= a0 && i0 + 8 <= a1;
         float c[8];
-        if (i0 >= a0 && i0 + 8 <= a1) {
+        if (whole) {
 #pragma unroll
             for (int r = 0; r < 8; r++) c[r] = contrib[u[r]];
+        }
+        g += blockDim.x;
+        if ((g << 3) < a1) {
+            p = __builtin_nontemporal_load(src4 + 2 * g);
+            q = __builtin_nontemporal_load(src4 + 2 * g + 1);
+            z = __builtin_nontemporal_load(slot8 + g);
+        }
+        if (whole) {
 #pragma unroll
-            for (int r = 0; r < 8; r++) atomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], c[r]);
+            for (int r = 0; r < 8; r++)
+                unsafeAtomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], (double)c[r]);
         } else {  // the segment's first or last group: its pairs only
 #pragma unroll
             for (int r = 0; r < 8; r++)
                 if (i0 + r >= a0 && i0 + r < a1)
-                    atomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], contrib[u[r]]);
+                    unsafeAtomicAdd(&s_a[(zz[r >> 1] >> (16 * (r & 1))) & 0xFFFFu], (double)contrib[u[r]]);
         }
     }
     __syncthreads();
     const uint64_t base = (uint64_t)f << shift;
     const uint32_t lim = (uint32_t)min((uint64_t)fine, n - base);
     if (!multi) {
-        for (uint32_t k = threadIdx.x; k < lim; k += blockDim.x) acc[base + k] += s_a[pg_place(k)];
+        for (uint32_t k = threadIdx.x; k < lim; k += blockDim.x) acc[base + k] += (float)s_a[pg_place(k)];
     } else {
         for (uint32_t k = threadIdx.x; k < lim; k += blockDim.x) {
-            const float y = s_a[pg_place(k)];
+            const float y = (float)s_a[pg_place(k)];
             if (y != 0.0f) unsafeAtomicAdd(acc + base + k, y);
         }
     }
@@ -3022,14 +3038,14 @@ __global__ __launch_bounds__(256) void k_rg_gather(const uint32_t* __restrict__ 
                                                    const uint32_t* __restrict__ segs, uint32_t seg, uint32_t shift,
                                                    uint64_t n, const float* __restrict__ contrib,
                                                    float* __restrict__ acc) {
-    extern __shared__ float s_a[];
+    extern __shared__ double s_a[];
     const uint32_t fine = 1u << shift;
     uint32_t* s_b = (uint32_t*)(s_a + fine);  // blocks + 1 starts
     const uint32_t f = segs[2 * blockIdx.x], j = segs[2 * blockIdx.x + 1];
     const uint32_t b0 = foff[f], b1 = foff[f + 1];
     const bool multi = b1 - b0 > seg;
     const uint64_t a0 = b0 + (uint64_t)j * seg, a1 = min((uint64_t)b1, a0 + seg);
-    for (uint32_t k = threadIdx.x; k < fine; k += 256) s_a[k] = 0.0f;
+    for (uint32_t k = threadIdx.x; k < fine; k += 256) s_a[k] = 0.0;
     for (uint32_t k = threadIdx.x; k <= blocks; k += 256) s_b[k] = (uint32_t)start[(uint64_t)f * blocks + k];
     __syncthreads();
     const u32x4* p4 = (const u32x4*)pairs;
@@ -3058,13 +3074,13 @@ __global__ __launch_bounds__(256) void k_rg_gather(const uint32_t* __restrict__ 
         }
 #pragma unroll
         for (int r = 0; r < 8; r++)
-            if (i0 + r >= a0 && i0 + r < a1) atomicAdd(&s_a[w[r] >> 16], c[r]);
+            if (i0 + r >= a0 && i0 + r < a1) unsafeAtomicAdd(&s_a[w[r] >> 16], (double)c[r]);
     }
     __syncthreads();
     const uint64_t base = (uint64_t)f << shift;
     const uint32_t lim = (uint32_t)min((uint64_t)fine, n - base);
     for (uint32_t k = threadIdx.x; k < lim; k += 256) {
-        const float y = s_a[pg_place(k)];
+        const float y = (float)s_a[pg_place(k)];
         float* at = acc + acc_slot((uint32_t)(base + k));
         if (!multi)
             *at += y;
@@ -3645,7 +3661,7 @@ hipError_t launch_pg_gather(const uint32_t* src, const uint16_t* slot, uint64_t 
     if (!nsegs) return hipSuccess;
     // sums of 32 KB and more leave room for few workgroups per CU: larger ones
     if (seg == 0 || shift < PG_MIN_SHIFT || shift > PG_MAX_SHIFT) return hipErrorInvalidValue;
-    k_pg_gather<<<nsegs, shift > 12 ? 512 : 256, sizeof(float) << shift, st>>>(src, slot, e0, foff, segs, seg, shift, n, contrib,
+    k_pg_gather<<<nsegs, shift >= 12 ? 512 : 256, sizeof(double) << shift, st>>>(src, slot, e0, foff, segs, seg, shift, n, contrib,
                                                                    acc);
     return hipGetLastError();
 }
@@ -3674,7 +3690,7 @@ hipError_t launch_rg_gather(const uint32_t* pairs, const uint64_t* start, uint32
                             const uint32_t* segs, uint32_t nsegs, uint32_t seg, uint32_t shift, uint64_t n,
                             const float* contrib, float* acc, hipStream_t st) {
     if (!nsegs) return hipSuccess;
-    const size_t lds = (sizeof(float) << shift) + 4 * ((size_t)blocks + 1);
+    const size_t lds = (sizeof(double) << shift) + 4 * ((size_t)blocks + 1);
     if (seg == 0 || shift < PG_MIN_SHIFT || lds > RG_MAX_LDS) return hipErrorInvalidValue;
     k_rg_gather<<<nsegs, 256, lds, st>>>(pairs, start, blocks, foff, segs, seg, shift, n, contrib, acc);
     return hipGetLastError();
@@ -3742,7 +3758,7 @@ hipError_t launch_pb_accum(const uint32_t* pv, const float* pc, const uint32_t* 
                            uint32_t* err, hipStream_t st) {
     if (!max_segs || !n) return hipSuccess;
     if (seg == 0) return hipErrorInvalidValue;
-    k_pb_accum<<<max_segs, PB_ACC_THREADS, 0, st>>>(pv, pc, foff, segs, nsegs, seg, n, acc, err);
+    k_pb_accum<<<max_segs, PB_ACC_THREADS, sizeof(double) * PB_FINE, st>>>(pv, pc, foff, segs, nsegs, seg, n, acc, err);
     return hipGetLastError();
 }
 

@@ -1136,13 +1136,13 @@ bool in_ready(RunCtx& rc, hipStream_t main) {
     return true;
 }
 
-// Vertices per destination bin, as a shift: 2^11 sums (8 KB of LDS) measured best, down to 512
+// Vertices per destination bin, as a shift: 2^13 sums (64 KB of LDS) measured best, down to 512
 // bins on smaller graphs, so that a piece has workgroups for the 256 CUs, and more sums per
-// bin past 2^25 vertices, where the bins reach the sort's limit.
+// bin past 2^27 vertices, where the bins reach the sort's limit.
 uint32_t pg_shift(uint64_t n) {
     uint32_t bits = 0;
     while (bits < 32 && (n - 1) >> bits) bits++;
-    uint32_t sh = std::min(std::max(bits, PG_MIN_SHIFT + 9) - 9, 11u);
+    uint32_t sh = std::min(std::max(bits, PG_MIN_SHIFT + 9) - 9, 13u);
     while ((n + (1ull << sh) - 1) >> sh > PB_MAX_FINE) sh++;  // n <= 2^28: at most PG_MAX_SHIFT
     return sh;
 }
@@ -1150,7 +1150,7 @@ uint32_t pg_shift(uint64_t n) {
 // Bytes of the compact plan over `edges` resident edges of vertices below nv.
 uint64_t rg_bytes(const hytm_graph* g, uint64_t edges, uint64_t nv, uint32_t* shift, uint32_t* nfine, uint32_t* blocks,
                   uint32_t* seg) {
-    *shift = pg_shift(g->n);
+    *shift = std::min(pg_shift(g->n), 12u);  // beside the streamed pushes' workgroups
     while (*nfine = (uint32_t)((g->n + (1ull << *shift) - 1) >> *shift), *nfine > RG_MAX_FINE) ++*shift;
     *blocks = (uint32_t)((nv + 0xFFFF) >> 16);
     *seg = pb_seg_len(*nfine, edges);
@@ -1180,7 +1180,7 @@ uint32_t rg_partitions(const RunCtx& rc) {
         uint32_t shift, nfine, blocks, seg;
         return edges < UINT32_MAX && g->n <= (1ull << 26) &&  // bins of at most 2^13 sums
                rg_bytes(g, edges, g->pv[p], &shift, &nfine, &blocks, &seg) <= 16 * std::max<uint64_t>(g->n, 1ull << 20) &&
-               (sizeof(float) << shift) + 4 * (blocks + 1ull) <= RG_MAX_LDS;
+               (sizeof(double) << shift) + 4 * (blocks + 1ull) <= RG_MAX_LDS;
     };
     uint32_t lo = 0, hi = std::min(rc.plan.nres, g->npart) + 1;  // fits(lo), not fits(hi)
     while (hi - lo > 1) {
