@@ -137,7 +137,7 @@ inline uint32_t pr_acc_copies(bool pieces, uint64_t n) { return pieces ? 1u : n 
 // read-modify-writes.  Bucket sizes of a piece are the same in every PageRank iteration
 // (every vertex is active), so they are counted once.
 constexpr uint32_t PB_FINE_SHIFT = 14;
-constexpr uint32_t PB_FINE = 1u << PB_FINE_SHIFT;   // accumulator slots per fine bin (128 KB of LDS)
+constexpr uint32_t PB_FINE = 1u << PB_FINE_SHIFT;   // accumulator slots per fine bin (64 KB of LDS)
 constexpr uint32_t PB_MAX_FINE = 16384;             // fine bins (LDS histogram): n <= 2^28
 constexpr uint32_t PB_FINE_PER_COARSE = 32;
 // Fine bins of n vertices; the accumulation segment length for pieces of `pairs` (twice a

@@ -2446,9 +2446,13 @@ __global__ __launch_bounds__(PB_THREADS) void k_pb_scatter_a(const uint32_t* __r
     if (bad) atomicOr(err, 1u);
 }
 
-constexpr int PB_ACC_THREADS = 1024;
+constexpr int PB_ACC_THREADS = 512;
 constexpr uint32_t PB_ACC_BATCH = 8;  // pairs per thread with loads in flight together
 
+// FP32 sums, although the LDS adds FP64 ones ten times faster (k_pg_gather): a bin's FP64 sums
+// take 128 KB of LDS, and workgroups of that size wait for a CU that the edge streams beside
+// them have left (R-MAT 28 under 8 GB, 160 pieces: 2,709 ms with FP32 sums, 3,395 ms with FP64,
+// and the streams 3% slower).
 __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __restrict__ pv,
                                                              const float* __restrict__ pc,
                                                              const uint32_t* __restrict__ foff,
@@ -2457,7 +2461,8 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
                                                              uint64_t n, float* __restrict__ acc,
                                                              uint32_t* __restrict__ err) {
     constexpr uint32_t Q4 = PB_FINE / 4 / PB_ACC_THREADS;  // float4 slots per thread
-    extern __shared__ double s_a[];  // PB_FINE sums (FP64 adds: see k_pg_gather)
+    __shared__ float4 s_a4[PB_FINE / 4];
+    float* s_a = (float*)s_a4;
     const uint32_t s = blockIdx.x;
     if (s >= *nsegs) return;  // the same for every thread of the workgroup
     const uint32_t f = segs[2 * s], j = segs[2 * s + 1];
@@ -2466,7 +2471,7 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
     const uint32_t end = min(b1, start + seg);
     const bool multi = b1 - b0 > seg;
 #pragma unroll
-    for (uint32_t q = 0; q < 4 * Q4; q++) s_a[q * PB_ACC_THREADS + threadIdx.x] = 0.0;
+    for (uint32_t q = 0; q < Q4; q++) s_a4[q * PB_ACC_THREADS + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     bool bad = false;
     for (uint32_t i0 = start; i0 < end; i0 += PB_ACC_BATCH * PB_ACC_THREADS) {
@@ -2482,7 +2487,7 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
         for (uint32_t r = 0; r < PB_ACC_BATCH; r++) {
             if (i0 + r * PB_ACC_THREADS + threadIdx.x >= end) continue;
             if ((v[r] >> PB_FINE_SHIFT) == f && v[r] < n)
-                unsafeAtomicAdd(&s_a[acc_slot(v[r]) & (PB_FINE - 1)], (double)c[r]);
+                atomicAdd(&s_a[acc_slot(v[r]) & (PB_FINE - 1)], c[r]);
             else
                 bad = true;
         }
@@ -2504,16 +2509,17 @@ __global__ __launch_bounds__(PB_ACC_THREADS) void k_pb_accum(const uint32_t* __r
         for (uint32_t q = 0; q < Q4; q++) {
             const uint32_t k = q * PB_ACC_THREADS + threadIdx.x;
             if (k < lim4) {
-                x[q].x += (float)s_a[4 * k];
-                x[q].y += (float)s_a[4 * k + 1];
-                x[q].z += (float)s_a[4 * k + 2];
-                x[q].w += (float)s_a[4 * k + 3];
+                const float4 y = s_a4[k];
+                x[q].x += y.x;
+                x[q].y += y.y;
+                x[q].z += y.z;
+                x[q].w += y.w;
                 a4[k] = x[q];
             }
         }
     } else {
         for (uint32_t q = threadIdx.x; q < lim4 * 4; q += PB_ACC_THREADS)
-            if (s_a[q] != 0.0) unsafeAtomicAdd(acc + base + q, (float)s_a[q]);
+            if (s_a[q] != 0.0f) unsafeAtomicAdd(acc + base + q, s_a[q]);
     }
 }
 
@@ -3183,23 +3189,37 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_fstream(const FTask* __re
             }
             __syncthreads();
             block_prefix_max_u16<8>(s_owner, cnt, s_wave);
-            bool ok[UNROLL];
-            uint32_t val[UNROLL];
-#pragma unroll
-            for (int r = 0; r < UNROLL; r++) {
+            auto edge = [&](int r, uint32_t& val) {
                 const uint64_t e = ((line0 + half + (uint64_t)LINE_HALVES * r) << ZC_LINE_SHIFT) + lane;
-                ok[r] = false;
-                val[r] = 0;
-                if (e >= ce0 && e < ce1) {
-                    const uint32_t q = (uint32_t)(e - ce0);
-                    const uint32_t k = s_owner[q];
-                    ok[r] = q >= s_s[k] && q < s_e[k];
-                    val[r] = s_val[k];
-                }
+                val = 0;
                 if (Op::weighted) wv[r] = pk_w(cv[r], wv[r], pk);
                 cv[r] = pk_v(cv[r], pk);
+                if (e < ce0 || e >= ce1) return false;
+                const uint32_t q = (uint32_t)(e - ce0);
+                const uint32_t k = s_owner[q];
+                val = s_val[k];
+                return q >= s_s[k] && q < s_e[k];
+            };
+            if constexpr (Op::steps) {
+                bool ok[UNROLL];
+                uint32_t val[UNROLL];
+#pragma unroll
+                for (int r = 0; r < UNROLL; r++) ok[r] = edge(r, val[r]);
+                push_batch<UNROLL>(op, ok, val, cv, wv);
+            } else {
+                // edge by edge: collecting them before the first add, as above, sent the adds
+                // in bursts and cost PageRank 2% beside the pieces (R-MAT 28 under 8 GB:
+                // 3,740 ms, 3,660 edge by edge)
+#pragma unroll
+                for (int r = 0; r < UNROLL; r++) {
+                    uint32_t val;
+                    const bool ok = edge(r, val);
+                    if constexpr (Op::wave)
+                        op.push_wave(ok, val, cv[r], wv[r]);
+                    else if (ok)
+                        op.push(val, cv[r], wv[r]);
+                }
             }
-            push_batch<UNROLL>(op, ok, val, cv, wv);
         }
         __syncthreads();
     }
@@ -3758,7 +3778,7 @@ hipError_t launch_pb_accum(const uint32_t* pv, const float* pc, const uint32_t* 
                            uint32_t* err, hipStream_t st) {
     if (!max_segs || !n) return hipSuccess;
     if (seg == 0) return hipErrorInvalidValue;
-    k_pb_accum<<<max_segs, PB_ACC_THREADS, sizeof(double) * PB_FINE, st>>>(pv, pc, foff, segs, nsegs, seg, n, acc, err);
+    k_pb_accum<<<max_segs, PB_ACC_THREADS, 0, st>>>(pv, pc, foff, segs, nsegs, seg, n, acc, err);
     return hipGetLastError();
 }
 
