@@ -1579,17 +1579,23 @@ __global__ void k_init_lanes(AlgoState s, LaneSources src, uint32_t* __restrict_
     if (blockIdx.x == 0 && threadIdx.x == 0 && s.overflow) s.overflow[0] = s.overflow[1] = 0;
 }
 
-// Lane extraction through LDS: a workgroup loads the rows of EX_V vertices with
-// coalesced reads (row pitch padded by one word against bank conflicts), then writes
-// each requested lane as a contiguous run of EX_V values.
-constexpr uint32_t EX_V = 64;
+// Lane extraction through LDS: a workgroup loads the rows of V vertices with coalesced
+// reads (row pitch padded by one word against bank conflicts), then writes each requested
+// lane as a contiguous run of V values.  Into host memory the link bounds it: 64 lanes of
+// 2^20 vertices in 4.81 ms, 55.8 GB/s, where extracting four lanes at a time into device
+// rows and copying those took 5.3 ms (a copy in flight holds up the extraction of the next
+// rows, 14 us on its own, to its end).  Rows of an odd length start in the middle of a
+// write: runs of 64 values then reach 49.2 GB/s, of 256 values 52.6; below EX_WIDE vertices
+// runs of 64 give the chip more workgroups (1,000 vertices: 13 us, 24 us in runs of 256).
+constexpr uint64_t EX_WIDE = 1ull << 15;
+template <uint32_t V>
 __global__ __launch_bounds__(256) void k_extract_lanes(const uint32_t* __restrict__ vals, uint64_t n,
                                                        uint32_t lshift, LaneSet set, uint32_t nsel, bool sub_base,
-                                                       const uint32_t* __restrict__ order,
-                                                       uint32_t* __restrict__ out) {
-    __shared__ uint32_t tile[EX_V * (MAX_LANES + 1)];
+                                                       const uint32_t* __restrict__ rank, LaneRows out) {
+    extern __shared__ uint32_t ex_tile[];  // V rows of pitch words
     __shared__ uint8_t s_lane[MAX_LANES];
     __shared__ uint32_t s_base[MAX_LANES];
+    __shared__ uint32_t* s_out[MAX_LANES];
     const uint32_t S = 1u << lshift, pitch = S + 1;
     if (threadIdx.x < MAX_LANES) {
         // k-th set lane of the mask, k = threadIdx.x
@@ -1599,21 +1605,25 @@ __global__ __launch_bounds__(256) void k_extract_lanes(const uint32_t* __restric
             const uint32_t l = __ffsll((unsigned long long)m) - 1;
             s_lane[threadIdx.x] = (uint8_t)l;
             s_base[threadIdx.x] = set.base[l];
+            s_out[threadIdx.x] = out.row[threadIdx.x];
         }
     }
-    for (uint64_t v0 = (uint64_t)blockIdx.x * EX_V; v0 < n; v0 += (uint64_t)gridDim.x * EX_V) {
-        const uint32_t nv = (uint32_t)(n - v0 < EX_V ? n - v0 : EX_V);
+    for (uint64_t v0 = (uint64_t)blockIdx.x * V; v0 < n; v0 += (uint64_t)gridDim.x * V) {
+        const uint32_t nv = (uint32_t)(n - v0 < V ? n - v0 : V);
         __syncthreads();
         const uint32_t cells = nv << lshift;
-        const uint32_t* src = vals + (v0 << lshift);
-        for (uint32_t c = threadIdx.x; c < cells; c += blockDim.x) tile[(c >> lshift) * pitch + (c & (S - 1))] = src[c];
+        for (uint32_t c = threadIdx.x; c < cells; c += blockDim.x) {
+            const uint32_t i = c >> lshift;
+            const uint64_t r = rank ? rank[v0 + i] : v0 + i;
+            ex_tile[i * pitch + (c & (S - 1))] = vals[(r << lshift) + (c & (S - 1))];
+        }
         __syncthreads();
-        for (uint32_t q = threadIdx.x; q < nsel * EX_V; q += blockDim.x) {
-            const uint32_t k = q / EX_V, i = q % EX_V;
+        for (uint32_t q = threadIdx.x; q < nsel * V; q += blockDim.x) {
+            const uint32_t k = q / V, i = q % V;
             if (i >= nv) continue;
-            uint32_t x = tile[i * pitch + s_lane[k]];
+            uint32_t x = ex_tile[i * pitch + s_lane[k]];
             if (sub_base && x != UNREACHED) x -= s_base[k];
-            out[(uint64_t)k * n + (order ? order[v0 + i] : v0 + i)] = x;
+            s_out[k][v0 + i] = x;
         }
     }
 }
@@ -3278,10 +3288,15 @@ hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_
 }
 
 hipError_t launch_extract_lanes(const uint32_t* vals, uint64_t n, uint32_t lshift, const LaneSet& set, bool sub_base,
-                                const uint32_t* order, uint32_t* out, hipStream_t st) {
+                                const uint32_t* rank, const LaneRows& out, hipStream_t st) {
     const uint32_t nsel = (uint32_t)__builtin_popcountll(set.mask);
     if (!n || !nsel || lshift > 6 || (set.mask >> 1 >> ((1u << lshift) - 1))) return n && nsel ? hipErrorInvalidValue : hipSuccess;
-    k_extract_lanes<<<grid_for(n, EX_V, 16384), 256, 0, st>>>(vals, n, lshift, set, nsel, sub_base, order, out);
+    const size_t row = sizeof(uint32_t) * ((1u << lshift) + 1);
+    if (n < EX_WIDE)
+        k_extract_lanes<64><<<grid_for(n, 64, 4096), 256, 64 * row, st>>>(vals, n, lshift, set, nsel, sub_base, rank, out);
+    else
+        k_extract_lanes<256><<<grid_for(n, 256, 4096), 256, 256 * row, st>>>(vals, n, lshift, set, nsel, sub_base, rank,
+                                                                             out);
     return hipGetLastError();
 }
 

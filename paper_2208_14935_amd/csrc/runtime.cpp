@@ -2200,43 +2200,80 @@ uint32_t lane_shift(uint32_t lanes) {
     return sh;
 }
 
-// Copy the lanes of `set` (values of n vertices each, in rows of 2^lshift) into
-// consecutive n-value rows of the host buffer `out`: the device rows' two halves of
-// EXTRACT_LANES / 2 lanes alternate, one being copied while the other is extracted.
+// The device's view of host memory [p, p + bytes) if all of it lies in one page-locked
+// allocation made for this device, else null.
+uint32_t* mapped_host(const hytm_graph* g, void* p, uint64_t bytes) {
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (((uintptr_t)p & 3) || hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeHost ||
+        !at.devicePointer || at.device != g->device ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)at.devicePointer) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const uint64_t at0 = (uint64_t)((char*)at.devicePointer - (char*)base);
+    return at0 <= size && bytes <= size - at0 ? (uint32_t*)at.devicePointer : nullptr;
+}
+
+// Copy the lanes in set.mask out of the interleaved values `vals` (n rows of 2^lshift), in
+// increasing lane order: lane k of them goes to the n values at outs[k].  Rows in page-locked
+// memory are written by the extraction itself; the others go through device rows, whose two
+// halves of EXTRACT_LANES / 2 lanes alternate, one being copied while the other is extracted.
 constexpr uint32_t EXTRACT_LANES = 8;
 void copy_lanes_out(hytm_graph* g, const uint32_t* vals, uint32_t lshift, const LaneSet& set, bool sub_base,
                     void* const* outs, hipStream_t main) {
     const uint64_t n = g->n;
-    g->d_xout.ensure(n * EXTRACT_LANES);
+    const uint32_t* rank = g->hub_sorted() ? g->d_rank.p : nullptr;
+    LaneSet direct = set;
+    LaneRows rows{};
+    void* staged[MAX_LANES];
+    uint32_t nd = 0, ns = 0, k = 0;
+    direct.mask = 0;
+    for (uint64_t m = set.mask; m; m &= m - 1, k++) {
+        uint32_t* r = mapped_host(g, outs[k], n * 4);
+        if (r) {
+            rows.row[nd++] = r;
+            direct.mask |= m & (~m + 1);
+        } else {
+            staged[ns++] = outs[k];
+        }
+    }
+    if (nd) HIP_CHECK(launch_extract_lanes(vals, n, lshift, direct, sub_base, rank, rows, main));
+    if (ns) g->d_xout.ensure(n * EXTRACT_LANES);
     constexpr uint32_t HALF = EXTRACT_LANES / 2;
-    uint64_t rest = set.mask;
-    uint32_t k = 0;
+    uint64_t rest = set.mask & ~direct.mask;
+    k = 0;
     for (uint32_t pass = 0; rest; pass++) {
         const uint32_t b = pass & 1;
         LaneSet part = set;
+        LaneRows half{};
         part.mask = 0;
-        for (uint32_t c = 0; c < HALF && rest; c++) {
+        uint32_t* at = g->d_xout.p + b * HALF * n;
+        uint32_t cnt = 0;
+        for (; cnt < HALF && rest; cnt++) {
             part.mask |= rest & (~rest + 1);
             rest &= rest - 1;
+            half.row[cnt] = at + cnt * n;
         }
-        uint32_t* rows = g->d_xout.p + b * HALF * n;
         if (pass >= 2) HIP_CHECK(hipStreamWaitEvent(main, g->ev_free[b], 0));  // copied out
-        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, g->hub_sorted() ? g->d_order.p : nullptr, rows,
-                                       main));
+        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, rank, half, main));
         HIP_CHECK(hipEventRecord(g->ev_copied[b], main));
         HIP_CHECK(hipStreamWaitEvent(g->s_copy, g->ev_copied[b], 0));
-        const uint32_t cnt = (uint32_t)__builtin_popcountll(part.mask);
         // rows that lie behind one another in the caller's memory go in one copy: copies of a
         // few MB stand 11 us apart, an eighth of their time
         for (uint32_t c = 0, c1; c < cnt; c = c1) {
-            for (c1 = c + 1; c1 < cnt && (char*)outs[k + c1] == (char*)outs[k + c] + (uint64_t)(c1 - c) * n * 4;) c1++;
-            HIP_CHECK(hipMemcpyAsync(outs[k + c], rows + (uint64_t)c * n, (uint64_t)(c1 - c) * n * 4,
+            for (c1 = c + 1;
+                 c1 < cnt && (char*)staged[k + c1] == (char*)staged[k + c] + (uint64_t)(c1 - c) * n * 4;)
+                c1++;
+            HIP_CHECK(hipMemcpyAsync(staged[k + c], at + (uint64_t)c * n, (uint64_t)(c1 - c) * n * 4,
                                      hipMemcpyDeviceToHost, g->s_copy));
         }
         HIP_CHECK(hipEventRecord(g->ev_free[b], g->s_copy));
         k += cnt;
     }
-    HIP_CHECK(hipStreamSynchronize(g->s_copy));
+    if (nd) HIP_CHECK(hipStreamSynchronize(main));
+    if (ns) HIP_CHECK(hipStreamSynchronize(g->s_copy));
 }
 
 // One run.  lanes == 0: single source `sources[0]` (BFS/SSSP) or none (CC/PR), values_out
