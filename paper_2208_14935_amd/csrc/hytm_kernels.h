@@ -24,7 +24,10 @@ constexpr int SEG_R = 0, SEG_F = 1, SEG_Z = 2, SEG_C = 3;
 enum Algo : int {
     ALGO_BFS = 0, ALGO_SSSP = 1, ALGO_CC = 2, ALGO_PR = 3, ALGO_MBFS = 4, ALGO_MSSSP = 5, ALGO_MPPR = 6,
     ALGO_BFS_RELAX = 7,
-    ALGO_CC_LINK = 8  // edges of a resident graph join their ends' trees (launch_push_edges only)
+    ALGO_CC_LINK = 8,  // edges of a resident graph join their ends' trees (launch_push_edges only)
+    ALGO_BFS_WIDE = 9,  // a BFS iteration that leaves its discoveries in the levels (LevelScan)
+    ALGO_SSSP_WIDE = 10,  // SSSP and components: an iteration that leaves its improved vertices
+    ALGO_CC_WIDE = 11     // in marks
 };
 constexpr uint32_t MAX_LANES = 64;
 
@@ -111,6 +114,8 @@ struct AlgoState {
     uint32_t link_grid;   // 0, or at most this many workgroups for the host-reading pushes
     uint32_t* far;        // SSSP with a bound: improved vertices at or above it wait here (bitmap)
     uint32_t bound;       // SSSP: distances below it join the next frontier; 0xFFFFFFFF = no bound
+    uint8_t* marks;       // SSSP, CC, wide iterations: vertices improved in this one hold its tag, a byte of 1..255
+    uint32_t tag;
 };
 
 // PageRank spreads its atomic adds over up to one accumulator copy per XCD (the die id,
@@ -249,6 +254,18 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStrea
 // p[0, np) and q[0, nq) in one launch.
 hipError_t launch_fill2_u32(uint32_t* p, uint64_t np, uint32_t* q, uint64_t nq, uint32_t value, hipStream_t st);
 
+// After a wide iteration (ALGO_..._WIDE) the frontier is not in its bitmap:
+// it is the vertices v with lvl[v] == level (BFS), or, lvl null, those with marks[v] == level.  The
+// statistics write its bitmap, cur, and add it to visited (or null).  cur null: the frontier
+// is in its bitmap already.  marks: a multiple of 64 bytes.
+struct LevelScan {
+    const uint32_t* lvl;
+    const uint8_t* marks;
+    uint32_t* cur;
+    uint32_t* visited;
+    uint64_t n;
+    uint32_t level;
+};
 // Partitions cut into units of at most 64 aligned windows of 64 vertices, in order: unit u
 // covers partition part[u]'s windows q[u] .. q[u] + 63; partition i's units are first[i] ..
 // first[i + 1).  multi: the partitions of several units; rec: one record per unit (those of
@@ -270,7 +287,7 @@ constexpr uint32_t UNIT_WINDOWS = 64;
 hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
                                const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
                                unsigned long long* lanes, const SelParams& sp, uint8_t* mode, uint32_t* nA,
-                               uint32_t* nF, uint64_t* Ea, uint64_t* K, hipStream_t st);
+                               uint32_t* nF, uint64_t* Ea, uint64_t* K, const LevelScan& ls, hipStream_t st);
 
 // Batched runs: initialise lane masks, lane values and the union frontier.
 hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_t* cur_union, uint32_t nwords,

@@ -253,13 +253,70 @@ __device__ __forceinline__ uint8_t engine_of(uint32_t i, uint64_t E, uint64_t c,
     return select_engine(E, c, ea, rq, sp);
 }
 
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
+// The bytes of a word that equal `tag`, one bit each.
+__device__ __forceinline__ uint64_t bytes_equal(uint64_t w, uint64_t tag) {
+    const uint64_t t = w ^ (tag * 0x0101010101010101ull), low = 0x7F7F7F7F7F7F7F7Full;
+    const uint64_t z = ~(((t & low) + low) | t | low);  // 0x80 in every zero byte of t
+    return ((z >> 7) * 0x0102040810204080ull) >> 56;
+}
+
+// Window q0 + lane of a unit's windows [q0, qe), its vertices of [vb, ve), as a wide iteration
+// left it (LevelScan).  Whole windows go into the frontier and visited bitmaps; a window that
+// two partitions share is written by the waves of both, with the same words.
+__device__ __forceinline__ uint64_t level_bits(const LevelScan& ls, uint32_t q0, uint32_t qe, uint32_t vb,
+                                               uint32_t ve, uint32_t nwords) {
+    constexpr uint32_t G = 16;  // windows with their loads in flight together
+    const uint32_t lane = threadIdx.x & 63;
+    uint64_t bits = 0;
+    if (ls.lvl) {  // uniform
+        for (uint32_t q = q0; q < qe; q += G) {
+            uint32_t x[G];
+#pragma unroll
+            for (uint32_t r = 0; r < G; r++) {
+                const uint64_t v = ((uint64_t)(q + r) << 6) + lane;
+                x[r] = q + r < qe && v < ls.n ? ls.lvl[v] : UNREACHED;
+            }
+#pragma unroll
+            for (uint32_t r = 0; r < G; r++) {
+                const uint64_t b = __ballot(x[r] == ls.level);
+                if (q + r - q0 == lane) bits = b;
+            }
+        }
+    } else if (q0 + lane < qe) {
+        const u64x2* m = (const u64x2*)(ls.marks + ((uint64_t)(q0 + lane) << 6));
+        u64x2 x[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) x[r] = m[r];
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+            bits |= (bytes_equal(x[r].x, ls.level) | bytes_equal(x[r].y, ls.level) << 8) << (16 * r);
+    }
+    if (q0 + lane >= qe) return 0;
+    const uint32_t w = 2 * (q0 + lane), lo = (uint32_t)bits, hi = (uint32_t)(bits >> 32);
+    ls.cur[w] = lo;
+    if (w + 1 < nwords) ls.cur[w + 1] = hi;
+    if (ls.visited) {
+        if (lo) ls.visited[w] |= lo;
+        if (hi) ls.visited[w + 1] |= hi;
+    }
+    const uint32_t v0 = (q0 + lane) << 6;
+    if (v0 < vb) bits &= ~0ull << (vb - v0);
+    if (ve - v0 < 64) bits &= (1ull << (ve - v0)) - 1ull;
+    return bits;
+}
+
 // The record of unit u, taken by a whole wave (the same in every lane).  clear (or null): a
 // bitmap of nwords words zeroed along the way (the frontier after next).  mcur (or null): *lm
 // gains the lane masks of the active vertices.
+// SCAN: the frontier is not in cur yet but the vertices at level ls.level (ls).
+template <bool SCAN>
 __device__ __forceinline__ UnitRec unit_record(const Units& un, uint32_t u, const uint32_t* __restrict__ pv,
                                                const uint64_t* __restrict__ off, const uint32_t* __restrict__ cur,
                                                uint32_t* __restrict__ clear, uint32_t nwords,
-                                               const uint64_t* __restrict__ mcur, const SelParams& sp, uint64_t* lm) {
+                                               const uint64_t* __restrict__ mcur, const SelParams& sp,
+                                               const LevelScan& ls, uint64_t* lm) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t i = un.part[u], q0 = un.q[u];
     const uint32_t vb = pv[i], ve = pv[i + 1];
@@ -267,7 +324,11 @@ __device__ __forceinline__ UnitRec unit_record(const Units& un, uint32_t u, cons
     // request lines matter where the cost model decides, kernel lines to zero-copy
     const bool lines = i >= sp.nres && (!sp.force || sp.force == P_ZC);
     SelAcc a;
-    const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
+    uint64_t wbits;
+    if constexpr (SCAN)
+        wbits = level_bits(ls, q0, qe, vb, ve, nwords);
+    else
+        wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
     if (clear && q0 + lane < qe) {  // windows shared by two partitions are zeroed by both
         const uint32_t w = 2 * (q0 + lane);
         clear[w] = 0;
@@ -309,6 +370,7 @@ __device__ __forceinline__ UnitRec unit_record(const Units& un, uint32_t u, cons
 }
 
 // lanes: *lanes |= the lane masks of the active vertices (with mcur).
+template <bool SCAN>
 __global__ __launch_bounds__(256) void k_unit_stats(Units un, const uint32_t* __restrict__ pv,
                                                     const uint64_t* __restrict__ off,
                                                     const uint32_t* __restrict__ cur, uint32_t* __restrict__ clear,
@@ -316,12 +378,12 @@ __global__ __launch_bounds__(256) void k_unit_stats(Units un, const uint32_t* __
                                                     unsigned long long* __restrict__ lanes, SelParams sp,
                                                     uint8_t* __restrict__ mode, uint32_t* __restrict__ nA,
                                                     uint32_t* __restrict__ nF, uint64_t* __restrict__ Ea,
-                                                    uint64_t* __restrict__ K) {
+                                                    uint64_t* __restrict__ K, LevelScan ls) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wpb = blockDim.x >> 6, waves = gridDim.x * wpb;
     for (uint32_t u = blockIdx.x * wpb + (threadIdx.x >> 6); u < un.count; u += waves) {
         uint64_t lm = 0;
-        const UnitRec r = unit_record(un, u, pv, off, cur, clear, nwords, mcur, sp, &lm);
+        const UnitRec r = unit_record<SCAN>(un, u, pv, off, cur, clear, nwords, mcur, sp, ls, &lm);
         if (lane != 0) continue;
         if (lm && (lm & ~(uint64_t)*lanes)) atomicOr(lanes, (unsigned long long)lm);
         const uint32_t i = un.part[u];
@@ -830,7 +892,7 @@ __global__ __launch_bounds__(1024) void k_select_small(uint32_t npart, Units un,
     __syncthreads();
     for (uint32_t u = wid; u < un.count; u += 16) {
         uint64_t lm = 0;
-        const UnitRec r = unit_record(un, u, pv, off, cur, clear, nwords, mcur, sp, &lm);
+        const UnitRec r = unit_record<false>(un, u, pv, off, cur, clear, nwords, mcur, sp, LevelScan{}, &lm);
         if (lane == 0) {
             s_rec[u] = r;
             if (lm) atomicOr(&s_lanes, (unsigned long long)lm);
@@ -946,6 +1008,27 @@ struct OpBfs {
     }
 };
 
+// A wide iteration's BFS: discoveries are plain stores of the level (every thread that finds v
+// undiscovered stores the same one), and the next selection takes the frontier from the
+// levels.  OpBfs is bound by its two atomics per discovery, which go past the L2 to bitmaps
+// with few hot lines, about 10 G/s (random ones 27): R-MAT 22, 14M and 49M active edges with
+// 2.4M and 1.4M atomic requests, 324 and 518 us; the whole traversal 1.55 -> 1.06 ms.
+struct OpBfsWide {
+    static constexpr bool steps = true;
+    static constexpr bool weighted = false;
+    const uint32_t* visited;  // as of the iteration's start
+    uint32_t* lvl;
+    uint32_t level_next;
+    __device__ __forceinline__ uint32_t src(uint32_t) const { return 0; }
+    __device__ __forceinline__ uint32_t probe(uint32_t v) const { return visited[v >> 5]; }
+    __device__ __forceinline__ bool want(uint32_t, uint32_t v, uint32_t, uint32_t p) const { return !((p >> (v & 31)) & 1); }
+    __device__ __forceinline__ uint32_t update(uint32_t, uint32_t v, uint32_t) const {
+        lvl[v] = level_next;
+        return 0;
+    }
+    __device__ __forceinline__ void mark(uint32_t, uint32_t, uint32_t, uint32_t) const {}
+};
+
 struct OpSssp {
     static constexpr bool steps = true;
     static constexpr bool weighted = true;
@@ -970,6 +1053,15 @@ struct OpSssp {
     __device__ __forceinline__ void mark(uint32_t du, uint32_t v, uint32_t w, uint32_t old) const {
         const uint32_t nd = du + w;
         if (nd < old) mark_next(nd < bound ? next : far, v);
+    }
+};
+
+// A wide iteration's SSSP: improved vertices are marked by plain byte stores.
+struct OpSsspWide : OpSssp {
+    uint8_t* marks;
+    uint8_t tag;
+    __device__ __forceinline__ void mark(uint32_t du, uint32_t v, uint32_t w, uint32_t old) const {
+        if (du + w < old) marks[v] = tag;
     }
 };
 
@@ -1000,6 +1092,14 @@ struct OpCc {
     __device__ __forceinline__ uint32_t update(uint32_t lu, uint32_t v, uint32_t) const { return atomicMin(lab + v, lu); }
     __device__ __forceinline__ void mark(uint32_t lu, uint32_t v, uint32_t, uint32_t old) const {
         if (lu < old) mark_next(next, v);
+    }
+};
+
+struct OpCcWide : OpCc {
+    uint8_t* marks;
+    uint8_t tag;
+    __device__ __forceinline__ void mark(uint32_t lu, uint32_t v, uint32_t, uint32_t old) const {
+        if (lu < old) marks[v] = tag;
     }
 };
 
@@ -3477,10 +3577,13 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStrea
 hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,
                                const uint32_t* cur, uint32_t* clear, uint32_t nwords, const uint64_t* mcur,
                                unsigned long long* lanes, const SelParams& sp, uint8_t* mode, uint32_t* nA,
-                               uint32_t* nF, uint64_t* Ea, uint64_t* K, hipStream_t st) {
+                               uint32_t* nF, uint64_t* Ea, uint64_t* K, const LevelScan& ls, hipStream_t st) {
     if (!npart) return hipSuccess;
-    k_unit_stats<<<grid_for(un.count, 4, GRID_CAP), 256, 0, st>>>(un, pv, off, cur, clear, nwords, mcur, lanes, sp,
-                                                                  mode, nA, nF, Ea, K);
+    const unsigned g = grid_for(un.count, 4, GRID_CAP);
+    if (ls.cur)
+        k_unit_stats<true><<<g, 256, 0, st>>>(un, pv, off, cur, clear, nwords, mcur, lanes, sp, mode, nA, nF, Ea, K, ls);
+    else
+        k_unit_stats<false><<<g, 256, 0, st>>>(un, pv, off, cur, clear, nwords, mcur, lanes, sp, mode, nA, nF, Ea, K, ls);
     if (un.multis)
         k_part_combine<<<(un.multis + 3) / 4, 256, 0, st>>>(un, pv, off, sp, mode, nA, nF, Ea, K);
     return hipGetLastError();
@@ -3561,9 +3664,18 @@ hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uin
     case ALGO_BFS:
         return push_edges_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
                              off, col, w, shift, compacted, s.pk, st);
+    case ALGO_BFS_WIDE:
+        return push_edges_op(OpBfsWide{s.visited, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, shift, compacted, s.pk, st);
     case ALGO_SSSP:
         return push_edges_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w,
                              shift, compacted, s.pk, st);
+    case ALGO_SSSP_WIDE:
+        return push_edges_op(OpSsspWide{{s.val, s.next, s.overflow, s.far, s.bound}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, shift, compacted, s.pk, st);
+    case ALGO_CC_WIDE:
+        return push_edges_op(OpCcWide{{s.val, s.next}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, shift, compacted, s.pk, st);
     case ALGO_CC:
         return push_edges_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
                              compacted, s.pk, st);
@@ -3606,8 +3718,17 @@ hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uin
     case ALGO_BFS:
         return push_lines_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
                              off, col, w, distinct, s.pk, st);
+    case ALGO_BFS_WIDE:
+        return push_lines_op(OpBfsWide{s.visited, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, distinct, s.pk, st);
     case ALGO_SSSP:
         return push_lines_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
+    case ALGO_SSSP_WIDE:
+        return push_lines_op(OpSsspWide{{s.val, s.next, s.overflow, s.far, s.bound}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, distinct, s.pk, st);
+    case ALGO_CC_WIDE:
+        return push_lines_op(OpCcWide{{s.val, s.next}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
+                             off, col, w, distinct, s.pk, st);
     case ALGO_CC:
         return push_lines_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_BFS_RELAX:
@@ -3815,8 +3936,17 @@ hipError_t launch_push_fstream(const AlgoState& s, const FTask* tasks, uint32_t 
     case ALGO_BFS:
         return push_fstream_op(OpBfs{s.visited, s.next, s.val, s.level_next}, tasks, ntasks, total_chunks, list,
                                off, col, w, s.pk, st);
+    case ALGO_BFS_WIDE:
+        return push_fstream_op(OpBfsWide{s.visited, s.val, s.level_next}, tasks, ntasks, total_chunks, list, off, col, w,
+                               s.pk, st);
     case ALGO_SSSP:
         return push_fstream_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, tasks, ntasks, total_chunks, list, off, col, w, s.pk, st);
+    case ALGO_SSSP_WIDE:
+        return push_fstream_op(OpSsspWide{{s.val, s.next, s.overflow, s.far, s.bound}, s.marks, (uint8_t)s.tag}, tasks, ntasks, total_chunks, list, off, col,
+                               w, s.pk, st);
+    case ALGO_CC_WIDE:
+        return push_fstream_op(OpCcWide{{s.val, s.next}, s.marks, (uint8_t)s.tag}, tasks, ntasks, total_chunks, list, off, col,
+                               w, s.pk, st);
     case ALGO_CC:
         return push_fstream_op(OpCc{s.val, s.next}, tasks, ntasks, total_chunks, list, off, col, w, s.pk, st);
     case ALGO_BFS_RELAX:
