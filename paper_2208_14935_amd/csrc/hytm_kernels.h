@@ -27,7 +27,8 @@ enum Algo : int {
     ALGO_CC_LINK = 8,  // edges of a resident graph join their ends' trees (launch_push_edges only)
     ALGO_BFS_WIDE = 9,  // a BFS iteration that leaves its discoveries in the levels (LevelScan)
     ALGO_SSSP_WIDE = 10,  // SSSP and components: an iteration that leaves its improved vertices
-    ALGO_CC_WIDE = 11     // in marks
+    ALGO_CC_WIDE = 11,    // in marks
+    ALGO_MBFS_WIDE = 12   // batched BFS: an iteration that leaves the gained lanes in mnext only
 };
 constexpr uint32_t MAX_LANES = 64;
 
@@ -297,6 +298,9 @@ hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_
 // values; with sub_base, a value other than UNREACHED has the lane's base subtracted (BFS
 // levels of lanes that joined late).  rank (or null): position v of a row takes the value of
 // vertex rank[v] (back to the caller's ids).
+// The end of an iteration of ALGO_MBFS_WIDE: levels, reached lanes and the next bitmap (nwords
+// words, all written) from the gained lanes in mnext.
+hipError_t launch_settle_lanes(const AlgoState& s, uint32_t nwords, hipStream_t st);
 struct LaneRows {
     uint32_t* row[MAX_LANES];
 };

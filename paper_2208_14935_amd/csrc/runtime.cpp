@@ -1387,12 +1387,14 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
         rc.rg_wa = p < npart ? g->h_wbase.p[p] : h.seg_work_start[SEG_R] + h.seg_work_total[SEG_R];
     }
     if (select_only) return HYTM_OK;
-    if (g->nunits > SMALL_UNITS && (as.visited || as.marks)) {  // a wide iteration?
+    if (g->nunits > SMALL_UNITS && (as.visited || as.marks || as.mvisited)) {  // a wide iteration?
         uint64_t edges = 0;
         for (int s = 0; s < NSEG; s++) edges += h.seg_edges[s];
         const bool wide = edges >= g->n / kWide;
         if (as.visited) {
             as.algo = wide ? ALGO_BFS_WIDE : ALGO_BFS;
+        } else if (as.mvisited) {
+            as.algo = wide ? ALGO_MBFS_WIDE : ALGO_MBFS;
         } else {
             as.algo = rc.algo == HYTM_SSSP ? (wide ? ALGO_SSSP_WIDE : ALGO_SSSP) : (wide ? ALGO_CC_WIDE : ALGO_CC);
             if (wide && as.tag++ % 255 == 0) {
@@ -2106,6 +2108,10 @@ hytm_status step_once(RunCtx& rc, hipStream_t main, uint64_t* lanes_out, bool* e
             HIP_CHECK(kt.run(HYTM_K_OTHER, 1, main, [&] {
                 return launch_ppr_restart(as, rc.ppr, rc.ppr_scaled ? 0.f : restart, main);
             }));
+        }
+        if (as.algo == ALGO_MBFS_WIDE) {
+            HIP_CHECK(kt.run(HYTM_K_OTHER, n, main, [&] { return launch_settle_lanes(as, rc.nwords, main); }));
+            as.algo = ALGO_MBFS;
         }
         if (rc.spare) {  // cleared by this iteration's selection
             uint32_t* done = rc.cur;

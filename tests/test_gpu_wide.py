@@ -76,3 +76,23 @@ def test_wide_components(n, m, pe):
         g.set_resident_fraction("cc", 0.4)
         r = g.run("cc")
     assert np.array_equal(r.values, oracle.cc(soff, scol)[0])
+
+
+@pytest.mark.parametrize("resident", [1.0, 0.3])
+@pytest.mark.parametrize("lanes", [1, 2, 7, 33, 64])
+def test_wide_batches(lanes, resident):
+    n = 70_001
+    off, col = gen.er(n, 500_000, seed=4)
+    srcs = gen.sources(off, lanes, 11)
+    with hy.Graph(off, col) as g:
+        g.set_params(partition_edges=1000)
+        g.set_resident_fraction("bfs", resident)
+        vals, its, _ = g.run_batch("bfs", srcs)
+        with hy.Server(g, bfs=8, sssp=0, ppr=0) as srv:  # lanes that join at different iterations
+            qs = [srv.submit("bfs", int(s)) for s in srcs]
+            for q in qs:
+                srv.wait(q)
+    for i, s in enumerate(srcs):
+        lvl, it = oracle.bfs(off, col, int(s))
+        assert np.array_equal(vals[i], lvl) and its[i] == it
+        assert np.array_equal(qs[i].values, lvl) and qs[i].result["iterations"] == it
