@@ -267,8 +267,8 @@ struct LevelScan {
     uint64_t n;
     uint32_t level;
 };
-// Partitions cut into units of at most 64 aligned windows of 64 vertices, in order: unit u
-// covers partition part[u]'s windows q[u] .. q[u] + 63; partition i's units are first[i] ..
+// Partitions cut into units of at most `windows` (a power of two, <= 64) aligned windows of 64
+// vertices, in order: unit u covers partition part[u]'s windows from q[u] on; partition i's units are first[i] ..
 // first[i + 1).  multi: the partitions of several units; rec: one record per unit (those of
 // the other partitions are not used).
 struct UnitRec {
@@ -278,11 +278,11 @@ struct UnitRec {
     uint64_t first, last, first_w, last_w;  // (line + 1) of the first and last line, 0 = none
 };
 struct Units {
-    uint32_t count, multis;
+    uint32_t count, multis, windows;
     const uint32_t *part, *q, *first, *multi;
     UnitRec* rec;
 };
-constexpr uint32_t UNIT_WINDOWS = 64;
+constexpr uint32_t UNIT_WINDOWS = 64, UNIT_WINDOWS_MIN = 8, UNITS_WANTED = 2048;
 // Statistics and engine of every partition.  clear (or null): nwords words to zero; mcur and
 // lanes (or null): *lanes |= the lane masks of the active vertices.
 hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* pv, const uint64_t* off,

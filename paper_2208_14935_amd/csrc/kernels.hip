@@ -1,7 +1,7 @@
 // Device side of the hybrid-transfer traversal, written for gfx950 (wave64).
 //
 // Per iteration (Sec. 4 overview, Algorithm 1):
-//   k_unit_stats    one wave per run of at most 4,096 vertices of a partition: active vertices,
+//   k_unit_stats    one wave per unit (512 to 4,096 vertices) of a partition: active vertices,
 //                   active edges and request lines from the frontier bitmap, then (in
 //                   k_part_combine for partitions of several runs) the engine choice of
 //                   Sec. 5.1 (Eq. 1-3, alpha/beta rule) in exact integer arithmetic;
@@ -322,7 +322,7 @@ __device__ __forceinline__ UnitRec unit_record(const Units& un, uint32_t u, cons
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t i = un.part[u], q0 = un.q[u];
     const uint32_t vb = pv[i], ve = pv[i + 1];
-    const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+    const uint32_t qe = min(q0 + un.windows, (ve + 63) >> 6);
     // request lines matter where the cost model decides, kernel lines to zero-copy
     const bool lines = i >= sp.nres && (!sp.force || sp.force == P_ZC);
     SelAcc a;
@@ -835,7 +835,7 @@ __device__ __forceinline__ void unit_list(const Units& un, uint32_t u, uint32_t 
     const bool by_lines = m == P_ZC;
     const uint32_t i = un.part[u], q0 = un.q[u];
     const uint32_t vb = pv[i], ve = pv[i + 1];
-    const uint32_t qe = min(q0 + 64, (ve + 63) >> 6);
+    const uint32_t qe = min(q0 + un.windows, (ve + 63) >> 6);
     const uint64_t wbits = q0 + lane < qe ? window_bits(cur, q0 + lane, vb, ve) : 0ull;
     if (!__ballot(wbits != 0)) return;
     const uint32_t cnt = __popcll(wbits);

@@ -224,10 +224,10 @@ struct hytm_graph {
     // units of the partitions (see Units): part, q, first and multi behind one another
     DevBuf<uint32_t> d_units;
     DevBuf<UnitRec> d_unit_rec;
-    uint32_t nunits = 0, nmulti = 0;
+    uint32_t nunits = 0, nmulti = 0, unit_windows = 0;
     Units units() const {
         const uint32_t* p = d_units.p;
-        return Units{nunits, nmulti, p, p + nunits, p + 2 * (size_t)nunits, p + 2 * (size_t)nunits + npart + 1, d_unit_rec.p};
+        return Units{nunits, nmulti, unit_windows, p, p + nunits, p + 2 * (size_t)nunits, p + 2 * (size_t)nunits + npart + 1, d_unit_rec.p};
     }
 
     // per-vertex / per-partition device state
@@ -413,16 +413,33 @@ void partition_graph(hytm_graph* g) {
     HIP_CHECK(hipMemcpy(g->d_pv.p, g->pv.data(), g->pv.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     g->res_valid = false;
     std::vector<uint32_t> part, q, first, multi;
-    for (uint32_t p = 0; p < g->npart; p++) {
-        first.push_back((uint32_t)part.size());
-        const uint32_t qe = (uint32_t)(((uint64_t)g->pv[p + 1] + 63) >> 6);
-        for (uint32_t w = g->pv[p] >> 6; w < qe; w += UNIT_WINDOWS) {
-            part.push_back(p);
-            q.push_back(w);
+    auto cut = [&](uint32_t windows) {
+        for (auto* v : {&part, &q, &first, &multi}) v->clear();
+        for (uint32_t p = 0; p < g->npart; p++) {
+            first.push_back((uint32_t)part.size());
+            const uint32_t qe = (uint32_t)(((uint64_t)g->pv[p + 1] + 63) >> 6);
+            for (uint32_t w = g->pv[p] >> 6; w < qe; w += windows) {
+                part.push_back(p);
+                q.push_back(w);
+            }
+            if (part.size() - first[p] > 1) multi.push_back(p);
         }
-        if (part.size() - first[p] > 1) multi.push_back(p);
+        first.push_back((uint32_t)part.size());
+        g->unit_windows = windows;
+    };
+    cut(UNIT_WINDOWS);
+    // A unit is a wave's work: on graphs that would have fewer than UNITS_WANTED of them they
+    // are cut smaller (one wave that takes 4,096 active vertices needs 20-60 us).  Measured with
+    // 64 / 32 / 16 / 8 / 4 windows: BFS of 2^22 vertices 1.17 / 1.13 / 1.15 / 1.20 / 1.28 ms, of 2^24
+    // 3.19 / 3.22 / 3.29 / 3.49 / 3.87, of 2^18 0.346 / 0.333 / 0.316 / 0.307 / 0.300; SSSP of 2.5M
+    // 1.55 / 1.52 / 1.49 / 1.54 / 1.62, of 100K 1.23 / 1.10 / 1.04 / 1.01 / 1.01; 37 lanes of SSSP of
+    // 2^18 3.92 / 3.84 / 3.75 / 3.67 / 3.72.
+    if (part.size() > SMALL_UNITS) {
+        uint32_t windows = UNIT_WINDOWS;
+        const uint64_t units = part.size();
+        while (windows > UNIT_WINDOWS_MIN && units * (UNIT_WINDOWS / windows) < UNITS_WANTED) windows /= 2;
+        if (windows < UNIT_WINDOWS) cut(windows);
     }
-    first.push_back((uint32_t)part.size());
     g->nunits = (uint32_t)part.size();
     g->nmulti = (uint32_t)multi.size();
     std::vector<uint32_t> all;
