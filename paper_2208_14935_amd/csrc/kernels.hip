@@ -2833,7 +2833,7 @@ __global__ __launch_bounds__(256) void k_in_scatter(const uint64_t* __restrict__
 // or of batched SSSP (the least distance over the active sources).  Two forms by the width
 // of a row, S = 2^LSH:
 //
-// Rows of 16 lanes and more (k_pull_runs): S threads take a run of IN_RUN consecutive
+// Rows of 16 lanes and more (k_pull_runs): S threads take a run of `run` consecutive
 // in-edges, S of them at a time: each thread loads one edge's source, destination and lane
 // mask, then all of them take the sources' rows, one lane per thread, IN_UNROLL rows in
 // flight, and hand the result over whenever the destination changes.  A destination inside
@@ -2845,9 +2845,17 @@ __global__ __launch_bounds__(256) void k_in_scatter(const uint64_t* __restrict__
 //
 // Bound by the gathered rows (a wave per vertex waited through six dependent loads for the
 // few edges of an average in-list).  Measured on R-MAT 20 with 64 PPR lanes: 16M rows of 256
-// bytes in 1.6 ms, 2.6 TB/s; the push's FP64 atomic adds took 10 ms.
-constexpr int IN_UNROLL = 8;
-constexpr uint32_t IN_RUN = 128;
+// bytes in 1.3 ms, 3.3 TB/s; the push's FP64 atomic adds took 10 ms.
+//
+// Four rows in flight per wave suffice with 8 waves on a SIMD, and more registers cost waves:
+// 37 lanes of SSSP on R-MAT 18 3.65 ms with eight, 3.34 with four.  Long runs cut fewer lists
+// (atomics), short ones give small graphs enough waves: with runs of 64 / 128 / 256 / 512 edges,
+// R-MAT 20 PPR 26.8 / 20.4 / 18.4 / 18.6 ms, uniform 2^18 with 64 SSSP lanes 12.6 / 8.2 / 7.3 / 7.0,
+// R-MAT 18 with 37 4.2 / 3.34 / 3.40 / 4.05, R-MAT 16 PPR 2.60 / 2.12 / 2.55 / 3.40, 70K vertices
+// with 17 lanes 1.38 / 1.59 / 2.26 / 3.52: a run is the longest power of two that gives
+// PULL_WAVES waves, at most IN_RUN_MAX and at least 64 and two rounds of its S threads.
+constexpr int IN_UNROLL = 4;
+constexpr uint32_t IN_RUN_MAX = 256, PULL_WAVES = 12288;
 
 // What a destination gathers: PPR sums in FP64 and the lanes that received a share, SSSP the
 // least candidate distance.
@@ -2922,21 +2930,21 @@ struct PullSssp {
 };
 
 template <int LSH, class P>
-__global__ __launch_bounds__(256) void k_pull_runs(AlgoState s, InLists in) {
+__global__ __launch_bounds__(256) void k_pull_runs(AlgoState s, InLists in, uint32_t run_len) {
     constexpr uint32_t S = 1u << LSH;
     const uint32_t lane = threadIdx.x & 63, ln = lane & (S - 1), g0 = lane & ~(S - 1);
     const uint64_t groups = (uint64_t)gridDim.x * (256u >> LSH);
-    const uint64_t runs = (in.m + IN_RUN - 1) / IN_RUN;
+    const uint64_t runs = (in.m + run_len - 1) / run_len;
     const uint64_t first = (blockIdx.x * 256ull + threadIdx.x) >> LSH;
     // whole waves stay together: a group past the last run goes through the loop with no edges
     for (uint64_t w0 = first - (lane >> LSH); w0 < runs; w0 += groups) {
         const uint64_t run = w0 + (lane >> LSH);
-        const uint64_t b = min(run * IN_RUN, in.m), e = min(b + IN_RUN, in.m);
+        const uint64_t b = min(run * run_len, in.m), e = min(b + run_len, in.m);
         uint32_t cur = UNREACHED;
         bool head = b > 0 && b < e && in.tdst[b - 1] == in.tdst[b];  // the first destination began earlier
         typename P::Acc acc = P::none();
         uint64_t got = 0;
-        for (uint32_t k = 0; k < IN_RUN; k += S) {
+        for (uint32_t k = 0; k < run_len; k += S) {
             const uint64_t i = b + k + ln;
             const bool ok = i < e;
             const uint32_t u = ok ? in.tsrc[i] : 0u, d = ok ? in.tdst[i] : UNREACHED;
@@ -3603,7 +3611,9 @@ template <class P>
 static hipError_t pull_op(const AlgoState& s, const InLists& in, hipStream_t st) {
     if (!in.nseg) return hipSuccess;
     const unsigned gs = grid_for(in.nseg, 16, GRID_CAP);
-    const unsigned gr = grid_for((in.m + IN_RUN - 1) / IN_RUN, 256u >> s.lshift, GRID_CAP);
+    uint32_t run = IN_RUN_MAX;
+    while (run > std::max(64u, 2u << s.lshift) && ((in.m / run) << s.lshift) / 64 < PULL_WAVES) run /= 2;
+    const unsigned gr = grid_for((in.m + run - 1) / run, 256u >> s.lshift, GRID_CAP);
     if constexpr (P::narrow) {
         if (s.lshift == 0) k_pull_segs<0, P><<<gs, 256, 0, st>>>(s, in);
         if (s.lshift == 1) k_pull_segs<1, P><<<gs, 256, 0, st>>>(s, in);
@@ -3612,9 +3622,9 @@ static hipError_t pull_op(const AlgoState& s, const InLists& in, hipStream_t st)
         if (s.lshift < 4) return hipGetLastError();
     }
     switch (s.lshift) {
-    case 4: k_pull_runs<4, P><<<gr, 256, 0, st>>>(s, in); break;
-    case 5: k_pull_runs<5, P><<<gr, 256, 0, st>>>(s, in); break;
-    case 6: k_pull_runs<6, P><<<gr, 256, 0, st>>>(s, in); break;
+    case 4: k_pull_runs<4, P><<<gr, 256, 0, st>>>(s, in, run); break;
+    case 5: k_pull_runs<5, P><<<gr, 256, 0, st>>>(s, in, run); break;
+    case 6: k_pull_runs<6, P><<<gr, 256, 0, st>>>(s, in, run); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
