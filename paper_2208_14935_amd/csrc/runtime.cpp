@@ -2476,8 +2476,12 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     }
     const bool components = algo == HYTM_CC && g->budget == UINT64_MAX && g->m > 0;  // nothing to reprocess either
     if (((algo == HYTM_SSSP && !near_far) || (algo == HYTM_CC && !components)) && !batched && !rc.reprocess) {
-        g->d_marks.ensure(mark_bytes(n));
-        as.marks = g->d_marks.p;
+        try {
+            g->d_marks.ensure(mark_bytes(n));
+            as.marks = g->d_marks.p;
+        } catch (const HipError& e) {  // no room: the run goes without wide iterations
+            if (e.status != HYTM_E_NOMEM) throw;
+        }
     }
     rc.cur = g->d_cur.p;
     rc.nxt = g->d_next.p;
