@@ -342,6 +342,16 @@ hytm_status hytm_graph_set_parts(hytm_graph *g, uint32_t count, const uint64_t *
    effect at the next run. */
 hytm_status hytm_set_device_budget(hytm_graph *g, uint64_t edge_bytes);
 
+/* Device memory that g may keep between calls for sorted forms of its edges, besides the
+   budget: PageRank's pairs sorted by destination (see pr_blocking) and, on a graph without a
+   budget, the in-edge lists that wide batched PPR and SSSP steps read (8 bytes per edge, 12
+   with weights, and 12 to 16 per vertex).  The first call that uses a form makes it; what does
+   not fit goes without, with the same results.  UINT64_MAX (the default): each form may take
+   half of the device memory free when it is made; 0: none.  What is kept beyond the new limit
+   is released at once.  A call on any handle that finds the device full has the forms of the
+   handles that no other call or server is using released and is made again. */
+hytm_status hytm_set_plan_limit(hytm_graph *g, uint64_t bytes);
+
 /* Bytes of the budget that the engines' buffers take for `algo` under the current
    parameters: filter = `streams` staging slots, each holding the largest combined task
    (max(combine_k * partition_edges, largest partition) edges); compaction = two chunk
@@ -449,7 +459,8 @@ typedef struct hytm_server hytm_server;
 typedef struct {
     uint32_t struct_size;      /* sizeof(hytm_server_config) */
     uint32_t lanes[3];         /* lanes of the BFS, SSSP and PPR groups: 0 (no group) or 1..64 */
-    uint64_t state_budget;     /* device bytes for lane state; 0 = no limit */
+    uint64_t state_budget;     /* device bytes for lane state, and for in-edge lists made while
+                                  serving (hytm_set_plan_limit) what it leaves; 0 = no limit */
     uint64_t max_pending;      /* queue bound; submit returns E_STATE when full (0 = no bound) */
 } hytm_server_config;
 

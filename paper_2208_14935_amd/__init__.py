@@ -120,6 +120,7 @@ _SIGNATURES = {
                                          ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_int,
                                          ctypes.POINTER(ctypes.c_void_p)]),
     "hytm_set_device_budget": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint64]),
+    "hytm_set_plan_limit": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint64]),
     "hytm_graph_set_parts": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p]),
     "hytm_hub_order": (ctypes.c_int, [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p, ctypes.c_uint32,
                                       ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_uint64)]),
@@ -328,6 +329,11 @@ class Graph:
     def set_budget(self, edge_bytes):
         """Device bytes for edge data (None = uncapped, every partition resident)."""
         _check(load().hytm_set_device_budget(self._h, UNCAPPED if edge_bytes is None else int(edge_bytes)))
+
+    def set_plan_limit(self, bytes_):
+        """Device bytes the graph may keep for sorted forms of its edges (None = half of the free
+        device memory each, 0 = none); see hytm_set_plan_limit."""
+        _check(load().hytm_set_plan_limit(self._h, UNCAPPED if bytes_ is None else int(bytes_)))
 
     def params(self) -> Params:
         p = Params()

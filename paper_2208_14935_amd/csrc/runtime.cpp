@@ -75,6 +75,17 @@ double now_ms() {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
+// Device memory that this thread's buffers may still take (hytm_test_device_room): what a test
+// sets to meet a full device without filling one.  UINT64_MAX = no such bound.
+thread_local uint64_t t_room = UINT64_MAX;
+
+// Free device memory, as far as a buffer may take it.
+uint64_t device_room() {
+    size_t room = 0, total = 0;
+    HIP_CHECK(hipMemGetInfo(&room, &total));
+    return std::min<uint64_t>(room, t_room);
+}
+
 // ------------------------------------------------------------ device buffer
 // Owns its allocation, or (view) points into another buffer's.
 template <class T>
@@ -85,7 +96,10 @@ struct DevBuf {
     void ensure(size_t count) {
         if (count <= n && p && owns) return;
         release();
-        HIP_CHECK(hipMalloc((void**)&p, std::max<size_t>(count, 1) * sizeof(T)));
+        const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+        if (bytes > t_room) HIP_CHECK(hipErrorOutOfMemory);
+        HIP_CHECK(hipMalloc((void**)&p, bytes));
+        if (t_room != UINT64_MAX) t_room -= bytes;
         n = count;
         owns = true;
     }
@@ -95,8 +109,12 @@ struct DevBuf {
         n = count;
         owns = false;
     }
+    uint64_t bytes() const { return p && owns ? std::max<size_t>(n, 1) * sizeof(T) : 0; }
     void release() {
-        if (p && owns) (void)hipFree(p);
+        if (p && owns) {
+            (void)hipFree(p);
+            if (t_room != UINT64_MAX) t_room += bytes();
+        }
         p = nullptr;
         n = 0;
         owns = true;
@@ -267,6 +285,12 @@ struct hytm_graph {
     DevBuf<uint32_t> d_pb_v[3];
     DevBuf<float> d_pb_c[3];
     DevBuf<uint32_t> d_pb_hist, d_pb_foff, d_pb_segs, d_pb_nsegs, d_pb_offa, d_pb_fcur, d_pb_err, d_pb_tj;
+    // The three sorted forms of the edges that follow are kept to save making them again.  A
+    // call on any handle that finds the device full has those of the others given back
+    // (spare_room), so only the holder of `call` touches them.
+    std::mutex call;                        // held by the call or the server at work on the handle
+    uint64_t keep_limit = UINT64_MAX;       // hytm_set_plan_limit
+
     // PageRank gather plan (graphs without a budget): every edge's (source, place) pair
     // sorted by destination bin within each piece; made by the first run that uses it and
     // kept while the graph stays without a budget (the edges never change)
@@ -673,6 +697,60 @@ void rg_release(hytm_graph* g) {
     for (auto* b : {&g->rg.pairs, &g->rg.foff, &g->rg.segs}) b->release();
 }
 
+// ----------------------------------------------- kept forms of the edges
+uint64_t kept_bytes(const hytm_graph* g) {
+    uint64_t b = g->pg.slot.bytes() + g->in.toff.bytes() + g->rg.start.bytes();
+    for (const auto* x : {&g->pg.src, &g->pg.foff, &g->pg.segs, &g->in.soff, &g->in.seg_v, &g->in.tsrc, &g->in.tdst,
+                          &g->in.tw, &g->rg.pairs, &g->rg.foff, &g->rg.segs})
+        b += x->bytes();
+    return b;
+}
+
+// Whether a form of `kept` bytes, made with `temps` bytes beside it, may be made: within the
+// caller's limit together with the others, and in at most half of the free memory, so that as
+// much stays free for later calls, other handles and other users of the device.
+bool may_keep(const hytm_graph* g, uint64_t kept, uint64_t temps) {
+    if (kept > g->keep_limit || kept_bytes(g) > g->keep_limit - kept) return false;
+    const uint64_t room = device_room();
+    return kept <= room / 2 && kept + temps + (64ull << 20) <= room;
+}
+
+bool give_back(hytm_graph* g) {
+    const bool held = kept_bytes(g) > 0;
+    pg_release(g);
+    in_release(g);
+    rg_release(g);
+    return held;
+}
+
+// The open handles.  Held while a handle joins or leaves and while spare_room is at work, which
+// only tries the other handles' `call` locks: nobody waits for one handle holding another.
+struct OpenGraphs {
+    std::mutex mu;
+    std::vector<hytm_graph*> graphs;
+};
+OpenGraphs& open_graphs() {
+    static OpenGraphs* o = new OpenGraphs;  // outlives handles closed at the process's end
+    return *o;
+}
+
+// A device found full: the forms kept by `own` (its `call` lock is held here; or null) and by
+// the handles on the device that no call or server is at work on are given back.  False when
+// there were none.
+bool spare_room(hytm_graph* own, int device) {
+    if (hipSetDevice(device) != hipSuccess) return false;
+    (void)hipDeviceSynchronize();  // the failed call may have left work that reads them
+    bool any = own && give_back(own);
+    OpenGraphs& o = open_graphs();
+    std::lock_guard<std::mutex> lk(o.mu);
+    for (hytm_graph* g : o.graphs) {
+        if (g == own || g->device != device || !g->call.try_lock()) continue;
+        any |= give_back(g);
+        g->call.unlock();
+    }
+    return any;
+}
+
 void release_all(hytm_graph* g) {
     if (g->s_copy) (void)hipDeviceSynchronize();
     g->d_units.release();
@@ -718,9 +796,7 @@ void release_all(hytm_graph* g) {
     for (auto* b : {&g->d_pb_hist, &g->d_pb_foff, &g->d_pb_segs, &g->d_pb_nsegs, &g->d_pb_offa, &g->d_pb_fcur,
                     &g->d_pb_err, &g->d_pb_tj})
         b->release();
-    pg_release(g);
-    in_release(g);
-    rg_release(g);
+    (void)give_back(g);
     for (uint32_t i = 0; i < kMaxSlots; i++) {
         g->d_slot_col[i].release();
         g->d_slot_w[i].release();
@@ -823,7 +899,9 @@ struct RunCtx {
     } replay;
     uint32_t last_ftasks = 0;                  // streaming filter tasks of the last pass
     uint64_t last_fchunks = 0;
+    bool keep = true;                          // sorted forms of the edges may be made, kept and used
     bool pull = false;                         // batched PPR / SSSP: dense steps may go over the in-edge lists
+    uint64_t pull_bytes = UINT64_MAX;          // ... which may take this much when they are made
     uint32_t rg_parts = 0;                     // PageRank: partitions whose edges go through the compact plan
     uint32_t rg_ja = 0;                        // ... and where the other resident ones start in the lists
     uint64_t rg_wa = 0;
@@ -1076,7 +1154,7 @@ void init_ctx(RunCtx& rc, hytm_graph* g, int algo, bool batched, const Plan& pl,
     rc.sp.allow_filter = pl.allow_filter || g->budget == UINT64_MAX;
     rc.sp.allow_compact = pl.allow_compact || g->budget == UINT64_MAX;
     rc.nwords = (uint32_t)((g->n + 31) / 32);
-    rc.pull = (algo == HYTM_PPR || (algo == HYTM_SSSP && batched)) && g->budget == UINT64_MAX && g->m > 0 &&
+    rc.pull = rc.keep && (algo == HYTM_PPR || (algo == HYTM_SSSP && batched)) && g->budget == UINT64_MAX && g->m > 0 &&
               in_max_segs(g->n, g->m) < UINT32_MAX;
     rc.as.n = g->n;
     rc.as.overflow = g->d_overflow.p;
@@ -1122,9 +1200,8 @@ bool in_ready(RunCtx& rc, hipStream_t main) {
         tot.release();
     };
     try {
-        size_t room = 0, total = 0;
-        HIP_CHECK(hipMemGetInfo(&room, &total));
-        if ((weights ? 12 : 8) * m + 16 * n + 4 * segs + 16 * in_tiles(n) + (64ull << 20) > room) {
+        const uint64_t kept = (weights ? 12 : 8) * m + 12 * (n + 1) + 4 * segs;
+        if (kept > rc.pull_bytes || !may_keep(g, kept, 4 * n + 16 * in_tiles(n))) {
             rc.pull = false;
             return false;
         }
@@ -1190,7 +1267,7 @@ uint64_t rg_bytes(const hytm_graph* g, uint64_t edges, uint64_t nv, uint32_t* sh
 // only: pr_blocking = 2 asks for the pieces.
 uint32_t rg_partitions(const RunCtx& rc) {
     const hytm_graph* g = rc.g;
-    if (rc.algo != HYTM_PAGERANK || rc.batched || g->budget == UINT64_MAX || g->params.pr_blocking != 1 ||
+    if (!rc.keep || rc.algo != HYTM_PAGERANK || rc.batched || g->budget == UINT64_MAX || g->params.pr_blocking != 1 ||
         g->params.mode == HYTM_MODE_COMPACT || g->params.filter_engine != HYTM_FILTER_STREAM ||
         pb_fine_bins(g->n) > PB_MAX_FINE)
         return 0;
@@ -1212,15 +1289,17 @@ uint32_t rg_partitions(const RunCtx& rc) {
     return g->h_off[g->pv[lo]] ? lo : 0;
 }
 
-// The compact plan of the run's resident edges, made on first use.
-void rg_build(RunCtx& rc, hipStream_t main) {
+// The compact plan of the run's resident edges, made on first use.  False when the device has
+// no room for it.
+bool rg_build(RunCtx& rc, hipStream_t main) {
     hytm_graph* g = rc.g;
     auto& rg = g->rg;
     const uint64_t nv = g->pv[rc.rg_parts], edges = g->h_off[nv];
-    if (rg.ok && rg.edges == edges) return;
+    if (rg.ok && rg.edges == edges) return true;
     rg_release(g);
-    rg_bytes(g, edges, nv, &rg.shift, &rg.nfine, &rg.blocks, &rg.seg);
+    const uint64_t kept = rg_bytes(g, edges, nv, &rg.shift, &rg.nfine, &rg.blocks, &rg.seg);
     const uint64_t keys = (uint64_t)rg.nfine * rg.blocks;
+    if (!may_keep(g, kept, 4 * (keys + rg.nfine + 2) + 16 * in_tiles(keys))) return false;
     struct Temps {
         DevBuf<uint32_t> cnt, hist, nsegs, err;
         DevBuf<uint64_t> tot;
@@ -1229,15 +1308,21 @@ void rg_build(RunCtx& rc, hipStream_t main) {
             tot.release();
         }
     } t;
-    rg.start.ensure(keys + 1);
-    rg.pairs.ensure((edges + 7) & ~uint64_t(7));
-    rg.foff.ensure(rg.nfine + 1);
-    rg.segs.ensure(2ull * pb_max_segs(rg.nfine, edges, rg.seg));
-    t.cnt.ensure(keys);
-    t.hist.ensure(rg.nfine);
-    t.nsegs.ensure(1);
-    t.err.ensure(1);
-    t.tot.ensure(2 * in_tiles(keys));
+    try {
+        rg.start.ensure(keys + 1);
+        rg.pairs.ensure((edges + 7) & ~uint64_t(7));
+        rg.foff.ensure(rg.nfine + 1);
+        rg.segs.ensure(2ull * pb_max_segs(rg.nfine, edges, rg.seg));
+        t.cnt.ensure(keys);
+        t.hist.ensure(rg.nfine);
+        t.nsegs.ensure(1);
+        t.err.ensure(1);
+        t.tot.ensure(2 * in_tiles(keys));
+    } catch (const HipError& e) {
+        rg_release(g);
+        if (e.status != HYTM_E_NOMEM) throw;
+        return false;
+    }
     HIP_CHECK(launch_fill_u32(t.err.p, 1, 0u, main));
     HIP_CHECK(g->timer.run(HYTM_K_OTHER, edges, main, [&] {
         return launch_rg_build(g->d_off.p, g->d_res_col.p, g->pk.mask, edges, nv, g->n, rg.shift, rg.nfine, rg.blocks,
@@ -1255,7 +1340,7 @@ void rg_build(RunCtx& rc, hipStream_t main) {
     }
     rg.nsegs = out[0];
     rg.edges = edges;
-    rg.ok = true;
+    return rg.ok = true;
 }
 
 // The push over the resident segment of a selection.
@@ -1879,7 +1964,7 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
 // iteration, remains for budgeted graphs: there device memory per edge is what is short.
 bool pg_eligible(const RunCtx& rc) {
     const hytm_graph* g = rc.g;
-    return pb_eligible(rc) && g->budget == UINT64_MAX;
+    return rc.keep && pb_eligible(rc) && g->budget == UINT64_MAX;
 }
 
 // Pairs per piece: pr_block_pairs if given, else four per vertex (a piece costs a
@@ -1919,11 +2004,9 @@ hytm_status pg_build(RunCtx& rc, const Header& h, hipStream_t main, bool* made) 
     const uint32_t keys_a = two ? pb_coarse_bins(nfine) : nfine;
     const uint32_t shift_a = two ? pg.shift + 5 : pg.shift, stride_a = two ? PB_FINE_PER_COARSE : 1;
     const uint64_t pad = (g->m + 7) & ~uint64_t(7);
-    size_t room = 0, total = 0;
-    HIP_CHECK(hipMemGetInfo(&room, &total));
-    const uint64_t need = 6 * pad + 4 * pg.cap * (two ? 4 : 2) + 8ull * np * (nfine + 2 * pg.max_segs) +
-                          4 * (pb_max_offa(keys_a) + tj + 2ull * nfine) + (64ull << 20);
-    if (need > room) return HYTM_OK;
+    const uint64_t kept = 6 * pad + 4ull * np * (nfine + 1 + 2ull * pg.max_segs);
+    if (!may_keep(g, kept, 4 * pg.cap * (two ? 4 : 2) + 4 * (pb_max_offa(keys_a) + tj + 2ull * nfine + np + 2)))
+        return HYTM_OK;
     try {
         pg.src.ensure(pad);
         pg.slot.ensure(pad);
@@ -2373,8 +2456,9 @@ uint64_t sssp_overflow_lanes(hytm_graph* g, const uint32_t* dist, uint32_t lshif
     return out;
 }
 
+// keep = false: without making or using the sorted forms of the edges.
 hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uint32_t lanes, void* values_out,
-                     uint32_t* iterations_out, hytm_run_stats* stats, void* hip_stream) {
+                     uint32_t* iterations_out, hytm_run_stats* stats, void* hip_stream, bool keep) {
     HIP_CHECK(hipSetDevice(g->device));
     ensure_streams(g);
     const double t_begin = now_ms();
@@ -2393,6 +2477,7 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     if (ps != HYTM_OK) return ps;
     if (stats) HIP_CHECK(launch_fill_u32((uint32_t*)g->d_zcl.p, 2, 0u, main));
     if (batched) HIP_CHECK(launch_fill_u32((uint32_t*)g->d_lanes.p, 2, 0u, main));
+    rc.keep = keep;
     init_ctx(rc, g, algo, batched, pl, stats);
     rc.pb_on = pb_eligible(rc);
     rc.pg_on = pg_eligible(rc);
@@ -2403,19 +2488,6 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
     }
     rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on || rc.rg_parts);
     if (algo == HYTM_PAGERANK) rc.as.acc_copies = pr_acc_copies(rc.pb_on, g->n);
-    if (rc.rg_parts) {
-        try {
-            rg_build(rc, main);
-        } catch (const HipError& e) {
-            if (e.status != HYTM_E_NOMEM) throw;
-            rg_release(g);  // no room for it: as without
-            rc.rg_parts = 0;
-            rc.pb_on = rc.rg_block;
-            rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on);
-            rc.as.acc_copies = pr_acc_copies(rc.pb_on, g->n);
-        }
-    }
-
     const uint64_t n = g->n;
     const uint32_t nwords = rc.nwords;
     const uint32_t lsh = batched ? lane_shift(lanes) : 0;
@@ -2457,6 +2529,15 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
         } else {
             g->d_lval.ensure(n << lsh);
         }
+    }
+    // the results' way out as well, before any sorted form of the edges takes its room
+    if (batched && !mapped_host(g, values_out, (uint64_t)lanes * n * 4)) g->d_xout.ensure(n * EXTRACT_LANES);
+    if (!batched && g->hub_sorted()) g->d_xout.ensure(n);
+    if (rc.rg_parts && !rg_build(rc, main)) {  // no room for it: as without
+        rc.rg_parts = 0;
+        rc.pb_on = rc.rg_block;
+        rc.sp.zc_tie = resolve_tie(g, algo, rc.pb_on);
+        rc.as.acc_copies = pr_acc_copies(rc.pb_on, n);
     }
 
     AlgoState& as = rc.as;
@@ -2566,7 +2647,6 @@ hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uin
         const uint32_t* src = pr_like ? (const uint32_t*)g->d_x.p : g->d_val.p;
         if (g->hub_sorted()) {
             // back to the caller's ids (CC: labels become the smallest original id)
-            g->d_xout.ensure(n);
             if (algo == HYTM_CC) {
                 g->d_minold.ensure(n);
                 HIP_CHECK(launch_cc_relabel(src, g->d_order.p, g->d_rank.p, n, g->d_minold.p, g->d_xout.p, main));
@@ -2631,6 +2711,16 @@ hytm_status guarded(F&& f) {
     } catch (const std::bad_alloc&) {
         return fail(HYTM_E_NOMEM, "host allocation failed");
     }
+}
+
+// A call f(keep) on g (its `call` lock is held): when it finds the device full, the sorted forms of
+// edges that the handles keep are given back and it is made again without.
+template <class F>
+hytm_status with_room(hytm_graph* g, F&& f) {
+    hytm_status st = guarded([&] { return f(true); });
+    if (st != HYTM_E_NOMEM || !spare_room(g, g->device)) return st;
+    g_err.clear();
+    return guarded([&] { return f(false); });
 }
 
 }  // namespace
@@ -2751,6 +2841,7 @@ void serve_loop(hytm_server* s) {
     hytm_graph* g = s->g;
     hipStream_t main = g->s_main;
     hytm_status st = HYTM_OK;
+    std::lock_guard<std::mutex> call(g->call);
     try {
         HIP_CHECK(hipSetDevice(g->device));
         for (;;) {
@@ -2870,7 +2961,16 @@ void serve_loop(hytm_server* s) {
     s->cv_done.notify_all();
 }
 
-hytm_status server_setup(hytm_server* s) {
+// Device bytes of a server's lane state: the groups' and the extraction's staging rows.
+uint64_t server_bytes(const hytm_graph* g, const hytm_server_config& cfg) {
+    static const int algos[3] = {HYTM_BFS, HYTM_SSSP, HYTM_PPR};
+    uint64_t b = g->n * EXTRACT_LANES * 4;
+    for (int k = 0; k < 3; k++)
+        if (cfg.lanes[k]) b += group_state_bytes(g->n, algos[k], cfg.lanes[k]);
+    return b;
+}
+
+hytm_status server_setup(hytm_server* s, bool keep) {
     hytm_graph* g = s->g;
     HIP_CHECK(hipSetDevice(g->device));
     ensure_streams(g);
@@ -2901,6 +3001,9 @@ hytm_status server_setup(hytm_server* s) {
         } else {
             gr.lval.ensure(n << gr.lshift);
         }
+        gr.rc.keep = keep;
+        // in-edge lists made while serving count against the server's memory
+        if (s->cfg.state_budget) gr.rc.pull_bytes = s->cfg.state_budget - server_bytes(g, s->cfg);
         init_ctx(gr.rc, g, gr.algo, true, pl, nullptr);
         AlgoState& as = gr.rc.as;
         as.algo = gr.algo == HYTM_BFS ? ALGO_MBFS : gr.algo == HYTM_SSSP ? ALGO_MSSSP : ALGO_MPPR;
@@ -2933,6 +3036,9 @@ hytm_status server_setup(hytm_server* s) {
 }  // namespace
 
 // =================================================================== C ABI
+static hytm_status create_graph(uint64_t n, uint64_t m, const void* offsets, uint32_t offset_bytes, const uint32_t* col,
+                                const uint32_t* weights, uint32_t flags, int hip_device, hytm_graph** out);
+
 extern "C" {
 
 void hytm_default_params(hytm_params* p) {
@@ -2974,6 +3080,31 @@ const char* hytm_last_error(void) { return g_err.c_str(); }
 hytm_status hytm_graph_create(uint64_t n, uint64_t m, const void* offsets, uint32_t offset_bytes, const uint32_t* col,
                               const uint32_t* weights, uint32_t flags, int hip_device, hytm_graph** out) {
     g_err.clear();
+    hytm_status st = create_graph(n, m, offsets, offset_bytes, col, weights, flags, hip_device, out);
+    if (st == HYTM_E_NOMEM && spare_room(nullptr, hip_device)) {
+        g_err.clear();
+        st = create_graph(n, m, offsets, offset_bytes, col, weights, flags, hip_device, out);
+    }
+    if (st != HYTM_OK) return st;
+    return guarded([&] {
+        OpenGraphs& o = open_graphs();
+        std::lock_guard<std::mutex> lk(o.mu);
+        try {
+            o.graphs.push_back(*out);
+        } catch (...) {
+            release_all(*out);
+            delete *out;
+            *out = nullptr;
+            throw;
+        }
+        return HYTM_OK;
+    });
+}
+
+}  // extern "C"
+
+static hytm_status create_graph(uint64_t n, uint64_t m, const void* offsets, uint32_t offset_bytes, const uint32_t* col,
+                                const uint32_t* weights, uint32_t flags, int hip_device, hytm_graph** out) {
     if (!out) return fail(HYTM_E_INVAL, "out is NULL");
     if (!offsets) return fail(HYTM_E_INVAL, "offsets is NULL");
     if (m > 0 && !col) return fail(HYTM_E_INVAL, "col is NULL");
@@ -3127,6 +3258,8 @@ hytm_status hytm_graph_create(uint64_t n, uint64_t m, const void* offsets, uint3
     return HYTM_OK;
 }
 
+extern "C" {
+
 hytm_status hytm_hub_order(uint64_t n, uint64_t m, const void* offsets, uint32_t offset_bytes, const uint32_t* col,
                            uint32_t* order_out, uint64_t* hubs_out) {
     g_err.clear();
@@ -3165,7 +3298,8 @@ hytm_status hytm_graph_set_parts(hytm_graph* g, uint32_t count, const uint64_t* 
         return fail(HYTM_E_INVAL, "vertex_bounds must run from 0 to n = %llu", (unsigned long long)g->n);
     for (uint32_t i = 0; i < count; i++)
         if (vertex_bounds[i + 1] <= vertex_bounds[i]) return fail(HYTM_E_INVAL, "graph %u has no vertices", i);
-    return guarded([&]() -> hytm_status {
+    std::lock_guard<std::mutex> call(g->call);
+    return with_room(g, [&](bool) -> hytm_status {
         // every edge must stay inside its graph (checked in the held order, mapped back)
         std::vector<uint32_t> order;
         if (g->hub_sorted()) {
@@ -3200,6 +3334,7 @@ hytm_status hytm_set_device_budget(hytm_graph* g, uint64_t edge_bytes) {
     g_err.clear();
     if (!g) return fail(HYTM_E_INVAL, "graph is NULL");
     if (g->server) return fail(HYTM_E_STATE, "a query server is open on this graph");
+    std::lock_guard<std::mutex> call(g->call);
     if (edge_bytes != g->budget) {
         g->res_valid = false;
         if (edge_bytes != UINT64_MAX && (g->pg.ok || g->in.ok)) {  // they are for graphs without a budget
@@ -3216,6 +3351,23 @@ hytm_status hytm_set_device_budget(hytm_graph* g, uint64_t edge_bytes) {
     return HYTM_OK;
 }
 
+hytm_status hytm_set_plan_limit(hytm_graph* g, uint64_t bytes) {
+    g_err.clear();
+    if (!g) return fail(HYTM_E_INVAL, "graph is NULL");
+    if (g->server) return fail(HYTM_E_STATE, "a query server is open on this graph");
+    std::lock_guard<std::mutex> call(g->call);
+    g->keep_limit = bytes;
+    if (kept_bytes(g) > bytes) {
+        (void)hipSetDevice(g->device);
+        (void)give_back(g);
+    }
+    return HYTM_OK;
+}
+
+// Not part of hytm.h: bounds what this thread's calls may still allocate on the device, so that a
+// test meets a full one.  UINT64_MAX lifts the bound.
+void hytm_test_device_room(uint64_t bytes) { t_room = bytes; }
+
 hytm_status hytm_set_params(hytm_graph* g, const hytm_params* p) {
     g_err.clear();
     if (!g) return fail(HYTM_E_INVAL, "graph is NULL");
@@ -3231,12 +3383,14 @@ hytm_status hytm_set_params(hytm_graph* g, const hytm_params* p) {
     if (!params_valid(np, &why)) return fail(HYTM_E_INVAL, "bad params: %s", why.c_str());
     const bool repart = np.partition_edges != g->params.partition_edges;
     g->params = np;
-    if (repart)
-        return guarded([&]() -> hytm_status {
+    if (repart) {
+        std::lock_guard<std::mutex> call(g->call);
+        return with_room(g, [&](bool) -> hytm_status {
             HIP_CHECK(hipSetDevice(g->device));
             partition_graph(g);
             return HYTM_OK;
         });
+    }
     // the resident cache stays valid: a run refills it only if its partition count or
     // edge arrays change under the new parameters
     return HYTM_OK;
@@ -3307,7 +3461,10 @@ hytm_status hytm_run(hytm_graph* g, hytm_algo algo, uint32_t source, void* value
         return fail(HYTM_E_INVAL, "pr_iterations must be > 0");
     // personalized PageRank runs as one lane of the batched form
     const uint32_t lanes = algo == HYTM_PPR ? 1 : 0;
-    return guarded([&] { return run_impl(g, algo, &source, lanes, values_out, iterations_out, stats, hip_stream); });
+    std::lock_guard<std::mutex> call(g->call);
+    return with_room(g, [&](bool keep) {
+        return run_impl(g, algo, &source, lanes, values_out, iterations_out, stats, hip_stream, keep);
+    });
 }
 
 hytm_status hytm_run_batch(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uint32_t nsources,
@@ -3325,8 +3482,10 @@ hytm_status hytm_run_batch(hytm_graph* g, hytm_algo algo, const uint32_t* source
         if (sources[l] >= g->n)
             return fail(HYTM_E_RANGE, "sources[%u] = %u >= n = %llu", l, sources[l], (unsigned long long)g->n);
     if (algo == HYTM_SSSP && !g->weighted) return fail(HYTM_E_INVAL, "SSSP needs edge weights");
-    return guarded(
-        [&] { return run_impl(g, algo, sources, nsources, values_out, iterations_out, stats, hip_stream); });
+    std::lock_guard<std::mutex> call(g->call);
+    return with_room(g, [&](bool keep) {
+        return run_impl(g, algo, sources, nsources, values_out, iterations_out, stats, hip_stream, keep);
+    });
 }
 
 hytm_status hytm_select_engines(hytm_graph* g, uint64_t npart, const uint64_t* E, const uint64_t* nA,
@@ -3341,7 +3500,8 @@ hytm_status hytm_select_engines(hytm_graph* g, uint64_t npart, const uint64_t* E
             (Ea[i] > 0 && nA[i] == 0))
             return fail(HYTM_E_INVAL, "partition %llu: statistics out of range", (unsigned long long)i);
     if (npart == 0) return HYTM_OK;
-    return guarded([&]() -> hytm_status {
+    std::lock_guard<std::mutex> call(g->call);
+    return with_room(g, [&](bool) -> hytm_status {
         HIP_CHECK(hipSetDevice(g->device));
         ensure_streams(g);
         SelParams sp = make_sel(g, edge_arrays);
@@ -3515,17 +3675,15 @@ hytm_status hytm_server_open(hytm_graph* g, const hytm_server_config* cfg, hytm_
     *out = nullptr;
     if (cfg->struct_size != sizeof(hytm_server_config)) return fail(HYTM_E_INVAL, "config.struct_size mismatch");
     if (g->server) return fail(HYTM_E_STATE, "a query server is already open on this graph");
-    static const hytm_algo algos[3] = {HYTM_BFS, HYTM_SSSP, HYTM_PPR};
-    uint64_t need = g->n * EXTRACT_LANES * 4;  // extraction staging
     uint32_t groups = 0;
     for (int k = 0; k < 3; k++) {
         if (cfg->lanes[k] > MAX_LANES) return fail(HYTM_E_INVAL, "lanes[%d] = %u exceeds 64", k, cfg->lanes[k]);
         if (!cfg->lanes[k]) continue;
         groups++;
-        need += group_state_bytes(g->n, algos[k], cfg->lanes[k]);
     }
     if (!groups) return fail(HYTM_E_INVAL, "no lane group: every lanes[] entry is 0");
     if (cfg->lanes[1] && !g->weighted) return fail(HYTM_E_INVAL, "an SSSP group needs edge weights");
+    const uint64_t need = server_bytes(g, *cfg);
     if (cfg->state_budget && need > cfg->state_budget)
         return fail(HYTM_E_BUDGET, "lane state needs %llu bytes, state_budget is %llu", (unsigned long long)need,
                     (unsigned long long)cfg->state_budget);
@@ -3533,10 +3691,13 @@ hytm_status hytm_server_open(hytm_graph* g, const hytm_server_config* cfg, hytm_
     if (!s) return fail(HYTM_E_NOMEM, "host allocation failed");
     s->g = g;
     s->cfg = *cfg;
-    hytm_status st = guarded([&] { return server_setup(s.get()); });
-    if (st != HYTM_OK) {
-        for (LaneGroup& gr : s->grp) gr.release();
-        return st;
+    {
+        std::lock_guard<std::mutex> call(g->call);
+        hytm_status st = with_room(g, [&](bool keep) { return server_setup(s.get(), keep); });
+        if (st != HYTM_OK) {
+            for (LaneGroup& gr : s->grp) gr.release();
+            return st;
+        }
     }
     g->server = s.get();
     s->worker = std::thread(serve_loop, s.get());
@@ -3623,6 +3784,11 @@ hytm_status hytm_graph_destroy(hytm_graph* g) {
     g_err.clear();
     if (!g) return HYTM_OK;
     if (g->server) return fail(HYTM_E_STATE, "close the query server on this graph first");
+    {
+        OpenGraphs& o = open_graphs();
+        std::lock_guard<std::mutex> lk(o.mu);
+        o.graphs.erase(std::find(o.graphs.begin(), o.graphs.end(), g));
+    }
     (void)hipSetDevice(g->device);
     release_all(g);
     delete g;
