@@ -1961,10 +1961,11 @@ hytm_status pb_pass(RunCtx& rc, hipStream_t main, hytm_iter_stats* rec, int64_t 
 // moves the same (source, destination) pairs, so they are sorted by destination bin once
 // (6 bytes per edge beside the resident edges) and an iteration only gathers and sums.  The
 // pieces path above, which writes, sorts and reads back 28 bytes per edge in every
-// iteration, remains for budgeted graphs: there device memory per edge is what is short.
+// iteration, remains for budgeted graphs, where device memory per edge is what is short, for a
+// device without room for the plan, and for pr_blocking = 2, which asks for it.
 bool pg_eligible(const RunCtx& rc) {
     const hytm_graph* g = rc.g;
-    return rc.keep && pb_eligible(rc) && g->budget == UINT64_MAX;
+    return rc.keep && g->params.pr_blocking == 1 && pb_eligible(rc) && g->budget == UINT64_MAX;
 }
 
 // Pairs per piece: pr_block_pairs if given, else four per vertex (a piece costs a

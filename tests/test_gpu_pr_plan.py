@@ -151,3 +151,20 @@ def test_compact_plan_of_wide_bins():
     with hy.Graph(off, col) as g:
         g.set_resident_fraction("pagerank", 0.4)
         check(g.run("pagerank"), want)
+
+
+def test_pieces_are_run_where_they_are_asked_for():
+    """pr_blocking = 2 sorts each piece anew in every iteration, also over a fully resident graph:
+    preparing and applying are launches of their own there, one pass over the kept plan."""
+    off, col = GRAPHS["rmat 16"]()
+    want = oracle.pagerank(off, col, 0.85, 20)
+    other, block = hy.KERNEL_CLASSES.index("other"), hy.KERNEL_CLASSES.index("pr_blocking")
+    with hy.Graph(off, col) as g:
+        g.set_params(pr_block_pairs=200_000)
+        for blocking in (1, 2):
+            g.set_params(pr_blocking=blocking)
+            g.run("pagerank")
+            res = g.run("pagerank", time_kernels=True)
+            check(res, want)
+            assert res.stats["kernel_launches"][block] >= 20 * 4
+            assert (res.stats["kernel_launches"][other] >= 40) == (blocking == 2)
