@@ -167,11 +167,11 @@ typedef struct {
                                    Streamed partitions keep their atomic adds (the host link delivers
                                    fewer edges per second than the atomics take).  1 (default): when at
                                    least 3/8 of the edges are resident; 2: whenever some are; 0: never.
-                                   With 1 the pairs are sorted once and kept with the graph instead,
-                                   whatever the resident share: every pair (6 bytes per edge) on a
-                                   graph without a budget, else as many as 16 bytes per vertex (at
-                                   least 16 MiB) hold, at 4 bytes each; the other resident edges
-                                   are added atomically.
+                                   With 1 the pairs are sorted once and kept with the graph instead
+                                   where that is the faster, whatever the resident share: every pair
+                                   (6 bytes per edge) on a graph without a budget, else as many as 16
+                                   bytes per vertex (at least 16 MiB) hold, at 4 bytes each; the other
+                                   resident edges are then added atomically.
                                    Applies to single PageRank runs with n <= 2^28 in the hybrid, filter
                                    (streaming engine) or zero-copy modes; the result is the same sum in
                                    another order.  Needs 16 bytes per pair of a piece of device memory

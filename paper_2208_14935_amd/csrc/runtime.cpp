@@ -1257,14 +1257,22 @@ uint64_t rg_bytes(const hytm_graph* g, uint64_t edges, uint64_t nv, uint32_t* sh
 // The compact plan.  A budgeted graph's resident edges compete with the streamed ones for the
 // atomic units (12-18 G adds/s, below what the link and the resident cache feed together), and
 // the sorting passes of the pieces compete for CUs; the plan takes the resident adds into LDS at
-// 4 bytes of pairs per edge.  20 iterations, atomic or pieces (automatic) -> plan: R-MAT 22 at
-// 25 / 35 / 50% resident 98 / 93 / 87 -> 78 / 71 / 68 ms, R-MAT 24 at 25 / 50% 338 / 302 -> 295 / 256,
-// uniform 3M vertices 64 / 52 -> 57 / 47 ms.
-// PageRank's resident edges of a budgeted graph go through the compact plan as far as it fits
-// the device memory that pr_blocking may take outside the budget (16 bytes per vertex, at
-// least 16 MiB): the longest prefix of the resident partitions whose plan does, the others are
-// pushed with atomic adds.  Returns that many partitions, 0 = no plan.  Automatic blocking
-// only: pr_blocking = 2 asks for the pieces.
+// 4 bytes of pairs per edge.  PageRank's resident edges of a budgeted graph go through it as far
+// as it fits the device memory that pr_blocking may take outside the budget (16 bytes per
+// vertex, at least 16 MiB): the longest prefix of the resident partitions whose plan does, the
+// others are pushed with atomic adds.  Returns that many partitions, 0 = no plan.  Automatic
+// blocking only: pr_blocking = 2 asks for the pieces.
+// Against atomic adds (less than 3/8 resident) it is the faster whatever it covers: 20
+// iterations of R-MAT 22 with 16 / 32 edges per vertex at 25% resident 98 -> 78 and 181 -> 151 ms, of
+// R-MAT 24 338 -> 295, of 2M uniform vertices with 16 / 24 per vertex at 40% 42.5 -> 35.8 and 59.8 -> 54.7.
+// Against the pieces, which take every resident edge, it has to cover kRgShare / 16 of them.
+// Pieces -> plan covering 100%: R-MAT 24 and 22 with 8 edges per vertex 146 -> 105 and 43 -> 30 ms,
+// uniform 2^24 and 3M 137 -> 109 and 25.6 -> 22.8; 63-70%: 102 -> 89, 34 -> 24, 105 -> 90, 17.8 -> 17.0;
+// 53-62% (16 per vertex): 259 -> 259, 68.3 -> 68.1, uniform 2^22 and 3M 62.5 -> 64.8 and 45.4 -> 46.9, R-MAT
+// 21 39.6 -> 42.1; 31-34%: 181 -> 228, 58.0 -> 61.9, 45.0 -> 56.2, 35.2 -> 41.5; 21%: R-MAT 22 88.9 -> 97.2,
+// uniform 64.3 -> 88.7.  Up to kRgSmall vertices a piece (at least 2^20 pairs) has few pairs per
+// sum and the plan wins at any share: R-MAT 20, 18 at 16-62% 1.14-3.2 times, uniform 1.02-1.7 (once 0.98).
+constexpr uint64_t kRgShare = 10, kRgSmall = 1ull << 20;
 uint32_t rg_partitions(const RunCtx& rc) {
     const hytm_graph* g = rc.g;
     if (!rc.keep || rc.algo != HYTM_PAGERANK || rc.batched || g->budget == UINT64_MAX || g->params.pr_blocking != 1 ||
@@ -1286,7 +1294,9 @@ uint32_t rg_partitions(const RunCtx& rc) {
         else
             hi = mid;
     }
-    return g->h_off[g->pv[lo]] ? lo : 0;
+    const uint64_t covered = g->h_off[g->pv[lo]], resident = g->h_off[g->pv[std::min(rc.plan.nres, g->npart)]];
+    if (rc.pb_on && g->n > kRgSmall && 16 * covered < kRgShare * resident) return 0;
+    return covered ? lo : 0;
 }
 
 // The compact plan of the run's resident edges, made on first use.  False when the device has

@@ -168,3 +168,19 @@ def test_pieces_are_run_where_they_are_asked_for():
             check(res, want)
             assert res.stats["kernel_launches"][block] >= 20 * 4
             assert (res.stats["kernel_launches"][other] >= 40) == (blocking == 2)
+
+
+@pytest.mark.parametrize("degree,planned", [(3, True), (12, False)])
+def test_plan_or_pieces_by_the_share_that_the_plan_covers(degree, planned):
+    """More than 3/8 resident: 16 bytes per vertex hold the pairs of every resident edge (2.1 per
+    vertex), which take one launch an iteration; or of half of them (8.4), which go in pieces."""
+    n = (1 << 20) + 3
+    off, col = gen.er(n, degree * n, seed=6)
+    want = oracle.pagerank(off, col, 0.85, 20)
+    with hy.Graph(off, col) as g:
+        g.set_params(pr_block_pairs=1 << 20)
+        g.set_resident_fraction("pagerank", 0.7)
+        res = g.run("pagerank", time_kernels=True)
+        check(res, want)
+        launches = res.stats["kernel_launches"][hy.KERNEL_CLASSES.index("pr_blocking")]
+        assert launches == 20 if planned else launches >= 20 * 8
