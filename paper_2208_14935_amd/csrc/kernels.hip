@@ -1191,7 +1191,6 @@ struct OpMBfs {
     }
 };
 
-// Batched SSSP: every lane active at u relaxes (u, v) in its own distance row.
 // A wide iteration's batched BFS: the lanes an edge may improve are added to mnext only; the
 // lanes reached, the levels and the frontier bitmap follow from it at the iteration's end
 // (k_settle_lanes).  OpMBfs updates a second mask and the bitmap atomically and stores a
@@ -1199,7 +1198,6 @@ struct OpMBfs {
 // iterations 547 and 413 us alone, 228 us and (beside a stream) 531 us here with 40 us each
 // to settle, the call 9.56 -> 9.42 ms of which the host link takes 7.7.
 struct OpMBfsWide : BatchOp {
-    static constexpr bool wave = false, steps = false;
     static constexpr bool weighted = false;
     const uint64_t* mcur;
     uint64_t* mnext;
@@ -1220,6 +1218,10 @@ struct OpMBfsWide : BatchOp {
             if (m[r] & ~seen[r]) atomicOr((unsigned long long*)(mnext + v[r]), (unsigned long long)(m[r] & ~seen[r]));
     }
 };
+
+// Batched SSSP: every lane active at u relaxes (u, v) in its own distance row.  WU: edges that a
+// thread of the wave form takes side by side.
+template <int WU>
 struct OpMSssp {
     static constexpr bool wave = true, steps = false;
     static constexpr bool weighted = true;
@@ -1261,7 +1263,6 @@ struct OpMSssp {
     // It pays when the rows are dense (a batch started together); when the wave's edges
     // carry fewer than a quarter row of active lanes on average (queries at different stages)
     // each thread relaxes its own edge's lanes.  Called by every thread of the wave.
-    static constexpr int WU = 4;
     __device__ __forceinline__ void push_wave(bool ok, uint32_t u, uint32_t v, uint32_t w) const {
         uint32_t active = ok ? (uint32_t)__popcll(mcur[u]) : 0u;
 #pragma unroll
@@ -3375,24 +3376,24 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_fstream(const FTask* __re
                 val = s_val[k];
                 return q >= s_s[k] && q < s_e[k];
             };
-            if constexpr (Op::steps || std::is_base_of<BatchOp, Op>::value) {
+            // The thread's edges are collected and then pushed; batched SSSP takes one edge at a
+            // time through its wave form (OpMSssp<1>), since the pushes beside it already fill
+            // the memory system: 64 lanes of 2^20 vertices at 25% resident, uniform 16M / R-MAT
+            // 16M edges 50.9 / 20.2 ms, four at a time 51.6 / 20.8; found and pushed edge by edge
+            // 54.9 / 21.9 and 55.6 / 22.2.  PageRank's adds alone are issued edge by edge:
+            // collected they went out in bursts and cost 2% beside the pieces (R-MAT 28 under
+            // 8 GB: 3,740 ms, 3,660 edge by edge).
+            if constexpr (!std::is_same<Op, OpPr>::value) {
                 bool ok[UNROLL];
                 uint32_t val[UNROLL];
 #pragma unroll
                 for (int r = 0; r < UNROLL; r++) ok[r] = edge(r, val[r]);
                 push_batch<UNROLL>(op, ok, val, cv, wv);
             } else {
-                // edge by edge: collecting them before the first add, as above, sent the adds
-                // in bursts and cost PageRank 2% beside the pieces (R-MAT 28 under 8 GB:
-                // 3,740 ms, 3,660 edge by edge)
 #pragma unroll
                 for (int r = 0; r < UNROLL; r++) {
                     uint32_t val;
-                    const bool ok = edge(r, val);
-                    if constexpr (Op::wave)
-                        op.push_wave(ok, val, cv[r], wv[r]);
-                    else if (ok)
-                        op.push(val, cv[r], wv[r]);
+                    if (edge(r, val)) op.push(val, cv[r], wv[r]);
                 }
             }
         }
@@ -3766,7 +3767,7 @@ hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uin
         return push_edges_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, tile, ja, jb,
                              item_lo, item_hi, off, col, w, shift, compacted, s.pk, st);
     case ALGO_MSSSP:
-        return push_edges_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
+        return push_edges_op(OpMSssp<4>{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, shift, compacted, s.pk, st);
     case ALGO_MPPR:
         return push_edges_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, tile, ja, jb, item_lo,
@@ -3817,7 +3818,7 @@ hipError_t launch_push_lines(const AlgoState& s, const uint32_t* list, const uin
         return push_lines_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, tile, ja, jb,
                              item_lo, item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_MSSSP:
-        return push_lines_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
+        return push_lines_op(OpMSssp<4>{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
                              item_hi, off, col, w, distinct, s.pk, st);
     case ALGO_MPPR:
         return push_lines_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, tile, ja, jb, item_lo,
@@ -4037,7 +4038,7 @@ hipError_t launch_push_fstream(const AlgoState& s, const FTask* tasks, uint32_t 
         return push_fstream_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, tasks, ntasks,
                                total_chunks, list, off, col, w, s.pk, st);
     case ALGO_MSSSP:
-        return push_fstream_op(OpMSssp{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, tasks, ntasks, total_chunks,
+        return push_fstream_op(OpMSssp<1>{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, tasks, ntasks, total_chunks,
                                list, off, col, w, s.pk, st);
     case ALGO_MPPR:
         return push_fstream_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, tasks, ntasks, total_chunks,

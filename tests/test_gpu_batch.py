@@ -83,3 +83,20 @@ def test_batch_equals_single_runs_on_random_graph():
             vals, its, _ = g.run_batch(algo, srcs)
             for l, s in enumerate(srcs):
                 np.testing.assert_array_equal(vals[l], g.run(algo, int(s)).values)
+
+
+@pytest.mark.parametrize("mode", ["filter", "zerocopy"])
+@pytest.mark.parametrize("lanes", [4, 5, 8, 9, 16, 17, 32, 33, 64])
+def test_streamed_sssp_rows_match_oracle(mode, lanes):
+    """Batched SSSP over the host link, row widths from 4 to 64: an edge per thread below a
+    quarter row of active lanes, rows across the wave's threads above."""
+    off, col = gen.rmat(11, 16, seed=11)
+    w = gen.weights(off, col, 5)
+    srcs = np.random.default_rng(lanes).choice(np.nonzero(np.diff(off.astype(np.int64)))[0], lanes).astype(np.uint32)
+    with hy.Graph(off, col, weights=w) as g:
+        g.set_params(mode=mode, partition_edges=2048)
+        g.set_resident_fraction("sssp", 0.1)
+        got, _, st = g.run_batch("sssp", srcs, stats=True)
+    assert st["nres"] < st["npart"]
+    for l, s in enumerate(srcs):
+        assert np.array_equal(got[l], oracle.sssp(off, col, w, int(s))), l
