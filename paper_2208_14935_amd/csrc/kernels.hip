@@ -1198,6 +1198,7 @@ struct OpMBfs {
 // iterations 547 and 413 us alone, 228 us and (beside a stream) 531 us here with 40 us each
 // to settle, the call 9.56 -> 9.42 ms of which the host link takes 7.7.
 struct OpMBfsWide : BatchOp {
+    static constexpr bool steps = false;
     static constexpr bool weighted = false;
     const uint64_t* mcur;
     uint64_t* mnext;
@@ -1562,6 +1563,12 @@ constexpr int LINE_UNROLL = 8;                  // lines per half wave per pass
 constexpr int LINE_IPB = LINE_HALVES * LINE_UNROLL;
 static_assert(LINE_IPB == 1 << LINE_TILE_SHIFT, "the tile table's lines per pass");
 
+// A pass waits for its lines behind all that are queued on the link (up to 0.2 ms), while the
+// values that its vertices push may have improved.  Operators in steps, whose states only improve,
+// read them once the lines are there: components of 2^20 uniform vertices, a quarter resident, zero-copy
+// 3.7 -> 2.9 ms (values of the start of the pass made the third iteration push 12M edges again, 1.7M
+// so), 3M vertices 9.5 -> 9.4; nothing else became slower.  (The streaming filter's chunks are one
+// per workgroup at a time either way; there it gained nothing.)
 template <class Op>
 __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __restrict__ list,
                                                              const uint64_t* __restrict__ wpre,
@@ -1574,7 +1581,7 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __r
     __shared__ uint64_t s_pre[LINE_IPB];
     __shared__ uint64_t s_s[LINE_IPB];
     __shared__ uint64_t s_e[LINE_IPB];
-    __shared__ uint32_t s_val[LINE_IPB];
+    __shared__ uint32_t s_val[LINE_IPB];  // the pushed value; operators in steps: the vertex
     __shared__ uint64_t s_prev_end;  // end offset of the list entry before the staged ones
     __shared__ uint32_t s_cnt;
     uint32_t my_lines = 0;  // distinct lines of the items this half wave loaded
@@ -1596,7 +1603,7 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __r
             s_pre[k] = wpre[j0 + k];
             s_s[k] = off[v];
             s_e[k] = off[v + 1];
-            s_val[k] = op.src(v);
+            s_val[k] = Op::steps ? v : op.src(v);
         }
         if (distinct && threadIdx.x == 0) s_prev_end = j0 > ja ? off[list[j0 - 1] + 1] : UINT64_MAX;
         __syncthreads();
@@ -1636,9 +1643,14 @@ __global__ __launch_bounds__(LINE_THREADS) void k_push_lines(const uint32_t* __r
                 }
             }
         }
+        if constexpr (Op::steps) {  // the loads below stay behind the lines' arrival
+#pragma unroll
+            for (int r = 0; r < LINE_UNROLL; r++) asm volatile("" : "+v"(cv[r]), "+v"(wv[r]) : : "memory");
+        }
 #pragma unroll
         for (int r = 0; r < LINE_UNROLL; r++) {
             kk[r] = s_val[kk[r]];
+            if constexpr (Op::steps) kk[r] = ok[r] ? op.src(kk[r]) : 0u;
             if (Op::weighted) wv[r] = pk_w(cv[r], wv[r], pk);
             cv[r] = pk_v(cv[r], pk);
         }
