@@ -428,11 +428,12 @@ inline uint64_t tile_entries(uint64_t n, uint64_t m, uint32_t shift) { return ((
 // Push over edge items [item_lo, item_hi) of list entries [ja, jb).  Edge e of vertex
 // list[j] is read at col[off[v] - shift + (item - wpre[j])]; with compacted = true it
 // is read at col[item - shift] (the compaction buffer starts at item `shift`).  Unless
-// compacted, item_lo = wpre[ja] and tile = the edge tile table.
+// compacted, item_lo = wpre[ja] and tile = the edge tile table.  cap: 0, or at most this many
+// workgroups.
 hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, uint64_t shift, bool compacted,
-                             hipStream_t st);
+                             hipStream_t st, unsigned cap = 0);
 
 // Push over 128-byte line items [item_lo, item_hi) of list entries [ja, jb) (item_lo =
 // wpre[ja]; tile = the line tile table), reading

@@ -3733,8 +3733,9 @@ hipError_t launch_fill2_u32(uint32_t* p, uint64_t np, uint32_t* q, uint64_t nq, 
 template <class Op>
 static hipError_t push_edges_op(const Op& op, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja, uint32_t jb,
                                 uint64_t lo, uint64_t hi, const uint64_t* off, const uint32_t* col,
-                                const uint32_t* w, uint64_t shift, bool compacted, const Pack& pk, hipStream_t st) {
-    const unsigned g = grid_for(((hi - 1) >> EDGE_TILE_SHIFT) - (lo >> EDGE_TILE_SHIFT) + 1, 1, GRID_CAP);
+                                const uint32_t* w, uint64_t shift, bool compacted, const Pack& pk, hipStream_t st,
+                                unsigned cap) {
+    const unsigned g = grid_for(((hi - 1) >> EDGE_TILE_SHIFT) - (lo >> EDGE_TILE_SHIFT) + 1, 1, cap ? cap : GRID_CAP);
     if (compacted)
         k_push_edges<Op, true><<<g, EDGE_THREADS, 0, st>>>(list, wpre, tile, ja, jb, lo, hi, off, col, w, shift, op, pk);
     else
@@ -3745,48 +3746,48 @@ static hipError_t push_edges_op(const Op& op, const uint32_t* list, const uint64
 hipError_t launch_push_edges(const AlgoState& s, const uint32_t* list, const uint64_t* wpre, const uint32_t* tile, uint32_t ja,
                              uint32_t jb, uint64_t item_lo, uint64_t item_hi, const uint64_t* off,
                              const uint32_t* col, const uint32_t* w, uint64_t shift, bool compacted,
-                             hipStream_t st) {
+                             hipStream_t st, unsigned cap) {
     if (item_hi <= item_lo || jb <= ja) return hipSuccess;
     switch (s.algo) {
     case ALGO_BFS:
         return push_edges_op(OpBfs{s.visited, s.next, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
-                             off, col, w, shift, compacted, s.pk, st);
+                             off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_BFS_WIDE:
         return push_edges_op(OpBfsWide{s.visited, s.val, s.level_next}, list, wpre, tile, ja, jb, item_lo, item_hi,
-                             off, col, w, shift, compacted, s.pk, st);
+                             off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_SSSP:
         return push_edges_op(OpSssp{s.val, s.next, s.overflow, s.far, s.bound}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w,
-                             shift, compacted, s.pk, st);
+                             shift, compacted, s.pk, st, cap);
     case ALGO_SSSP_WIDE:
         return push_edges_op(OpSsspWide{{s.val, s.next, s.overflow, s.far, s.bound}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
-                             off, col, w, shift, compacted, s.pk, st);
+                             off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_CC_WIDE:
         return push_edges_op(OpCcWide{{s.val, s.next}, s.marks, (uint8_t)s.tag}, list, wpre, tile, ja, jb, item_lo, item_hi,
-                             off, col, w, shift, compacted, s.pk, st);
+                             off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_CC:
         return push_edges_op(OpCc{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
-                             compacted, s.pk, st);
+                             compacted, s.pk, st, cap);
     case ALGO_CC_LINK:
         return push_edges_op(OpLink{s.val}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift, compacted,
-                             s.pk, st);
+                             s.pk, st, cap);
     case ALGO_BFS_RELAX:
         return push_edges_op(OpBfsRelax{s.val, s.next}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
-                             compacted, s.pk, st);
+                             compacted, s.pk, st, cap);
     case ALGO_MBFS_WIDE:
         return push_edges_op(OpMBfsWide(s), list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
-                             compacted, s.pk, st);
+                             compacted, s.pk, st, cap);
     case ALGO_MBFS:
         return push_edges_op(OpMBfs{s.mcur, s.mnext, s.mvisited, s.lval, s.next, s.level_next, s.lshift}, list, wpre, tile, ja, jb,
-                             item_lo, item_hi, off, col, w, shift, compacted, s.pk, st);
+                             item_lo, item_hi, off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_MSSSP:
         return push_edges_op(OpMSssp<4>{s.mcur, s.mnext, s.lval, s.next, s.overflow, s.lshift}, list, wpre, tile, ja, jb, item_lo,
-                             item_hi, off, col, w, shift, compacted, s.pk, st);
+                             item_hi, off, col, w, shift, compacted, s.pk, st, cap);
     case ALGO_MPPR:
         return push_edges_op(OpMPpr{s.mcur, s.mnext, s.lx, s.lacc, s.next, s.lshift}, list, wpre, tile, ja, jb, item_lo,
-                             item_hi, off, col, w, shift, compacted, s.pk, st);
+                             item_hi, off, col, w, shift, compacted, s.pk, st, cap);
     default:
         return push_edges_op(OpPr{s.acc, acc_slots(s.n), s.contrib, s.acc_copies - 1}, list, wpre, tile, ja, jb, item_lo, item_hi, off, col, w, shift,
-                             compacted, s.pk, st);
+                             compacted, s.pk, st, cap);
     }
 }
 

@@ -1353,6 +1353,23 @@ bool rg_build(RunCtx& rc, hipStream_t main) {
     return rg.ok = true;
 }
 
+// Workgroups of SSSP's and components' resident push beside engines that use the host link (0 = no
+// bound).  Resident edges go at several times the link's rate, and a push that fills the GPU
+// holds up the streamed pushes' workgroups, so that the link idles until it ends; a push of two
+// or four workgroups per CU ends within the link's time all the same.  Iterations
+// over mostly resident edges keep four, since there the resident push is the longer one.  Measured with
+// 512 / 1024 / unbounded: components of R-MAT 28 under 8 GB (23% resident) 961 / 966 / 991 ms, of 3M
+// uniform vertices at 25 / 50% 8.5 / 9.5 / 9.4 and 5.7 / 7.1 / 7.1, at 80% 4.8 / 4.5 / 4.5, of R-MAT 24
+// at 80% 14.6 / 11.0 / 11.5; SSSP of R-MAT 24 at 25 / 60% 34.0 / 34.3 / 33.8 and 19.5 / 19.2 / 19.6, at
+// 80% 13.3 unbounded, 12.2 with 1024.  BFS, whose pushes are short, gains nothing and loses 1-2%
+// (R-MAT 24 at 25 / 80% 19.4 -> 19.6 and 8.7 -> 8.9); rows of lanes and ranks take more per edge (SSSP
+// with 64 lanes at 70% 37.1 / 27.5 / 27.0, PPR 177 / 163 / 160 ms): they go unbounded.
+unsigned resident_cap(const RunCtx& rc, const Header& h) {
+    if (rc.batched || (rc.algo != HYTM_SSSP && rc.algo != HYTM_CC)) return 0;
+    const uint64_t linked = h.seg_edges[SEG_F] + h.seg_edges[SEG_Z];
+    return linked == 0 ? 0 : h.seg_edges[SEG_R] <= linked ? 512 : 1024;
+}
+
 // The push over the resident segment of a selection.
 void push_resident(RunCtx& rc, const Header& h, hipStream_t main) {
     hytm_graph* g = rc.g;
@@ -1383,7 +1400,7 @@ void push_resident(RunCtx& rc, const Header& h, hipStream_t main) {
     }
     HIP_CHECK(kt.run(HYTM_K_PUSH_RES, wb - wa, main, [&] {
         return launch_push_edges(as, g->d_list.p, g->d_wpre.p, g->d_tile_e.p, ja, jb, wa, wb, g->d_off.p,
-                                 g->d_res_col.p, g->d_res_w.p, 0, false, main);
+                                 g->d_res_col.p, g->d_res_w.p, 0, false, main, resident_cap(rc, h));
     }));
 }
 

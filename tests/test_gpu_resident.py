@@ -77,3 +77,20 @@ def test_budget_change_resizes_the_region(case):
             g.set_budget(stage + int(frac * 8 * g.m) if frac is not None else 2**64 - 1)
             np.testing.assert_array_equal(g.run("sssp", 0).values, want_sssp)
             np.testing.assert_array_equal(g.run("bfs", 0).values, want_bfs)
+
+
+@pytest.mark.parametrize("algo", ["sssp", "cc"])
+@pytest.mark.parametrize("resident", [0.4, 0.8])
+def test_resident_pushes_of_more_tiles_than_workgroups(algo, resident):
+    """Beside the host link SSSP's and components' resident pushes run in 512 workgroups, in 1024
+    where they hold more edges than the link: 0.4 and 0.8 of 3.9M edges are 1,500 and 3,000 tiles."""
+    off, col = gen.rmat(17, 16, seed=17)
+    off, col = gen.symmetrize(off, col)
+    w = gen.weights(off, col, 9)
+    want = oracle.cc(off, col)[0] if algo == "cc" else oracle.sssp(off, col, w, 5)
+    with hy.Graph(off, col, weights=w, symmetric=True) as g:
+        g.set_params(partition_edges=4096, compact_chunk_edges=1 << 14)
+        g.set_resident_fraction(algo, resident)
+        res = g.run(algo, 5, stats=True)
+    assert 0 < res.stats["nres"] < res.stats["npart"]
+    assert np.array_equal(res.values, want)
