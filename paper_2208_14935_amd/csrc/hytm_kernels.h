@@ -293,14 +293,14 @@ hipError_t launch_stats_select(uint32_t npart, const Units& un, const uint32_t* 
 // Batched runs: initialise lane masks, lane values and the union frontier.
 hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_t* cur_union, uint32_t nwords,
                              hipStream_t st);
+// The end of an iteration of ALGO_MBFS_WIDE: levels, reached lanes and the next bitmap (nwords
+// words, all written) from the gained lanes in mnext.
+hipError_t launch_settle_lanes(const AlgoState& s, uint32_t nwords, hipStream_t st);
 // out.row[k], k = 0.. (n values each, in device memory or in host memory that the device
 // maps) <- the lanes of `set` in increasing lane order, from n rows of 2^lshift 32-bit
 // values; with sub_base, a value other than UNREACHED has the lane's base subtracted (BFS
 // levels of lanes that joined late).  rank (or null): position v of a row takes the value of
 // vertex rank[v] (back to the caller's ids).
-// The end of an iteration of ALGO_MBFS_WIDE: levels, reached lanes and the next bitmap (nwords
-// words, all written) from the gained lanes in mnext.
-hipError_t launch_settle_lanes(const AlgoState& s, uint32_t nwords, hipStream_t st);
 struct LaneRows {
     uint32_t* row[MAX_LANES];
 };

@@ -2853,7 +2853,7 @@ __global__ __launch_bounds__(256) void k_in_scatter(const uint64_t* __restrict__
 // the run is written with plain stores (no other run holds its edges); the run's first and
 // last one may continue in the neighbouring runs and are updated atomically.
 //
-// Narrower rows (k_pull_segs): 16 threads take a segment of one vertex's in-list, 16 / S of
+// Narrower rows, PPR's only (k_pull_segs): 16 threads take a segment of one vertex's in-list, 16 / S of
 // its edges at once.
 //
 // Bound by the gathered rows (a wave per vertex waited through six dependent loads for the
@@ -2874,7 +2874,7 @@ constexpr uint32_t IN_RUN_MAX = 256, PULL_WAVES = 12288;
 // least candidate distance.
 struct PullPpr {
     typedef double Acc;
-    static constexpr bool weighted = false, narrow = true;  // narrow: rows of 1..8 lanes too
+    static constexpr bool weighted = false;
     static __device__ __forceinline__ Acc none() { return 0.0; }
     static __device__ __forceinline__ Acc join(Acc a, Acc b) { return a + b; }
     // value of lane ln of source u's row, for an edge of weight w whose source has the lanes mu active
@@ -2902,7 +2902,7 @@ struct PullPpr {
 
 struct PullSssp {
     typedef uint32_t Acc;
-    static constexpr bool weighted = true, narrow = false;
+    static constexpr bool weighted = true;
     static __device__ __forceinline__ Acc none() { return UNREACHED; }
     static __device__ __forceinline__ Acc join(Acc a, Acc b) { return a < b ? a : b; }
     template <int LSH>
@@ -3008,43 +3008,38 @@ __global__ __launch_bounds__(256) void k_pull_runs(AlgoState s, InLists in, uint
     }
 }
 
-template <int LSH, class P>
+template <int LSH>
 __global__ __launch_bounds__(256) void k_pull_segs(AlgoState s, InLists in) {
     constexpr uint32_t S = 1u << LSH, W = 16, E = W / S;
     const uint32_t sl = threadIdx.x & (W - 1), grp = sl >> LSH, ln = sl & (S - 1);
-    const uint32_t groups = gridDim.x * (256 / W);
-    for (uint32_t sg = (blockIdx.x * 256 + threadIdx.x) / W; sg < in.nseg; sg += groups) {  // uniform over 16 threads
+    const uint64_t groups = gridDim.x * (256ull / W);
+    for (uint64_t sg = (blockIdx.x * 256ull + threadIdx.x) / W; sg < in.nseg; sg += groups) {  // uniform over 16 threads
         const uint32_t v = in.seg_v[sg];
         const uint32_t s0 = in.soff[v];
         const bool multi = in.soff[v + 1] - s0 > 1;
-        const uint64_t b = in.toff[v] + (uint64_t)(sg - s0) * IN_SEG;
+        const uint64_t b = in.toff[v] + (sg - s0) * IN_SEG;
         const uint64_t e = min(b + IN_SEG, in.toff[v + 1]);
-        typename P::Acc acc = P::none();
+        double acc = 0.0;
         uint32_t m = 0;  // S <= 8 lanes
         for (uint64_t i = b; i < e; i += W) {
             const bool ok = i + sl < e;
             const uint32_t u = ok ? in.tsrc[i + sl] : 0u;
-            const uint32_t w = P::weighted && ok ? in.tw[i + sl] : 0u;
             const uint32_t mu = ok ? (uint32_t)s.mcur[u] : 0u;
             m |= mu;
-            decltype(P::template take<LSH>(s, 0u, 0ull, 0u)) x[S];
-            uint32_t mm[S], ww[S];
+            float x[S];
 #pragma unroll
             for (uint32_t t = 0; t < S; t++) {
                 const uint32_t q = t * E + grp;
-                const uint32_t uu = __shfl(u, q, W);
-                mm[t] = __shfl(mu, q, W);
-                ww[t] = P::weighted ? __shfl(w, q, W) : 0u;
-                x[t] = P::template take<LSH>(s, uu, mm[t], ln);
+                x[t] = PullPpr::take<LSH>(s, __shfl(u, q, W), __shfl(mu, q, W), ln);
             }
 #pragma unroll
-            for (uint32_t t = 0; t < S; t++) acc = P::join(acc, P::value(s, x[t], ww[t], mm[t], ln));
+            for (uint32_t t = 0; t < S; t++) acc += x[t];
         }
 #pragma unroll
         for (uint32_t d = W / 2; d >= 1; d >>= 1) m |= __shfl_xor(m, d, W);
 #pragma unroll
-        for (uint32_t d = S; d < W; d <<= 1) acc = P::join(acc, __shfl_xor(acc, (int)d, W));
-        if (grp == 0) P::template hand_over<LSH>(s, v, ln, acc, m, multi);
+        for (uint32_t d = S; d < W; d <<= 1) acc += __shfl_xor(acc, (int)d, W);
+        if (grp == 0) PullPpr::hand_over<LSH>(s, v, ln, acc, m, multi);
     }
 }
 
@@ -3623,17 +3618,9 @@ hipError_t launch_in_lists(const uint64_t* off, const uint32_t* col, const uint3
 template <class P>
 static hipError_t pull_op(const AlgoState& s, const InLists& in, hipStream_t st) {
     if (!in.nseg) return hipSuccess;
-    const unsigned gs = grid_for(in.nseg, 16, GRID_CAP);
     uint32_t run = IN_RUN_MAX;
     while (run > std::max(64u, 2u << s.lshift) && ((in.m / run) << s.lshift) / 64 < PULL_WAVES) run /= 2;
     const unsigned gr = grid_for((in.m + run - 1) / run, 256u >> s.lshift, GRID_CAP);
-    if constexpr (P::narrow) {
-        if (s.lshift == 0) k_pull_segs<0, P><<<gs, 256, 0, st>>>(s, in);
-        if (s.lshift == 1) k_pull_segs<1, P><<<gs, 256, 0, st>>>(s, in);
-        if (s.lshift == 2) k_pull_segs<2, P><<<gs, 256, 0, st>>>(s, in);
-        if (s.lshift == 3) k_pull_segs<3, P><<<gs, 256, 0, st>>>(s, in);
-        if (s.lshift < 4) return hipGetLastError();
-    }
     switch (s.lshift) {
     case 4: k_pull_runs<4, P><<<gr, 256, 0, st>>>(s, in, run); break;
     case 5: k_pull_runs<5, P><<<gr, 256, 0, st>>>(s, in, run); break;
@@ -3644,6 +3631,15 @@ static hipError_t pull_op(const AlgoState& s, const InLists& in, hipStream_t st)
 }
 
 hipError_t launch_pull(const AlgoState& s, const InLists& in, hipStream_t st) {
+    if (s.algo == ALGO_MPPR && s.lshift < 4) {
+        if (!in.nseg) return hipSuccess;
+        const unsigned g = grid_for(in.nseg, 16, GRID_CAP);
+        if (s.lshift == 0) k_pull_segs<0><<<g, 256, 0, st>>>(s, in);
+        if (s.lshift == 1) k_pull_segs<1><<<g, 256, 0, st>>>(s, in);
+        if (s.lshift == 2) k_pull_segs<2><<<g, 256, 0, st>>>(s, in);
+        if (s.lshift == 3) k_pull_segs<3><<<g, 256, 0, st>>>(s, in);
+        return hipGetLastError();
+    }
     if (s.algo == ALGO_MPPR) return pull_op<PullPpr>(s, in, st);
     if (s.algo == ALGO_MSSSP && in.tw) return pull_op<PullSssp>(s, in, st);
     return hipErrorInvalidValue;

@@ -1412,6 +1412,12 @@ void push_resident(RunCtx& rc, const Header& h, hipStream_t main) {
 // BFS of 2^22 vertices, R-MAT 1.53 / 1.14 / 1.15 / 1.15 / 1.15 / 1.14 ms, uniform with 4 edges
 // each 1.89 / 1.88 / 1.34 / 1.26 / 1.25 / 1.25; SSSP of 2.5M 1.76 / 1.57 / 1.57 / 1.55 / 1.56 /
 // 1.55, uniform 2^22 3.83 / 3.66 / 3.06 / 2.96 / 2.93 / 2.93.
+// The same rule for batched BFS, which settles its wide iterations by 8 bytes per vertex; never wide
+// / from 2n / n/2 / n/8 / n/32 / n/128: uniform 2^22 with 4 edges each, 1 / 8 / 64 lanes 2.11 / 2.11 /
+// 2.06 / 2.07 / 2.09 / 2.10, 7.80 / 6.95 / 6.64 / 6.44 / 6.44 / 6.48 and 32.0 / 28.0 / 27.9 / 28.0 / 28.0 /
+// 28.1 ms, 2^23 with 8 lanes 15.5 / 13.4 / 13.2 / 13.0 / 13.1 / 13.1; R-MAT 20, 8 and 64 lanes 1.56 / 1.59 /
+// 1.57 / 1.58 / 1.57 / 1.58 and 6.34 / 6.26 / 6.26 / 6.29 / 6.27 / 6.27; one lane of it alone pays for it,
+// 0.65 / 0.67 / 0.70 / 0.71 / 0.70 / 0.70.
 constexpr uint64_t kWide = 32;
 uint64_t mark_bytes(uint64_t n) { return (n + 63) & ~uint64_t(63); }
 
