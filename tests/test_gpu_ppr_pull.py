@@ -1,6 +1,8 @@
 """GPU: personalized PageRank and batched SSSP steps over the in-edge lists (dense steps of
-graphs without a budget) against the oracle (PPR in FP64, distances exact): row widths from 1 to 64 lanes, edge counts around a run's 128
-edges and a segment's 256, and in-lists spanning many runs and segments."""
+graphs without a budget) against the oracle (PPR in FP64, distances exact): row widths from 1 to
+64 lanes, edge counts around the runs' 64 (rows of up to 32 lanes) and 128 edges (64 lanes) of
+small graphs, the 256 of large ones and a segment's 256, and in-lists spanning many runs and
+segments."""
 import numpy as np
 import pytest
 
@@ -25,6 +27,9 @@ def ring(n):
 
 GRAPHS = {
     "2 edges": lambda: ring(2),
+    "63 edges": lambda: ring(63),
+    "64 edges": lambda: ring(64),
+    "65 edges": lambda: ring(65),
     "127 edges": lambda: ring(127),
     "128 edges": lambda: ring(128),
     "129 edges": lambda: ring(129),
@@ -98,3 +103,25 @@ def test_pulled_sssp_reports_overflow():
         got, _, _ = g.run_batch("sssp", srcs[13:].repeat(3))  # at most six edges from the end
         for l, s in enumerate(srcs[13:].repeat(3)):
             assert np.array_equal(got[l], oracle.sssp(off, col, w, int(s)))
+
+
+def test_pulled_runs_of_a_large_graph():
+    """Rows of 64 lanes over 3.4M edges, which go in runs of 256: lists of about 110 edges, cut by
+    the runs anywhere, and one of 20000 that spans many."""
+    n, hub = 30_000, np.arange(1, 20_001, dtype=np.uint32)
+    rng = np.random.default_rng(9)
+    src = np.concatenate([rng.integers(0, n, 3_400_000).astype(np.uint32), hub])
+    dst = np.concatenate([rng.integers(0, n, 3_400_000).astype(np.uint32), np.zeros(len(hub), np.uint32)])
+    off, col = gen.from_pairs(n, src, dst)
+    assert len(col) >= 256 * 12288
+    w = gen.weights(off, col, 4)
+    srcs = rng.choice(n, 4).astype(np.uint32)
+    with hy.Graph(off, col, weights=w) as g:
+        ppr, _, _ = g.run_batch("ppr", np.tile(srcs, 16))
+        dist, _, _ = g.run_batch("sssp", np.tile(srcs, 16))
+    for k, s in enumerate(srcs):
+        want, wd = oracle.ppr(off, col, int(s), 0.85, 10), oracle.sssp(off, col, w, int(s))
+        for l in range(k, 64, 4):
+            # as above, and the FP64 sums' own roundings are far below
+            assert np.all(np.abs(ppr[l] - want) <= 1.3e-6 * want + 1e-30)
+            assert np.array_equal(dist[l], wd)

@@ -27,7 +27,8 @@ GRAPHS = {
     "2^15 + 1": lambda: gen.er((1 << 15) + 1, 1 << 18, seed=3),
     "rmat 16": lambda: gen.rmat(16, 16, seed=16),
     "2^20 + 3": lambda: gen.er((1 << 20) + 3, 3 << 20, seed=4),
-    "2^21 + 1": lambda: gen.er((1 << 21) + 1, 3 << 20, seed=5),  # 1025 bins: two sorting passes
+    "2^21 + 1": lambda: gen.er((1 << 21) + 1, 3 << 20, seed=5),  # 257 bins, the last of one vertex
+    "2^23 + 1": lambda: gen.er((1 << 23) + 1, 9 << 20, seed=7),  # 1025 bins: two sorting passes
 }
 
 
@@ -144,13 +145,26 @@ def test_compact_plan_ends_inside_the_resident_prefix():
     assert res.stats["kernel_launches"][hy.KERNEL_CLASSES.index("pr_blocking")] == 20
 
 
-def test_compact_plan_of_wide_bins():
-    """17M vertices: 2^12 vertices per bin keep the bins within the sort's LDS."""
+def test_compact_plan_of_many_bins():
+    """17M vertices: 4,151 bins of 2^12 vertices."""
     off, col = gen.er(17_000_000, 34_000_000, seed=9)
     want = oracle.pagerank(off, col, 0.85, 20)
     with hy.Graph(off, col) as g:
         g.set_resident_fraction("pagerank", 0.4)
         check(g.run("pagerank"), want)
+
+
+def test_compact_plan_of_wide_bins():
+    """2^25 + 1 vertices: bins of 2^12 would be one more than the 8,192 that the sort counts in LDS, so
+    they hold 2^13.  Two iterations: at most ~10 equal shares per sum, each rounded to FP32."""
+    off, col = gen.er((1 << 25) + 1, 34_000_000, seed=9)
+    want = oracle.pagerank(off, col, 0.85, 2)
+    with hy.Graph(off, col) as g:
+        g.set_params(pr_iterations=2)
+        g.set_resident_fraction("pagerank", 0.3)
+        for _ in range(2):
+            got = g.run("pagerank").values.astype(np.float64)
+            assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
 
 
 def test_pieces_are_run_where_they_are_asked_for():
@@ -184,3 +198,15 @@ def test_plan_or_pieces_by_the_share_that_the_plan_covers(degree, planned):
         check(res, want)
         launches = res.stats["kernel_launches"][hy.KERNEL_CLASSES.index("pr_blocking")]
         assert launches == 20 if planned else launches >= 20 * 8
+
+
+def test_plan_of_widest_bins():
+    """2^27 + 1 vertices: bins of 2^13 would be one more than the sort's 2^14, so they hold 2^14 sums.
+    Two iterations of few equal shares, each rounded to FP32; the second over the kept plan's pairs."""
+    off, col = gen.er((1 << 27) + 1, 2_000_000, seed=10)
+    want = oracle.pagerank(off, col, 0.85, 2)
+    with hy.Graph(off, col) as g:
+        g.set_params(pr_iterations=2)
+        for _ in range(2):
+            got = g.run("pagerank").values
+            assert np.abs(got / want - 1).max() <= 2e-6
