@@ -296,8 +296,8 @@ hipError_t launch_init_lanes(const AlgoState& s, const LaneSources& src, uint32_
 // The end of an iteration of ALGO_MBFS_WIDE: levels, reached lanes and the next bitmap (nwords
 // words, all written) from the gained lanes in mnext.
 hipError_t launch_settle_lanes(const AlgoState& s, uint32_t nwords, hipStream_t st);
-// out.row[k], k = 0.. (n values each, in device memory or in host memory that the device
-// maps) <- the lanes of `set` in increasing lane order, from n rows of 2^lshift 32-bit
+// out.row[k], k = 0.. (n values each, in device memory or, to_host, in host memory that the
+// device maps) <- the lanes of `set` in increasing lane order, from n rows of 2^lshift 32-bit
 // values; with sub_base, a value other than UNREACHED has the lane's base subtracted (BFS
 // levels of lanes that joined late).  rank (or null): position v of a row takes the value of
 // vertex rank[v] (back to the caller's ids).
@@ -305,7 +305,7 @@ struct LaneRows {
     uint32_t* row[MAX_LANES];
 };
 hipError_t launch_extract_lanes(const uint32_t* vals, uint64_t n, uint32_t lshift, const LaneSet& set, bool sub_base,
-                                const uint32_t* rank, const LaneRows& out, hipStream_t st);
+                                const uint32_t* rank, const LaneRows& out, bool to_host, hipStream_t st);
 // Back to the caller's ids after hub sorting: dst[v] = src[rank[v]] for v < n.
 hipError_t launch_gather_u32(const uint32_t* src, const uint32_t* rank, uint64_t n, uint32_t* dst, hipStream_t st);
 // CC labels back to the caller's ids: every component's label becomes its smallest

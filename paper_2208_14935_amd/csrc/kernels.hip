@@ -1752,11 +1752,12 @@ __global__ __launch_bounds__(256) void k_settle_lanes(AlgoState s, uint32_t nwor
 // Lane extraction through LDS: a workgroup loads the rows of V vertices with coalesced
 // reads (row pitch padded by one word against bank conflicts), then writes each requested
 // lane as a contiguous run of V values.  Into host memory the link bounds it: 64 lanes of
-// 2^20 vertices in 4.81 ms, 55.8 GB/s, where extracting four lanes at a time into device
-// rows and copying those took 5.3 ms (a copy in flight holds up the extraction of the next
-// rows, 14 us on its own, to its end).  Rows of an odd length start in the middle of a
+// 2^20 vertices in 4.81 ms, 55.8 GB/s, where extracting eight lanes at a time into device
+// rows and copying those took 5.3 ms.  Rows of an odd length start in the middle of a
 // write: runs of 64 values then reach 49.2 GB/s, of 256 values 52.6; below EX_WIDE vertices
 // runs of 64 give the chip more workgroups (1,000 vertices: 13 us, 24 us in runs of 256).
+// Into device rows the reads bound it, and runs of 64, whose 16 KB of LDS leave eight workgroups
+// to a CU, read 64 lanes of 2^21 vertices in 0.17 ms where runs of 256 took 0.49.
 constexpr uint64_t EX_WIDE = 1ull << 15;
 template <uint32_t V>
 __global__ __launch_bounds__(256) void k_extract_lanes(const uint32_t* __restrict__ vals, uint64_t n,
@@ -3468,11 +3469,11 @@ hipError_t launch_settle_lanes(const AlgoState& s, uint32_t nwords, hipStream_t 
 }
 
 hipError_t launch_extract_lanes(const uint32_t* vals, uint64_t n, uint32_t lshift, const LaneSet& set, bool sub_base,
-                                const uint32_t* rank, const LaneRows& out, hipStream_t st) {
+                                const uint32_t* rank, const LaneRows& out, bool to_host, hipStream_t st) {
     const uint32_t nsel = (uint32_t)__builtin_popcountll(set.mask);
     if (!n || !nsel || lshift > 6 || (set.mask >> 1 >> ((1u << lshift) - 1))) return n && nsel ? hipErrorInvalidValue : hipSuccess;
     const size_t row = sizeof(uint32_t) * ((1u << lshift) + 1);
-    if (n < EX_WIDE)
+    if (!to_host || n < EX_WIDE)
         k_extract_lanes<64><<<grid_for(n, 64, 4096), 256, 64 * row, st>>>(vals, n, lshift, set, nsel, sub_base, rank, out);
     else
         k_extract_lanes<256><<<grid_for(n, 256, 4096), 256, 256 * row, st>>>(vals, n, lshift, set, nsel, sub_base, rank,

@@ -2388,8 +2388,8 @@ uint32_t* mapped_host(const hytm_graph* g, void* p, uint64_t bytes) {
 
 // Copy the lanes in set.mask out of the interleaved values `vals` (n rows of 2^lshift), in
 // increasing lane order: lane k of them goes to the n values at outs[k].  Rows in page-locked
-// memory are written by the extraction itself; the others go through device rows, whose two
-// halves of EXTRACT_LANES / 2 lanes alternate, one being copied while the other is extracted.
+// memory are written by the extraction itself; the others go through device rows,
+// EXTRACT_LANES at a time.
 constexpr uint32_t EXTRACT_LANES = 8;
 void copy_lanes_out(hytm_graph* g, const uint32_t* vals, uint32_t lshift, const LaneSet& set, bool sub_base,
                     void* const* outs, hipStream_t main) {
@@ -2409,47 +2409,29 @@ void copy_lanes_out(hytm_graph* g, const uint32_t* vals, uint32_t lshift, const 
             staged[ns++] = outs[k];
         }
     }
-    if (nd) HIP_CHECK(launch_extract_lanes(vals, n, lshift, direct, sub_base, rank, rows, main));
+    if (nd) HIP_CHECK(launch_extract_lanes(vals, n, lshift, direct, sub_base, rank, rows, true, main));
     if (ns) g->d_xout.ensure(n * EXTRACT_LANES);
-    constexpr uint32_t HALF = EXTRACT_LANES / 2;
     uint64_t rest = set.mask & ~direct.mask;
-    k = 0;
-    for (uint32_t pass = 0; rest; pass++) {
-        const uint32_t b = pass & 1;
+    for (k = 0; rest;) {
         LaneSet part = set;
-        LaneRows half{};
+        LaneRows dev{};
         part.mask = 0;
-        uint32_t* at = g->d_xout.p + b * HALF * n;
         uint32_t cnt = 0;
-        for (; cnt < HALF && rest; cnt++) {
+        for (; cnt < EXTRACT_LANES && rest; cnt++) {
             part.mask |= rest & (~rest + 1);
             rest &= rest - 1;
-            half.row[cnt] = at + cnt * n;
+            dev.row[cnt] = g->d_xout.p + cnt * n;
         }
-        if (pass >= 2) HIP_CHECK(hipStreamWaitEvent(main, g->ev_free[b], 0));  // copied out
-        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, rank, half, main));
-        HIP_CHECK(hipEventRecord(g->ev_copied[b], main));
-        HIP_CHECK(hipStreamWaitEvent(g->s_copy, g->ev_copied[b], 0));
-        // rows that lie behind one another in the caller's memory go in one copy: copies of a
-        // few MB stand 11 us apart, an eighth of their time
-        for (uint32_t c = 0, c1; c < cnt; c = c1) {
-            for (c1 = c + 1;
-                 c1 < cnt && (char*)staged[k + c1] == (char*)staged[k + c] + (uint64_t)(c1 - c) * n * 4;)
-                c1++;
-            HIP_CHECK(hipMemcpyAsync(staged[k + c], at + (uint64_t)c * n, (uint64_t)(c1 - c) * n * 4,
-                                     hipMemcpyDeviceToHost, g->s_copy));
-        }
-        HIP_CHECK(hipEventRecord(g->ev_free[b], g->s_copy));
+        HIP_CHECK(launch_extract_lanes(vals, n, lshift, part, sub_base, rank, dev, false, main));
+        for (uint32_t c = 0; c < cnt; c++)
+            HIP_CHECK(hipMemcpyAsync(staged[k + c], dev.row[c], n * 4, hipMemcpyDeviceToHost, main));
+        // the staging rows are reused by the next pass
+        HIP_CHECK(hipStreamSynchronize(main));
         k += cnt;
     }
     if (nd) HIP_CHECK(hipStreamSynchronize(main));
-    if (ns) HIP_CHECK(hipStreamSynchronize(g->s_copy));
 }
 
-// One run.  lanes == 0: single source `sources[0]` (BFS/SSSP) or none (CC/PR), values_out
-// holds n values, iterations_out one count.  lanes in 1..64: batched BFS/SSSP/PPR from
-// sources[0..lanes), values_out holds lanes rows of n values, iterations_out one count per
-// lane (the non-empty frontiers of that lane; PPR: its steps).
 // SSSP with sssp_delta, once the frontier is empty: the bound rises to the smallest multiple
 // of sssp_delta above the smallest distance waiting in the far set, and the far vertices
 // below it become the frontier.  *more = false when nothing waits (the run is over).
