@@ -1550,7 +1550,12 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
 
     // The engines that use the host link are launched first: it bounds a pass that uses it,
     // and a resident push that has filled the GPU delays even the copy of the filter tasks
-    // (80 us on R-MAT 20 with 64 lanes), while it finds its CUs beside them.
+    // (80 us on R-MAT 20 with 64 lanes), while it finds its CUs beside them.  The copying filter
+    // takes the host a call per task and more, which the resident push would wait for: it goes
+    // first there (components, 30% resident: 2^20 uniform vertices 7.4 ms, last 11.0; R-MAT 21 10.7
+    // and 13.2; R-MAT 18 2.7 and 3.0).
+    const bool copying = use_f && !fstream;
+    if (copying) push_resident(rc, h, main);
     // zero-copy: one kernel over all zero-copy vertices (Vz)
     if (h.seg_list_count[SEG_Z]) {
         HIP_CHECK(kt.run(HYTM_K_PUSH_ZC, h.seg_work_total[SEG_Z], g->s_zc, [&] {
@@ -1646,7 +1651,7 @@ hytm_status engine_pass(RunCtx& rc, const uint32_t* cur, hipStream_t main, Heade
             }
             rec->filter_tasks += gidx;
         }
-        push_resident(rc, h, main);  // no transfer
+        if (!copying) push_resident(rc, h, main);  // no transfer
     } catch (const HipError& e) {
         fst = e.status;
     }
