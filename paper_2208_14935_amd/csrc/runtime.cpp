@@ -1363,9 +1363,13 @@ bool rg_build(RunCtx& rc, hipStream_t main) {
 // at 80% 14.6 / 11.0 / 11.5; SSSP of R-MAT 24 at 25 / 60% 34.0 / 34.3 / 33.8 and 19.5 / 19.2 / 19.6, at
 // 80% 13.3 unbounded, 12.2 with 1024.  BFS, whose pushes are short, gains nothing and loses 1-2%
 // (R-MAT 24 at 25 / 80% 19.4 -> 19.6 and 8.7 -> 8.9); rows of lanes and ranks take more per edge (SSSP
-// with 64 lanes at 70% 37.1 / 27.5 / 27.0, PPR 177 / 163 / 160 ms): they go unbounded.
+// with 64 lanes at 70% 37.1 / 27.5 / 27.0, PPR 177 / 163 / 160 ms): they go unbounded.  So do pushes of
+// fewer than kCapEdges edges, over in 0.2 ms: components of 2^20 uniform vertices at 25% (1.6M edges
+// resident beside the staging), zero-copy 3.3 bounded, 2.9 unbounded; with 5.8M edges 5.3 and 6.8 (2^21
+// at 25%), 2.93 and 2.98 (2^20 at 50%).
+constexpr uint64_t kCapEdges = 3ull << 20;
 unsigned resident_cap(const RunCtx& rc, const Header& h) {
-    if (rc.batched || (rc.algo != HYTM_SSSP && rc.algo != HYTM_CC)) return 0;
+    if (rc.batched || (rc.algo != HYTM_SSSP && rc.algo != HYTM_CC) || h.seg_edges[SEG_R] < kCapEdges) return 0;
     const uint64_t linked = h.seg_edges[SEG_F] + h.seg_edges[SEG_Z];
     return linked == 0 ? 0 : h.seg_edges[SEG_R] <= linked ? 512 : 1024;
 }

@@ -83,8 +83,9 @@ def test_budget_change_resizes_the_region(case):
 @pytest.mark.parametrize("resident", [0.4, 0.8])
 def test_resident_pushes_of_more_tiles_than_workgroups(algo, resident):
     """Beside the host link SSSP's and components' resident pushes run in 512 workgroups, in 1024
-    where they hold more edges than the link: 0.4 and 0.8 of 3.9M edges are 1,500 and 3,000 tiles."""
-    off, col = gen.rmat(17, 16, seed=17)
+    where they hold more edges than the link, from 3M edges on: 0.4 and 0.8 of 16.8M edges are 6,500
+    and 13,000 tiles."""
+    off, col = gen.er(1 << 18, 1 << 23, seed=17)
     off, col = gen.symmetrize(off, col)
     w = gen.weights(off, col, 9)
     want = oracle.cc(off, col)[0] if algo == "cc" else oracle.sssp(off, col, w, 5)
