@@ -2078,51 +2078,102 @@ __global__ void k_reset_lanes(AlgoState s, uint64_t mask) {
     }
 }
 
-// x of each active (vertex, lane) scaled to x / D_o, one thread per value: a wave's accesses
-// are contiguous rows (a thread per vertex walking its row took 0.54 ms of 1M rows of 64).
-__global__ __launch_bounds__(256) void k_ppr_prepare(AlgoState s, const uint64_t* __restrict__ off) {
-    const uint64_t cells = s.n << s.lshift;
-    const uint32_t lmask = (1u << s.lshift) - 1;
-    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
-        const uint64_t v = i >> s.lshift;
-        if (!((s.mcur[v] >> ((uint32_t)i & lmask)) & 1)) continue;
-        const uint64_t d = off[v + 1] - off[v];
-        if (d) s.lx[i] = s.lx[i] / (float)d;
+// The steps of personalized PageRank over its values, at the (vertex, lane) cells whose bits
+// are set in cell_mask.  A wave takes windows of `rows` vertices (a power of two, at most 64, whole
+// accesses): it loads their masks, passes over the rows without a set bit (of few active vertices
+// almost all) and takes the others 64 cells at a time, contiguous, PPR_ROWS of these accesses in
+// flight.  Bound by the rows' bytes where the frontier is dense, by the masks' where it is sparse:
+// whole calls, one thread per cell and this, 12 lanes of 2^25 uniform vertices with 2 edges each 39.8
+// -> 34.6 ms (a thread per vertex 36.1, but 0.54 ms a pass of 1M dense rows of 64), 64 lanes of R-MAT
+// 20 18.7 -> 18.2.
+constexpr int PPR_ROWS = 4;
+template <class Op>
+__device__ __forceinline__ void ppr_cells(const AlgoState& s, uint32_t rows, const Op& op) {
+    const uint32_t lane = threadIdx.x & 63, ln = lane & ((1u << s.lshift) - 1), slot = lane >> s.lshift;
+    const uint32_t per = 64u >> s.lshift;  // rows per access
+    const uint64_t some = per == 64 ? ~0ull : (1ull << per) - 1;
+    const uint64_t step = (uint64_t)gridDim.x * 4 * rows;
+    for (uint64_t v0 = (blockIdx.x * 4ull + (threadIdx.x >> 6)) * rows; v0 < s.n; v0 += step) {
+        const uint64_t m = lane < rows && v0 + lane < s.n ? op.cell_mask(v0 + lane) : 0ull;
+        uint64_t left = __ballot(m != 0);  // vertices whose rows are to come
+        while (left) {                     // uniform
+            uint64_t v[PPR_ROWS];
+            bool on[PPR_ROWS];
+            typename Op::Reg x[PPR_ROWS];
+#pragma unroll
+            for (int r = 0; r < PPR_ROWS; r++) {
+                const uint32_t j = left ? ((uint32_t)__ffsll((unsigned long long)left) - 1) & ~(per - 1) : 0u;
+                const uint64_t y = __shfl(m, (int)(j + slot), 64);
+                on[r] = left && ((y >> ln) & 1);
+                v[r] = v0 + j + slot;
+                if (on[r]) x[r] = op.load(v[r], (v[r] << s.lshift) + ln);
+                left &= ~(some << j);
+            }
+#pragma unroll
+            for (int r = 0; r < PPR_ROWS; r++)
+                if (on[r]) op.store(v[r], (v[r] << s.lshift) + ln, ln, x[r]);
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_ppr_apply(AlgoState s, float damping) {
-    const uint64_t cells = s.n << s.lshift;
-    const uint32_t lmask = (1u << s.lshift) - 1;
-    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
-        const uint64_t v = i >> s.lshift;
-        if (!(((s.mcur[v] | s.mnext[v]) >> ((uint32_t)i & lmask)) & 1)) continue;
-        s.lx[i] = (float)((double)damping * s.lacc[i]);
+// x of each active cell scaled to x / D_o.
+struct PprPrepare {
+    struct Reg {
+        float x;
+        uint64_t d;
+    };
+    const AlgoState& s;
+    const uint64_t* __restrict__ off;
+    __device__ __forceinline__ uint64_t cell_mask(uint64_t v) const { return s.mcur[v]; }
+    __device__ __forceinline__ Reg load(uint64_t v, uint64_t i) const { return Reg{s.lx[i], off[v + 1] - off[v]}; }
+    __device__ __forceinline__ void store(uint64_t, uint64_t i, uint32_t, const Reg& r) const {
+        if (r.d) s.lx[i] = r.x / (float)r.d;
+    }
+};
+__global__ __launch_bounds__(256) void k_ppr_prepare(AlgoState s, uint32_t rows, const uint64_t* __restrict__ off) {
+    ppr_cells(s, rows, PprPrepare{s, off});
+}
+
+struct PprApply {
+    typedef double Reg;
+    const AlgoState& s;
+    float damping;
+    __device__ __forceinline__ uint64_t cell_mask(uint64_t v) const { return s.mcur[v] | s.mnext[v]; }
+    __device__ __forceinline__ Reg load(uint64_t, uint64_t i) const { return s.lacc[i]; }
+    __device__ __forceinline__ void store(uint64_t, uint64_t i, uint32_t, Reg a) const {
+        s.lx[i] = (float)((double)damping * a);
         s.lacc[i] = 0.0;
     }
+};
+__global__ __launch_bounds__(256) void k_ppr_apply(AlgoState s, uint32_t rows, float damping) {
+    ppr_cells(s, rows, PprApply{s, damping});
 }
 
 // k_ppr_apply and the next step's k_ppr_prepare in one pass, for lanes that all step on: the
-// values after the restart of each lane's source, scaled by 1 / D_o where there are out-edges.
-__global__ __launch_bounds__(256) void k_ppr_apply_next(AlgoState s, const uint64_t* __restrict__ off, LaneSet set,
-                                                        float damping, float restart) {
+// values after the restart of each lane's source (active in every step, so among the cells),
+// scaled by 1 / D_o where there are out-edges.
+struct PprApplyNext : PprApply {
+    struct Reg {
+        double a;
+        uint64_t d;
+    };
+    const uint64_t* __restrict__ off;
+    const uint32_t* src;  // per lane (LDS)
+    float restart;
+    __device__ __forceinline__ Reg load(uint64_t v, uint64_t i) const { return Reg{s.lacc[i], off[v + 1] - off[v]}; }
+    __device__ __forceinline__ void store(uint64_t v, uint64_t i, uint32_t l, const Reg& r) const {
+        float x = (float)((double)damping * r.a);
+        if (src[l] == v) x += restart;
+        s.lx[i] = r.d ? x / (float)r.d : x;
+        s.lacc[i] = 0.0;
+    }
+};
+__global__ __launch_bounds__(256) void k_ppr_apply_next(AlgoState s, uint32_t rows, const uint64_t* __restrict__ off,
+                                                        LaneSet set, float damping, float restart) {
     __shared__ uint32_t s_src[MAX_LANES];
     if (threadIdx.x < MAX_LANES) s_src[threadIdx.x] = (set.mask >> threadIdx.x) & 1 ? set.src[threadIdx.x] : UNREACHED;
     __syncthreads();
-    const uint64_t cells = s.n << s.lshift;
-    const uint32_t lmask = (1u << s.lshift) - 1;
-    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < cells; i += (uint64_t)gridDim.x * 256) {
-        const uint64_t v = i >> s.lshift;
-        const uint32_t l = (uint32_t)i & lmask;
-        const bool source = s_src[l] == v;
-        const bool got = ((s.mcur[v] | s.mnext[v]) >> l) & 1;
-        if (!got && !source) continue;
-        float x = got ? (float)((double)damping * s.lacc[i]) : s.lx[i];
-        if (source) x += restart;
-        const uint64_t d = off[v + 1] - off[v];
-        s.lx[i] = d ? x / (float)d : x;
-        if (got) s.lacc[i] = 0.0;
-    }
+    ppr_cells(s, rows, PprApplyNext{{s, damping}, off, s_src, restart});
 }
 
 __global__ void k_ppr_restart(AlgoState s, LaneSet set, float restart) {
@@ -3582,22 +3633,35 @@ hipError_t launch_reset_lanes(const AlgoState& s, uint64_t mask, hipStream_t st)
     return hipGetLastError();
 }
 
+// Vertices per window: 64, fewer on small graphs so that there are PPR_WAVES of them, but whole accesses
+// of 64 cells (64 lanes of 70K vertices, whole call: 2.52 ms in windows of 64, 2.25 so; 4,096 or 65,536
+// waves 2.27 and 2.32, of 2^18 vertices 5.25 and 5.17 against 5.14).
+constexpr uint64_t PPR_WAVES = 16384;
+static uint32_t ppr_rows(const AlgoState& s) {
+    uint32_t rows = 64;
+    while (rows > (64u >> s.lshift) && s.n / rows < PPR_WAVES) rows /= 2;
+    return rows;
+}
+
 hipError_t launch_ppr_prepare(const AlgoState& s, const uint64_t* off, hipStream_t st) {
     if (!s.n) return hipSuccess;
-    k_ppr_prepare<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, off);
+    const uint32_t rows = ppr_rows(s);
+    k_ppr_prepare<<<grid_for(s.n, 4 * rows, 16384), 256, 0, st>>>(s, rows, off);
     return hipGetLastError();
 }
 
 hipError_t launch_ppr_apply_next(const AlgoState& s, const uint64_t* off, const LaneSet& set, float damping,
                                  float restart, hipStream_t st) {
     if (!s.n) return hipSuccess;
-    k_ppr_apply_next<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, off, set, damping, restart);
+    const uint32_t rows = ppr_rows(s);
+    k_ppr_apply_next<<<grid_for(s.n, 4 * rows, 16384), 256, 0, st>>>(s, rows, off, set, damping, restart);
     return hipGetLastError();
 }
 
 hipError_t launch_ppr_apply(const AlgoState& s, float damping, hipStream_t st) {
     if (!s.n) return hipSuccess;
-    k_ppr_apply<<<grid_for(s.n << s.lshift, 256, 16384), 256, 0, st>>>(s, damping);
+    const uint32_t rows = ppr_rows(s);
+    k_ppr_apply<<<grid_for(s.n, 4 * rows, 16384), 256, 0, st>>>(s, rows, damping);
     return hipGetLastError();
 }
 

@@ -125,3 +125,19 @@ def test_pulled_runs_of_a_large_graph():
             # as above, and the FP64 sums' own roundings are far below
             assert np.all(np.abs(ppr[l] - want) <= 1.3e-6 * want + 1e-30)
             assert np.array_equal(dist[l], wd)
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 12, 33, 64])
+@pytest.mark.parametrize("n", [61, 5003, (1 << 20) + 3])
+def test_sparse_steps_match_oracle(n, lanes):
+    """One edge a vertex: few cells are active, in windows of a few rows (small graphs) to 64 vertices
+    (from 2^20), the last one cut off."""
+    off, col = gen.er(n, n, seed=n)
+    rng = np.random.default_rng(lanes)
+    srcs = rng.choice(np.nonzero(np.diff(off.astype(np.int64)))[0], min(lanes, 3)).astype(np.uint32)
+    with hy.Graph(off, col) as g:
+        got, _, _ = g.run_batch("ppr", np.resize(srcs, lanes))
+    for k, s in enumerate(srcs):
+        want = oracle.ppr(off, col, int(s), 0.85, 10)
+        for l in range(k, lanes, len(srcs)):
+            assert np.all(np.abs(got[l] - want) <= 1.3e-6 * want + 1e-30)  # as above
