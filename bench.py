@@ -416,10 +416,11 @@ def main():
             per_launch = d_items * 16 / max(d_launches, 1)
             bound, peak = "hbm", HBM_PEAK_GBPS
         achieved = per_launch / (avg_ms / 1e3) / 1e9
-        op = {"bfs": "OpBfs", "sssp": "OpSssp", "cc": "OpCc", "pagerank": "OpPr"}[dalgo]
+        # BFS, SSSP and CC: the operator of wide iterations, which take the most of their time
+        op = {"bfs": "OpBfsWide", "sssp": "OpSsspWide", "cc": "OpCcWide", "pagerank": "OpPr"}[dalgo]
         symbol = {"push_zerocopy": f"k_push_lines<{op}>", "push_filter": f"k_push_fstream<{op}>",
                   "push_resident": f"k_push_edges<{op}, false>", "push_compact": f"k_push_edges<{op}, true>",
-                  "stats": "k_stats_select", "lists": "k_build_lists"}.get(name, name)
+                  "stats": "k_unit_stats", "lists": "k_build_lists"}.get(name, name)
         traffic = None
         src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2208_14935_amd", "csrc", "kernels.hip")
         with open(src, "rb") as fh:

@@ -347,8 +347,8 @@ hytm_status hytm_set_device_budget(hytm_graph *g, uint64_t edge_bytes);
    budget, the in-edge lists that wide batched PPR and SSSP steps read (8 bytes per edge, 12
    with weights, and 12 to 16 per vertex).  The first call that uses a form makes it; what does
    not fit goes without, with the same results.  UINT64_MAX (the default): each form may take
-   half of the device memory free when it is made; 0: none.  What is kept beyond the new limit
-   is released at once.  A call on any handle that finds the device full has the forms of the
+   half of the device memory free when it is made; 0: none.  A graph that keeps more than a
+   new limit releases all of it at once.  A call on any handle that finds the device full has the forms of the
    handles that no other call or server is using released and is made again. */
 hytm_status hytm_set_plan_limit(hytm_graph *g, uint64_t bytes);
 

@@ -738,7 +738,10 @@ OpenGraphs& open_graphs() {
 // the handles on the device that no call or server is at work on are given back.  False when
 // there were none.
 bool spare_room(hytm_graph* own, int device) {
-    if (hipSetDevice(device) != hipSuccess) return false;
+    if (hipSetDevice(device) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     (void)hipDeviceSynchronize();  // the failed call may have left work that reads them
     bool any = own && give_back(own);
     OpenGraphs& o = open_graphs();
@@ -2481,7 +2484,11 @@ uint64_t sssp_overflow_lanes(hytm_graph* g, const uint32_t* dist, uint32_t lshif
     return out;
 }
 
-// keep = false: without making or using the sorted forms of the edges.
+// One run.  lanes == 0: single source `sources[0]` (BFS/SSSP) or none (CC/PR), values_out
+// holds n values, iterations_out one count.  lanes in 1..64: batched BFS/SSSP/PPR from
+// sources[0..lanes), values_out holds lanes rows of n values, iterations_out one count per
+// lane (the non-empty frontiers of that lane; PPR: its steps).  keep = false: without making or
+// using the sorted forms of the edges.
 hytm_status run_impl(hytm_graph* g, hytm_algo algo, const uint32_t* sources, uint32_t lanes, void* values_out,
                      uint32_t* iterations_out, hytm_run_stats* stats, void* hip_stream, bool keep) {
     HIP_CHECK(hipSetDevice(g->device));
